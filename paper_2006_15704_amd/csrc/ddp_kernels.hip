@@ -257,10 +257,13 @@ __device__ __forceinline__ void add_into(float (&acc)[Fmt<DT>::VEC], u32x4 x) {
 }
 
 // Interior work (every vector of the block lies inside the data): no lane is
-// predicated.  base_of(r) returns replica r's block-uniform base address; the
-// per-thread part of the address is a 32-bit byte offset, so the loads take the
-// scalar-base + vector-offset form.  All C*U loads are issued before the adds,
-// which run in ascending r.
+// predicated.  base_of(r) returns replica r's block-uniform base address, which
+// need only be element-aligned; the per-thread part of the address is a 32-bit
+// byte offset, so the loads take the scalar-base + vector-offset form.  All C*U
+// loads are issued before the adds, which run in ascending r.  (The instruction
+// is the same for any alignment; a base off the 16-byte grid costs one more
+// cache line per wave and load, which the non-temporal hint does not evict
+// before the neighbouring wave has used it: plain loads were 7 % slower.)
 template <int DT, bool NT, int C, int U, typename BaseFn>
 __device__ __forceinline__ void chunk_interior(BaseFn base_of, int r, const uint32_t (&lane_off)[U],
                                                float (&acc)[U][Fmt<DT>::VEC]) {
@@ -271,7 +274,7 @@ __device__ __forceinline__ void chunk_interior(BaseFn base_of, int r, const uint
 #pragma unroll
     for (int i = 0; i < C; ++i)
 #pragma unroll
-        for (int u = 0; u < U; ++u) x[i][u] = load16<NT>(base[i] + lane_off[u]);
+        for (int u = 0; u < U; ++u) x[i][u] = load16u<NT>(base[i] + lane_off[u]);
 #pragma unroll
     for (int i = 0; i < C; ++i)
 #pragma unroll
@@ -480,8 +483,8 @@ __device__ __forceinline__ void store_out32_wave(char* out, int64_t in_byte_off,
         a[k] = static_cast<uint32_t>(upper ? a_hi : a_lo);
         b[k] = static_cast<uint32_t>(upper ? b_hi : b_lo);
     }
-    store16s<NT>(wave_base + 16 * lane, a);
-    store16s<NT>(wave_base + 1024 + 16 * lane, b);
+    store16u<NT>(wave_base + 16 * lane, a);
+    store16u<NT>(wave_base + 1024 + 16 * lane, b);
 }
 
 template <int DT, bool OUT32 = false>
@@ -548,15 +551,16 @@ __device__ __forceinline__ void fused_tile(const SegTables& t, int64_t tile, int
     const bool zero = used == 0;            // ... or become zeros
     const bool all_used = used == everyone;
     const int sh = si.lead_bytes() / ES;    // replica 0's tensor starts this many elements past a 16-byte boundary
-    // every replica's tensor sits at the same offset modulo 16 (and, with binary32 outputs, the
-    // output tensor sits where whole input vectors map to whole output vectors)
-    const bool src_aligned = si.congruent();
-    const bool fast = src_aligned && (!OUT32 || si.out_congruent());
+    const bool src_aligned = si.congruent();   // every replica's tensor sits at the same offset modulo 16
     char* const outp = OUT32 ? static_cast<char*>(t.out[g]) : nullptr;
     const int64_t e_tile = ltile * (TILE_BYTES / ES) - sh;
 
-    if (fast && all_used && e_tile >= 0 && e_tile + TILE_BYTES / ES <= numel) {
-        // the whole tile is inside the segment, every replica took part and all are aligned alike
+    // The whole tile is inside the segment and every replica took part.  Where the replicas sit
+    // modulo 16 does not matter: vectors are cut on replica 0's 16-byte grid, the other replicas (and
+    // a binary32 output tensor that is off the grid) are accessed with element-aligned vectors.  90
+    // densely packed tensors of odd sizes, R = 8, 120 MB each, replicas 4 bytes apart modulo 16: 235 us
+    // when such tiles took the predicated path below, 203 us here (5.3 TB/s; 5.9 when congruent).
+    if (all_used && e_tile >= 0 && e_tile + TILE_BYTES / ES <= numel) {
         const int64_t tile_byte = e_tile * ES;
 #pragma unroll 1
         for (int step = 0; step < TILE_VECS / (BLOCK * U); ++step) {
@@ -579,7 +583,7 @@ __device__ __forceinline__ void fused_tile(const SegTables& t, int64_t tile, int
                 const u32x4 out = scaled<DT>(sc, acc[u]);
                 store16s<NT>(const_cast<char*>(pre[0]) + tile_byte + lane_off[u], out);
                 for (int w = 1; w < nwrite; ++w)
-                    store16s<NT>(static_cast<char*>(row[w]) + tile_byte + lane_off[u], out);
+                    store16u<NT>(static_cast<char*>(row[w]) + tile_byte + lane_off[u], out);
             }
         }
         return;

@@ -1,0 +1,81 @@
+"""GPU parity of the unpredicated path of whole tiles, at the sizes where tiles begin and end:
+segments of one element more or less than whole tiles, replicas that are shifted against each
+other modulo 16 bytes, replica counts on both sides of a chunk of eight.  The sums run in the
+oracle's order, so the results are expected bit for bit."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+
+pytestmark = pytest.mark.gpu
+
+FP32, FP16, BF16 = 0, 1, 2
+ES = {FP32: 4, FP16: 2, BF16: 2}
+FUSED = 1
+TILE = 8192                      # bytes of gradient data per replica and thread block
+
+
+def lib():
+    import paper_2006_15704_amd as d
+    from paper_2006_15704_amd import harness
+    return d, harness
+
+
+def edge_sizes(es):
+    t = TILE // es
+    return [t - 1, t, t + 1, 3 * t + 5, 2 * t, 1, 2 * t - 1, 16 // es]
+
+
+@pytest.mark.parametrize("dtype", [FP32, FP16, BF16])
+@pytest.mark.parametrize("R", [2, 7, 8, 9, 17])
+def test_replicas_shifted_modulo_16(dtype, R):
+    d, harness = lib()
+    es = ES[dtype]
+    numel = edge_sizes(es)
+    n, cap = len(numel), 40000
+    skew = [es * (3 * i % 8) for i in range(n)]
+    replica_skew = [es * (5 * r % (16 // es)) for r in range(R)]
+    reps = [workloads.gaussian_replica(700 + R, r, 0, numel, 1e-2, dtype) for r in range(R)]
+    want, _, wlog = oracle.synchronize(numel, [dtype] * n, cap, reps)
+    for write_all in (False, True):
+        grads = harness.DeviceGrads(numel, [dtype] * n, R, skew=skew, replica_skew=replica_skew, fill=0xFF)
+        for r in range(R):
+            grads.upload_replica(r, reps[r])
+        with harness.Session(grads, cap, FUSED, write_all) as s:
+            s.sync()
+            assert d.ddp_get_launch_log(s.ctx, 1) == wlog
+        for i in range(n):
+            for r in range(R):
+                expect = want[i] if r == 0 or write_all else reps[r][i]
+                assert grads.download(r, i).tobytes() == np.asarray(expect).tobytes(), f"replica {r} parameter {i}"
+        for r in range(R):       # nothing outside the tensors was written
+            raw = grads.bufs[r].cpu().numpy()
+            inside = np.zeros(raw.size, dtype=bool)
+            for i in range(n):
+                o = grads.offsets[i] + grads.replica_skew[r]
+                inside[o:o + grads.nbytes(i)] = True
+            assert (raw[~inside] == 0xFF).all(), f"replica {r}: bytes between the tensors were written"
+
+
+@pytest.mark.parametrize("transport", [FP16, BF16])
+@pytest.mark.parametrize("out_skew", [0, 4, 12])
+def test_shifted_replicas_with_binary32_outputs(transport, out_skew):
+    d, harness = lib()
+    numel = edge_sizes(2)
+    n, R, cap = len(numel), 9, 40000
+    sent = [workloads.gaussian_replica(720, r, 0, numel, 1e-2, transport) for r in range(R)]
+    want, _, _ = oracle.synchronize_transport(numel, [transport] * n, cap, sent)
+    grads = harness.DeviceGrads(numel, [transport] * n, R, replica_skew=[2 * (3 * r % 8) for r in range(R)], fill=0xFF)
+    for r in range(R):
+        grads.upload_replica(r, sent[r])
+    outs = harness.DeviceGrads(numel, [FP32] * n, 1, skew=[out_skew] * n, fill=0x55)
+    with harness.Session(grads, cap, FUSED, outputs=outs) as s:
+        s.sync()
+    for i in range(n):
+        assert outs.download(0, i).tobytes() == want[i].tobytes(), f"parameter {i}"
+    raw = outs.bufs[0].cpu().numpy()
+    inside = np.zeros(raw.size, dtype=bool)
+    for i in range(n):
+        inside[outs.offsets[i]:outs.offsets[i] + outs.nbytes(i)] = True
+    assert (raw[~inside] == 0x55).all(), "bytes between the output tensors were written"
