@@ -204,8 +204,10 @@ typedef struct ddp_ctx ddp_ctx;
 
 /* DDP_PIPELINE_STAGED follows the paper's data flow literally: gradients are
  * copied into flat per-replica bucket buffers (Algorithm 1, autograd_hook),
- * the bucket is reduced, and the averaged bucket is copied back to the
- * gradient tensors by the finalizing step.  DDP_PIPELINE_FUSED computes the
+ * the bucket is reduced (in the same pass over the gradients; with
+ * DDP_OPT_TIMING 1 by a kernel of its own, so that both can be stamped), and
+ * the averaged bucket is copied back to the gradient tensors by the finalizing
+ * step.  DDP_PIPELINE_FUSED computes the
  * same values in one pass per bucket: the kernel gathers each replica's
  * gradients through the bucket's segment table, sums and averages in
  * registers, and writes straight to the gradient tensors; the flat bucket is

@@ -211,8 +211,10 @@ bool long_launch(const ddp_ctx* c, int64_t launch_bytes) {
     return launch_bytes * (c->R + 1) >= c->cap_min_traffic;
 }
 
-unsigned occupancy_lds(const ddp_ctx* c, int64_t launch_bytes) {
-    const int32_t blocks = c->blocks_per_cu < 0 ? auto_blocks_per_cu(c->R) : c->blocks_per_cu;
+// copies: the staged pass, which writes as much as it reads and gains nothing from a cap (ResNet-50,
+// R = 8: 375 us a synchronization with none or four blocks, 384 with two).
+unsigned occupancy_lds(const ddp_ctx* c, int64_t launch_bytes, bool copies) {
+    const int32_t blocks = c->blocks_per_cu >= 0 ? c->blocks_per_cu : copies ? 0 : auto_blocks_per_cu(c->R);
     if (blocks <= 0 || !long_launch(c, launch_bytes)) return 0;
     return static_cast<unsigned>((c->lds_per_cu / blocks) & ~int64_t(1023));
 }
@@ -507,7 +509,8 @@ int32_t launch_range(ddp_ctx* c, int32_t first, int32_t last, Target target) {
         c->open_group = c->timed.size() - 1;
     }
     if (c->timing == 2) c->timed[c->open_group].bucket += 1;   // counts the launches
-    if (c->pipeline == DDP_PIPELINE_STAGED) {
+    if (c->pipeline == DDP_PIPELINE_STAGED && c->timing == 1) {
+        // pack and reduce as launches of their own, so that each can be stamped
         char* in0 = c->slabs + c->bucket_slab_off[first];
         char* out = c->slabs + static_cast<int64_t>(c->R) * c->slab_stride + c->bucket_slab_off[first];
         // the range of the slab from the first bucket's base to the last one's padded end
@@ -519,14 +522,16 @@ int32_t launch_range(ddp_ctx* c, int32_t first, int32_t last, Target target) {
         if ((rc = timed_begin(c, DDP_K_REDUCE, id, st, &slot)) != DDP_OK) return rc;
         HIPCHK(c, ddp::launch_flat_reduce(bf.dtype, in0, c->slab_stride, out, nvec, c->R, sc,
                                           c->nontemporal != 0,
-                                          occupancy_lds(c, bytes), st));
+                                          occupancy_lds(c, bytes, false), st));
         if ((rc = timed_end(c, slot, st)) != DDP_OK) return rc;
     } else {
+        const bool staged = c->pipeline == DDP_PIPELINE_STAGED;
+        const ddp::FlatBuckets flat{staged ? c->slabs : nullptr, staged ? c->slab_stride : 0};
         if ((rc = timed_begin(c, DDP_K_REDUCE, id, st, &slot)) != DDP_OK) return rc;
         HIPCHK(c, ddp::launch_fused_reduce(bf.dtype, c->tables, tile_base, ntiles, c->R,
                                            c->write_all ? c->R : 1, d_flags, c->find_unused != 0, sc,
-                                           c->nontemporal != 0, occupancy_lds(c, bytes),
-                                           gate, static_cast<uint32_t>(c->iteration + 1), sig, st));
+                                           c->nontemporal != 0, occupancy_lds(c, bytes, staged),
+                                           flat, gate, static_cast<uint32_t>(c->iteration + 1), sig, st));
         if ((rc = timed_end(c, slot, st)) != DDP_OK) return rc;
     }
     return DDP_OK;

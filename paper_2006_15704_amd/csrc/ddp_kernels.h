@@ -55,6 +55,13 @@ struct SegTables {
     int32_t R;
 };
 
+// The staged pipeline's flat buckets: replica r's slab at slab0 + r * stride (r < R), the averaged one
+// at slab0 + R * stride; a segment lies flat_byte into each.  slab0 null = no flat buckets.
+struct FlatBuckets {
+    char* slab0;
+    int64_t stride;
+};
+
 struct Scale {       // y = use_mul ? s * mul : s / div
     float div;
     float mul;
@@ -105,8 +112,11 @@ hipError_t launch_flat_reduce(int dtype, const char* in0, int64_t stride, char* 
 // K2 (fused): gather R replicas through the segment table, reduce, scatter to
 // the gradient tensors of replicas [0, nwrite).  local / keep_unused as above
 // (a replica with flag 0 contributes +0 and is not read; a parameter nobody
-// used is skipped with keep_unused, else written as zeros).  pair = blocks
-// take two tiles each (for large launches).
+// used is skipped with keep_unused, else written as zeros).
+// With flat.slab0 set (staged pipeline) the launch does K1's and K2's work in
+// one pass instead: every replica's gradients are copied into its flat bucket
+// (zeros for a replica that did not use the parameter) and the average goes to
+// the averaged bucket; nwrite and keep_unused do not matter then.
 struct GateRecord;   // below, with the flag-ordering kernels
 
 // gate (may be null): the record of the gate kernel enqueued in front of this
@@ -119,7 +129,7 @@ struct DispatchSignal {
 };
 hipError_t launch_fused_reduce(int dtype, const SegTables& t, int64_t tile_base, int64_t ntiles,
                                int R, int nwrite, const uint8_t* local, bool keep_unused, Scale sc,
-                               bool nontemporal, unsigned lds,
+                               bool nontemporal, unsigned lds, FlatBuckets flat,
                                const GateRecord* gate, uint32_t tag, DispatchSignal sig, hipStream_t s);
 // (with t.out set -- 16-bit gradients, binary32 averages written to t.out -- nwrite must be 1)
 

@@ -15,6 +15,7 @@
 
 #include <mutex>
 #include <set>
+#include <type_traits>
 #include <utility>
 
 namespace ddp {
@@ -90,6 +91,7 @@ template <> struct Fmt<0> {   // binary32
         for (int i = 0; i < 4; ++i) v[i] = __float_as_uint(f[i]);
         return v;
     }
+    static __device__ __forceinline__ float value(uint32_t bits) { return __uint_as_float(bits); }
     static __device__ __forceinline__ float load1(const char* p) {
         return gload<float>(p);
     }
@@ -119,6 +121,7 @@ template <> struct Fmt<1> {   // binary16: exact widening, round-to-nearest-even
         for (int i = 0; i < 4; ++i) v[i] = down(f[2 * i]) | (down(f[2 * i + 1]) << 16);
         return v;
     }
+    static __device__ __forceinline__ float value(uint32_t bits) { return up(bits); }
     static __device__ __forceinline__ float load1(const char* p) {
         return up(gload<uint16_t>(p));
     }
@@ -148,8 +151,9 @@ template <> struct Fmt<2> {   // bfloat16 = upper half of binary32
         for (int i = 0; i < 4; ++i) v[i] = down(f[2 * i]) | (down(f[2 * i + 1]) << 16);
         return v;
     }
+    static __device__ __forceinline__ float value(uint32_t bits) { return __uint_as_float(bits << 16); }
     static __device__ __forceinline__ float load1(const char* p) {
-        return __uint_as_float(static_cast<uint32_t>(gload<uint16_t>(p)) << 16);
+        return value(gload<uint16_t>(p));
     }
     static __device__ __forceinline__ void store1(char* p, float y) {
         gstore<uint16_t>(p, static_cast<uint16_t>(down(y)));
@@ -279,6 +283,39 @@ __device__ __forceinline__ void chunk_interior(BaseFn base_of, int r, const uint
     for (int i = 0; i < C; ++i)
 #pragma unroll
         for (int u = 0; u < U; ++u) add_into<DT>(acc[u], x[i][u]);
+}
+
+// The same for a tile that is also copied into the replicas' flat buckets (staged pipeline): slot is
+// the tile's place in replica r's buffer, `used` says whose tensors are read; a replica that did not
+// use the parameter contributes zeros to its bucket and to the sum.
+// Bound by HBM: a bucket of b bytes costs R b read and (R + 1) b written in this one pass, where packing
+// and reducing in two kernels read the copies back ((2 R + 1) b instead of (3 R + 1) b in all).
+// ResNet-50, R = 8, one call for all marks: 477 -> 375 us a synchronization including the write-back;
+// the copies are not read again on the path, and without the non-temporal hint on them it is 402 us.
+template <int DT, bool NT, int C, int U>
+__device__ __forceinline__ void chunk_copy(void* const* __restrict__ row, int r, uint64_t used, int64_t tile_byte,
+                                           char* slot, int64_t stride, const uint32_t (&lane_off)[U],
+                                           float (&acc)[U][Fmt<DT>::VEC]) {
+    const char* base[C];
+#pragma unroll
+    for (int i = 0; i < C; ++i) base[i] = static_cast<const char*>(row[r + i]) + tile_byte;
+    u32x4 x[C][U];
+#pragma unroll
+    for (int i = 0; i < C; ++i) {
+        const bool take = ((used >> (r + i)) & 1u) != 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            x[i][u] = zero16();
+            if (take) x[i][u] = load16u<NT>(base[i] + lane_off[u]);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < C; ++i)
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            store16s<NT>(slot + i * stride + lane_off[u], x[i][u]);
+            add_into<DT>(acc[u], x[i][u]);
+        }
 }
 
 // The last `left` (0..7) replicas as ONE chunk, so that all of their loads are
@@ -414,10 +451,11 @@ __global__ __launch_bounds__(BLOCK) void flat_reduce_kernel(const char* __restri
 // Fused variant, boundary tiles: replica pointers come from the segment table
 // and lanes are predicated.  The C pointers are fetched first (one scalar
 // load), then all C*U vector loads are issued, then the adds run in order.
+// With `slot` set (staged pipeline) the vectors also go to the replicas' flat buckets.
 template <int DT, bool NT, int C, int U>
 __device__ __forceinline__ void chunk_seg(void* const* __restrict__ row, int r, uint64_t used, bool aligned,
                                           const int64_t (&off)[U], const bool (&ok)[U],
-                                          float (&acc)[U][Fmt<DT>::VEC]) {
+                                          float (&acc)[U][Fmt<DT>::VEC], char* slot = nullptr, int64_t stride = 0) {
     const char* base[C];
 #pragma unroll
     for (int i = 0; i < C; ++i) base[i] = static_cast<const char*>(row[r + i]);
@@ -434,14 +472,21 @@ __device__ __forceinline__ void chunk_seg(void* const* __restrict__ row, int r, 
 #pragma unroll
     for (int i = 0; i < C; ++i)
 #pragma unroll
-        for (int u = 0; u < U; ++u) add_into<DT>(acc[u], x[i][u]);
+        for (int u = 0; u < U; ++u) {
+            if (slot != nullptr && ok[u]) store16s<NT>(slot + (r + i) * stride + off[u], x[i][u]);
+            add_into<DT>(acc[u], x[i][u]);
+        }
 }
 
-// Where the averages go.  Normally into the gradient tensors themselves, in
-// their own format (replica 0's, or all of them).  With OUT32 the gradients are a
+// Where the averages go.  OUT_GRAD: into the gradient tensors themselves, in their
+// own format (replica 0's, or all of them).  OUT_BINARY32: the gradients are a
 // 16-bit transport format (Section 6.2.3) and the averages are written as
 // binary32, unrounded, to a separate tensor per parameter (SegTables::out): two
-// 16-byte stores per 16-byte input vector, at twice the byte offset.
+// 16-byte stores per 16-byte input vector, at twice the byte offset.  OUT_FLAT
+// (staged pipeline): every replica's gradients are copied into its flat bucket
+// buffer and the average goes to the averaged bucket (FlatBuckets).
+enum { OUT_GRAD = 0, OUT_BINARY32 = 1, OUT_FLAT = 2 };
+
 template <int DT, bool NT>
 __device__ __forceinline__ void store_out32(char* out, int64_t in_byte_off, const float (&y)[Fmt<DT>::VEC],
                                             bool aligned = true) {
@@ -487,10 +532,26 @@ __device__ __forceinline__ void store_out32_wave(char* out, int64_t in_byte_off,
     store16u<NT>(wave_base + 1024 + 16 * lane, b);
 }
 
-template <int DT, bool OUT32 = false>
+template <int DT, int OUT>
 __device__ __forceinline__ void reduce_element(const SegTables& t, int g, int R, int nwrite,
-                                               int64_t idx, bool zero, uint64_t used, const Scale& sc) {
+                                               int64_t idx, bool zero, uint64_t used, const Scale& sc,
+                                               const FlatBuckets& flat, int64_t flat_byte) {
     constexpr int ES = Fmt<DT>::ES;
+    if (OUT == OUT_FLAT) {
+        // the copy moves bits, not values: a signalling NaN arrives in the bucket as it is
+        typedef typename std::conditional<ES == 4, uint32_t, uint16_t>::type bits;
+        char* slot = flat.slab0 + flat_byte + idx * ES;
+        float s = -0.0f;
+        for (int r = 0; r < R; ++r) {
+            bits x = 0;
+            if ((used >> r) & 1u)
+                x = gload<bits>(static_cast<const char*>(t.grad[static_cast<int64_t>(g) * t.R + r]) + idx * ES);
+            gstore<bits>(slot + r * flat.stride, x);
+            s += Fmt<DT>::value(x);
+        }
+        Fmt<DT>::store1(slot + R * flat.stride, apply_scale(sc, s));
+        return;
+    }
     float y = 0.0f;
     if (!zero) {
         float s = -0.0f;
@@ -502,7 +563,7 @@ __device__ __forceinline__ void reduce_element(const SegTables& t, int g, int R,
         }
         y = apply_scale(sc, s);
     }
-    if (OUT32) {
+    if (OUT == OUT_BINARY32) {
         gstore<float>(static_cast<char*>(t.out[g]) + idx * 4, y);
         return;
     }
@@ -523,11 +584,11 @@ __device__ __forceinline__ uint64_t used_mask(const uint8_t* __restrict__ flags,
 // not touch gradients that may still be incomplete; the repair launch redoes it.
 // The gate word is fetched together with the tile's tables (one round of scalar
 // loads, not one more in front of them) and looked at before any gradient is.
-template <int DT, bool NT, int U, bool OUT32 = false>
+template <int DT, bool NT, int U, int OUT>
 __device__ __forceinline__ void fused_tile(const SegTables& t, int64_t tile, int R, int nwrite,
                                            const uint8_t* __restrict__ local, int keep_unused,
-                                           const Scale& sc, const GateRecord* __restrict__ gate = nullptr,
-                                           uint32_t tag = 0) {
+                                           const Scale& sc, const FlatBuckets& flat,
+                                           const GateRecord* __restrict__ gate = nullptr, uint32_t tag = 0) {
     constexpr int ES = Fmt<DT>::ES;
     constexpr int VEC = Fmt<DT>::VEC;
     const uint32_t gate_word = gate != nullptr ? gate->failed_tag : ~tag;
@@ -547,12 +608,14 @@ __device__ __forceinline__ void fused_tile(const SegTables& t, int64_t tile, int
     // it); without a flag table every replica did
     const uint64_t everyone = R >= 64 ? ~uint64_t(0) : ((uint64_t(1) << R) - 1);
     const uint64_t used = local != nullptr ? used_mask(local + static_cast<int64_t>(g) * t.R, R) : everyone;
-    if (used == 0 && keep_unused) return;   // globally unused: the gradients stay as they are
-    const bool zero = used == 0;            // ... or become zeros
+    if (OUT != OUT_FLAT && used == 0 && keep_unused) return;   // globally unused: the gradients stay as they are
+    const bool zero = OUT != OUT_FLAT && used == 0;            // ... or become zeros (flat buckets always do)
     const bool all_used = used == everyone;
-    const int sh = si.lead_bytes() / ES;    // replica 0's tensor starts this many elements past a 16-byte boundary
+    // replica 0's tensor -- or the slot in the flat bucket -- starts this many elements past a 16-byte boundary
+    const int sh = (OUT == OUT_FLAT ? static_cast<int>(si.flat_byte & 15) : si.lead_bytes()) / ES;
     const bool src_aligned = si.congruent();   // every replica's tensor sits at the same offset modulo 16
-    char* const outp = OUT32 ? static_cast<char*>(t.out[g]) : nullptr;
+    char* const outp = OUT == OUT_BINARY32 ? static_cast<char*>(t.out[g]) : nullptr;
+    char* const slot = OUT == OUT_FLAT ? flat.slab0 + si.flat_byte : nullptr;
     const int64_t e_tile = ltile * (TILE_BYTES / ES) - sh;
 
     // The whole tile is inside the segment and every replica took part.  Where the replicas sit
@@ -560,7 +623,7 @@ __device__ __forceinline__ void fused_tile(const SegTables& t, int64_t tile, int
     // a binary32 output tensor that is off the grid) are accessed with element-aligned vectors.  90
     // densely packed tensors of odd sizes, R = 8, 120 MB each, replicas 4 bytes apart modulo 16: 235 us
     // when such tiles took the predicated path below, 203 us here (5.3 TB/s; 5.9 when congruent).
-    if (all_used && e_tile >= 0 && e_tile + TILE_BYTES / ES <= numel) {
+    if ((all_used || OUT == OUT_FLAT) && e_tile >= 0 && e_tile + TILE_BYTES / ES <= numel) {
         const int64_t tile_byte = e_tile * ES;
 #pragma unroll 1
         for (int step = 0; step < TILE_VECS / (BLOCK * U); ++step) {
@@ -568,16 +631,32 @@ __device__ __forceinline__ void fused_tile(const SegTables& t, int64_t tile, int
             float acc[U][VEC];
 #pragma unroll
             for (int u = 0; u < U; ++u) lane_off[u] = ((step * U + u) * BLOCK + threadIdx.x) * 16u;
+            if constexpr (OUT == OUT_FLAT) {
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int i = 0; i < VEC; ++i) acc[u][i] = -0.0f;
+                char* const place = slot + tile_byte;
+                int r = 0;
+                for (; r + 8 <= R; r += 8) chunk_copy<DT, NT, 8, U>(row, r, used, tile_byte, place + r * flat.stride, flat.stride, lane_off, acc);
+                if (r + 4 <= R) { chunk_copy<DT, NT, 4, U>(row, r, used, tile_byte, place + r * flat.stride, flat.stride, lane_off, acc); r += 4; }
+                if (r + 2 <= R) { chunk_copy<DT, NT, 2, U>(row, r, used, tile_byte, place + r * flat.stride, flat.stride, lane_off, acc); r += 2; }
+                if (r < R) chunk_copy<DT, NT, 1, U>(row, r, used, tile_byte, place + r * flat.stride, flat.stride, lane_off, acc);
+                // the averaged bucket is read again by the write-back
+#pragma unroll
+                for (int u = 0; u < U; ++u) store16(place + R * flat.stride + lane_off[u], scaled<DT>(sc, acc[u]));
+                continue;
+            }
             sum_interior_pre<DT, NT, U>(
                 pre, tile_byte, [&](int r) { return static_cast<const char*>(row[r]) + tile_byte; }, R,
                 lane_off, acc);
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                if (OUT32) {
+                if (OUT == OUT_BINARY32) {
                     float y[VEC];
 #pragma unroll
                     for (int i = 0; i < VEC; ++i) y[i] = apply_scale(sc, acc[u][i]);
-                    if constexpr (OUT32) store_out32_wave<DT, NT>(outp, tile_byte + lane_off[u], y);
+                    if constexpr (OUT == OUT_BINARY32) store_out32_wave<DT, NT>(outp, tile_byte + lane_off[u], y);
                     continue;
                 }
                 const u32x4 out = scaled<DT>(sc, acc[u]);
@@ -607,11 +686,13 @@ __device__ __forceinline__ void fused_tile(const SegTables& t, int64_t tile, int
         if (!zero) {
             // vectors sit on replica 0's 16-byte grid; replicas that are shifted against it
             // are read with element-aligned 16-byte loads
+            // (flat buckets: vectors sit on the slot's grid)
+            const bool aligned = OUT != OUT_FLAT && src_aligned;
             int r = 0;
-            for (; r + 8 <= R; r += 8) chunk_seg<DT, NT, 8, U>(row, r, used, src_aligned, off, ok, acc);
-            if (r + 4 <= R) { chunk_seg<DT, NT, 4, U>(row, r, used, src_aligned, off, ok, acc); r += 4; }
-            if (r + 2 <= R) { chunk_seg<DT, NT, 2, U>(row, r, used, src_aligned, off, ok, acc); r += 2; }
-            if (r < R) { chunk_seg<DT, NT, 1, U>(row, r, used, src_aligned, off, ok, acc); }
+            for (; r + 8 <= R; r += 8) chunk_seg<DT, NT, 8, U>(row, r, used, aligned, off, ok, acc, slot, flat.stride);
+            if (r + 4 <= R) { chunk_seg<DT, NT, 4, U>(row, r, used, aligned, off, ok, acc, slot, flat.stride); r += 4; }
+            if (r + 2 <= R) { chunk_seg<DT, NT, 2, U>(row, r, used, aligned, off, ok, acc, slot, flat.stride); r += 2; }
+            if (r < R) { chunk_seg<DT, NT, 1, U>(row, r, used, aligned, off, ok, acc, slot, flat.stride); }
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -620,8 +701,12 @@ __device__ __forceinline__ void fused_tile(const SegTables& t, int64_t tile, int
                 float y[VEC];
 #pragma unroll
                 for (int i = 0; i < VEC; ++i) y[i] = zero ? 0.0f : apply_scale(sc, acc[u][i]);
-                if (OUT32) {
-                    if constexpr (OUT32) store_out32<DT, NT>(outp, off[u], y, si.out_congruent());
+                if (OUT == OUT_BINARY32) {
+                    if constexpr (OUT == OUT_BINARY32) store_out32<DT, NT>(outp, off[u], y, si.out_congruent());
+                    continue;
+                }
+                if (OUT == OUT_FLAT) {
+                    store16(slot + R * flat.stride + off[u], Fmt<DT>::narrow(y));
                     continue;
                 }
                 const u32x4 out = zero ? zero16() : Fmt<DT>::narrow(y);
@@ -634,18 +719,18 @@ __device__ __forceinline__ void fused_tile(const SegTables& t, int64_t tile, int
             } else {
                 for (int i = 0; i < VEC; ++i) {
                     const int64_t idx = e[u] + i;
-                    if (idx >= 0 && idx < numel) reduce_element<DT, OUT32>(t, g, R, nwrite, idx, zero, used, sc);
+                    if (idx >= 0 && idx < numel) reduce_element<DT, OUT>(t, g, R, nwrite, idx, zero, used, sc, flat, si.flat_byte);
                 }
             }
         }
     }
 }
 
-template <int DT, bool NT, int U, bool OUT32 = false>
+template <int DT, bool NT, int U, int OUT>
 __global__ __launch_bounds__(BLOCK) void fused_reduce_kernel(SegTables t, int64_t tile_base, int R,
                                                              int nwrite,
                                                              const uint8_t* __restrict__ local,
-                                                             int keep_unused, Scale sc,
+                                                             int keep_unused, Scale sc, FlatBuckets flat,
                                                              const GateRecord* __restrict__ gate,
                                                              uint32_t tag, DispatchSignal sig) {
     // the last block of the grid tells that the launch has been dispatched in full (blocks start
@@ -654,7 +739,7 @@ __global__ __launch_bounds__(BLOCK) void fused_reduce_kernel(SegTables t, int64_
     // measured no better; 1024 and more blocks earlier lose the gain)
     if (sig.word != nullptr && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0)
         __hip_atomic_fetch_max(sig.word, sig.ord, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    fused_tile<DT, NT, U, OUT32>(t, tile_base + blockIdx.x, R, nwrite, local, keep_unused, sc, gate, tag);
+    fused_tile<DT, NT, U, OUT>(t, tile_base + blockIdx.x, R, nwrite, local, keep_unused, sc, flat, gate, tag);
 }
 
 // ---- stream ordering through device flags ------------------------------------
@@ -749,7 +834,7 @@ __global__ __launch_bounds__(64) void chain_wait_kernel(OrderState* st, unsigned
 
 // Launches whose gate gave up, redone once every gradient exists.  Block j takes
 // the tiles j, j + G, ... of each failed launch.
-template <int DT, bool NT, int U, bool OUT32 = false>
+template <int DT, bool NT, int U, int OUT>
 __global__ __launch_bounds__(BLOCK) void repair_kernel(SegTables t, OrderState* st,
                                                        const GateRecord* __restrict__ rec,
                                                        int nb, uint32_t tag, int R, int nwrite,
@@ -762,7 +847,7 @@ __global__ __launch_bounds__(BLOCK) void repair_kernel(SegTables t, OrderState* 
         if (r.failed_tag != tag || r.dtype != DT) continue;
         if (blockIdx.x == 0 && threadIdx.x == 0) st->repaired += 1;   // (repair launches run one after the other)
         for (int64_t i = blockIdx.x; i < r.ntiles; i += gridDim.x)
-            fused_tile<DT, NT, U, OUT32>(t, r.tile_base + i, R, nwrite, local, keep_unused, sc);
+            fused_tile<DT, NT, U, OUT>(t, r.tile_base + i, R, nwrite, local, keep_unused, sc, FlatBuckets{nullptr, 0});
     }
 }
 
@@ -1000,37 +1085,43 @@ hipError_t launch_flat_reduce(int dtype, const char* in0, int64_t stride, char* 
     }
 }
 
-template <int DT>
+template <int DT, int OUT>
 static hipError_t fused_dispatch(bool nt, int64_t ntiles, unsigned lds, hipStream_t s,
                                  const SegTables& t, int64_t tile_base, int R, int nwrite,
-                                 const uint8_t* local, int keep, Scale sc, const GateRecord* gate, uint32_t tag,
-                                 DispatchSignal sig) {
+                                 const uint8_t* local, int keep, Scale sc, FlatBuckets flat,
+                                 const GateRecord* gate, uint32_t tag, DispatchSignal sig) {
     dim3 grid(static_cast<unsigned>(ntiles));
-    if (nt) return launch(fused_reduce_kernel<DT, true, RU>, grid, lds, s, t, tile_base, R, nwrite, local, keep, sc, gate, tag, sig);
-    return launch(fused_reduce_kernel<DT, false, RU>, grid, lds, s, t, tile_base, R, nwrite, local, keep, sc, gate, tag, sig);
+    if (nt) return launch(fused_reduce_kernel<DT, true, RU, OUT>, grid, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
+    return launch(fused_reduce_kernel<DT, false, RU, OUT>, grid, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
 }
 
 hipError_t launch_fused_reduce(int dtype, const SegTables& t, int64_t tile_base, int64_t ntiles,
                                int R, int nwrite, const uint8_t* local, bool keep_unused, Scale sc,
-                               bool nontemporal, unsigned lds,
+                               bool nontemporal, unsigned lds, FlatBuckets flat,
                                const GateRecord* gate, uint32_t tag, DispatchSignal sig, hipStream_t s) {
     if (ntiles <= 0) return hipSuccess;
     const int keep = keep_unused ? 1 : 0;
     if (t.out != nullptr) {
         // 16-bit gradients, binary32 averages to separate tensors
-        constexpr int U = RU;
-        if (nwrite != 1 || (dtype != 1 && dtype != 2)) return hipErrorInvalidValue;
-        const dim3 grid(static_cast<unsigned>(ntiles));
-        if (dtype == 1)
-            return nontemporal ? launch(fused_reduce_kernel<1, true, U, true>, grid, lds, s, t, tile_base, R, nwrite, local, keep, sc, gate, tag, sig)
-                               : launch(fused_reduce_kernel<1, false, U, true>, grid, lds, s, t, tile_base, R, nwrite, local, keep, sc, gate, tag, sig);
-        return nontemporal ? launch(fused_reduce_kernel<2, true, U, true>, grid, lds, s, t, tile_base, R, nwrite, local, keep, sc, gate, tag, sig)
-                           : launch(fused_reduce_kernel<2, false, U, true>, grid, lds, s, t, tile_base, R, nwrite, local, keep, sc, gate, tag, sig);
+        if (nwrite != 1 || flat.slab0 != nullptr) return hipErrorInvalidValue;
+        switch (dtype) {
+            case 1: return fused_dispatch<1, OUT_BINARY32>(nontemporal, ntiles, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
+            case 2: return fused_dispatch<2, OUT_BINARY32>(nontemporal, ntiles, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
+            default: return hipErrorInvalidValue;
+        }
+    }
+    if (flat.slab0 != nullptr) {
+        switch (dtype) {
+            case 0: return fused_dispatch<0, OUT_FLAT>(nontemporal, ntiles, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
+            case 1: return fused_dispatch<1, OUT_FLAT>(nontemporal, ntiles, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
+            case 2: return fused_dispatch<2, OUT_FLAT>(nontemporal, ntiles, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
+            default: return hipErrorInvalidValue;
+        }
     }
     switch (dtype) {
-        case 0: return fused_dispatch<0>(nontemporal, ntiles, lds, s, t, tile_base, R, nwrite, local, keep, sc, gate, tag, sig);
-        case 1: return fused_dispatch<1>(nontemporal, ntiles, lds, s, t, tile_base, R, nwrite, local, keep, sc, gate, tag, sig);
-        case 2: return fused_dispatch<2>(nontemporal, ntiles, lds, s, t, tile_base, R, nwrite, local, keep, sc, gate, tag, sig);
+        case 0: return fused_dispatch<0, OUT_GRAD>(nontemporal, ntiles, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
+        case 1: return fused_dispatch<1, OUT_GRAD>(nontemporal, ntiles, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
+        case 2: return fused_dispatch<2, OUT_GRAD>(nontemporal, ntiles, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
         default: return hipErrorInvalidValue;
     }
 }
@@ -1076,18 +1167,18 @@ hipError_t launch_repair(int dtype, const SegTables& t, OrderState* st, const Ga
     if (t.out != nullptr) {
         if (nwrite != 1 || (dtype != 1 && dtype != 2)) return hipErrorInvalidValue;
         if (dtype == 1)
-            return nt ? launch(repair_kernel<1, true, U, true>, grid, 0u, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc)
-                      : launch(repair_kernel<1, false, U, true>, grid, 0u, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc);
-        return nt ? launch(repair_kernel<2, true, U, true>, grid, 0u, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc)
-                  : launch(repair_kernel<2, false, U, true>, grid, 0u, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc);
+            return nt ? launch(repair_kernel<1, true, U, OUT_BINARY32>, grid, 0u, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc)
+                      : launch(repair_kernel<1, false, U, OUT_BINARY32>, grid, 0u, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc);
+        return nt ? launch(repair_kernel<2, true, U, OUT_BINARY32>, grid, 0u, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc)
+                  : launch(repair_kernel<2, false, U, OUT_BINARY32>, grid, 0u, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc);
     }
     switch (dtype) {
-        case 0: return nt ? launch(repair_kernel<0, true, U>, grid, 0u, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc)
-                          : launch(repair_kernel<0, false, U>, grid, 0u, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc);
-        case 1: return nt ? launch(repair_kernel<1, true, U>, grid, 0u, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc)
-                          : launch(repair_kernel<1, false, U>, grid, 0u, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc);
-        case 2: return nt ? launch(repair_kernel<2, true, U>, grid, 0u, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc)
-                          : launch(repair_kernel<2, false, U>, grid, 0u, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc);
+        case 0: return nt ? launch(repair_kernel<0, true, U, OUT_GRAD>, grid, 0u, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc)
+                          : launch(repair_kernel<0, false, U, OUT_GRAD>, grid, 0u, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc);
+        case 1: return nt ? launch(repair_kernel<1, true, U, OUT_GRAD>, grid, 0u, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc)
+                          : launch(repair_kernel<1, false, U, OUT_GRAD>, grid, 0u, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc);
+        case 2: return nt ? launch(repair_kernel<2, true, U, OUT_GRAD>, grid, 0u, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc)
+                          : launch(repair_kernel<2, false, U, OUT_GRAD>, grid, 0u, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc);
         default: return hipErrorInvalidValue;
     }
 }

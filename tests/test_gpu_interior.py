@@ -79,3 +79,42 @@ def test_shifted_replicas_with_binary32_outputs(transport, out_skew):
     for i in range(n):
         inside[outs.offsets[i]:outs.offsets[i] + outs.nbytes(i)] = True
     assert (raw[~inside] == 0x55).all(), "bytes between the output tensors were written"
+
+
+@pytest.mark.parametrize("dtype", [FP32, FP16, BF16])
+@pytest.mark.parametrize("R", [1, 3, 8, 13])
+@pytest.mark.parametrize("masked", [False, True])
+def test_staged_buckets_in_one_pass_and_in_two(dtype, R, masked):
+    """The staged pipeline copies and reduces a bucket in one pass, or, when its kernels are timed
+    one by one, in two: flat buckets, averages and gradients have the same bits either way."""
+    d, harness = lib()
+    es = ES[dtype]
+    numel = edge_sizes(es)
+    n, cap = len(numel), 40000
+    rng = np.random.default_rng(740 + R)
+    reps = [workloads.gaussian_replica(740 + R, r, 0, numel, 1e-2, dtype) for r in range(R)]
+    for r in range(R):           # bits that arithmetic would not preserve must survive the copy
+        reps[r][3].view(np.uint32 if dtype == FP32 else np.uint16)[:2] = 0x7F800001 if dtype == FP32 else 0x7F81
+    used = np.ones((n, R), dtype=np.uint8) if not masked else (rng.random((n, R)) < 0.6).astype(np.uint8)
+    used[1] = 0 if masked else 1          # a parameter that nobody used: zeros everywhere
+    got = []
+    for timing in (0, 1):
+        grads = harness.DeviceGrads(numel, [dtype] * n, R, skew=[es * (3 * i % 8) for i in range(n)],
+                                    replica_skew=[es * (5 * r % (16 // es)) for r in range(R)], fill=0xFF)
+        for r in range(R):
+            grads.upload_replica(r, reps[r])
+        with harness.Session(grads, cap, 0) as s:
+            d.ddp_set_option(s.ctx, d.DDP_OPT_TIMING, timing)
+            for p in range(n - 1, -1, -1):
+                d.ddp_mark_ready_local(s.ctx, p, used[p].tolist())
+            d.ddp_finalize_backward(s.ctx)
+            d.ddp_synchronize(s.ctx)
+            flat = [[s.bucket_bytes(b, r).tobytes() for r in range(-1, R)] for b in range(s.n_buckets)]
+            bucket_of, offset = d.ddp_get_assignment(s.ctx, n)
+            for p in range(n):
+                for r in range(R):
+                    part = flat[bucket_of[p]][r + 1][offset[p] * es:(offset[p] + numel[p]) * es]
+                    expect = np.asarray(reps[r][p]).tobytes() if used[p][r] else bytes(numel[p] * es)
+                    assert part == expect, f"timing {timing} replica {r} parameter {p}: flat bucket"
+        got.append((flat, [grads.download(r, i).tobytes() for r in range(R) for i in range(n)]))
+    assert got[0] == got[1]
