@@ -120,9 +120,7 @@ typedef struct ddp_ctx ddp_ctx;
                                      launches are still enqueued in bucket order, but buckets on
                                      different streams may run at the same time.  Every stream waits
                                      for backward_stream like reduce_stream does, and at finalize
-                                     backward_stream is made to wait for all of them (directly in the
-                                     fused pipeline; through reduce_stream where the staged pipeline's
-                                     write-back or the bitmap step runs there).  Results are
+                                     backward_stream is made to wait for all of them.  Results are
                                      unchanged */
 #define DDP_OPT_REDUCE_BLOCKS_PER_CU 13 /* any time: cap on the thread blocks of the reduce kernels that
                                      are resident on one compute unit at a time (an LDS allocation
@@ -145,8 +143,7 @@ typedef struct ddp_ctx ddp_ctx;
                                      the API call that completes an iteration (the call after which
                                      the last bucket is launchable: every gradient exists, nothing
                                      of the backward pass is left to overlap with) are enqueued on
-                                     backward_stream instead of a reduction stream, fused pipeline
-                                     only.  Stream order then replaces the cross-stream event, whose
+                                     backward_stream instead of a reduction stream.  Stream order then replaces the cross-stream event, whose
                                      hand-over takes about 0.2 ms on this system when the waiting
                                      queue was armed long before the event fires.  0 = every bucket
                                      goes to a reduction stream */
@@ -163,8 +160,8 @@ typedef struct ddp_ctx ddp_ctx;
                                      each reduction up to n marks later.  Order, launch log and results
                                      are unchanged */
 #define DDP_OPT_FLAG_ORDER    18  /* between iterations: how a bucket launch on a reduction stream is ordered
-                                     after the work on backward_stream that produces its gradients
-                                     (fused pipeline).  -1 (default): through device flags where the
+                                     after the work on backward_stream that produces its gradients.
+                                     -1 (default): through device flags where the
                                      streams allow it -- ddp_mark_ready enqueues a one-block kernel on
                                      backward_stream that announces a sequence number, and a one-wave
                                      gate kernel in front of the bucket kernel waits for it; no event
@@ -242,9 +239,9 @@ int32_t ddp_set_option(ddp_ctx* ctx, int32_t option, int64_t value);
  * where that means "the library chooses"), except: DDP_OPT_COALESCE gives the
  * byte limit in effect (also when it was chosen from R) and DDP_OPT_FLAG_ORDER
  * gives 1 if the launches of the next iteration would be ordered through device
- * flags (the option allows it, the pipeline is the fused one, the buckets are
- * built and every reduction stream in use passed the concurrency probe), else
- * 0.  Also reads DDP_STAT_REPAIRED_LAUNCHES below.  Unknown option ->
+ * flags (the option allows it, the buckets are built, every reduction stream in
+ * use passed the concurrency probe, and not the staged pipeline with
+ * DDP_OPT_TIMING 1), else 0.  Also reads DDP_STAT_REPAIRED_LAUNCHES below.  Unknown option ->
  * DDP_ERR_ARG. */
 int32_t ddp_get_option(ddp_ctx* ctx, int32_t option, int64_t* value);
 

@@ -122,7 +122,6 @@ struct ddp_ctx {
     bool lane_used[kMaxLanes] = {};               // lane received work in the running iteration
     bool lane_ordered[kMaxLanes] = {};            // lane already waits for ev_call in the running API call
     int64_t launches_in_iter = 0;
-    bool tail_used = false;                       // some launch of the running iteration went to the backward stream
     bool backward_idle_in_call = false;           // backward stream was found drained in this API call
     bool ordered_in_call = false;   // backward stream position of this API call already examined
     int32_t hold_marks = 0;         // DDP_OPT_LAUNCH_HOLD: a launchable bucket waits for up to this many
@@ -202,6 +201,15 @@ int64_t coalesce_limit(const ddp_ctx* c) { return c->coalesce < 0 ? auto_coalesc
 
 // A launch is chained to the one in front of it if that one moves at least this many bytes.
 constexpr int64_t kChainMinTraffic = int64_t(160) << 20;
+
+// Whether a launch is one kernel, one that carries the gate check and reports its dispatch: always but
+// for the staged pipeline with its kernels timed one by one.
+bool one_kernel(const ddp_ctx* c) { return c->pipeline == DDP_PIPELINE_FUSED || c->timing != 1; }
+
+// Bytes that a launch over `launch_bytes` of bucket data moves.
+int64_t launch_traffic(const ddp_ctx* c, int64_t launch_bytes) {
+    return launch_bytes * (c->pipeline == DDP_PIPELINE_FUSED ? c->R + 1 : 2 * c->R + 1);
+}
 
 // Whether a launch over `launch_bytes` of bucket data is a long one: the cap on resident
 // blocks pays, and a second reduction stream does not, from about 360 MiB of traffic on
@@ -330,9 +338,9 @@ int32_t create_lane(ddp_ctx* c, int l) {
 }
 
 // Flags order the launches of the running API call if every reduction stream in use passed
-// the probe (fused pipeline only: its kernels carry the gate check).
+// the probe.
 bool flags_usable(const ddp_ctx* c) {
-    if (c->flag_order == 0 || c->pipeline != DDP_PIPELINE_FUSED || c->d_gate == nullptr) return false;
+    if (c->flag_order == 0 || !one_kernel(c) || c->d_gate == nullptr) return false;
     // (by default the second stream is only used if it passed the probe, see launch_range)
     const int lanes = c->n_streams < 0 ? 1 : c->n_streams;
     for (int l = 0; l < lanes; ++l)
@@ -392,7 +400,7 @@ int32_t launch_range(ddp_ctx* c, int32_t first, int32_t last, Target target) {
     const int64_t ntiles = c->h_tile0[seg_end] - tile_base;
     int64_t bytes = 0;
     for (int32_t b = first; b <= last; ++b) bytes += static_cast<int64_t>(c->plan.buckets[b].bytes());
-    const int64_t traffic = bytes * (c->R + 1);
+    const int64_t traffic = launch_traffic(c, bytes);
     const int32_t id = first + 65536 * (last - first);
     int lane = -1;                    // -1: the backward stream
     hipStream_t st = c->backward;
@@ -410,7 +418,6 @@ int32_t launch_range(ddp_ctx* c, int32_t first, int32_t last, Target target) {
         c->lane_used[lane] = true;
     } else {
         lane = -1;
-        c->tail_used = true;
     }
     const ddp::GateRecord* gate = nullptr;
     ddp::DispatchSignal sig{nullptr, 0};
@@ -436,7 +443,7 @@ int32_t launch_range(ddp_ctx* c, int32_t first, int32_t last, Target target) {
     const bool flags_in_use = c->call_by_flag || c->gates_in_iter > 0;
     const bool both_long = c->prev_launch_traffic >= c->cap_min_traffic && traffic >= c->cap_min_traffic;
     const bool chained = c->chain_launches != 0 && flags_in_use && c->prev_launch_ord != 0 && c->prev_launch_lane != lane &&
-                         ntiles > 0 && c->pipeline == DDP_PIPELINE_FUSED &&
+                         ntiles > 0 && one_kernel(c) &&
                          ((c->prev_launch_traffic >= kChainMinTraffic && !both_long) ||
                           (lane < 0 && traffic >= kChainMinTraffic));
     const long long wait_ticks = c->gate_wait_us * c->wall_clock_khz / 1000;
@@ -466,8 +473,7 @@ int32_t launch_range(ddp_ctx* c, int32_t first, int32_t last, Target target) {
         }
         c->lane_ordered[lane] = true;
     }
-    if (c->chain_launches != 0 && (c->call_by_flag || c->gates_in_iter > 0) && ntiles > 0 &&
-        c->pipeline == DDP_PIPELINE_FUSED) {
+    if (c->chain_launches != 0 && (c->call_by_flag || c->gates_in_iter > 0) && ntiles > 0 && one_kernel(c)) {
         // the launch reports when its last block starts, for whatever is chained behind it
         sig.word = &c->d_order->dispatched;
         sig.ord = ++c->launch_ord;
@@ -562,9 +568,11 @@ int32_t flush_deferred(ddp_ctx* c) {
     // produced and the backward stream has nothing left to overlap with.  The
     // call's launches then go to the backward stream: stream order replaces
     // the cross-stream event, whose hand-over costs about 0.2 ms here when the
-    // waiting queue was armed long before the event fires.  (The staged
-    // pipeline keeps its flat buffers and unpack on the reduction stream.)
-    const bool closing = c->tail_on_backward != 0 && c->pipeline == DDP_PIPELINE_FUSED &&
+    // waiting queue was armed long before the event fires.  (Staged pipeline: the write-back of the
+    // finalizing step follows on the same stream.  ResNet-50, R = 8, all marks in one call: 375 us a
+    // synchronization with the launches and the write-back on the reduction stream, 348 so; the eight
+    // small tensors in one bucket, R = 2: 46 and 8 us.)
+    const bool closing = c->tail_on_backward != 0 &&
                          todo.back() == static_cast<int32_t>(c->plan.buckets.size()) - 1;
     if (c->find_unused != 0 && c->pipeline == DDP_PIPELINE_FUSED && c->iter_zero) {
         // Skipping at the bucket level (Section 6.2.2): a bucket none of whose
@@ -1231,46 +1239,25 @@ int32_t ddp_finalize_backward(ddp_ctx* c) {
         if (st != DDP_OK) return st;
     }
     if (!c->plan_only) {
-        // Fused pipeline, no bitmap step: nothing else runs on the reduction side at finalize, and
-        // every reduction stream that received work joins the backward stream directly.  If the
+        // Every reduction stream that received work joins the backward stream directly.  If the
         // iteration's launches were ordered by device flags, so is the way back: each stream
         // stores the iteration's tag behind its last launch and one kernel on the backward
         // stream waits for the tags; the events behind it have fired by then.
-        const bool direct_join = c->pipeline == DDP_PIPELINE_FUSED && !c->iter_zero;
-        bool reduce_side_used = c->lane_used[0];
-        if (direct_join) {
-            const bool by_flag = c->gates_in_iter > 0;
-            const unsigned long long tag = static_cast<unsigned long long>(c->iteration + 1);
-            uint32_t mask = 0;
-            for (int l = 0; l < ddp_ctx::kMaxLanes; ++l)
-                if (c->lane_used[l] && c->lane[l] != c->backward) {
-                    HIPCHK(c, hipEventRecord(l == 0 ? c->ev_done : c->ev_join[l], c->lane[l]));
-                    if (by_flag) HIPCHK(c, ddp::launch_done(c->d_order, l, tag, c->lane[l]));
-                    mask |= 1u << l;
-                }
-            if (by_flag && mask)
-                HIPCHK(c, ddp::launch_join(c->d_order, mask, tag, c->gate_wait_us * c->wall_clock_khz / 1000, c->backward));
-            for (int l = 0; l < ddp_ctx::kMaxLanes; ++l)
-                if ((mask >> l) & 1u) HIPCHK(c, hipStreamWaitEvent(c->backward, l == 0 ? c->ev_done : c->ev_join[l], 0));
-            if (mask) c->tail_used = true;       // the iteration's launches end on the backward stream
-            reduce_side_used = false;            // (joined already)
-        } else {
-            // every reduction stream that received work in this iteration joins the caller's
-            for (int l = 1; l < ddp_ctx::kMaxLanes; ++l)
-                if (c->lane_used[l]) {
-                    HIPCHK(c, hipEventRecord(c->ev_join[l], c->lane[l]));
-                    HIPCHK(c, hipStreamWaitEvent(c->reduce, c->ev_join[l], 0));
-                    reduce_side_used = true;
-                }
-        }
-        // the interval of this iteration's bucket launches ends here if all of them ran on the
-        // reduction side, else on the backward stream below
-        // an iteration that used gates ends with the repair launch on the backward stream
-        if (c->gates_in_iter > 0) c->tail_used = true;
-        if (c->open_group != static_cast<size_t>(-1) && !c->tail_used) {
-            HIPCHK(c, hipEventRecord(c->timed[c->open_group].stop, c->reduce));
-            c->open_group = static_cast<size_t>(-1);
-        }
+        const bool by_flag = c->gates_in_iter > 0;
+        const unsigned long long tag = static_cast<unsigned long long>(c->iteration + 1);
+        uint32_t mask = 0;
+        for (int l = 0; l < ddp_ctx::kMaxLanes; ++l)
+            if (c->lane_used[l] && c->lane[l] != c->backward) {
+                HIPCHK(c, hipEventRecord(l == 0 ? c->ev_done : c->ev_join[l], c->lane[l]));
+                if (by_flag) HIPCHK(c, ddp::launch_done(c->d_order, l, tag, c->lane[l]));
+                mask |= 1u << l;
+            }
+        if (by_flag && mask)
+            HIPCHK(c, ddp::launch_join(c->d_order, mask, tag, c->gate_wait_us * c->wall_clock_khz / 1000, c->backward));
+        for (int l = 0; l < ddp_ctx::kMaxLanes; ++l)
+            if ((mask >> l) & 1u) HIPCHK(c, hipStreamWaitEvent(c->backward, l == 0 ? c->ev_done : c->ev_join[l], 0));
+        // from here on the backward stream is behind every bucket launch of the iteration, and
+        // what is left runs on it
         const int par = static_cast<int>(c->iteration & 1);
         if (c->iter_zero) {
             // The bitmap step of Section 4.2: the host bitmap goes to the device
@@ -1282,35 +1269,20 @@ int32_t ddp_finalize_backward(ddp_ctx* c) {
             }
             const size_t flag_bytes = static_cast<size_t>(n) * c->R;
             std::memcpy(c->h_local[par], c->local_cur.data(), flag_bytes);
-            HIPCHK(c, hipMemcpyAsync(c->d_local, c->h_local[par], flag_bytes, hipMemcpyHostToDevice, c->reduce));
-            HIPCHK(c, ddp::launch_bitmap_or(c->d_local, c->d_global, n, c->R, c->reduce));
+            HIPCHK(c, hipMemcpyAsync(c->d_local, c->h_local[par], flag_bytes, hipMemcpyHostToDevice, c->backward));
+            HIPCHK(c, ddp::launch_bitmap_or(c->d_local, c->d_global, n, c->R, c->backward));
             if (c->global_in_flight) HIPCHK(c, hipEventSynchronize(c->ev_global));
-            HIPCHK(c, hipMemcpyAsync(c->h_global, c->d_global, static_cast<size_t>(n), hipMemcpyDeviceToHost, c->reduce));
-            HIPCHK(c, hipEventRecord(c->ev_global, c->reduce));
+            HIPCHK(c, hipMemcpyAsync(c->h_global, c->d_global, static_cast<size_t>(n), hipMemcpyDeviceToHost, c->backward));
+            HIPCHK(c, hipEventRecord(c->ev_global, c->backward));
             c->global_in_flight = true;
-            reduce_side_used = true;
         }
-        if (c->pipeline == DDP_PIPELINE_STAGED) {
-            size_t slot;
-            int32_t rc;
-            if ((rc = timed_begin(c, DDP_K_UNPACK, -1, c->reduce, &slot)) != DDP_OK) return rc;
-            HIPCHK(c, ddp::launch_unpack(c->tables, 0, c->h_tile0[n],
-                                         c->slabs + static_cast<int64_t>(c->R) * c->slab_stride,
-                                         c->write_all ? c->R : 1, c->iter_zero ? c->d_global : nullptr,
-                                         c->find_unused != 0, c->reduce));
-            if ((rc = timed_end(c, slot, c->reduce)) != DDP_OK) return rc;
-            reduce_side_used = true;
-        }
-        // the backward stream waits for whatever ran on the reduction side
-        if (c->backward != c->reduce && reduce_side_used) {
-            HIPCHK(c, hipEventRecord(c->ev_done, c->reduce));
-            HIPCHK(c, hipStreamWaitEvent(c->backward, c->ev_done, 0));
-        }
+        const bool staged = c->pipeline == DDP_PIPELINE_STAGED;
         if (c->gates_in_iter > 0) {
             // Gates wait a bounded time.  Launches whose gate gave up did nothing; they are
             // redone now that every gradient exists (normally there is none and the launch
             // ends at once).  With a zero participation flag in the iteration the whole
-            // bitmap is on the device by now (copied above on the reduction stream).
+            // bitmap is on the device by now (copied above).
+            const ddp::FlatBuckets flat{staged ? c->slabs : nullptr, staged ? c->slab_stride : 0};
             uint32_t dtypes_seen = 0;
             for (const ddp::BucketInfo& bk : c->plan.buckets) dtypes_seen |= 1u << bk.dtype;
             for (int dt = 0; dt < 3; ++dt)
@@ -1321,16 +1293,26 @@ int32_t ddp_finalize_backward(ddp_ctx* c) {
                                                  static_cast<uint32_t>(c->iteration + 1), c->R,
                                                  c->write_all ? c->R : 1, c->iter_zero ? c->d_local : nullptr,
                                                  c->find_unused != 0, make_scale(c->R), 2 * c->num_cus,
-                                                 c->nontemporal != 0, c->backward));
+                                                 c->nontemporal != 0, flat, c->backward));
+        }
+        if (c->open_group != static_cast<size_t>(-1)) {      // closes this iteration's bucket launches
+            HIPCHK(c, hipEventRecord(c->timed[c->open_group].stop, c->backward));
+            c->open_group = static_cast<size_t>(-1);
+        }
+        if (staged) {
+            size_t slot;
+            int32_t rc;
+            if ((rc = timed_begin(c, DDP_K_UNPACK, -1, c->backward, &slot)) != DDP_OK) return rc;
+            HIPCHK(c, ddp::launch_unpack(c->tables, 0, c->h_tile0[n],
+                                         c->slabs + static_cast<int64_t>(c->R) * c->slab_stride,
+                                         c->write_all ? c->R : 1, c->iter_zero ? c->d_global : nullptr,
+                                         c->find_unused != 0, c->backward));
+            if ((rc = timed_end(c, slot, c->backward)) != DDP_OK) return rc;
         }
         // from here on the backward stream is behind everything of this iteration
         if (c->pin_ready_iter == c->iteration) {      // the flag staging buffer was used: free for reuse after this
             HIPCHK(c, hipEventRecord(c->ev_local[par], c->backward));
             c->local_in_flight[par] = true;
-        }
-        if (c->open_group != static_cast<size_t>(-1)) {      // closes this iteration's bucket launches
-            HIPCHK(c, hipEventRecord(c->timed[c->open_group].stop, c->backward));
-            c->open_group = static_cast<size_t>(-1);
         }
     }
     c->log_closed.swap(c->log_running);
@@ -1352,7 +1334,6 @@ int32_t ddp_finalize_backward(ddp_ctx* c) {
     c->iter_zero = false;
     for (bool& b : c->lane_used) b = false;
     c->launches_in_iter = 0;
-    c->tail_used = false;
     c->gates_in_iter = 0;
     c->prev_launch_ord = 0;
     ++c->iteration;

@@ -195,7 +195,7 @@ hipError_t launch_gate(OrderState* st, unsigned long long need, long long wait_t
 // (rec[0..nb)).  `blocks` persistent blocks; normally there is nothing to do.
 hipError_t launch_repair(int dtype, const SegTables& t, OrderState* st, const GateRecord* rec, int nb, uint32_t tag,
                          int R, int nwrite, const uint8_t* local, bool keep_unused, Scale sc,
-                         int blocks, bool nontemporal, hipStream_t s);
+                         int blocks, bool nontemporal, FlatBuckets flat, hipStream_t s);
 
 // Bounded probe: one wave on stream `waiter` polls word[0] for `value` (at most
 // wait_ticks), then a one-thread kernel on stream `writer` stores it.

@@ -839,7 +839,7 @@ __global__ __launch_bounds__(BLOCK) void repair_kernel(SegTables t, OrderState* 
                                                        const GateRecord* __restrict__ rec,
                                                        int nb, uint32_t tag, int R, int nwrite,
                                                        const uint8_t* __restrict__ local,
-                                                       int keep_unused, Scale sc) {
+                                                       int keep_unused, Scale sc, FlatBuckets flat) {
     // rec[nb] is the row's summary: no gate of the iteration gave up (the normal case), nothing to look for
     if (rec[nb].failed_tag != tag) return;
     for (int b = 0; b < nb; ++b) {
@@ -847,7 +847,7 @@ __global__ __launch_bounds__(BLOCK) void repair_kernel(SegTables t, OrderState* 
         if (r.failed_tag != tag || r.dtype != DT) continue;
         if (blockIdx.x == 0 && threadIdx.x == 0) st->repaired += 1;   // (repair launches run one after the other)
         for (int64_t i = blockIdx.x; i < r.ntiles; i += gridDim.x)
-            fused_tile<DT, NT, U, OUT>(t, r.tile_base + i, R, nwrite, local, keep_unused, sc, FlatBuckets{nullptr, 0});
+            fused_tile<DT, NT, U, OUT>(t, r.tile_base + i, R, nwrite, local, keep_unused, sc, flat);
     }
 }
 
@@ -1157,28 +1157,40 @@ hipError_t launch_gate(OrderState* st, unsigned long long need, long long wait_t
     return after_launch();
 }
 
+template <int DT, int OUT>
+static hipError_t repair_dispatch(bool nt, int blocks, hipStream_t s, const SegTables& t, OrderState* st,
+                                  const GateRecord* rec, int nb, uint32_t tag, int R, int nwrite,
+                                  const uint8_t* local, int keep, Scale sc, FlatBuckets flat) {
+    const dim3 grid(static_cast<unsigned>(blocks));
+    if (nt) return launch(repair_kernel<DT, true, RU, OUT>, grid, 0u, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc, flat);
+    return launch(repair_kernel<DT, false, RU, OUT>, grid, 0u, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc, flat);
+}
+
 hipError_t launch_repair(int dtype, const SegTables& t, OrderState* st, const GateRecord* rec, int nb, uint32_t tag,
                          int R, int nwrite, const uint8_t* local, bool keep_unused, Scale sc,
-                         int blocks, bool nt, hipStream_t s) {
+                         int blocks, bool nt, FlatBuckets flat, hipStream_t s) {
     if (blocks <= 0 || nb <= 0) return hipSuccess;
-    constexpr int U = RU;
-    const dim3 grid(static_cast<unsigned>(blocks));
     const int keep = keep_unused ? 1 : 0;
     if (t.out != nullptr) {
-        if (nwrite != 1 || (dtype != 1 && dtype != 2)) return hipErrorInvalidValue;
-        if (dtype == 1)
-            return nt ? launch(repair_kernel<1, true, U, OUT_BINARY32>, grid, 0u, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc)
-                      : launch(repair_kernel<1, false, U, OUT_BINARY32>, grid, 0u, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc);
-        return nt ? launch(repair_kernel<2, true, U, OUT_BINARY32>, grid, 0u, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc)
-                  : launch(repair_kernel<2, false, U, OUT_BINARY32>, grid, 0u, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc);
+        if (nwrite != 1 || flat.slab0 != nullptr) return hipErrorInvalidValue;
+        switch (dtype) {
+            case 1: return repair_dispatch<1, OUT_BINARY32>(nt, blocks, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc, flat);
+            case 2: return repair_dispatch<2, OUT_BINARY32>(nt, blocks, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc, flat);
+            default: return hipErrorInvalidValue;
+        }
+    }
+    if (flat.slab0 != nullptr) {
+        switch (dtype) {
+            case 0: return repair_dispatch<0, OUT_FLAT>(nt, blocks, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc, flat);
+            case 1: return repair_dispatch<1, OUT_FLAT>(nt, blocks, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc, flat);
+            case 2: return repair_dispatch<2, OUT_FLAT>(nt, blocks, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc, flat);
+            default: return hipErrorInvalidValue;
+        }
     }
     switch (dtype) {
-        case 0: return nt ? launch(repair_kernel<0, true, U, OUT_GRAD>, grid, 0u, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc)
-                          : launch(repair_kernel<0, false, U, OUT_GRAD>, grid, 0u, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc);
-        case 1: return nt ? launch(repair_kernel<1, true, U, OUT_GRAD>, grid, 0u, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc)
-                          : launch(repair_kernel<1, false, U, OUT_GRAD>, grid, 0u, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc);
-        case 2: return nt ? launch(repair_kernel<2, true, U, OUT_GRAD>, grid, 0u, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc)
-                          : launch(repair_kernel<2, false, U, OUT_GRAD>, grid, 0u, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc);
+        case 0: return repair_dispatch<0, OUT_GRAD>(nt, blocks, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc, flat);
+        case 1: return repair_dispatch<1, OUT_GRAD>(nt, blocks, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc, flat);
+        case 2: return repair_dispatch<2, OUT_GRAD>(nt, blocks, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc, flat);
         default: return hipErrorInvalidValue;
     }
 }

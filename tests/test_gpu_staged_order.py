@@ -1,0 +1,77 @@
+"""GPU parity of the staged pipeline's launches under device-flag ordering: gradients start as NaN
+and are produced by the synthetic backward stream after a delay, so a launch that ran ahead of its
+gate, or one that was skipped and not repaired, shows in the flat buckets and in the results.  A
+gate wait of 0 makes every gate give up without waiting (every kernel still ends normally)."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+
+pytestmark = pytest.mark.gpu
+
+FP32, FP16, BF16 = 0, 1, 2
+STAGED = 0
+
+
+def lib():
+    import paper_2006_15704_amd as d
+    from paper_2006_15704_amd import harness
+    return d, harness
+
+
+@pytest.mark.parametrize("dtype", [FP32, FP16, BF16])
+@pytest.mark.parametrize("gate_wait_us", [100000, 0])
+@pytest.mark.parametrize("tail_on_backward", [1, 0])
+def test_staged_launches_wait_for_the_backward_stream(dtype, gate_wait_us, tail_on_backward):
+    d, harness = lib()
+    import torch
+    numel = [5, 3000, 3 * 4096 + 7, 8192, 1, 777, 2 * 8192, 4000, 60, 5000]
+    n, R, cap = len(numel), 3, 32 << 10
+    es = 4 if dtype == FP32 else 2
+    dtypes = [dtype] * n
+    grads = harness.DeviceGrads(numel, dtypes, R, fill=0xFF)
+    keep = harness.DeviceGrads(numel, dtypes, 2, fill=0)
+    srcs, reps, wants = [], [], []
+    for it in range(2):
+        reps.append([workloads.gaussian_replica(680 + it, r, 0, numel, 1.0, dtype) for r in range(R)])
+        srcs.append(harness.DeviceGrads(numel, dtypes, R))
+        for r in range(R):
+            srcs[it].upload_replica(r, reps[it][r])
+        wants.append(oracle.synchronize(numel, dtypes, cap, reps[it]))
+    streams = None
+    for _ in range(8):           # a pair of streams on separate hardware queues, if there is one
+        s = harness.Session(grads, cap, STAGED, streams=streams)
+        if d.ddp_get_option(s.ctx, d.DDP_OPT_FLAG_ORDER):
+            break
+        s.close()
+        streams = (torch.cuda.Stream(), torch.cuda.Stream())
+    else:
+        pytest.skip("no pair of streams on separate hardware queues was found")
+    with s:
+        d.ddp_set_option(s.ctx, d.DDP_OPT_COALESCE, 0)
+        d.ddp_set_option(s.ctx, d.DDP_OPT_REDUCE_STREAMS, 2)
+        d.ddp_set_option(s.ctx, d.DDP_OPT_TAIL_ON_BACKWARD, tail_on_backward)
+        d.ddp_set_option(s.ctx, d.DDP_OPT_GATE_WAIT_US, gate_wait_us)
+        assert d.ddp_get_option(s.ctx, d.DDP_OPT_FLAG_ORDER) == 1
+        order = list(range(n - 1, -1, -1))
+        for it in range(2):      # two iterations enqueued without host synchronization in between
+            d.ddp_synth_backward(s.ctx, order, [150_000] * n, srcs[it].ptrs(), True)
+            d.ddp_finalize_backward(s.ctx)
+            assert d.ddp_get_launch_log(s.ctx, 1) == wants[it][2]
+            with torch.cuda.stream(s.backward_stream):
+                keep.bufs[it].copy_(grads.bufs[0], non_blocking=True)
+        d.ddp_synchronize(s.ctx)
+        torch.cuda.synchronize()
+        repaired = d.ddp_get_option(s.ctx, d.DDP_STAT_REPAIRED_LAUNCHES)
+        assert repaired == 0 if gate_wait_us else repaired >= 2
+        bucket_of, offset = d.ddp_get_assignment(s.ctx, n)
+        flat = [[s.bucket_bytes(b, r).tobytes() for r in range(-1, R)] for b in range(s.n_buckets)]
+        for p in range(n):       # the buckets hold the second iteration's gradients and average
+            at = slice(int(offset[p]) * es, (int(offset[p]) + numel[p]) * es)
+            assert flat[bucket_of[p]][0][at] == wants[1][0][p].tobytes(), f"averaged bucket, parameter {p}"
+            for r in range(R):
+                assert flat[bucket_of[p]][r + 1][at] == np.asarray(reps[1][r][p]).tobytes(), f"replica {r} parameter {p}"
+    for it in range(2):
+        for p in range(n):
+            assert keep.download(it, p).tobytes() == wants[it][0][p].tobytes(), f"iteration {it} parameter {p}"
