@@ -241,8 +241,9 @@ if not os.path.exists(_fast_path):
 _spec = _ilu.spec_from_file_location("_ddp_fastcall", _fast_path)
 _fast = _ilu.module_from_spec(_spec)
 _spec.loader.exec_module(_fast)
-_fast.bind(C.cast(_lib.ddp_mark_ready, _vp).value, C.cast(_lib.ddp_finalize_backward, _vp).value)
-_fast_mark, _fast_finalize = _fast.mark_ready, _fast.finalize_backward
+_fast.bind(C.cast(_lib.ddp_mark_ready, _vp).value, C.cast(_lib.ddp_finalize_backward, _vp).value,
+           C.cast(_lib.ddp_mark_ready_local, _vp).value)
+_fast_mark, _fast_finalize, _fast_mark_local = _fast.mark_ready, _fast.finalize_backward, _fast.mark_ready_local
 
 
 def ddp_mark_ready(ctx, param_id: int) -> None:
@@ -253,10 +254,9 @@ def ddp_mark_ready(ctx, param_id: int) -> None:
 
 def ddp_mark_ready_local(ctx, param_id: int, used) -> None:
     """used: R flags, non-zero = that replica produced a gradient for the parameter."""
-    arr = np.ascontiguousarray([1 if u else 0 for u in used], dtype=np.uint8)
-    if arr.size != _replicas.get(ctx.value, arr.size):     # the library reads exactly R bytes
-        raise ValueError(f"used has {arr.size} flags, the context has {_replicas[ctx.value]} replicas")
-    _check(ctx, _lib.ddp_mark_ready_local(ctx, param_id, _as(arr, C.c_uint8)))
+    status = _fast_mark_local(ctx.value, param_id, used, _replicas.get(ctx.value, -1))
+    if status < 0:
+        _check(ctx, status)
 
 
 def ddp_get_global_used(ctx, n: int) -> np.ndarray:

@@ -81,24 +81,19 @@ struct ddp_ctx {
     void* d_tables = nullptr;                // one allocation holding all segment tables
     int32_t* d_tile_seg = nullptr;           // [tiles] segment index of every tile
     ddp::SegTables tables{};
-    // participation flags: [segment][replica], 1 = the replica used the parameter
+    // participation: one mask per segment, bit r = replica r used the parameter
     int32_t find_unused = 0;                 // 1: parameters nobody used keep their gradients
-    std::vector<uint8_t> local_cur;          // running iteration (rows of marked parameters are valid)
-    std::vector<uint8_t> acc_used;           // recorded by ddp_no_sync_accumulate since the last finalize
-    std::vector<uint8_t> bucket_zero;        // per bucket: some flag of the running iteration is 0
-    bool iter_zero = false;                  // any flag of the running iteration is 0
+    std::vector<uint64_t> local_cur;         // running iteration (entries of marked parameters are valid)
+    std::vector<uint64_t> acc_used;          // recorded by ddp_no_sync_accumulate since the last finalize
+    std::vector<uint8_t> bucket_zero;        // per bucket: some bit of the running iteration is 0
+    bool iter_zero = false;                  // any bit of the running iteration is 0
     int64_t iteration = 0;
-    int64_t pin_ready_iter = -1;             // iteration for which the pinned staging buffer was claimed
     std::vector<uint8_t> global_closed;      // [n] host view of the closed iteration's global bitmap
     bool global_on_device = false;           // closed iteration: the bitmap kernel ran, result in h_global
-    uint8_t* d_local = nullptr;              // [G*R]
+    uint64_t* d_local = nullptr;             // [G]
     uint8_t* d_global = nullptr;             // [G]
-    uint8_t* h_local[2] = {nullptr, nullptr};   // pinned staging, one per iteration parity
-    uint8_t* h_global = nullptr;             // pinned
-    hipEvent_t ev_local[2] = {nullptr, nullptr};
+    uint8_t* h_global = nullptr;             // pinned, written by the bitmap kernel
     hipEvent_t ev_global = nullptr;
-    bool local_in_flight[2] = {false, false};
-    bool global_in_flight = false;
     void** d_micro = nullptr;
     void** h_micro = nullptr;                // pinned
     void** d_emit = nullptr;
@@ -481,25 +476,17 @@ int32_t launch_range(ddp_ctx* c, int32_t first, int32_t last, Target target) {
         c->prev_launch_lane = lane;
         c->prev_launch_traffic = traffic;
     }
-    // Participation flags travel to the device only for launches that hold a
-    // zero flag (a replica that did not use a parameter, or a parameter nobody
-    // marked); everything else runs without a flag table.
-    const uint8_t* d_flags = nullptr;
+    // Participation masks travel to the device only for launches that hold a
+    // zero bit (a replica that did not use a parameter, or a parameter nobody
+    // marked); everything else runs without a mask table.
+    const uint64_t* d_flags = nullptr;
     bool need_flags = false;
     for (int32_t b = first; b <= last; ++b) need_flags = need_flags || c->bucket_zero[b] != 0;
     if (need_flags) {
-        const int par = static_cast<int>(c->iteration & 1);
-        if (c->pin_ready_iter != c->iteration) {      // first use in this iteration: the copies of
-            if (c->local_in_flight[par])               // two iterations ago must have left the buffer
-                HIPCHK(c, hipEventSynchronize(c->ev_local[par]));
-            c->pin_ready_iter = c->iteration;
-        }
-        const size_t off = static_cast<size_t>(seg_begin) * c->R;
-        const size_t len = static_cast<size_t>(seg_end - seg_begin) * c->R;
-        std::memcpy(c->h_local[par] + off, c->local_cur.data() + off, len);
         // After the ordering above the stream is also behind the previous iteration's readers of
-        // the table; finalize records ev_local[par] once every stream of the iteration is joined.
-        HIPCHK(c, hipMemcpyAsync(c->d_local + off, c->h_local[par] + off, len, hipMemcpyHostToDevice, st));
+        // the table (or its gate gave up and nothing is written).
+        HIPCHK(c, ddp::launch_mask_write(c->d_local + seg_begin, c->local_cur.data() + seg_begin, seg_end - seg_begin,
+                                         gate, static_cast<uint32_t>(c->iteration + 1), st));
         d_flags = c->d_local;
     }
     const ddp::Scale sc = make_scale(c->R);
@@ -547,8 +534,8 @@ int32_t launch_range(ddp_ctx* c, int32_t first, int32_t last, Target target) {
 bool bucket_all_unused(const ddp_ctx* c, int32_t b) {
     if (!c->bucket_zero[b]) return false;
     const ddp::BucketInfo& bk = c->plan.buckets[b];
-    const size_t begin = static_cast<size_t>(bk.seg_begin) * c->R;
-    const size_t end = begin + bk.params.size() * static_cast<size_t>(c->R);
+    const size_t begin = static_cast<size_t>(bk.seg_begin);
+    const size_t end = begin + bk.params.size();
     for (size_t k = begin; k < end; ++k)
         if (c->local_cur[k]) return false;
     return true;
@@ -648,10 +635,6 @@ void release_build(ddp_ctx* c) {
     if (c->d_micro) (void)hipFree(c->d_micro);
     if (c->d_gate) (void)hipFree(c->d_gate);
     c->d_gate = nullptr;
-    for (int k = 0; k < 2; ++k) {
-        if (c->h_local[k]) (void)hipHostFree(c->h_local[k]);
-        c->h_local[k] = nullptr;
-    }
     if (c->h_global) (void)hipHostFree(c->h_global);
     if (c->h_micro) (void)hipHostFree(c->h_micro);
     c->slabs = nullptr; c->d_tables = nullptr; c->d_tile_seg = nullptr; c->d_local = nullptr;
@@ -674,7 +657,7 @@ void release_device(ddp_ctx* c) {
     }
     drop_timed(c);
     release_build(c);
-    for (hipEvent_t* e : {&c->ev_done, &c->ev_micro, &c->ev_emit, &c->ev_local[0], &c->ev_local[1], &c->ev_global})
+    for (hipEvent_t* e : {&c->ev_done, &c->ev_micro, &c->ev_emit, &c->ev_global})
         if (*e) { (void)hipEventDestroy(*e); *e = nullptr; }
     if (c->d_order_mem) (void)hipFree(c->d_order_mem);
     c->d_order_mem = nullptr; c->d_order = nullptr; c->d_probe = nullptr;
@@ -734,8 +717,6 @@ int32_t ddp_create(ddp_ctx** out, int32_t R, int32_t device, void* reduce_stream
         if (e == hipSuccess) e = hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, device);
         if (e == hipSuccess && lds >= 64 * 1024) c->lds_per_cu = lds;
         if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_done, kOrderEvent);
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_local[0], hipEventDisableTiming);
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_local[1], hipEventDisableTiming);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_global, hipEventDisableTiming);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_micro, hipEventDisableTiming);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_emit, hipEventDisableTiming);
@@ -958,8 +939,8 @@ static int32_t build_internal(ddp_ctx* c, uint64_t cap_bytes, const std::vector<
     const int32_t nb = static_cast<int32_t>(c->plan.buckets.size());
     c->used_running.assign(n, 0);
     c->used_closed.assign(n, 0);
-    c->local_cur.assign(static_cast<size_t>(n) * c->R, 0);
-    c->acc_used.assign(static_cast<size_t>(n) * c->R, 0);
+    c->local_cur.assign(n, 0);
+    c->acc_used.assign(n, 0);
     c->bucket_zero.assign(nb, 0);
     c->global_closed.assign(n, 0);
 
@@ -1010,11 +991,8 @@ static int32_t build_internal(ddp_ctx* c, uint64_t cap_bytes, const std::vector<
             c->tables.tile_seg = c->d_tile_seg;
         }
 
-        const size_t flag_bytes = static_cast<size_t>(n) * R;
-        HIPCHK(c, hipMalloc(reinterpret_cast<void**>(&c->d_local), flag_bytes + 16));
+        HIPCHK(c, hipMalloc(reinterpret_cast<void**>(&c->d_local), sizeof(uint64_t) * n));
         HIPCHK(c, hipMalloc(reinterpret_cast<void**>(&c->d_global), static_cast<size_t>(n) + 16));
-        for (int k = 0; k < 2; ++k)
-            HIPCHK(c, hipHostMalloc(reinterpret_cast<void**>(&c->h_local[k]), flag_bytes, hipHostMallocDefault));
         HIPCHK(c, hipHostMalloc(reinterpret_cast<void**>(&c->h_global), static_cast<size_t>(n), hipHostMallocDefault));
         HIPCHK(c, hipMalloc(reinterpret_cast<void**>(&c->d_micro), sizeof(void*) * R * n));
         HIPCHK(c, hipHostMalloc(reinterpret_cast<void**>(&c->h_micro), sizeof(void*) * R * n, hipHostMallocDefault));
@@ -1048,7 +1026,7 @@ int32_t ddp_rebuild_buckets(ddp_ctx* c, uint64_t cap_bytes) {
     if (!c->built) return fail(c, DDP_ERR_STATE, "ddp_rebuild_buckets before ddp_build_buckets");
     if (c->tracker.marks() != 0 || !c->deferred.empty())
         return fail(c, DDP_ERR_STATE, "ddp_rebuild_buckets in the middle of an iteration");
-    for (uint8_t u : c->acc_used)
+    for (uint64_t u : c->acc_used)
         if (u) return fail(c, DDP_ERR_STATE, "ddp_rebuild_buckets between a no_sync accumulation and its synchronization");
     const int32_t n = static_cast<int32_t>(c->plan.params.size());
     // visit order: the trace of the closed iteration, then what it never saw in
@@ -1072,10 +1050,7 @@ int32_t ddp_rebuild_buckets(ddp_ctx* c, uint64_t cap_bytes) {
             c->global_on_device = false;
         }
         drop_timed(c);
-        c->local_in_flight[0] = c->local_in_flight[1] = false;
-        c->global_in_flight = false;
         c->micro_in_flight = false;
-        c->pin_ready_iter = -1;
     }
     const std::vector<uint8_t> keep_global = c->global_closed, keep_used = c->used_closed;
     c->built = false;
@@ -1130,23 +1105,19 @@ int32_t ddp_get_bucket_ptr(const ddp_ctx* c, int32_t b, int32_t r, void** ptr) {
     return DDP_OK;
 }
 
-// Writes the participation row of a parameter: used[r] (null = every replica),
-// OR what no_sync iterations recorded.  Returns whether any replica used it.
-static bool set_participation(ddp_ctx* c, int32_t param_id, const uint8_t* used) {
+static uint64_t everyone_mask(const ddp_ctx* c) { return c->R >= 64 ? ~uint64_t(0) : (uint64_t(1) << c->R) - 1; }
+
+// Writes the participation mask of a parameter: `used`, OR what no_sync
+// iterations recorded.  Returns whether any replica used it.
+static bool set_participation(ddp_ctx* c, int32_t param_id, uint64_t used) {
     const ddp::ParamInfo& p = c->plan.params[param_id];
-    const size_t row = static_cast<size_t>(p.segment) * c->R;
-    bool any = false, zero = false;
-    for (int32_t r = 0; r < c->R; ++r) {
-        const uint8_t eff = ((used == nullptr || used[r] != 0) || c->acc_used[row + r] != 0) ? 1 : 0;
-        c->local_cur[row + r] = eff;
-        any = any || eff != 0;
-        zero = zero || eff == 0;
-    }
-    if (zero) {
+    const uint64_t eff = used | c->acc_used[p.segment];
+    c->local_cur[p.segment] = eff;
+    if (eff != everyone_mask(c)) {
         c->bucket_zero[p.bucket] = 1;
         c->iter_zero = true;
     }
-    return any;
+    return eff != 0;
 }
 
 // What a single ready-mark call does with the buckets that are launchable: enqueue them now
@@ -1166,7 +1137,7 @@ static int32_t flush_or_hold(ddp_ctx* c) {
     return now ? flush_deferred(c) : DDP_OK;
 }
 
-static int32_t mark_one(ddp_ctx* c, int32_t param_id, const uint8_t* used) {
+static int32_t mark_one(ddp_ctx* c, int32_t param_id, uint64_t used) {
     std::vector<int32_t> launch;
     const int rc = c->tracker.mark(param_id, launch);
     if (rc == -1) return fail(c, DDP_ERR_ARG, "ddp_mark_ready: parameter id out of range");
@@ -1183,7 +1154,7 @@ int32_t ddp_mark_ready(ddp_ctx* c, int32_t param_id) {
     if (!c) return DDP_ERR_ARG;
     if (!c->built) return fail(c, DDP_ERR_STATE, "ddp_mark_ready before ddp_build_buckets");
     new_call(c);
-    const int32_t st = mark_one(c, param_id, nullptr);
+    const int32_t st = mark_one(c, param_id, everyone_mask(c));
     if (st != DDP_OK) return st;
     return flush_or_hold(c);
 }
@@ -1193,7 +1164,10 @@ int32_t ddp_mark_ready_local(ddp_ctx* c, int32_t param_id, const uint8_t* used) 
     if (!c->built) return fail(c, DDP_ERR_STATE, "ddp_mark_ready_local before ddp_build_buckets");
     if (!used) return fail(c, DDP_ERR_ARG, "ddp_mark_ready_local: used is null");
     new_call(c);
-    const int32_t st = mark_one(c, param_id, used);
+    uint64_t mask = 0;
+    for (int32_t r = 0; r < c->R; ++r)
+        if (used[r] != 0) mask |= uint64_t(1) << r;
+    const int32_t st = mark_one(c, param_id, mask);
     if (st != DDP_OK) return st;
     return flush_or_hold(c);
 }
@@ -1203,7 +1177,7 @@ int32_t ddp_mark_ready_many(ddp_ctx* c, const int32_t* ids, int32_t count) {
     if (!c->built) return fail(c, DDP_ERR_STATE, "ddp_mark_ready_many before ddp_build_buckets");
     new_call(c);
     for (int32_t k = 0; k < count; ++k) {
-        const int32_t st = mark_one(c, ids[k], nullptr);
+        const int32_t st = mark_one(c, ids[k], everyone_mask(c));
         if (st != DDP_OK) {
             (void)flush_deferred(c);   // what the earlier marks completed is still launched
             return st;
@@ -1228,10 +1202,7 @@ int32_t ddp_finalize_backward(ddp_ctx* c) {
         // before this point was complete, so only the buckets in `launch` can
         // contain such parameters.
         for (int32_t i = 0; i < n; ++i)
-            if (!c->tracker.marked(i)) {
-                static const uint8_t nobody[DDP_MAX_REPLICAS] = {0};
-                if (set_participation(c, i, nobody)) c->used_running[i] = 1;
-            }
+            if (!c->tracker.marked(i) && set_participation(c, i, 0)) c->used_running[i] = 1;
     }
     for (int32_t b : launch) note_launch(c, b, marks);
     {
@@ -1258,23 +1229,12 @@ int32_t ddp_finalize_backward(ddp_ctx* c) {
             if ((mask >> l) & 1u) HIPCHK(c, hipStreamWaitEvent(c->backward, l == 0 ? c->ev_done : c->ev_join[l], 0));
         // from here on the backward stream is behind every bucket launch of the iteration, and
         // what is left runs on it
-        const int par = static_cast<int>(c->iteration & 1);
         if (c->iter_zero) {
             // The bitmap step of Section 4.2: the host bitmap goes to the device
-            // with a non-blocking copy and one extra reduction (an OR over the
-            // replicas) yields the parameters that somebody used.
-            if (c->pin_ready_iter != c->iteration) {
-                if (c->local_in_flight[par]) HIPCHK(c, hipEventSynchronize(c->ev_local[par]));
-                c->pin_ready_iter = c->iteration;
-            }
-            const size_t flag_bytes = static_cast<size_t>(n) * c->R;
-            std::memcpy(c->h_local[par], c->local_cur.data(), flag_bytes);
-            HIPCHK(c, hipMemcpyAsync(c->d_local, c->h_local[par], flag_bytes, hipMemcpyHostToDevice, c->backward));
-            HIPCHK(c, ddp::launch_bitmap_or(c->d_local, c->d_global, n, c->R, c->backward));
-            if (c->global_in_flight) HIPCHK(c, hipEventSynchronize(c->ev_global));
-            HIPCHK(c, hipMemcpyAsync(c->h_global, c->d_global, static_cast<size_t>(n), hipMemcpyDeviceToHost, c->backward));
+            // with the launch that ORs it over the replicas, which yields the
+            // parameters that somebody used.
+            HIPCHK(c, ddp::launch_bitmap_or(c->d_local, c->d_global, c->h_global, c->local_cur.data(), n, c->backward));
             HIPCHK(c, hipEventRecord(c->ev_global, c->backward));
-            c->global_in_flight = true;
         }
         const bool staged = c->pipeline == DDP_PIPELINE_STAGED;
         if (c->gates_in_iter > 0) {
@@ -1309,11 +1269,6 @@ int32_t ddp_finalize_backward(ddp_ctx* c) {
                                          c->find_unused != 0, c->backward));
             if ((rc = timed_end(c, slot, c->backward)) != DDP_OK) return rc;
         }
-        // from here on the backward stream is behind everything of this iteration
-        if (c->pin_ready_iter == c->iteration) {      // the flag staging buffer was used: free for reuse after this
-            HIPCHK(c, hipEventRecord(c->ev_local[par], c->backward));
-            c->local_in_flight[par] = true;
-        }
     }
     c->log_closed.swap(c->log_running);
     c->log_running.clear();
@@ -1322,12 +1277,7 @@ int32_t ddp_finalize_backward(ddp_ctx* c) {
     c->used_closed = c->used_running;
     std::fill(c->used_running.begin(), c->used_running.end(), 0);
     // host view of the global bitmap (all ones unless a flag was zero)
-    for (int32_t i = 0; i < n; ++i) {
-        const size_t row = static_cast<size_t>(c->plan.params[i].segment) * c->R;
-        uint8_t any = 0;
-        for (int32_t r = 0; r < c->R; ++r) any |= c->local_cur[row + r];
-        c->global_closed[i] = any;
-    }
+    for (int32_t i = 0; i < n; ++i) c->global_closed[i] = c->local_cur[c->plan.params[i].segment] != 0 ? 1 : 0;
     c->global_on_device = c->iter_zero && !c->plan_only;
     std::fill(c->acc_used.begin(), c->acc_used.end(), 0);
     std::fill(c->bucket_zero.begin(), c->bucket_zero.end(), 0);
@@ -1409,14 +1359,12 @@ int32_t ddp_no_sync_accumulate(ddp_ctx* c, void* const* micro) {
     HIPCHK(c, ddp::launch_accumulate(c->tables, c->h_tile0[n], c->R, n, c->d_micro,
                                      lds_for_blocks(c, c->acc_blocks_per_cu), c->backward));
     if ((rc = timed_end(c, slot, c->backward)) != DDP_OK) return rc;
-    for (int32_t i = 0; i < n; ++i) {
-        const size_t row = static_cast<size_t>(c->plan.params[i].segment) * R;
-        for (int64_t r = 0; r < R; ++r)
+    for (int64_t r = 0; r < R; ++r)
+        for (int32_t i = 0; i < n; ++i)
             if (micro[r * n + i]) {
-                c->acc_used[row + r] = 1;
+                c->acc_used[c->plan.params[i].segment] |= uint64_t(1) << r;
                 c->used_running[i] = 1;
             }
-    }
     return DDP_OK;
 }
 
@@ -1485,7 +1433,7 @@ int32_t ddp_synth_backward(ddp_ctx* c, const int32_t* order, int32_t count, cons
                                        c->backward));
         }
         if (mark) {
-            const int32_t st = mark_one(c, p, nullptr);
+            const int32_t st = mark_one(c, p, everyone_mask(c));
             if (st != DDP_OK) {
                 (void)flush_deferred(c);
                 return st;

@@ -91,11 +91,10 @@ void time_next_launch(hipEvent_t start, hipEvent_t stop);
 bool timing_pair_unused();
 
 // K1: gradients -> flat replica slabs for all `nrep` replicas.  local (may be
-// null = every replica used every parameter): participation flags
-// [segment][replica]; 0 = write zeros into that replica's slot and do not read
-// its tensor.
+// null = every replica used every parameter): one participation mask per
+// segment; bit r = 0: write zeros into replica r's slot and do not read its tensor.
 hipError_t launch_pack(const SegTables& t, int64_t tile_base, int64_t ntiles, char* slab0,
-                       int64_t slab_stride, int nrep, const uint8_t* local, hipStream_t s);
+                       int64_t slab_stride, int nrep, const uint64_t* local, hipStream_t s);
 
 // K3: averaged slab -> gradient tensors of replicas [0, nrep).  global_used (may
 // be null): per segment, 0 = no replica used the parameter; with keep_unused
@@ -111,7 +110,7 @@ hipError_t launch_flat_reduce(int dtype, const char* in0, int64_t stride, char* 
 
 // K2 (fused): gather R replicas through the segment table, reduce, scatter to
 // the gradient tensors of replicas [0, nwrite).  local / keep_unused as above
-// (a replica with flag 0 contributes +0 and is not read; a parameter nobody
+// (a replica with bit 0 contributes +0 and is not read; a parameter nobody
 // used is skipped with keep_unused, else written as zeros).
 // With flat.slab0 set (staged pipeline) the launch does K1's and K2's work in
 // one pass instead: every replica's gradients are copied into its flat bucket
@@ -128,7 +127,7 @@ struct DispatchSignal {
     unsigned long long ord;
 };
 hipError_t launch_fused_reduce(int dtype, const SegTables& t, int64_t tile_base, int64_t ntiles,
-                               int R, int nwrite, const uint8_t* local, bool keep_unused, Scale sc,
+                               int R, int nwrite, const uint64_t* local, bool keep_unused, Scale sc,
                                bool nontemporal, unsigned lds, FlatBuckets flat,
                                const GateRecord* gate, uint32_t tag, DispatchSignal sig, hipStream_t s);
 // (with t.out set -- 16-bit gradients, binary32 averages written to t.out -- nwrite must be 1)
@@ -194,7 +193,7 @@ hipError_t launch_gate(OrderState* st, unsigned long long need, long long wait_t
 // Redo the launches of element type `dtype` whose gate gave up in iteration `tag`
 // (rec[0..nb)).  `blocks` persistent blocks; normally there is nothing to do.
 hipError_t launch_repair(int dtype, const SegTables& t, OrderState* st, const GateRecord* rec, int nb, uint32_t tag,
-                         int R, int nwrite, const uint8_t* local, bool keep_unused, Scale sc,
+                         int R, int nwrite, const uint64_t* local, bool keep_unused, Scale sc,
                          int blocks, bool nontemporal, FlatBuckets flat, hipStream_t s);
 
 // Bounded probe: one wave on stream `waiter` polls word[0] for `value` (at most
@@ -204,8 +203,17 @@ hipError_t launch_repair(int dtype, const SegTables& t, OrderState* st, const Ga
 hipError_t launch_probe(unsigned long long* word, unsigned long long value, long long wait_ticks,
                         hipStream_t waiter, hipStream_t writer);
 
-// global[g] = OR_r local[g*R + r]  (the bitmap AllReduce of Section 4.2).
-hipError_t launch_bitmap_or(const uint8_t* local, uint8_t* global, int G, int R, hipStream_t s);
+constexpr int kMaskChunk = 384;      // participation masks in one launch's arguments (3 KiB)
+
+// dst[0 .. count) = masks (host memory, copied before the call returns).  gate / tag as for
+// launch_fused_reduce: behind a gate that gave up nothing is written.
+hipError_t launch_mask_write(uint64_t* dst, const uint64_t* masks, int count, const GateRecord* gate, uint32_t tag,
+                             hipStream_t s);
+
+// For g < G: local[g] = masks[g], global[g] = host_global[g] = OR of its bits (the bitmap AllReduce of
+// Section 4.2).  masks: host memory, copied before the call returns; host_global: pinned.
+hipError_t launch_bitmap_or(uint64_t* local, uint8_t* global, uint8_t* host_global, const uint64_t* masks, int G,
+                            hipStream_t s);
 
 // K4: grad[r][g] += micro[r*n + param[g]] for all segments and replicas
 // (null micro pointers are skipped).  ntiles = tile0[G].

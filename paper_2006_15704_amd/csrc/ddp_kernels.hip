@@ -13,6 +13,7 @@
 
 #include <hip/hip_ext.h>
 
+#include <cstring>
 #include <mutex>
 #include <set>
 #include <type_traits>
@@ -222,7 +223,8 @@ __device__ __forceinline__ void copy_tile(const char* __restrict__ src, char* __
 template <bool PACK>
 __global__ __launch_bounds__(BLOCK) void seg_copy_kernel(SegTables t, int64_t tile_base,
                                                          char* slab0, int64_t slab_stride,
-                                                         const uint8_t* __restrict__ flags,
+                                                         const uint64_t* __restrict__ local,
+                                                         const uint8_t* __restrict__ global_used,
                                                          int keep_unused) {
     const int64_t tile = tile_base + blockIdx.x;
     const int r = blockIdx.y;
@@ -231,12 +233,12 @@ __global__ __launch_bounds__(BLOCK) void seg_copy_kernel(SegTables t, int64_t ti
     const int64_t numel = si.numel;
     const int64_t ltile = tile - si.tile0;
     char* grad = static_cast<char*>(t.grad[static_cast<int64_t>(g) * t.R + r]);
-    // PACK: flags = per (segment, replica) participation, 0 = the replica did
-    // not use the parameter: its slot gets zeros and its tensor is not read.
-    // UNPACK: flags = global bitmap per segment, 0 = no replica used the
-    // parameter: with keep_unused its gradients are left as they are.
-    const bool zero = PACK && flags != nullptr && flags[static_cast<int64_t>(g) * t.R + r] == 0;
-    if (!PACK && keep_unused && flags != nullptr && flags[g] == 0) return;
+    // PACK: local = participation masks, bit r = 0: the replica did not use the
+    // parameter, its slot gets zeros and its tensor is not read.
+    // UNPACK: global_used[g] = 0: no replica used the parameter, with keep_unused
+    // its gradients are left as they are.
+    const bool zero = PACK && local != nullptr && ((local[g] >> r) & 1u) == 0;
+    if (!PACK && keep_unused && global_used != nullptr && global_used[g] == 0) return;
     const char* src;
     char* dst;
     if (PACK) {
@@ -372,6 +374,29 @@ __device__ __forceinline__ void sum_interior_pre(const char* const (&pre)[8], in
     } else {
         tail_interior<DT, NT, U>(base_of, r, R - r, lane_off, acc);
     }
+}
+
+// A tile of a parameter that only some replicas used: their tensors alone are read, in ascending
+// order.  Each of the others counts as +0, and there is at least one: a running sum that starts at
+// +0 differs from the sum with those +0 in their places only in the sign of a zero in between, and
+// both end in +0 where the sum is zero.
+template <int DT, bool NT, int U>
+__device__ __forceinline__ void sum_interior_used(void* const* __restrict__ row, int64_t byte0, uint64_t used,
+                                                  const uint32_t (&lane_off)[U],
+                                                  float (&acc)[U][Fmt<DT>::VEC]) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int i = 0; i < Fmt<DT>::VEC; ++i) acc[u][i] = 0.0f;
+    uint64_t rest = used;
+    auto next = [&](int) {
+        const int r = __builtin_ctzll(rest);
+        rest &= rest - 1;
+        return static_cast<const char*>(row[r]) + byte0;
+    };
+    int left = __popcll(used);
+    for (; left >= 8; left -= 8) chunk_interior<DT, NT, 8, U>(next, 0, lane_off, acc);
+    tail_interior<DT, NT, U>(next, 0, left, lane_off, acc);
 }
 
 template <int DT>
@@ -571,14 +596,6 @@ __device__ __forceinline__ void reduce_element(const SegTables& t, int g, int R,
         Fmt<DT>::store1(static_cast<char*>(t.grad[static_cast<int64_t>(g) * t.R + w]) + idx * ES, y);
 }
 
-// Block-uniform: the R participation bytes of a segment as a bit mask.
-__device__ __forceinline__ uint64_t used_mask(const uint8_t* __restrict__ flags, int R) {
-    uint64_t m = 0;
-    for (int r = 0; r < R; ++r)
-        if (flags[r] != 0) m |= uint64_t(1) << r;
-    return m;
-}
-
 // One tile of the fused gather-reduce-scatter.
 // gate / tag: see GateRecord (null = no gate).  A launch whose gate gave up must
 // not touch gradients that may still be incomplete; the repair launch redoes it.
@@ -586,7 +603,7 @@ __device__ __forceinline__ uint64_t used_mask(const uint8_t* __restrict__ flags,
 // loads, not one more in front of them) and looked at before any gradient is.
 template <int DT, bool NT, int U, int OUT>
 __device__ __forceinline__ void fused_tile(const SegTables& t, int64_t tile, int R, int nwrite,
-                                           const uint8_t* __restrict__ local, int keep_unused,
+                                           const uint64_t* __restrict__ local, int keep_unused,
                                            const Scale& sc, const FlatBuckets& flat,
                                            const GateRecord* __restrict__ gate = nullptr, uint32_t tag = 0) {
     constexpr int ES = Fmt<DT>::ES;
@@ -607,7 +624,7 @@ __device__ __forceinline__ void fused_tile(const SegTables& t, int64_t tile, int
     // participation of the R replicas in this parameter (bit r = replica r used
     // it); without a flag table every replica did
     const uint64_t everyone = R >= 64 ? ~uint64_t(0) : ((uint64_t(1) << R) - 1);
-    const uint64_t used = local != nullptr ? used_mask(local + static_cast<int64_t>(g) * t.R, R) : everyone;
+    const uint64_t used = local != nullptr ? local[g] : everyone;
     if (OUT != OUT_FLAT && used == 0 && keep_unused) return;   // globally unused: the gradients stay as they are
     const bool zero = OUT != OUT_FLAT && used == 0;            // ... or become zeros (flat buckets always do)
     const bool all_used = used == everyone;
@@ -618,12 +635,12 @@ __device__ __forceinline__ void fused_tile(const SegTables& t, int64_t tile, int
     char* const slot = OUT == OUT_FLAT ? flat.slab0 + si.flat_byte : nullptr;
     const int64_t e_tile = ltile * (TILE_BYTES / ES) - sh;
 
-    // The whole tile is inside the segment and every replica took part.  Where the replicas sit
+    // The whole tile is inside the segment.  Where the replicas sit
     // modulo 16 does not matter: vectors are cut on replica 0's 16-byte grid, the other replicas (and
     // a binary32 output tensor that is off the grid) are accessed with element-aligned vectors.  90
     // densely packed tensors of odd sizes, R = 8, 120 MB each, replicas 4 bytes apart modulo 16: 235 us
     // when such tiles took the predicated path below, 203 us here (5.3 TB/s; 5.9 when congruent).
-    if ((all_used || OUT == OUT_FLAT) && e_tile >= 0 && e_tile + TILE_BYTES / ES <= numel) {
+    if (e_tile >= 0 && e_tile + TILE_BYTES / ES <= numel) {
         const int64_t tile_byte = e_tile * ES;
 #pragma unroll 1
         for (int step = 0; step < TILE_VECS / (BLOCK * U); ++step) {
@@ -647,9 +664,12 @@ __device__ __forceinline__ void fused_tile(const SegTables& t, int64_t tile, int
                 for (int u = 0; u < U; ++u) store16(place + R * flat.stride + lane_off[u], scaled<DT>(sc, acc[u]));
                 continue;
             }
-            sum_interior_pre<DT, NT, U>(
-                pre, tile_byte, [&](int r) { return static_cast<const char*>(row[r]) + tile_byte; }, R,
-                lane_off, acc);
+            if (all_used)
+                sum_interior_pre<DT, NT, U>(
+                    pre, tile_byte, [&](int r) { return static_cast<const char*>(row[r]) + tile_byte; }, R,
+                    lane_off, acc);
+            else
+                sum_interior_used<DT, NT, U>(row, tile_byte, used, lane_off, acc);
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 if (OUT == OUT_BINARY32) {
@@ -729,7 +749,7 @@ __device__ __forceinline__ void fused_tile(const SegTables& t, int64_t tile, int
 template <int DT, bool NT, int U, int OUT>
 __global__ __launch_bounds__(BLOCK) void fused_reduce_kernel(SegTables t, int64_t tile_base, int R,
                                                              int nwrite,
-                                                             const uint8_t* __restrict__ local,
+                                                             const uint64_t* __restrict__ local,
                                                              int keep_unused, Scale sc, FlatBuckets flat,
                                                              const GateRecord* __restrict__ gate,
                                                              uint32_t tag, DispatchSignal sig) {
@@ -838,7 +858,7 @@ template <int DT, bool NT, int U, int OUT>
 __global__ __launch_bounds__(BLOCK) void repair_kernel(SegTables t, OrderState* st,
                                                        const GateRecord* __restrict__ rec,
                                                        int nb, uint32_t tag, int R, int nwrite,
-                                                       const uint8_t* __restrict__ local,
+                                                       const uint64_t* __restrict__ local,
                                                        int keep_unused, Scale sc, FlatBuckets flat) {
     // rec[nb] is the row's summary: no gate of the iteration gave up (the normal case), nothing to look for
     if (rec[nb].failed_tag != tag) return;
@@ -938,15 +958,32 @@ __global__ __launch_bounds__(BLOCK) void accumulate_kernel(SegTables t, int n,
 }
 
 // ---- global participation bitmap ---------------------------------------------
+// Masks reach the device inside kernel arguments: one launch per kMaskChunk segments instead of a
+// staged copy, which takes the host three times as long and the stream a copy packet with a hand-over
+// on each side.  ResNet-50, R = 8, 0.7 of the flags set, one mark per call: 502 us a synchronization
+// with copies, flag bytes, the predicated path for every such tile and marks that pass a numpy array
+// through ctypes; 149 us with masks, sum_interior_used and marks in C.
+struct MaskPayload { uint64_t m[kMaskChunk]; };
+
+// rows [0, count) of one launch; a launch whose gate gave up reads no masks, and its rows may still
+// be read by the previous iteration's repair launch
+__global__ __launch_bounds__(BLOCK) void mask_write_kernel(uint64_t* __restrict__ dst, MaskPayload p, int count,
+                                                           const GateRecord* __restrict__ gate, uint32_t tag) {
+    if (gate != nullptr && gate->failed_tag == tag) return;
+    for (int i = threadIdx.x; i < count; i += BLOCK) dst[i] = p.m[i];
+}
+
 // The one-GPU form of the extra AllReduce on the unused-parameter bitmap
-// (Section 4.2): global[g] = OR over the R replicas of local[g][r].
-__global__ __launch_bounds__(BLOCK) void bitmap_or_kernel(const uint8_t* __restrict__ local,
-                                                          uint8_t* __restrict__ global, int G, int R) {
-    const int g = blockIdx.x * BLOCK + threadIdx.x;
-    if (g >= G) return;
-    uint8_t any = 0;
-    for (int r = 0; r < R; ++r) any |= local[static_cast<int64_t>(g) * R + r] != 0 ? 1 : 0;
-    global[g] = any;
+// (Section 4.2): global[g] = OR over the R replicas of bit r of local[g], for the device (write-back)
+// and for the host (pinned memory, readable behind the event recorded after this launch).
+__global__ __launch_bounds__(BLOCK) void bitmap_or_kernel(uint64_t* __restrict__ local, uint8_t* __restrict__ global,
+                                                          uint8_t* __restrict__ host_global, MaskPayload p, int count) {
+    for (int g = threadIdx.x; g < count; g += BLOCK) {
+        const uint8_t any = p.m[g] != 0 ? 1 : 0;
+        local[g] = p.m[g];
+        global[g] = any;
+        host_global[g] = any;
+    }
 }
 
 // ---- K6: synthetic backward emitter -----------------------------------------
@@ -1046,10 +1083,10 @@ bool timing_pair_unused() {
 }
 
 hipError_t launch_pack(const SegTables& t, int64_t tile_base, int64_t ntiles, char* slab0,
-                       int64_t slab_stride, int nrep, const uint8_t* local, hipStream_t s) {
+                       int64_t slab_stride, int nrep, const uint64_t* local, hipStream_t s) {
     if (ntiles <= 0 || nrep <= 0) return hipSuccess;
     dim3 grid(static_cast<unsigned>(ntiles), static_cast<unsigned>(nrep));
-    return launch(seg_copy_kernel<true>, grid, 0u, s, t, tile_base, slab0, slab_stride, local, 0);
+    return launch(seg_copy_kernel<true>, grid, 0u, s, t, tile_base, slab0, slab_stride, local, nullptr, 0);
 }
 
 hipError_t launch_unpack(const SegTables& t, int64_t tile_base, int64_t ntiles,
@@ -1058,7 +1095,7 @@ hipError_t launch_unpack(const SegTables& t, int64_t tile_base, int64_t ntiles,
     if (ntiles <= 0 || nrep <= 0) return hipSuccess;
     dim3 grid(static_cast<unsigned>(ntiles), static_cast<unsigned>(nrep));
     const int keep = keep_unused ? 1 : 0;
-    return launch(seg_copy_kernel<false>, grid, 0u, s, t, tile_base, const_cast<char*>(out_slab), int64_t(0), global_used, keep);
+    return launch(seg_copy_kernel<false>, grid, 0u, s, t, tile_base, const_cast<char*>(out_slab), int64_t(0), nullptr, global_used, keep);
 }
 
 // Vectors per thread and replica in the reduce kernels: a tile's worth (two), which measured
@@ -1088,7 +1125,7 @@ hipError_t launch_flat_reduce(int dtype, const char* in0, int64_t stride, char* 
 template <int DT, int OUT>
 static hipError_t fused_dispatch(bool nt, int64_t ntiles, unsigned lds, hipStream_t s,
                                  const SegTables& t, int64_t tile_base, int R, int nwrite,
-                                 const uint8_t* local, int keep, Scale sc, FlatBuckets flat,
+                                 const uint64_t* local, int keep, Scale sc, FlatBuckets flat,
                                  const GateRecord* gate, uint32_t tag, DispatchSignal sig) {
     dim3 grid(static_cast<unsigned>(ntiles));
     if (nt) return launch(fused_reduce_kernel<DT, true, RU, OUT>, grid, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
@@ -1096,7 +1133,7 @@ static hipError_t fused_dispatch(bool nt, int64_t ntiles, unsigned lds, hipStrea
 }
 
 hipError_t launch_fused_reduce(int dtype, const SegTables& t, int64_t tile_base, int64_t ntiles,
-                               int R, int nwrite, const uint8_t* local, bool keep_unused, Scale sc,
+                               int R, int nwrite, const uint64_t* local, bool keep_unused, Scale sc,
                                bool nontemporal, unsigned lds, FlatBuckets flat,
                                const GateRecord* gate, uint32_t tag, DispatchSignal sig, hipStream_t s) {
     if (ntiles <= 0) return hipSuccess;
@@ -1160,14 +1197,14 @@ hipError_t launch_gate(OrderState* st, unsigned long long need, long long wait_t
 template <int DT, int OUT>
 static hipError_t repair_dispatch(bool nt, int blocks, hipStream_t s, const SegTables& t, OrderState* st,
                                   const GateRecord* rec, int nb, uint32_t tag, int R, int nwrite,
-                                  const uint8_t* local, int keep, Scale sc, FlatBuckets flat) {
+                                  const uint64_t* local, int keep, Scale sc, FlatBuckets flat) {
     const dim3 grid(static_cast<unsigned>(blocks));
     if (nt) return launch(repair_kernel<DT, true, RU, OUT>, grid, 0u, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc, flat);
     return launch(repair_kernel<DT, false, RU, OUT>, grid, 0u, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc, flat);
 }
 
 hipError_t launch_repair(int dtype, const SegTables& t, OrderState* st, const GateRecord* rec, int nb, uint32_t tag,
-                         int R, int nwrite, const uint8_t* local, bool keep_unused, Scale sc,
+                         int R, int nwrite, const uint64_t* local, bool keep_unused, Scale sc,
                          int blocks, bool nt, FlatBuckets flat, hipStream_t s) {
     if (blocks <= 0 || nb <= 0) return hipSuccess;
     const int keep = keep_unused ? 1 : 0;
@@ -1211,10 +1248,30 @@ hipError_t launch_accumulate(const SegTables& t, int64_t ntiles, int R, int n, v
     return launch(accumulate_kernel, grid, lds, s, t, n, micro);
 }
 
-hipError_t launch_bitmap_or(const uint8_t* local, uint8_t* global, int G, int R, hipStream_t s) {
-    if (G <= 0) return hipSuccess;
-    hipLaunchKernelGGL(bitmap_or_kernel, dim3((G + BLOCK - 1) / BLOCK), dim3(BLOCK), 0, s, local, global, G, R);
-    return after_launch();
+hipError_t launch_mask_write(uint64_t* dst, const uint64_t* masks, int count, const GateRecord* gate, uint32_t tag,
+                             hipStream_t s) {
+    for (int at = 0; at < count; at += kMaskChunk) {
+        MaskPayload p;
+        const int k = count - at < kMaskChunk ? count - at : kMaskChunk;
+        std::memcpy(p.m, masks + at, sizeof(uint64_t) * k);
+        hipLaunchKernelGGL(mask_write_kernel, dim3(1), dim3(BLOCK), 0, s, dst + at, p, k, gate, tag);
+        const hipError_t e = after_launch();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+hipError_t launch_bitmap_or(uint64_t* local, uint8_t* global, uint8_t* host_global, const uint64_t* masks, int G,
+                            hipStream_t s) {
+    for (int at = 0; at < G; at += kMaskChunk) {
+        MaskPayload p;
+        const int k = G - at < kMaskChunk ? G - at : kMaskChunk;
+        std::memcpy(p.m, masks + at, sizeof(uint64_t) * k);
+        hipLaunchKernelGGL(bitmap_or_kernel, dim3(1), dim3(BLOCK), 0, s, local + at, global + at, host_global + at, p, k);
+        const hipError_t e = after_launch();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_emit(int64_t ticks, void* const* ptrs, int R, int64_t nelem, int es,

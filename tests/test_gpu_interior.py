@@ -118,3 +118,65 @@ def test_staged_buckets_in_one_pass_and_in_two(dtype, R, masked):
                     assert part == expect, f"timing {timing} replica {r} parameter {p}: flat bucket"
         got.append((flat, [grads.download(r, i).tobytes() for r in range(R) for i in range(n)]))
     assert got[0] == got[1]
+
+
+@pytest.mark.parametrize("dtype", [FP32, FP16, BF16])
+@pytest.mark.parametrize("R", [2, 8, 9, 31, 64])
+def test_tiles_of_partly_used_parameters(dtype, R):
+    """Only the replicas that used a parameter are read; the others count as +0.  Every number of
+    users around a chunk of eight, replica 0 among them or not, and values of which many are -0."""
+    d, harness = lib()
+    es = ES[dtype]
+    numel = edge_sizes(es) + [2 * TILE // es] * 4
+    n, cap = len(numel), 40000
+    rng = np.random.default_rng(760 + R)
+    reps = [workloads.gaussian_replica(760 + R, r, 0, numel, 1e-2, dtype) for r in range(R)]
+    for r in range(R):
+        for i in range(n):       # three elements in four: -0 in every replica, or x and -x that cancel
+            x = reps[r][i].view(np.uint32 if dtype == FP32 else np.uint16)
+            x[0::4] = 1 << (8 * es - 1)
+            x[1::4] = (1 << (8 * es - 2)) | ((r & 1) << (8 * es - 1))
+            x[2::4] = (r % 3 == 0) << (8 * es - 1)
+    counts = [0, 1, R, R - 1, 7, 8, 9, 15, 16, 17, 2, R // 2]
+    used = np.zeros((n, R), dtype=np.uint8)
+    for i, c in enumerate(counts):
+        used[i, rng.choice(R, size=min(c, R), replace=False)] = 1
+    marks = [(p, used[p].tolist()) for p in range(n - 1, -1, -1)]
+    for find_unused in (0, 1):
+        want, _, _, glob = oracle.synchronize_local(numel, [dtype] * n, cap, reps, marks, find_unused=bool(find_unused))
+        grads = harness.DeviceGrads(numel, [dtype] * n, R, skew=[es * (3 * i % 8) for i in range(n)],
+                                    replica_skew=[es * (5 * r % (16 // es)) for r in range(R)], fill=0xFF)
+        for r in range(R):
+            grads.upload_replica(r, reps[r])
+        with harness.Session(grads, cap, FUSED) as s:
+            d.ddp_set_option(s.ctx, d.DDP_OPT_FIND_UNUSED, find_unused)
+            for p, u in marks:
+                d.ddp_mark_ready_local(s.ctx, p, u)
+            d.ddp_finalize_backward(s.ctx)
+            d.ddp_synchronize(s.ctx)
+            assert d.ddp_get_global_used(s.ctx, n).tolist() == glob.tolist()
+        for i in range(n):
+            assert grads.download(0, i).tobytes() == np.asarray(want[0][i]).tobytes(), f"parameter {i}, {counts[i]} users"
+
+
+@pytest.mark.parametrize("pipeline", [0, FUSED])
+def test_masks_of_more_segments_than_one_launch_carries(pipeline):
+    d, harness = lib()
+    n, R, cap = 800, 3, 1 << 20          # 384 masks travel in one launch's arguments
+    numel = [1 + i % 7 for i in range(n)]
+    reps = [workloads.gaussian_replica(780, r, 0, numel, 1.0, FP32) for r in range(R)]
+    used = (np.random.default_rng(780).random((n, R)) < 0.5).astype(np.uint8)
+    marks = [(p, used[p].tolist()) for p in range(n - 1, -1, -1)]
+    want, _, _, glob = oracle.synchronize_local(numel, [FP32] * n, cap, reps, marks, find_unused=True)
+    grads = harness.DeviceGrads(numel, [FP32] * n, R)
+    for r in range(R):
+        grads.upload_replica(r, reps[r])
+    with harness.Session(grads, cap, pipeline) as s:
+        d.ddp_set_option(s.ctx, d.DDP_OPT_FIND_UNUSED, 1)
+        for p, u in marks:
+            d.ddp_mark_ready_local(s.ctx, p, u)
+        d.ddp_finalize_backward(s.ctx)
+        d.ddp_synchronize(s.ctx)
+        assert d.ddp_get_global_used(s.ctx, n).tolist() == glob.tolist()
+    for i in range(n):
+        assert grads.download(0, i).tobytes() == np.asarray(want[0][i]).tobytes(), f"parameter {i}"
