@@ -1349,14 +1349,15 @@ int32_t ddp_no_sync_accumulate(ddp_ctx* c, void* const* micro) {
         }
     HIPCHK(c, hipSetDevice(c->device));
     if (c->micro_in_flight) HIPCHK(c, hipEventSynchronize(c->ev_micro));
-    std::memcpy(c->h_micro, micro, sizeof(void*) * R * n);
+    for (int64_t r = 0; r < R; ++r)
+        for (int32_t i = 0; i < n; ++i) c->h_micro[c->plan.params[i].segment * R + r] = micro[r * n + i];
     HIPCHK(c, hipMemcpyAsync(c->d_micro, c->h_micro, sizeof(void*) * R * n, hipMemcpyHostToDevice, c->backward));
     HIPCHK(c, hipEventRecord(c->ev_micro, c->backward));
     c->micro_in_flight = true;
     size_t slot;
     int32_t rc;
     if ((rc = timed_begin(c, DDP_K_ACCUMULATE, -1, c->backward, &slot)) != DDP_OK) return rc;
-    HIPCHK(c, ddp::launch_accumulate(c->tables, c->h_tile0[n], c->R, n, c->d_micro,
+    HIPCHK(c, ddp::launch_accumulate(c->tables, c->h_tile0[n], c->R, c->d_micro,
                                      lds_for_blocks(c, c->acc_blocks_per_cu), c->backward));
     if ((rc = timed_end(c, slot, c->backward)) != DDP_OK) return rc;
     for (int64_t r = 0; r < R; ++r)

@@ -215,9 +215,10 @@ hipError_t launch_mask_write(uint64_t* dst, const uint64_t* masks, int count, co
 hipError_t launch_bitmap_or(uint64_t* local, uint8_t* global, uint8_t* host_global, const uint64_t* masks, int G,
                             hipStream_t s);
 
-// K4: grad[r][g] += micro[r*n + param[g]] for all segments and replicas
+// K4: grad[r][g] += micro[g*R + r] for all segments and replicas (laid out as SegTables::grad, so that
+// a block fetches both pointers at once)
 // (null micro pointers are skipped).  ntiles = tile0[G].
-hipError_t launch_accumulate(const SegTables& t, int64_t ntiles, int R, int n, void* const* micro,
+hipError_t launch_accumulate(const SegTables& t, int64_t ntiles, int R, void* const* micro,
                              unsigned lds, hipStream_t s);
 
 // K6: a kernel that waits `ticks` of the device wall clock (bounded; skipped for

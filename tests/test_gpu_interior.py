@@ -180,3 +180,46 @@ def test_masks_of_more_segments_than_one_launch_carries(pipeline):
         assert d.ddp_get_global_used(s.ctx, n).tolist() == glob.tolist()
     for i in range(n):
         assert grads.download(0, i).tobytes() == np.asarray(want[0][i]).tobytes(), f"parameter {i}"
+
+
+@pytest.mark.parametrize("dtype", [FP32, FP16, BF16])
+@pytest.mark.parametrize("elems", [100, 3100000])         # 2 MiB of gradients and 378 MiB (in 16 bits)
+def test_accumulation_with_plain_and_with_streamed_gradients(dtype, elems):
+    """Gradients that may stay in a cache and gradients that cannot are accessed differently; whole
+    tiles and segment ends, micro-steps at other offsets modulo 16 than the gradients."""
+    d, harness = lib()
+    import torch
+    torch_type = {FP32: torch.float32, FP16: torch.float16, BF16: torch.bfloat16}[dtype]
+    es, R = ES[dtype], 64
+    numel = edge_sizes(es) + [elems + 1]
+    n = len(numel)
+    made = []
+    for k in (0, 1):
+        g = harness.DeviceGrads(numel, [dtype] * n, R, skew=[es * ((3 + 2 * k) * i % 8) for i in range(n)],
+                                replica_skew=[es * ((5 - 4 * k) * r % (16 // es)) for r in range(R)], fill=0xFF)
+        gen = torch.Generator("cuda")
+        gen.manual_seed(790 + k)
+        for r in range(R):
+            for i in range(n):
+                o = g.offsets[i] + g.replica_skew[r]
+                raw = torch.randn(numel[i], generator=gen, device="cuda").to(torch_type).view(torch.uint8)
+                g.bufs[r][o:o + g.nbytes(i)] = raw
+        made.append(g)
+    grads, micro = made
+    want = [b.clone() for b in grads.bufs]
+    for r in range(R):
+        for i in range(n):
+            o, m = grads.offsets[i] + grads.replica_skew[r], micro.offsets[i] + micro.replica_skew[r]
+            x = grads.bufs[r][o:o + grads.nbytes(i)].clone().view(torch_type).float()
+            y = micro.bufs[r][m:m + grads.nbytes(i)].clone().view(torch_type).float()
+            want[r][o:o + grads.nbytes(i)] = (x + y).to(torch_type).view(torch.uint8)
+    ptrs = micro.ptrs()
+    ptrs[3] = None                # replica 0 did not produce this one
+    o = grads.offsets[3] + grads.replica_skew[0]
+    want[0][o:o + grads.nbytes(3)] = grads.bufs[0][o:o + grads.nbytes(3)]
+    torch.cuda.synchronize()
+    with harness.Session(grads, 1 << 20, FUSED) as s:
+        d.ddp_no_sync_accumulate(s.ctx, ptrs)
+        d.ddp_synchronize(s.ctx)
+    for r in range(R):
+        assert torch.equal(grads.bufs[r], want[r]), f"replica {r}"
