@@ -67,6 +67,7 @@ struct ddp_ctx {
     int64_t lds_per_cu = 160 * 1024;              // read from the device at creation
 
     bool registered = false, built = false;
+    bool small_model = false;                     // set by build_internal, see kSmallModelTraffic
     ddp::BucketPlan plan;
     ddp::ReadyTracker tracker;
     std::vector<void*> grad_ptrs;            // [R][n], registration order
@@ -205,6 +206,18 @@ bool one_kernel(const ddp_ctx* c) { return c->pipeline == DDP_PIPELINE_FUSED || 
 int64_t launch_traffic(const ddp_ctx* c, int64_t launch_bytes) {
     return launch_bytes * (c->pipeline == DDP_PIPELINE_FUSED ? c->R + 1 : 2 * c->R + 1);
 }
+
+// A model of at most kSmallModelBuckets buckets that move less than this together keeps all of its
+// launches on the backward stream, unless the caller asked for a number of reduction streams.  Such a
+// launch takes 3 to 4 us there; to have it on a reduction stream the backward stream runs an
+// announcement of 1.5 us and the host makes three launches instead of one (2.3 us each), and the way
+// back costs two to four of each and an event pair per stream.  Eight small tensors in three buckets,
+// R = 2, one mark per call, staged: 60 us a synchronization with reduction streams, 14 us without;
+// 200000 elements in 13 buckets, R = 2: 153 and 44 us.  Under a running backward pass each launch
+// exposes 3.3 us more than its announcement did (ResNet-50's 161 tensors in a bucket each, R = 16:
+// 0.29 ms exposed and 0.81), which is why the rule is for few buckets only.
+constexpr int64_t kSmallModelTraffic = int64_t(4) << 20;
+constexpr size_t kSmallModelBuckets = 4;
 
 // Whether a launch over `launch_bytes` of bucket data is a long one: the cap on resident
 // blocks pays, and a second reduction stream does not, from about 360 MiB of traffic on
@@ -399,7 +412,9 @@ int32_t launch_range(ddp_ctx* c, int32_t first, int32_t last, Target target) {
     const int32_t id = first + 65536 * (last - first);
     int lane = -1;                    // -1: the backward stream
     hipStream_t st = c->backward;
-    if (target == Target::kLane) {
+    if (target == Target::kLane && c->n_streams < 0 && c->small_model) {
+        // stays on the backward stream
+    } else if (target == Target::kLane) {
         // Short launches gain from a neighbour on a second stream (start-up and drain of one
         // overlap with the other); launches long enough for the cap on resident blocks lose
         // when two of them share the memory system, so by default those stay on one stream.
@@ -943,6 +958,11 @@ static int32_t build_internal(ddp_ctx* c, uint64_t cap_bytes, const std::vector<
     c->acc_used.assign(n, 0);
     c->bucket_zero.assign(nb, 0);
     c->global_closed.assign(n, 0);
+
+    int64_t total_bytes = 0;
+    for (const ddp::BucketInfo& bk : c->plan.buckets) total_bytes += static_cast<int64_t>(bk.bytes());
+    c->small_model = c->plan.buckets.size() <= kSmallModelBuckets && total_bytes < kSmallModelTraffic &&
+                     launch_traffic(c, total_bytes) < kSmallModelTraffic;
 
     if (!c->plan_only) {
         // slab layout (bucket bases aligned to 256 bytes, lengths padded to 16) and segment

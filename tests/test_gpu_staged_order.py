@@ -75,3 +75,25 @@ def test_staged_launches_wait_for_the_backward_stream(dtype, gate_wait_us, tail_
     for it in range(2):
         for p in range(n):
             assert keep.download(it, p).tobytes() == wants[it][0][p].tobytes(), f"iteration {it} parameter {p}"
+
+
+@pytest.mark.parametrize("pipeline", [STAGED, 1])
+@pytest.mark.parametrize("n", [1, 4, 5])        # up to four buckets stay on the backward stream by default
+@pytest.mark.parametrize("elems", [3000, 140000])      # ... if they move less than 4 MiB together
+def test_small_models_wait_for_the_backward_stream(pipeline, n, elems):
+    d, harness = lib()
+    numel, R = [elems + i for i in range(n)], 2
+    reps = [workloads.gaussian_replica(690, r, 0, numel, 1.0, FP32) for r in range(R)]
+    want, _, wlog = oracle.synchronize(numel, [FP32] * n, 0, reps)
+    grads = harness.DeviceGrads(numel, [FP32] * n, R, fill=0xFF)
+    src = harness.DeviceGrads(numel, [FP32] * n, R, fill=0)
+    for r in range(R):
+        src.upload_replica(r, reps[r])
+    with harness.Session(grads, 0, pipeline) as s:
+        for it in range(2):      # NaN until the delayed backward pass has produced them (the first time)
+            d.ddp_synth_backward(s.ctx, list(range(n - 1, -1, -1)), [100_000] * n, src.ptrs(), True)
+            d.ddp_finalize_backward(s.ctx)
+            assert d.ddp_get_launch_log(s.ctx, 1) == wlog
+        d.ddp_synchronize(s.ctx)
+    for i in range(n):
+        assert grads.download(0, i).tobytes() == want[i].tobytes(), f"parameter {i}"
