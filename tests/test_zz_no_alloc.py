@@ -121,3 +121,38 @@ def test_static_entry_point_refuses_what_does_not_fit():
     assert d.ddp_sync_static(1, 0, stream.cuda_stream, numel, [FP32], g1.ptrs(), 0) == 1
     stream.synchronize()
     assert g1.download(0, 0).tobytes() == x.tobytes()      # R = 1: the average of one replica is itself
+
+
+def test_static_entry_point_with_tensors_that_share_memory():
+    """Where replica 0's tensors share bytes with other tensors of the list, every input is read
+    before any average is written, as the flat buckets do it."""
+    d, harness = lib()
+    import torch
+    stream = torch.cuda.Stream()
+    numel, R = [5000, 5000, 77, 5000], 3
+    reps = inputs(25, numel, R, 1.0, FP32)
+    for r in range(R):
+        reps[r][3] = reps[r][0].copy()             # one tensor under two parameters
+    want, _, _ = oracle.synchronize(numel, [FP32] * 4, 16384, reps)
+    grads = harness.DeviceGrads(numel, [FP32] * 4, R, fill=0xFF)
+    for r in range(R):
+        grads.upload_replica(r, reps[r])
+    ptrs = grads.ptrs()
+    for r in range(R):
+        ptrs[4 * r + 3] = ptrs[4 * r]
+    assert d.ddp_sync_static(R, 0, stream.cuda_stream, numel, [FP32] * 4, ptrs, 16384) >= 1
+    stream.synchronize()
+    for i in range(3):
+        assert grads.download(0, i).tobytes() == want[i].tobytes(), f"parameter {i}"
+    # replicas whose tensors lie between each other's (one region for all of them)
+    both = harness.DeviceGrads([x for x in numel for _ in range(R)], [FP32] * 4 * R, 1, fill=0xFF)
+    for i in range(4):
+        for r in range(R):
+            both.upload(0, R * i + r, reps[r][i])
+    ptrs = [both.ptr(0, R * i + r) for r in range(R) for i in range(4)]
+    d.ddp_sync_static(R, 0, stream.cuda_stream, numel, [FP32] * 4, ptrs, 16384)
+    stream.synchronize()
+    for i in range(4):
+        assert both.download(0, R * i).tobytes() == want[i].tobytes(), f"parameter {i}"
+        for r in range(1, R):
+            assert both.download(0, R * i + r).tobytes() == reps[r][i].tobytes()
