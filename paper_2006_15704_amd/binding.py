@@ -242,7 +242,7 @@ _spec = _ilu.spec_from_file_location("_ddp_fastcall", _fast_path)
 _fast = _ilu.module_from_spec(_spec)
 _spec.loader.exec_module(_fast)
 _fast.bind(C.cast(_lib.ddp_mark_ready, _vp).value, C.cast(_lib.ddp_finalize_backward, _vp).value,
-           C.cast(_lib.ddp_mark_ready_local, _vp).value)
+           C.cast(_lib.ddp_mark_ready_local, _vp).value, _i32)
 _fast_mark, _fast_finalize, _fast_mark_local = _fast.mark_ready, _fast.finalize_backward, _fast.mark_ready_local
 
 

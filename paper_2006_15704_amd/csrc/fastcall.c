@@ -18,10 +18,11 @@ typedef int32_t (*finalize_fn)(void*);
 static mark_fn g_mark = NULL;
 static mark_local_fn g_mark_local = NULL;
 static finalize_fn g_finalize = NULL;
+static PyObject* g_c_int32 = NULL;      /* ctypes.c_int32 */
 
 static PyObject* bind_entry_points(PyObject* self, PyObject* const* args, Py_ssize_t nargs) {
-    if (nargs != 3) {
-        PyErr_SetString(PyExc_TypeError, "bind(mark_ready_address, finalize_backward_address, mark_ready_local_address)");
+    if (nargs != 4 || !PyType_Check(args[3])) {
+        PyErr_SetString(PyExc_TypeError, "bind(mark_ready_address, finalize_backward_address, mark_ready_local_address, c_int32)");
         return NULL;
     }
     void* a = PyLong_AsVoidPtr(args[0]);
@@ -30,6 +31,9 @@ static PyObject* bind_entry_points(PyObject* self, PyObject* const* args, Py_ssi
     if (b == NULL && PyErr_Occurred()) return NULL;
     void* l = PyLong_AsVoidPtr(args[2]);
     if (l == NULL && PyErr_Occurred()) return NULL;
+    Py_INCREF(args[3]);
+    Py_XDECREF(g_c_int32);
+    g_c_int32 = args[3];
     g_mark_local = (mark_local_fn)l;
     g_mark = (mark_fn)a;
     g_finalize = (finalize_fn)b;
@@ -53,21 +57,30 @@ static PyObject* mark_ready(PyObject* self, PyObject* const* args, Py_ssize_t na
     return PyLong_FromLong((long)g_mark(ctx, (int32_t)p));
 }
 
-/* mark_ready_local(ctx_address, param_id, flags, R) -> status.  flags: any iterable of R truth values
- * (R < 0: of any number).  As a numpy array through ctypes a call took 2.5 us, as long as the bucket
+/* A parameter id as a ctypes int32_t argument takes it: an int, whatever converts to one without loss
+ * (__index__: numpy integers, one-element integer tensors) or a c_int32, modulo 2^32.  0 on success. */
+static int param_id_of(PyObject* o, int32_t* id) {
+    PyObject* v = PyLong_Check(o) ? (Py_INCREF(o), o)
+                  : PyObject_TypeCheck(o, (PyTypeObject*)g_c_int32) ? PyObject_GetAttrString(o, "value")
+                                                                    : PyNumber_Index(o);
+    if (v == NULL) return -1;
+    *id = (int32_t)PyLong_AsUnsignedLongMask(v);
+    Py_DECREF(v);
+    return 0;
+}
+
+/* mark_ready_local(ctx_address, param_id, flags, R) -> status.  ctx_address None = no context (the
+ * library's own error).  flags: any iterable of R truth values (R < 0: of any number).  As a numpy array through ctypes a call took 2.5 us, as long as the bucket
  * launches of a whole ResNet-50 iteration for its 161 marks together. */
 static PyObject* mark_ready_local(PyObject* self, PyObject* const* args, Py_ssize_t nargs) {
     if (nargs != 4 || g_mark_local == NULL) {
         PyErr_SetString(PyExc_TypeError, "mark_ready_local(ctx_address, param_id, flags, R) after bind()");
         return NULL;
     }
-    void* ctx = PyLong_AsVoidPtr(args[0]);
+    void* ctx = args[0] == Py_None ? NULL : PyLong_AsVoidPtr(args[0]);
     if (ctx == NULL && PyErr_Occurred()) return NULL;
-    if (!PyLong_Check(args[1])) {
-        PyErr_SetString(PyExc_TypeError, "param_id must be an int");
-        return NULL;
-    }
-    const int32_t p = (int32_t)PyLong_AsUnsignedLongMask(args[1]);
+    int32_t p;
+    if (param_id_of(args[1], &p) != 0) return NULL;
     const Py_ssize_t want = PyLong_AsSsize_t(args[3]);
     if (want == -1 && PyErr_Occurred()) return NULL;
     PyObject* seq = PySequence_Fast(args[2], "flags must be iterable");

@@ -240,6 +240,32 @@ def test_participation_argument_errors(d):
         d.ddp_destroy(ctx)
 
 
+def test_participation_mark_takes_what_an_int32_argument_takes(d):
+    """Parameter ids come as numpy integers, ctypes integers or anything with __index__ (a drawn
+    order, an element of an integer tensor); what is no integer is refused, and so is a null context."""
+    class Index:
+        def __index__(self):
+            return 1
+    for id_ in (1, True, np.int64(1), np.uint8(1), np.array(1), ctypes.c_int32(1), Index(), (1 << 32) + 1):
+        ctx, _ = plan(d, [4, 4, 4], [0, 0, 0], 0)
+        try:
+            d.ddp_mark_ready_local(ctx, id_, [1, 0])
+            assert d.ddp_get_used_map(ctx, 3, 0).tolist() == [0, 1, 0], repr(id_)
+        finally:
+            d.ddp_destroy(ctx)
+    ctx, _ = plan(d, [4, 4, 4], [0, 0, 0], 0)
+    try:
+        for id_ in (1.0, "1", None, ctypes.c_int64(1), ctypes.c_bool(True)):
+            with pytest.raises((TypeError, ctypes.ArgumentError)):
+                d.ddp_mark_ready_local(ctx, id_, [1, 0])
+        assert d.ddp_get_used_map(ctx, 3, 0).tolist() == [0, 0, 0]
+    finally:
+        d.ddp_destroy(ctx)
+    with pytest.raises(d.DdpError) as e:
+        d.ddp_mark_ready_local(ctypes.c_void_p(None), 1, [1, 0])
+    assert e.value.code == d.DDP_ERR_ARG
+
+
 def test_reduction_stream_option_is_validated(d):
     ctx, _ = plan(d, [4, 4, 4], [0, 0, 0], 0)
     try:
