@@ -601,7 +601,12 @@ __device__ __forceinline__ void reduce_element(const SegTables& t, int g, int R,
 // not touch gradients that may still be incomplete; the repair launch redoes it.
 // The gate word is fetched together with the tile's tables (one round of scalar
 // loads, not one more in front of them) and looked at before any gradient is.
-template <int DT, bool NT, int U, int OUT>
+// MASKED = local may be set.  Most launches have no masks, and the chunks of 1 to 8
+// replicas that sum_interior_used adds make the code a third longer, at the same
+// registers: the first 101 BERT-large tensors with masks compiled in / left out, binary16,
+// R = 16, one mark per call 681 / 677 us a synchronization; bfloat16, R = 8, 329 / 327, and with
+// the averages to every replica 627.5 / 626.5.
+template <int DT, bool NT, int U, int OUT, bool MASKED>
 __device__ __forceinline__ void fused_tile(const SegTables& t, int64_t tile, int R, int nwrite,
                                            const uint64_t* __restrict__ local, int keep_unused,
                                            const Scale& sc, const FlatBuckets& flat,
@@ -624,10 +629,10 @@ __device__ __forceinline__ void fused_tile(const SegTables& t, int64_t tile, int
     // participation of the R replicas in this parameter (bit r = replica r used
     // it); without a flag table every replica did
     const uint64_t everyone = R >= 64 ? ~uint64_t(0) : ((uint64_t(1) << R) - 1);
-    const uint64_t used = local != nullptr ? local[g] : everyone;
+    const uint64_t used = MASKED && local != nullptr ? local[g] : everyone;
     if (OUT != OUT_FLAT && used == 0 && keep_unused) return;   // globally unused: the gradients stay as they are
     const bool zero = OUT != OUT_FLAT && used == 0;            // ... or become zeros (flat buckets always do)
-    const bool all_used = used == everyone;
+    const bool all_used = !MASKED || used == everyone;
     // replica 0's tensor -- or the slot in the flat bucket -- starts this many elements past a 16-byte boundary
     const int sh = (OUT == OUT_FLAT ? static_cast<int>(si.flat_byte & 15) : si.lead_bytes()) / ES;
     const bool src_aligned = si.congruent();   // every replica's tensor sits at the same offset modulo 16
@@ -668,7 +673,7 @@ __device__ __forceinline__ void fused_tile(const SegTables& t, int64_t tile, int
                 sum_interior_pre<DT, NT, U>(
                     pre, tile_byte, [&](int r) { return static_cast<const char*>(row[r]) + tile_byte; }, R,
                     lane_off, acc);
-            else
+            else if constexpr (MASKED)
                 sum_interior_used<DT, NT, U>(row, tile_byte, used, lane_off, acc);
 #pragma unroll
             for (int u = 0; u < U; ++u) {
@@ -746,7 +751,7 @@ __device__ __forceinline__ void fused_tile(const SegTables& t, int64_t tile, int
     }
 }
 
-template <int DT, bool NT, int U, int OUT>
+template <int DT, bool NT, int U, int OUT, bool MASKED>
 __global__ __launch_bounds__(BLOCK) void fused_reduce_kernel(SegTables t, int64_t tile_base, int R,
                                                              int nwrite,
                                                              const uint64_t* __restrict__ local,
@@ -759,7 +764,7 @@ __global__ __launch_bounds__(BLOCK) void fused_reduce_kernel(SegTables t, int64_
     // measured no better; 1024 and more blocks earlier lose the gain)
     if (sig.word != nullptr && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0)
         __hip_atomic_fetch_max(sig.word, sig.ord, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    fused_tile<DT, NT, U, OUT>(t, tile_base + blockIdx.x, R, nwrite, local, keep_unused, sc, flat, gate, tag);
+    fused_tile<DT, NT, U, OUT, MASKED>(t, tile_base + blockIdx.x, R, nwrite, local, keep_unused, sc, flat, gate, tag);
 }
 
 // ---- stream ordering through device flags ------------------------------------
@@ -867,7 +872,7 @@ __global__ __launch_bounds__(BLOCK) void repair_kernel(SegTables t, OrderState* 
         if (r.failed_tag != tag || r.dtype != DT) continue;
         if (blockIdx.x == 0 && threadIdx.x == 0) st->repaired += 1;   // (repair launches run one after the other)
         for (int64_t i = blockIdx.x; i < r.ntiles; i += gridDim.x)
-            fused_tile<DT, NT, U, OUT>(t, r.tile_base + i, R, nwrite, local, keep_unused, sc, flat);
+            fused_tile<DT, NT, U, OUT, true>(t, r.tile_base + i, R, nwrite, local, keep_unused, sc, flat);
     }
 }
 
@@ -1150,14 +1155,24 @@ hipError_t launch_flat_reduce(int dtype, const char* in0, int64_t stride, char* 
     }
 }
 
+template <int DT, int OUT, bool MASKED>
+static hipError_t fused_launch(bool nt, int64_t ntiles, unsigned lds, hipStream_t s,
+                               const SegTables& t, int64_t tile_base, int R, int nwrite,
+                               const uint64_t* local, int keep, Scale sc, FlatBuckets flat,
+                               const GateRecord* gate, uint32_t tag, DispatchSignal sig) {
+    dim3 grid(static_cast<unsigned>(ntiles));
+    if (nt) return launch(fused_reduce_kernel<DT, true, RU, OUT, MASKED>, grid, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
+    return launch(fused_reduce_kernel<DT, false, RU, OUT, MASKED>, grid, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
+}
+
 template <int DT, int OUT>
 static hipError_t fused_dispatch(bool nt, int64_t ntiles, unsigned lds, hipStream_t s,
                                  const SegTables& t, int64_t tile_base, int R, int nwrite,
                                  const uint64_t* local, int keep, Scale sc, FlatBuckets flat,
                                  const GateRecord* gate, uint32_t tag, DispatchSignal sig) {
-    dim3 grid(static_cast<unsigned>(ntiles));
-    if (nt) return launch(fused_reduce_kernel<DT, true, RU, OUT>, grid, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
-    return launch(fused_reduce_kernel<DT, false, RU, OUT>, grid, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
+    if (local != nullptr)
+        return fused_launch<DT, OUT, true>(nt, ntiles, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
+    return fused_launch<DT, OUT, false>(nt, ntiles, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
 }
 
 hipError_t launch_fused_reduce(int dtype, const SegTables& t, int64_t tile_base, int64_t ntiles,
