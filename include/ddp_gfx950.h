@@ -112,7 +112,11 @@ typedef struct ddp_ctx ddp_ctx;
                                      (start-up and drain of a short launch then overlap with its
                                      neighbour: +2 to 3 points of HBM peak with one launch per 25 MiB
                                      bucket), one for larger launches (two long launches at a time share
-                                     the memory system and lose).
+                                     the memory system and lose), none for a small model (at most four
+                                     buckets that move less than 4 MiB together) unless
+                                     DDP_OPT_TAIL_ON_BACKWARD is 0: its launches stay on
+                                     backward_stream, where each takes less than the way to another
+                                     stream and back.
                                      The launches of an iteration take the streams in turn: the
                                      caller's reduce_stream first, then streams the library creates
                                      (default priority).  This is the one-GPU form of Section 3.3's
@@ -143,10 +147,11 @@ typedef struct ddp_ctx ddp_ctx;
                                      the API call that completes an iteration (the call after which
                                      the last bucket is launchable: every gradient exists, nothing
                                      of the backward pass is left to overlap with) are enqueued on
-                                     backward_stream instead of a reduction stream.  Stream order then replaces the cross-stream event, whose
-                                     hand-over takes about 0.2 ms on this system when the waiting
-                                     queue was armed long before the event fires.  0 = every bucket
-                                     goes to a reduction stream */
+                                     backward_stream instead of a reduction stream.  Stream order then
+                                     replaces the cross-stream event, whose hand-over takes about
+                                     0.2 ms on this system when the waiting queue was armed long
+                                     before the event fires.  0 = every bucket goes to a reduction
+                                     stream, those of a small model (DDP_OPT_REDUCE_STREAMS) too */
 #define DDP_OPT_LAUNCH_HOLD   21  /* between iterations: 0 (default) = a bucket is launched by the ready
                                      mark that completes it, as in Algorithm 1.  n > 0 = it is kept back
                                      until n further ready marks have arrived, the iteration's last
@@ -238,10 +243,10 @@ int32_t ddp_set_option(ddp_ctx* ctx, int32_t option, int64_t value);
 /* Reads back what is in effect for every DDP_OPT_ option as it was set (-1
  * where that means "the library chooses"), except: DDP_OPT_COALESCE gives the
  * byte limit in effect (also when it was chosen from R) and DDP_OPT_FLAG_ORDER
- * gives 1 if the launches of the next iteration would be ordered through device
- * flags (the option allows it, the buckets are built, every reduction stream in
- * use passed the concurrency probe, and not the staged pipeline with
- * DDP_OPT_TIMING 1), else 0.  Also reads DDP_STAT_REPAIRED_LAUNCHES below.  Unknown option ->
+ * gives 1 if launches of the next iteration on a reduction stream would be
+ * ordered through device flags (the option allows it, the buckets are built, every
+ * reduction stream in use passed the concurrency probe, and not the staged
+ * pipeline with DDP_OPT_TIMING 1), else 0.  Also reads DDP_STAT_REPAIRED_LAUNCHES below.  Unknown option ->
  * DDP_ERR_ARG. */
 int32_t ddp_get_option(ddp_ctx* ctx, int32_t option, int64_t* value);
 

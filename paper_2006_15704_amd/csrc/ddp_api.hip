@@ -208,7 +208,8 @@ int64_t launch_traffic(const ddp_ctx* c, int64_t launch_bytes) {
 }
 
 // A model of at most kSmallModelBuckets buckets that move less than this together keeps all of its
-// launches on the backward stream, unless the caller asked for a number of reduction streams.  Such a
+// launches on the backward stream, unless the caller asked for a number of reduction streams or for
+// launches that all go to them (DDP_OPT_TAIL_ON_BACKWARD 0).  Such a
 // launch takes 3 to 4 us there; to have it on a reduction stream the backward stream runs an
 // announcement of 1.5 us and the host makes three launches instead of one (2.3 us each), and the way
 // back costs two to four of each and an event pair per stream.  Eight small tensors in three buckets,
@@ -412,7 +413,7 @@ int32_t launch_range(ddp_ctx* c, int32_t first, int32_t last, Target target) {
     const int32_t id = first + 65536 * (last - first);
     int lane = -1;                    // -1: the backward stream
     hipStream_t st = c->backward;
-    if (target == Target::kLane && c->n_streams < 0 && c->small_model) {
+    if (target == Target::kLane && c->n_streams < 0 && c->tail_on_backward != 0 && c->small_model) {
         // stays on the backward stream
     } else if (target == Target::kLane) {
         // Short launches gain from a neighbour on a second stream (start-up and drain of one

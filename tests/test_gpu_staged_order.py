@@ -20,6 +20,18 @@ def lib():
     return d, harness
 
 
+def flag_ordered_session(d, harness, grads, cap, pipeline):
+    import torch
+    streams = None
+    for _ in range(8):           # a pair of streams on separate hardware queues, if there is one
+        s = harness.Session(grads, cap, pipeline, streams=streams)
+        if d.ddp_get_option(s.ctx, d.DDP_OPT_FLAG_ORDER):
+            return s
+        s.close()
+        streams = (torch.cuda.Stream(), torch.cuda.Stream())
+    pytest.skip("no pair of streams on separate hardware queues was found")
+
+
 @pytest.mark.parametrize("dtype", [FP32, FP16, BF16])
 @pytest.mark.parametrize("gate_wait_us", [100000, 0])
 @pytest.mark.parametrize("tail_on_backward", [1, 0])
@@ -39,16 +51,7 @@ def test_staged_launches_wait_for_the_backward_stream(dtype, gate_wait_us, tail_
         for r in range(R):
             srcs[it].upload_replica(r, reps[it][r])
         wants.append(oracle.synchronize(numel, dtypes, cap, reps[it]))
-    streams = None
-    for _ in range(8):           # a pair of streams on separate hardware queues, if there is one
-        s = harness.Session(grads, cap, STAGED, streams=streams)
-        if d.ddp_get_option(s.ctx, d.DDP_OPT_FLAG_ORDER):
-            break
-        s.close()
-        streams = (torch.cuda.Stream(), torch.cuda.Stream())
-    else:
-        pytest.skip("no pair of streams on separate hardware queues was found")
-    with s:
+    with flag_ordered_session(d, harness, grads, cap, STAGED) as s:
         d.ddp_set_option(s.ctx, d.DDP_OPT_COALESCE, 0)
         d.ddp_set_option(s.ctx, d.DDP_OPT_REDUCE_STREAMS, 2)
         d.ddp_set_option(s.ctx, d.DDP_OPT_TAIL_ON_BACKWARD, tail_on_backward)
@@ -97,3 +100,35 @@ def test_small_models_wait_for_the_backward_stream(pipeline, n, elems):
         d.ddp_synchronize(s.ctx)
     for i in range(n):
         assert grads.download(0, i).tobytes() == want[i].tobytes(), f"parameter {i}"
+
+
+def repaired_launches(d, harness, n, R, pipeline, options=()):
+    """Launches that went through a gate when `n` tensors, a bucket each, become ready one by one
+    under a delayed backward pass: with a gate wait of 0 each such launch is redone by the repair
+    launch, and launches on the backward stream have no gate."""
+    numel = [3000 + i for i in range(n)]
+    reps = [workloads.gaussian_replica(691, r, 0, numel, 1.0, FP32) for r in range(R)]
+    want, _, wlog = oracle.synchronize(numel, [FP32] * n, 0, reps)
+    grads = harness.DeviceGrads(numel, [FP32] * n, R, fill=0xFF)
+    src = harness.DeviceGrads(numel, [FP32] * n, R, fill=0)
+    for r in range(R):
+        src.upload_replica(r, reps[r])
+    with flag_ordered_session(d, harness, grads, 0, pipeline) as s:
+        d.ddp_set_option(s.ctx, d.DDP_OPT_GATE_WAIT_US, 0)
+        for option, value in options:
+            d.ddp_set_option(s.ctx, option, value)
+        d.ddp_synth_backward(s.ctx, list(range(n - 1, -1, -1)), [150_000] * n, src.ptrs(), True)
+        d.ddp_finalize_backward(s.ctx)
+        assert d.ddp_get_launch_log(s.ctx, 1) == wlog
+        repaired = d.ddp_get_option(s.ctx, d.DDP_STAT_REPAIRED_LAUNCHES)
+    for i in range(n):
+        assert grads.download(0, i).tobytes() == want[i].tobytes(), f"parameter {i}"
+    return repaired
+
+
+@pytest.mark.parametrize("pipeline", [STAGED, 1])
+def test_small_models_leave_the_backward_stream_when_told_to(pipeline):
+    """DDP_OPT_TAIL_ON_BACKWARD 0: every bucket goes to a reduction stream, whatever the model's size."""
+    d, harness = lib()
+    assert repaired_launches(d, harness, 4, 2, pipeline) == 0
+    assert repaired_launches(d, harness, 4, 2, pipeline, [(d.DDP_OPT_TAIL_ON_BACKWARD, 0)]) >= 3
