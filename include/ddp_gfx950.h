@@ -113,7 +113,8 @@ typedef struct ddp_ctx ddp_ctx;
                                      neighbour: +2 to 3 points of HBM peak with one launch per 25 MiB
                                      bucket), one for larger launches (two long launches at a time share
                                      the memory system and lose), none for a small model (at most four
-                                     buckets that move less than 4 MiB together) unless
+                                     buckets that move less than 4 MiB together, R times the number
+                                     of buckets less one at most 16) unless
                                      DDP_OPT_TAIL_ON_BACKWARD is 0: its launches stay on
                                      backward_stream, where each takes less than the way to another
                                      stream and back.

@@ -213,12 +213,17 @@ int64_t launch_traffic(const ddp_ctx* c, int64_t launch_bytes) {
 // launch takes 3 to 4 us there; to have it on a reduction stream the backward stream runs an
 // announcement of 1.5 us and the host makes three launches instead of one (2.3 us each), and the way
 // back costs two to four of each and an event pair per stream.  Eight small tensors in three buckets,
-// R = 2, one mark per call, staged: 60 us a synchronization with reduction streams, 14 us without;
-// 200000 elements in 13 buckets, R = 2: 153 and 44 us.  Under a running backward pass each launch
-// exposes 3.3 us more than its announcement did (ResNet-50's 161 tensors in a bucket each, R = 16:
-// 0.29 ms exposed and 0.81), which is why the rule is for few buckets only.
+// R = 2, one mark per call, staged: 70 us a synchronization with reduction streams, 13 us without.
+// Under a running backward pass every launch but the last exposes all of its own time, which grows
+// with R (a block sums its replicas one chunk after the other), instead of its announcement.  Twelve
+// tensors, 40 us of backward work each, exposed time with reduction streams / without, fused, 0.1 to
+// 3.5 MiB moved: R = 2 and 4, four buckets, 19 to 25 / 12 to 20 us; R = 8, three buckets 21 to 25 /
+// 17 to 22, four 25 to 27 / 24 to 30; R = 16, two buckets 16 to 21 / 8 to 19, four 25 to 28 / 18 to 38;
+// R = 32, two 18 to 32 / 12 to 42, four 24 to 41 / 26 to 86; R = 64, four 28 to 37 / 39 to 78.  So the
+// line is R x (buckets - 1) <= kSmallModelReplicas.  (ResNet-50 in 161 buckets, R = 16: 0.29 / 0.81 ms.)
 constexpr int64_t kSmallModelTraffic = int64_t(4) << 20;
-constexpr size_t kSmallModelBuckets = 4;
+constexpr int32_t kSmallModelBuckets = 4;
+constexpr int64_t kSmallModelReplicas = 16;
 
 // Whether a launch over `launch_bytes` of bucket data is a long one: the cap on resident
 // blocks pays, and a second reduction stream does not, from about 360 MiB of traffic on
@@ -962,7 +967,8 @@ static int32_t build_internal(ddp_ctx* c, uint64_t cap_bytes, const std::vector<
 
     int64_t total_bytes = 0;
     for (const ddp::BucketInfo& bk : c->plan.buckets) total_bytes += static_cast<int64_t>(bk.bytes());
-    c->small_model = c->plan.buckets.size() <= kSmallModelBuckets && total_bytes < kSmallModelTraffic &&
+    c->small_model = nb <= kSmallModelBuckets && int64_t(c->R) * (nb - 1) <= kSmallModelReplicas &&
+                     total_bytes < kSmallModelTraffic &&
                      launch_traffic(c, total_bytes) < kSmallModelTraffic;
 
     if (!c->plan_only) {

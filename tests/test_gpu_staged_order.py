@@ -132,3 +132,14 @@ def test_small_models_leave_the_backward_stream_when_told_to(pipeline):
     d, harness = lib()
     assert repaired_launches(d, harness, 4, 2, pipeline) == 0
     assert repaired_launches(d, harness, 4, 2, pipeline, [(d.DDP_OPT_TAIL_ON_BACKWARD, 0)]) >= 3
+
+
+@pytest.mark.parametrize("pipeline", [STAGED, 1])
+@pytest.mark.parametrize("n,R,stays", [(4, 5, True), (3, 8, True), (4, 6, False), (3, 9, False),
+                                       (2, 16, True), (2, 17, False), (1, 64, True), (5, 2, False)])
+def test_small_models_with_many_replicas_use_the_reduction_streams(pipeline, n, R, stays):
+    """A launch on the backward stream holds the backward pass up for its own time, which grows with
+    R: beyond R * (buckets - 1) = 16 the launches overlap with the backward pass instead."""
+    d, harness = lib()
+    repaired = repaired_launches(d, harness, n, R, pipeline)
+    assert repaired == 0 if stays else repaired >= n - 1
