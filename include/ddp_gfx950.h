@@ -30,8 +30,8 @@
  *   - Graph capture: the ready marks and ddp_finalize_backward of an iteration
  *     may be captured into a HIP graph on backward_stream (the capture forks
  *     to the reduction streams and joins again by itself) if every replica
- *     takes part in every parameter (no participation flags: a replay repeats
- *     the flags of the captured iteration), DDP_OPT_TIMING is
+ *     takes part in every parameter (no participation flags: they travel in kernel
+ *     arguments or in host memory that later iterations rewrite), DDP_OPT_TIMING is
  *     0 and the staged pipeline is not used.  The host state (launch log,
  *     iteration count) advances at capture time only; a replay repeats the same
  *     launches on whatever the gradient tensors hold then.

@@ -94,7 +94,10 @@ struct ddp_ctx {
     uint64_t* d_local = nullptr;             // [G]
     uint8_t* d_global = nullptr;             // [G]
     uint8_t* h_global = nullptr;             // pinned, written by the bitmap kernel
-    hipEvent_t ev_global = nullptr;
+    hipEvent_t ev_global[2] = {nullptr, nullptr};   // behind the bitmap step, by iteration parity
+    uint64_t* h_masks[2] = {nullptr, nullptr};   // pinned copies of local_cur, by iteration parity; see stage_masks
+    bool masks_in_flight[2] = {false, false};    // kernels of an earlier iteration may still read h_masks
+    int64_t masks_claimed_iter = -1;             // iteration for which h_masks was waited for
     void** d_micro = nullptr;
     void** h_micro = nullptr;                // pinned
     void** d_emit = nullptr;
@@ -398,6 +401,23 @@ int32_t order_call(ddp_ctx* c, int32_t first) {
     return DDP_OK;
 }
 
+// Where a mask launch takes the masks of segments [begin, end) of the running iteration from: up to
+// kMasksByValue go into kernel arguments, more are copied into pinned memory that the kernel reads.
+// All kernels that read an iteration's copy are in front of its bitmap step's event.
+int32_t stage_masks(ddp_ctx* c, int begin, int end, const uint64_t** masks) {
+    *masks = c->local_cur.data() + begin;
+    if (end - begin <= ddp::kMasksByValue) return DDP_OK;
+    const int par = static_cast<int>(c->iteration & 1);
+    if (c->masks_claimed_iter != c->iteration) {
+        if (c->masks_in_flight[par]) HIPCHK(c, hipEventSynchronize(c->ev_global[par]));
+        c->masks_in_flight[par] = false;
+        c->masks_claimed_iter = c->iteration;
+    }
+    std::memcpy(c->h_masks[par] + begin, *masks, sizeof(uint64_t) * (end - begin));
+    *masks = c->h_masks[par] + begin;
+    return DDP_OK;
+}
+
 // Where a launch goes: a reduction stream taken in turn, the backward stream (the API call that
 // completes the iteration, see flush_deferred), or the caller's reduction stream as the
 // partner of the backward stream when such a call makes several launches.
@@ -506,7 +526,10 @@ int32_t launch_range(ddp_ctx* c, int32_t first, int32_t last, Target target) {
     if (need_flags) {
         // After the ordering above the stream is also behind the previous iteration's readers of
         // the table (or its gate gave up and nothing is written).
-        HIPCHK(c, ddp::launch_mask_write(c->d_local + seg_begin, c->local_cur.data() + seg_begin, seg_end - seg_begin,
+        const uint64_t* masks;
+        const int32_t rcm = stage_masks(c, seg_begin, seg_end, &masks);
+        if (rcm != DDP_OK) return rcm;
+        HIPCHK(c, ddp::launch_mask_write(c->d_local + seg_begin, masks, seg_end - seg_begin,
                                          gate, static_cast<uint32_t>(c->iteration + 1), st));
         d_flags = c->d_local;
     }
@@ -657,6 +680,10 @@ void release_build(ddp_ctx* c) {
     if (c->d_gate) (void)hipFree(c->d_gate);
     c->d_gate = nullptr;
     if (c->h_global) (void)hipHostFree(c->h_global);
+    for (uint64_t*& m : c->h_masks) {
+        if (m) (void)hipHostFree(m);
+        m = nullptr;
+    }
     if (c->h_micro) (void)hipHostFree(c->h_micro);
     c->slabs = nullptr; c->d_tables = nullptr; c->d_tile_seg = nullptr; c->d_local = nullptr;
     c->d_global = nullptr; c->d_micro = nullptr; c->h_global = nullptr; c->h_micro = nullptr;
@@ -678,7 +705,7 @@ void release_device(ddp_ctx* c) {
     }
     drop_timed(c);
     release_build(c);
-    for (hipEvent_t* e : {&c->ev_done, &c->ev_micro, &c->ev_emit, &c->ev_global})
+    for (hipEvent_t* e : {&c->ev_done, &c->ev_micro, &c->ev_emit, &c->ev_global[0], &c->ev_global[1]})
         if (*e) { (void)hipEventDestroy(*e); *e = nullptr; }
     if (c->d_order_mem) (void)hipFree(c->d_order_mem);
     c->d_order_mem = nullptr; c->d_order = nullptr; c->d_probe = nullptr;
@@ -738,7 +765,8 @@ int32_t ddp_create(ddp_ctx** out, int32_t R, int32_t device, void* reduce_stream
         if (e == hipSuccess) e = hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, device);
         if (e == hipSuccess && lds >= 64 * 1024) c->lds_per_cu = lds;
         if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_done, kOrderEvent);
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_global, hipEventDisableTiming);
+        for (hipEvent_t& ev : c->ev_global)
+            if (e == hipSuccess) e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_micro, hipEventDisableTiming);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_emit, hipEventDisableTiming);
         int cus = 0;
@@ -1021,6 +1049,9 @@ static int32_t build_internal(ddp_ctx* c, uint64_t cap_bytes, const std::vector<
         HIPCHK(c, hipMalloc(reinterpret_cast<void**>(&c->d_local), sizeof(uint64_t) * n));
         HIPCHK(c, hipMalloc(reinterpret_cast<void**>(&c->d_global), static_cast<size_t>(n) + 16));
         HIPCHK(c, hipHostMalloc(reinterpret_cast<void**>(&c->h_global), static_cast<size_t>(n), hipHostMallocDefault));
+        if (n > ddp::kMasksByValue)
+            for (uint64_t*& m : c->h_masks)
+                HIPCHK(c, hipHostMalloc(reinterpret_cast<void**>(&m), sizeof(uint64_t) * n, hipHostMallocDefault));
         HIPCHK(c, hipMalloc(reinterpret_cast<void**>(&c->d_micro), sizeof(void*) * R * n));
         HIPCHK(c, hipHostMalloc(reinterpret_cast<void**>(&c->h_micro), sizeof(void*) * R * n, hipHostMallocDefault));
         HIPCHK(c, hipMalloc(reinterpret_cast<void**>(&c->d_gate), sizeof(ddp::GateRecord) * (nb + 1) * ddp_ctx::kGateRows));
@@ -1078,6 +1109,8 @@ int32_t ddp_rebuild_buckets(ddp_ctx* c, uint64_t cap_bytes) {
         }
         drop_timed(c);
         c->micro_in_flight = false;
+        c->masks_in_flight[0] = c->masks_in_flight[1] = false;
+        c->masks_claimed_iter = -1;
     }
     const std::vector<uint8_t> keep_global = c->global_closed, keep_used = c->used_closed;
     c->built = false;
@@ -1260,8 +1293,12 @@ int32_t ddp_finalize_backward(ddp_ctx* c) {
             // The bitmap step of Section 4.2: the host bitmap goes to the device
             // with the launch that ORs it over the replicas, which yields the
             // parameters that somebody used.
-            HIPCHK(c, ddp::launch_bitmap_or(c->d_local, c->d_global, c->h_global, c->local_cur.data(), n, c->backward));
-            HIPCHK(c, hipEventRecord(c->ev_global, c->backward));
+            const uint64_t* masks;
+            const int32_t rc = stage_masks(c, 0, n, &masks);
+            if (rc != DDP_OK) return rc;
+            HIPCHK(c, ddp::launch_bitmap_or(c->d_local, c->d_global, c->h_global, masks, n, c->backward));
+            HIPCHK(c, hipEventRecord(c->ev_global[c->iteration & 1], c->backward));
+            c->masks_in_flight[c->iteration & 1] = n > ddp::kMasksByValue;
         }
         const bool staged = c->pipeline == DDP_PIPELINE_STAGED;
         if (c->gates_in_iter > 0) {
@@ -1325,7 +1362,7 @@ int32_t ddp_get_global_used(ddp_ctx* c, uint8_t* used) {
     if (c->global_on_device) {
         // what the bitmap kernel computed, brought back by the copy enqueued at finalize
         HIPCHK(c, hipSetDevice(c->device));
-        HIPCHK(c, hipEventSynchronize(c->ev_global));
+        HIPCHK(c, hipEventSynchronize(c->ev_global[(c->iteration - 1) & 1]));
         for (int32_t i = 0; i < n; ++i) used[i] = c->h_global[c->plan.params[i].segment];
     } else {
         std::memcpy(used, c->global_closed.data(), static_cast<size_t>(n));

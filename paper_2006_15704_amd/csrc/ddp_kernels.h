@@ -203,15 +203,17 @@ hipError_t launch_repair(int dtype, const SegTables& t, OrderState* st, const Ga
 hipError_t launch_probe(unsigned long long* word, unsigned long long value, long long wait_ticks,
                         hipStream_t waiter, hipStream_t writer);
 
-constexpr int kMaskChunk = 384;      // participation masks in one launch's arguments (3 KiB)
+// Participation masks that travel in one launch's arguments (3 KiB); more are read from pinned memory.
+constexpr int kMasksByValue = 384;
 
-// dst[0 .. count) = masks (host memory, copied before the call returns).  gate / tag as for
+// dst[0 .. count) = masks: host memory, copied before the call returns; more than kMasksByValue: pinned
+// memory that stays as it is until the launch has run.  gate / tag as for
 // launch_fused_reduce: behind a gate that gave up nothing is written.
 hipError_t launch_mask_write(uint64_t* dst, const uint64_t* masks, int count, const GateRecord* gate, uint32_t tag,
                              hipStream_t s);
 
 // For g < G: local[g] = masks[g], global[g] = host_global[g] = OR of its bits (the bitmap AllReduce of
-// Section 4.2).  masks: host memory, copied before the call returns; host_global: pinned.
+// Section 4.2).  masks as above; host_global: pinned.
 hipError_t launch_bitmap_or(uint64_t* local, uint8_t* global, uint8_t* host_global, const uint64_t* masks, int G,
                             hipStream_t s);
 

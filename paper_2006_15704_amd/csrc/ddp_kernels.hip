@@ -991,32 +991,43 @@ __global__ __launch_bounds__(BLOCK) void accumulate_kernel(SegTables t, void* co
 }
 
 // ---- global participation bitmap ---------------------------------------------
-// Masks reach the device inside kernel arguments: one launch per kMaskChunk segments instead of a
-// staged copy, which takes the host three times as long and the stream a copy packet with a hand-over
+// Up to kMasksByValue masks reach the device inside kernel arguments instead of by
+// a staged copy, which takes the host three times as long and the stream a copy packet with a hand-over
 // on each side.  ResNet-50, R = 8, 0.7 of the flags set, one mark per call: 502 us a synchronization
 // with copies, flag bytes, the predicated path for every such tile and marks that pass a numpy array
 // through ctypes; 149 us with masks, sum_interior_used and marks in C.
-struct MaskPayload { uint64_t m[kMaskChunk]; };
+struct MaskPayload { uint64_t m[kMasksByValue]; };
+
+// More are read from pinned memory, by one launch whatever their number.  A tenth of the parameters
+// never marked, R = 4, all marks in one call, us a synchronization with staged copies / a launch of
+// arguments for every 384 masks / pinned memory: 500 parameters 51 / 38 / 25, 1000 61 / 50 / 33,
+// 4000 114 / 155 / 82, 20000 404 / 683 / 345.  (Pinned memory for fewer than 384 is no faster than
+// arguments, 24 / 24, and has the host wait for the iteration before the last.)
+struct MaskPointer { const uint64_t* m; };
 
 // rows [0, count) of one launch; a launch whose gate gave up reads no masks, and its rows may still
 // be read by the previous iteration's repair launch
-__global__ __launch_bounds__(BLOCK) void mask_write_kernel(uint64_t* __restrict__ dst, MaskPayload p, int count,
+template <typename Masks>
+__global__ __launch_bounds__(BLOCK) void mask_write_kernel(uint64_t* __restrict__ dst, Masks p, int count,
                                                            const GateRecord* __restrict__ gate, uint32_t tag) {
     if (gate != nullptr && gate->failed_tag == tag) return;
-    for (int i = threadIdx.x; i < count; i += BLOCK) dst[i] = p.m[i];
+    const int i = blockIdx.x * BLOCK + threadIdx.x;
+    if (i < count) dst[i] = p.m[i];
 }
 
 // The one-GPU form of the extra AllReduce on the unused-parameter bitmap
 // (Section 4.2): global[g] = OR over the R replicas of bit r of local[g], for the device (write-back)
 // and for the host (pinned memory, readable behind the event recorded after this launch).
+template <typename Masks>
 __global__ __launch_bounds__(BLOCK) void bitmap_or_kernel(uint64_t* __restrict__ local, uint8_t* __restrict__ global,
-                                                          uint8_t* __restrict__ host_global, MaskPayload p, int count) {
-    for (int g = threadIdx.x; g < count; g += BLOCK) {
-        const uint8_t any = p.m[g] != 0 ? 1 : 0;
-        local[g] = p.m[g];
-        global[g] = any;
-        host_global[g] = any;
-    }
+                                                          uint8_t* __restrict__ host_global, Masks p, int count) {
+    const int g = blockIdx.x * BLOCK + threadIdx.x;
+    if (g >= count) return;
+    const uint64_t mask = p.m[g];
+    const uint8_t any = mask != 0 ? 1 : 0;
+    local[g] = mask;
+    global[g] = any;
+    host_global[g] = any;
 }
 
 // ---- K6: synthetic backward emitter -----------------------------------------
@@ -1303,28 +1314,30 @@ hipError_t launch_accumulate(const SegTables& t, int64_t ntiles, int R, void* co
 
 hipError_t launch_mask_write(uint64_t* dst, const uint64_t* masks, int count, const GateRecord* gate, uint32_t tag,
                              hipStream_t s) {
-    for (int at = 0; at < count; at += kMaskChunk) {
-        MaskPayload p;
-        const int k = count - at < kMaskChunk ? count - at : kMaskChunk;
-        std::memcpy(p.m, masks + at, sizeof(uint64_t) * k);
-        hipLaunchKernelGGL(mask_write_kernel, dim3(1), dim3(BLOCK), 0, s, dst + at, p, k, gate, tag);
-        const hipError_t e = after_launch();
-        if (e != hipSuccess) return e;
+    if (count <= 0) return hipSuccess;
+    const dim3 grid((count + BLOCK - 1) / BLOCK);
+    if (count > kMasksByValue) {
+        hipLaunchKernelGGL(mask_write_kernel<MaskPointer>, grid, dim3(BLOCK), 0, s, dst, MaskPointer{masks}, count, gate, tag);
+        return after_launch();
     }
-    return hipSuccess;
+    MaskPayload p;
+    std::memcpy(p.m, masks, sizeof(uint64_t) * count);
+    hipLaunchKernelGGL(mask_write_kernel<MaskPayload>, grid, dim3(BLOCK), 0, s, dst, p, count, gate, tag);
+    return after_launch();
 }
 
 hipError_t launch_bitmap_or(uint64_t* local, uint8_t* global, uint8_t* host_global, const uint64_t* masks, int G,
                             hipStream_t s) {
-    for (int at = 0; at < G; at += kMaskChunk) {
-        MaskPayload p;
-        const int k = G - at < kMaskChunk ? G - at : kMaskChunk;
-        std::memcpy(p.m, masks + at, sizeof(uint64_t) * k);
-        hipLaunchKernelGGL(bitmap_or_kernel, dim3(1), dim3(BLOCK), 0, s, local + at, global + at, host_global + at, p, k);
-        const hipError_t e = after_launch();
-        if (e != hipSuccess) return e;
+    if (G <= 0) return hipSuccess;
+    const dim3 grid((G + BLOCK - 1) / BLOCK);
+    if (G > kMasksByValue) {
+        hipLaunchKernelGGL(bitmap_or_kernel<MaskPointer>, grid, dim3(BLOCK), 0, s, local, global, host_global, MaskPointer{masks}, G);
+        return after_launch();
     }
-    return hipSuccess;
+    MaskPayload p;
+    std::memcpy(p.m, masks, sizeof(uint64_t) * G);
+    hipLaunchKernelGGL(bitmap_or_kernel<MaskPayload>, grid, dim3(BLOCK), 0, s, local, global, host_global, p, G);
+    return after_launch();
 }
 
 hipError_t launch_emit(int64_t ticks, void* const* ptrs, int R, int64_t nelem, int es,

@@ -353,3 +353,44 @@ def test_wholly_unused_buckets_are_not_launched():
                 for r in range(R):
                     for p in range(n):
                         assert grads.download(r, p).tobytes() == want[r][p].tobytes(), f"r{r} p{p}"
+
+
+@pytest.mark.parametrize("pipeline", [STAGED, FUSED])
+@pytest.mark.parametrize("n", [384, 385, 1000])
+def test_masks_of_consecutive_iterations(pipeline, n):
+    """Masks reach the device in kernel arguments (up to 384 of a launch) or through pinned memory
+    that later iterations write again: five iterations with flags of their own are enqueued without
+    host synchronization, the first behind a delayed backward pass."""
+    d, harness = lib()
+    import torch
+    R, cap, iterations = 3, 1 << 20, 5
+    numel, dtypes, reps, _, _, _ = random_case(40 + n, n, R, FP32, 40, p_used=1.0, n_nobody=0, n_unmarked=0)
+    rng = np.random.default_rng(41 + n)
+    src = harness.DeviceGrads(numel, dtypes, R, fill=0xFF)
+    grads = harness.DeviceGrads(numel, dtypes, R, fill=0xFF)
+    keep = harness.DeviceGrads(numel, dtypes, iterations, fill=0)
+    for r in range(R):
+        src.upload_replica(r, reps[r])
+    marks, want = [], []
+    for it in range(iterations):
+        order = [int(p) for p in rng.permutation(n)][: n - 2]
+        marks.append([(p, [int(u) for u in rng.integers(0, 2, size=R)]) for p in order])
+        want.append(oracle.synchronize_local(numel, dtypes, cap, reps, marks[it], find_unused=False))
+    torch.cuda.synchronize()
+    with harness.Session(grads, cap, pipeline) as s:
+        d.ddp_synth_backward(s.ctx, [0], [5_000_000], None, False)
+        for it in range(iterations):
+            with torch.cuda.stream(s.backward_stream):
+                for r in range(R):
+                    grads.bufs[r].copy_(src.bufs[r], non_blocking=True)
+            for p, used in marks[it]:
+                d.ddp_mark_ready_local(s.ctx, p, used)
+            d.ddp_finalize_backward(s.ctx)
+            with torch.cuda.stream(s.backward_stream):
+                keep.bufs[it].copy_(grads.bufs[0], non_blocking=True)
+        assert d.ddp_get_global_used(s.ctx, n).tolist() == want[-1][3].tolist()
+        d.ddp_synchronize(s.ctx)
+        torch.cuda.synchronize()
+    for it in range(iterations):
+        for p in range(n):
+            assert keep.download(it, p).tobytes() == want[it][0][0][p].tobytes(), f"iteration {it} parameter {p}"
