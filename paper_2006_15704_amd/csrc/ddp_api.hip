@@ -86,6 +86,7 @@ struct ddp_ctx {
     int32_t find_unused = 0;                 // 1: parameters nobody used keep their gradients
     std::vector<uint64_t> local_cur;         // running iteration (entries of marked parameters are valid)
     std::vector<uint64_t> acc_used;          // recorded by ddp_no_sync_accumulate since the last finalize
+    std::vector<uint64_t> micro_used;        // of the running ddp_no_sync_accumulate call
     std::vector<uint8_t> bucket_zero;        // per bucket: some bit of the running iteration is 0
     bool iter_zero = false;                  // any bit of the running iteration is 0
     int64_t iteration = 0;
@@ -990,6 +991,7 @@ static int32_t build_internal(ddp_ctx* c, uint64_t cap_bytes, const std::vector<
     c->used_closed.assign(n, 0);
     c->local_cur.assign(n, 0);
     c->acc_used.assign(n, 0);
+    c->micro_used.assign(n, 0);
     c->bucket_zero.assign(nb, 0);
     c->global_closed.assign(n, 0);
 
@@ -1413,8 +1415,19 @@ int32_t ddp_no_sync_accumulate(ddp_ctx* c, void* const* micro) {
         }
     HIPCHK(c, hipSetDevice(c->device));
     if (c->micro_in_flight) HIPCHK(c, hipEventSynchronize(c->ev_micro));
-    for (int64_t r = 0; r < R; ++r)
-        for (int32_t i = 0; i < n; ++i) c->h_micro[c->plan.params[i].segment * R + r] = micro[r * n + i];
+    // a parameter at a time: its row of the table is written in one go (R = 32, 1600 tensors: 82 us of
+    // host time a call when every pointer went to a cache line of its own, 44 so)
+    for (int32_t i = 0; i < n; ++i) {
+        const int32_t segment = c->plan.params[i].segment;
+        void** row = c->h_micro + segment * R;
+        uint64_t used = 0;
+        for (int64_t r = 0; r < R; ++r) {
+            void* const p = micro[r * n + i];
+            row[r] = p;
+            used |= static_cast<uint64_t>(p != nullptr) << r;
+        }
+        c->micro_used[segment] = used;
+    }
     HIPCHK(c, hipMemcpyAsync(c->d_micro, c->h_micro, sizeof(void*) * R * n, hipMemcpyHostToDevice, c->backward));
     HIPCHK(c, hipEventRecord(c->ev_micro, c->backward));
     c->micro_in_flight = true;
@@ -1424,12 +1437,11 @@ int32_t ddp_no_sync_accumulate(ddp_ctx* c, void* const* micro) {
     HIPCHK(c, ddp::launch_accumulate(c->tables, c->h_tile0[n], c->R, c->d_micro,
                                      lds_for_blocks(c, c->acc_blocks_per_cu), c->backward));
     if ((rc = timed_end(c, slot, c->backward)) != DDP_OK) return rc;
-    for (int64_t r = 0; r < R; ++r)
-        for (int32_t i = 0; i < n; ++i)
-            if (micro[r * n + i]) {
-                c->acc_used[c->plan.params[i].segment] |= uint64_t(1) << r;
-                c->used_running[i] = 1;
-            }
+    for (int32_t i = 0; i < n; ++i) {
+        const int32_t segment = c->plan.params[i].segment;
+        c->acc_used[segment] |= c->micro_used[segment];
+        if (c->micro_used[segment] != 0) c->used_running[i] = 1;
+    }
     return DDP_OK;
 }
 
