@@ -134,12 +134,14 @@ typedef struct ddp_ctx ddp_ctx;
                                      unit fill the memory system; more only interleave more request
                                      streams at the DRAM channels and throughput drops.  0 = no cap
                                      (wave slots decide: 8).  Default -1 =
-                                     chosen from R: no cap up to R = 4 (few loads per block), else 2 */
+                                     chosen from R: no cap up to R = 4 (few loads per block), else 2;
+                                     none for the staged pipeline's launches, which write as much as
+                                     they read */
 #define DDP_OPT_REDUCE_CAP_MIN_BYTES 14 /* any time: the cap applies to launches that move at least this
-                                     many bytes, counted as (R + 1) x the launch's bucket bytes
-                                     (measured at R = 8: it gains 1 to 2.5 points of HBM peak from
-                                     50 MiB of bucket data up and loses 1.5 to 3 on launches of 25
-                                     MiB and less; at R = 16 and 32 a 25 MiB bucket is already a long
+                                     many bytes, counted as (R + 1) x the launch's bucket bytes in
+                                     both pipelines (measured at R = 8: it gains 1 to 2.5 points of
+                                     HBM peak from 50 MiB of bucket data up and loses 1.5 to 3 on
+                                     launches of 25 MiB and less; at R = 16 and 32 a 25 MiB bucket is already a long
                                      launch and gains 2.5 points).  Default 360 MiB (40 MiB of bucket
                                      data at R = 8) */
 #define DDP_OPT_ACCUMULATE_BLOCKS_PER_CU 16 /* any time: likewise for the accumulate kernel (two loads
@@ -188,8 +190,9 @@ typedef struct ddp_ctx ddp_ctx;
                                      streams keep events.  0: events always */
 #define DDP_OPT_CHAIN_LAUNCHES 22 /* any time: 1 (default) = with flag ordering, a bucket launch that
                                      follows another one of the same iteration on a different stream,
-                                     one that moves at least 160 MiB ((R + 1) x its bucket bytes;
-                                     unless both move DDP_OPT_REDUCE_CAP_MIN_BYTES or more),
+                                     one that moves at least 160 MiB ((R + 1) x its bucket bytes, in
+                                     the staged pipeline (2 R + 1) x; unless both count
+                                     DDP_OPT_REDUCE_CAP_MIN_BYTES or more),
                                      starts when that one has started its last thread block (its gate
                                      waits for that too, bounded like every wait; the iteration's
                                      last launches on backward_stream get a one-wave kernel of their
@@ -197,8 +200,9 @@ typedef struct ddp_ctx ddp_ctx;
                                      and the next starts up instead of sharing the memory system
                                      from the start; and an API call that completes the iteration
                                      with several launches spreads them over backward_stream and
-                                     reduce_stream in turn under the same rule instead of queueing
-                                     them on backward_stream.  0 = launches on different streams
+                                     reduce_stream in turn instead of queueing them on
+                                     backward_stream, except that two neighbours that both move
+                                     DDP_OPT_REDUCE_CAP_MIN_BYTES or more stay on one stream.  0 = launches on different streams
                                      start as soon as their gradients are there.  Scheduling only:
                                      results are unchanged */
 #define DDP_OPT_GATE_WAIT_US  19  /* any time: upper bound, in microseconds, on a gate's wait (0 = look

@@ -58,7 +58,8 @@ struct ddp_ctx {
                                                   // over the context's life)
     unsigned long long prev_launch_ord = 0;       // this iteration's latest such launch (0 = none yet), ...
     int prev_launch_lane = -1;                    // ... the reduction stream it went to (-1 = the backward stream) ...
-    int64_t prev_launch_traffic = 0;              // ... and the bytes it moves, (R + 1) x its bucket bytes
+    int64_t prev_launch_traffic = 0;              // ... the bytes it moves
+    bool prev_launch_long = false;                // ... and whether it is a long one
     int32_t tail_on_backward = 1;                 // the call that completes an iteration launches on the backward stream
     int32_t blocks_per_cu = -1;                   // reduce kernels: resident blocks per compute unit (0 = no cap,
                                                   // -1 = chosen from R, see auto_blocks_per_cu)
@@ -206,7 +207,7 @@ constexpr int64_t kChainMinTraffic = int64_t(160) << 20;
 // for the staged pipeline with its kernels timed one by one.
 bool one_kernel(const ddp_ctx* c) { return c->pipeline == DDP_PIPELINE_FUSED || c->timing != 1; }
 
-// Bytes that a launch over `launch_bytes` of bucket data moves.
+// Bytes that a launch over `launch_bytes` of bucket data moves (the staged pass writes R copies too).
 int64_t launch_traffic(const ddp_ctx* c, int64_t launch_bytes) {
     return launch_bytes * (c->pipeline == DDP_PIPELINE_FUSED ? c->R + 1 : 2 * c->R + 1);
 }
@@ -233,6 +234,10 @@ constexpr int64_t kSmallModelReplicas = 16;
 // blocks pays, and a second reduction stream does not, from about 360 MiB of traffic on
 // (R = 8: 40 MiB of bucket data; R = 32: every 25 MiB bucket, 72.0 against 69.4 % of peak with
 // one mark per call; R = 16 likewise 71.7 against 69.4 %).
+// The count is (R + 1) x bucket bytes in both pipelines, for the streams that launches take in turn, for
+// the cap and for whether two neighbours on two streams are chained.  Staged, one mark per
+// call, 25 MiB buckets: BERT-large, R = 8, 4.73 ms when neighbours counted as long by the bytes they
+// move and as short so took two streams unchained, 4.67 chained on two streams, 4.82 on one stream.
 bool long_launch(const ddp_ctx* c, int64_t launch_bytes) {
     return launch_bytes * (c->R + 1) >= c->cap_min_traffic;
 }
@@ -478,7 +483,7 @@ int32_t launch_range(ddp_ctx* c, int32_t first, int32_t last, Target target) {
     // with back-to-back iterations it would otherwise run next to the iteration's first
     // launches for all of its time.
     const bool flags_in_use = c->call_by_flag || c->gates_in_iter > 0;
-    const bool both_long = c->prev_launch_traffic >= c->cap_min_traffic && traffic >= c->cap_min_traffic;
+    const bool both_long = c->prev_launch_long && long_launch(c, bytes);
     const bool chained = c->chain_launches != 0 && flags_in_use && c->prev_launch_ord != 0 && c->prev_launch_lane != lane &&
                          ntiles > 0 && one_kernel(c) &&
                          ((c->prev_launch_traffic >= kChainMinTraffic && !both_long) ||
@@ -517,6 +522,7 @@ int32_t launch_range(ddp_ctx* c, int32_t first, int32_t last, Target target) {
         c->prev_launch_ord = sig.ord;
         c->prev_launch_lane = lane;
         c->prev_launch_traffic = traffic;
+        c->prev_launch_long = long_launch(c, bytes);
     }
     // Participation masks travel to the device only for launches that hold a
     // zero bit (a replica that did not use a parameter, or a parameter nobody
@@ -648,8 +654,10 @@ int32_t flush_deferred(ddp_ctx* c) {
     for (size_t k = 0; k < ranges.size(); ++k) {
         int64_t bytes = 0;
         for (int32_t b = ranges[k].first; b <= ranges[k].second; ++b) bytes += static_cast<int64_t>(c->plan.buckets[b].bytes());
-        const bool is_long = long_launch(c, bytes);
-        // (two long launches do best one after the other on one stream)
+        // Two launches that both move as much as a long one do best one after the other on one stream.
+        // (Staged, 2 R + 1 times the bucket bytes: the first 101 BERT-large tensors, R = 2, 400 MiB and
+        // 100, 520 us with the second on the partner, 501 so; 140 tensors, R = 8, 1908 and 1878.)
+        const bool is_long = launch_traffic(c, bytes) >= c->cap_min_traffic;
         const bool to_partner = partner && k > 0 && prev_on_backward && !(prev_long && is_long);
         const Target target = !closing ? Target::kLane : to_partner ? Target::kPartner : Target::kBackward;
         const int32_t st = launch_range(c, ranges[k].first, ranges[k].second, target);
