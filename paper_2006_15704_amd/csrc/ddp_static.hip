@@ -117,10 +117,11 @@ bool writes_are_apart(const ddp::BucketPlan& plan, void* const* grad_ptrs, int32
     return true;
 }
 
-// With many replicas the gradients that fit the scratch array are small, and one block that sums all
-// replicas of a tile in turn is no faster than a copy per replica and a reduction: 90000 bfloat16
-// elements, R = 64: 82 to 91 us in flat buckets, 91 to 93 fused; 700000 binary16 elements, R = 16: 72
-// and 48.
+// One block sums all replicas of a tile in turn, and the ends of a 16-bit tensor element by element: with
+// many replicas a short 16-bit list takes longer so than with a copy per replica and a reduction.  us a call
+// in flat buckets / fused: 500 bfloat16 elements in three tensors R = 17 25 / 25, R = 24 26 / 32,
+// R = 32 28 / 40; 400000 binary16 elements in thirty, R = 20 to 32 69 to 82 / 50 to 63, R = 64 (150000)
+// 120 / 110; 700000, R = 16, 72 / 48.  (Binary32 lists are faster fused at every R: R = 64 54 / 46 and 119 / 108.)
 constexpr int32_t kFusedReplicas = 16;
 
 #define HIPCHK0(expr)                                                                        \

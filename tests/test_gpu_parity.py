@@ -320,7 +320,8 @@ def test_no_sync_accumulation_then_one_reduction(pipeline, dtype):
 # ---- overlap plumbing: the reduction must wait for the backward stream ------------------
 @pytest.mark.parametrize("pipeline", [STAGED, FUSED])
 @pytest.mark.parametrize("tail_on_backward", [1, 0])
-def test_reduction_waits_for_gradients_produced_on_the_backward_stream(pipeline, tail_on_backward):
+@pytest.mark.parametrize("streams", [-1, 1, 2])      # a model of this size uses reduction streams if told to
+def test_reduction_waits_for_gradients_produced_on_the_backward_stream(pipeline, tail_on_backward, streams):
     """Gradient memory starts as NaN; the synthetic backward stream writes the
     real gradients after a delay, parameter by parameter, and marks them ready.
     Any reduction that ran ahead of its inputs would average NaNs."""
@@ -335,6 +336,7 @@ def test_reduction_waits_for_gradients_produced_on_the_backward_stream(pipeline,
     want, _, _ = oracle.synchronize(numel, [FP32] * 8, 16384, reps)
     with harness.Session(grads, 16384, pipeline) as s:
         d.ddp_set_option(s.ctx, d.DDP_OPT_TAIL_ON_BACKWARD, tail_on_backward)
+        d.ddp_set_option(s.ctx, d.DDP_OPT_REDUCE_STREAMS, streams)
         order = list(range(7, -1, -1))
         d.ddp_synth_backward(s.ctx, order, [200_000] * 8, src.ptrs(), True)
         d.ddp_finalize_backward(s.ctx)

@@ -1,4 +1,4 @@
-"""GPU parity of the staged pipeline's launches under device-flag ordering: gradients start as NaN
+"""GPU parity of launch ordering, the staged pipeline's above all, by device flags and by events: gradients start as NaN
 and are produced by the synthetic backward stream after a delay, so a launch that ran ahead of its
 gate, or one that was skipped and not repaired, shows in the flat buckets and in the results.  A
 gate wait of 0 makes every gate give up without waiting (every kernel still ends normally)."""
@@ -36,6 +36,17 @@ def flag_ordered_session(d, harness, grads, cap, pipeline):
 @pytest.mark.parametrize("gate_wait_us", [100000, 0])
 @pytest.mark.parametrize("tail_on_backward", [1, 0])
 def test_staged_launches_wait_for_the_backward_stream(dtype, gate_wait_us, tail_on_backward):
+    staged_launches_wait(dtype, gate_wait_us, tail_on_backward, by_flag=True)
+
+
+@pytest.mark.parametrize("dtype", [FP32, FP16, BF16])
+@pytest.mark.parametrize("streams", [1, 2])
+@pytest.mark.parametrize("tail_on_backward", [1, 0])
+def test_staged_launches_ordered_by_events_wait_for_the_backward_stream(dtype, streams, tail_on_backward):
+    staged_launches_wait(dtype, 100000, tail_on_backward, by_flag=False, streams=streams)
+
+
+def staged_launches_wait(dtype, gate_wait_us, tail_on_backward, by_flag, streams=2):
     d, harness = lib()
     import torch
     numel = [5, 3000, 3 * 4096 + 7, 8192, 1, 777, 2 * 8192, 4000, 60, 5000]
@@ -51,12 +62,14 @@ def test_staged_launches_wait_for_the_backward_stream(dtype, gate_wait_us, tail_
         for r in range(R):
             srcs[it].upload_replica(r, reps[it][r])
         wants.append(oracle.synchronize(numel, dtypes, cap, reps[it]))
-    with flag_ordered_session(d, harness, grads, cap, STAGED) as s:
+    with (flag_ordered_session(d, harness, grads, cap, STAGED) if by_flag
+          else harness.Session(grads, cap, STAGED)) as s:
         d.ddp_set_option(s.ctx, d.DDP_OPT_COALESCE, 0)
-        d.ddp_set_option(s.ctx, d.DDP_OPT_REDUCE_STREAMS, 2)
+        d.ddp_set_option(s.ctx, d.DDP_OPT_REDUCE_STREAMS, streams)
+        d.ddp_set_option(s.ctx, d.DDP_OPT_FLAG_ORDER, -1 if by_flag else 0)
         d.ddp_set_option(s.ctx, d.DDP_OPT_TAIL_ON_BACKWARD, tail_on_backward)
         d.ddp_set_option(s.ctx, d.DDP_OPT_GATE_WAIT_US, gate_wait_us)
-        assert d.ddp_get_option(s.ctx, d.DDP_OPT_FLAG_ORDER) == 1
+        assert d.ddp_get_option(s.ctx, d.DDP_OPT_FLAG_ORDER) == int(by_flag)
         order = list(range(n - 1, -1, -1))
         for it in range(2):      # two iterations enqueued without host synchronization in between
             d.ddp_synth_backward(s.ctx, order, [150_000] * n, srcs[it].ptrs(), True)
@@ -143,3 +156,45 @@ def test_small_models_with_many_replicas_use_the_reduction_streams(pipeline, n, 
     d, harness = lib()
     repaired = repaired_launches(d, harness, n, R, pipeline)
     assert repaired == 0 if stays else repaired >= n - 1
+
+
+@pytest.mark.parametrize("pipeline", [STAGED, 1])
+@pytest.mark.parametrize("marks", ["each", "closing"])
+@pytest.mark.parametrize("flag_order", [-1, 0])
+def test_long_launches_wait_for_the_backward_stream(pipeline, marks, flag_order):
+    """Launches of more than 160 MiB: chained on two reduction streams while gradients are still being
+    produced, and spread over the backward stream and its partner by a call that completes the
+    iteration behind a delayed backward pass.  Gradients start as NaN; the sums run in ascending
+    order, so torch gives the same bits."""
+    d, harness = lib()
+    import torch
+    R, n = 8, 5
+    elems = [(10 << 18) + 3 * i for i in range(n)]     # 10 MiB each: 170 MiB a staged launch, 90 MiB a fused one
+    if pipeline != STAGED:
+        elems = [2 * x for x in elems]
+    grads = harness.DeviceGrads(elems, [FP32] * n, R, fill=0xFF)
+    src = harness.DeviceGrads(elems, [FP32] * n, R, fill=0)
+    gen = torch.Generator("cuda")
+    for r in range(R):
+        gen.manual_seed(700 + r)
+        for i in range(n):
+            src.view(r, i).view(torch.float32).normal_(generator=gen)
+    torch.cuda.synchronize()
+    with (flag_ordered_session(d, harness, grads, 0, pipeline) if flag_order
+          else harness.Session(grads, 0, pipeline)) as s:
+        d.ddp_set_option(s.ctx, d.DDP_OPT_COALESCE, 0)
+        d.ddp_set_option(s.ctx, d.DDP_OPT_FLAG_ORDER, flag_order)
+        order = list(range(n - 1, -1, -1))
+        for _ in range(2):       # two iterations enqueued without host synchronization in between
+            d.ddp_synth_backward(s.ctx, order, [100_000] * n, src.ptrs(), marks == "each")
+            if marks == "closing":
+                d.ddp_mark_ready_many(s.ctx, order)
+            d.ddp_finalize_backward(s.ctx)
+        d.ddp_synchronize(s.ctx)
+        assert d.ddp_get_option(s.ctx, d.DDP_STAT_REPAIRED_LAUNCHES) == 0
+    for i in range(n):
+        want = src.view(0, i).view(torch.float32).clone()
+        for r in range(1, R):
+            want += src.view(r, i).view(torch.float32)
+        want /= R
+        assert torch.equal(grads.view(0, i).view(torch.float32).view(torch.int32), want.view(torch.int32)), f"parameter {i}"

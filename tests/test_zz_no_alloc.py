@@ -2,7 +2,9 @@
 is a variant of -- ddp_mark_ready_many + ddp_finalize_backward on a staged
 context -- and against the CPU oracle, bit for bit, on two calls in a row (the
 second with a smaller input, so that what the first call left in the static
-scratch array must not leak into it)."""
+scratch array must not leak into it).  Up to 16 replicas whose tensors lie apart
+the call reduces in place; more replicas, and tensors that share memory, go
+through the flat buckets in the array."""
 import numpy as np
 import pytest
 
@@ -72,16 +74,22 @@ def check_case(d, harness, torch, stream, config, numel, dtype, R, sigma, cap, w
             assert out_s[r][i].tobytes() == reps[r][i].tobytes(), f"{what}: replica {r} parameter {i} was modified"
 
 
-def test_static_entry_point_matches_context_path_twice_in_a_row():
-    d, harness = lib()
-    import torch
-    stream = torch.cuda.Stream()
+def used_stream(d, harness, torch):
     # The runtime loads the library's code object -- the static array is part of its image -- when
-    # the process first uses it; that one-time load is not an allocation of the call.  Touch it
-    # once so that the free-memory comparison around the calls below sees the calls alone.
+    # the process first uses it, and a stream gets its queue when it is first used; neither is an
+    # allocation of the call.  Touch them once so that the free-memory comparison around the calls
+    # sees the calls alone.
+    stream = torch.cuda.Stream()
     warm = harness.DeviceGrads([4], [FP32], 1, fill=0)
     d.ddp_sync_static(1, 0, stream.cuda_stream, [4], [FP32], warm.ptrs(), 0)
     stream.synchronize()
+    return stream
+
+
+def test_static_entry_point_matches_context_path_twice_in_a_row():
+    d, harness = lib()
+    import torch
+    stream = used_stream(d, harness, torch)
     # first call: 40 ragged fp32 tensors, R = 4, several buckets, close to 5 MiB of flat buckets
     numel_a = ragged_list(11, 40, 12000)
     check_case(d, harness, torch, stream, 21, numel_a, FP32, 4, 1e-2, 64 << 10, "first call")
@@ -90,6 +98,48 @@ def test_static_entry_point_matches_context_path_twice_in_a_row():
     check_case(d, harness, torch, stream, 22, numel_b, FP16, 2, 1.0, 16384, "second call")
     # third: bf16 with a replica count that is not a power of two (true division)
     check_case(d, harness, torch, stream, 23, ragged_list(12, 9, 3000), BF16, 3, 1e-3, 0, "third call")
+
+
+@pytest.mark.parametrize("dtype", [FP32, FP16, BF16])
+@pytest.mark.parametrize("R", [16, 17, 64])       # the last that is reduced in place, and flat buckets
+def test_static_entry_point_with_many_replicas_on_shrinking_lists(dtype, R):
+    """Two calls in a row, the second with fewer and shorter tensors of odd lengths in buckets of other
+    sizes: padding and slots that the first one filled lie inside the second one's buckets."""
+    d, harness = lib()
+    import torch
+    stream = used_stream(d, harness, torch)
+    rng = np.random.default_rng(100 + R)
+    for call, (n, most, cap) in enumerate(((14, 4000, 16 << 10), (9, 500, 1 << 10), (3, 60, 0))):
+        numel = [int(x) | 1 for x in rng.integers(1, most, size=n)]
+        check_case(d, harness, torch, stream, 30 + call, numel, dtype, R, 1e-2, cap, f"R {R} call {call}")
+
+
+@pytest.mark.parametrize("dtype", [FP32, FP16, BF16])
+def test_static_entry_point_with_shared_memory_on_shrinking_lists(dtype):
+    """Likewise for few replicas where one tensor stands under two parameters."""
+    d, harness = lib()
+    import torch
+    stream = torch.cuda.Stream()
+    R = 3
+    for call, (numel, cap) in enumerate((([4001, 77, 9001, 4001], 16 << 10), ([301, 5, 301], 1 << 10), ([7, 7], 0))):
+        n = len(numel)
+        reps = inputs(35 + call, numel, R, 1.0, dtype)
+        for r in range(R):
+            reps[r][n - 1] = reps[r][0].copy()
+        want, _, _ = oracle.synchronize(numel, [dtype] * n, cap, reps)
+        grads = harness.DeviceGrads(numel, [dtype] * n, R, fill=0xFF)
+        for r in range(R):
+            grads.upload_replica(r, reps[r])
+        ptrs = grads.ptrs()
+        for r in range(R):
+            ptrs[n * r + n - 1] = ptrs[n * r]
+        torch.cuda.synchronize()
+        d.ddp_sync_static(R, 0, stream.cuda_stream, numel, [dtype] * n, ptrs, cap)
+        stream.synchronize()
+        for i in range(n - 1):
+            assert grads.download(0, i).tobytes() == want[i].tobytes(), f"call {call} parameter {i}"
+            for r in range(1, R):
+                assert grads.download(r, i).tobytes() == reps[r][i].tobytes()
 
 
 def test_static_entry_point_refuses_what_does_not_fit():
