@@ -254,7 +254,7 @@ def ddp_mark_ready(ctx, param_id: int) -> None:
 
 def ddp_mark_ready_local(ctx, param_id: int, used) -> None:
     """used: R flags, non-zero = that replica produced a gradient for the parameter."""
-    status = _fast_mark_local(ctx.value, param_id, used, _replicas.get(ctx.value, -1))
+    status = _fast_mark_local(ctx.value, param_id, used, _replicas)
     if status < 0:
         _check(ctx, status)
 

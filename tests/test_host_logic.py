@@ -6,6 +6,8 @@ symbol the header declares."""
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -264,6 +266,38 @@ def test_participation_mark_takes_what_an_int32_argument_takes(d):
     with pytest.raises(d.DdpError) as e:
         d.ddp_mark_ready_local(ctypes.c_void_p(None), 1, [1, 0])
     assert e.value.code == d.DDP_ERR_ARG
+
+
+def test_participation_mark_lets_other_threads_run(d):
+    """ddp_mark_ready_local can wait for the GPU; the interpreter is free meanwhile.  The module's C
+    entry point is replaced by usleep here, in a process of its own."""
+    script = f"""
+import ctypes, importlib.util, threading, time
+spec = importlib.util.spec_from_file_location("_ddp_fastcall", {d.binding._fast_path!r})
+fast = importlib.util.module_from_spec(spec)
+spec.loader.exec_module(fast)
+usleep = ctypes.cast(ctypes.CDLL(None).usleep, ctypes.c_void_p).value
+fast.bind(usleep, usleep, usleep, ctypes.c_int32)
+started, beats, over = threading.Event(), [], threading.Event()
+def other():
+    started.set()
+    while not over.is_set():
+        beats.append(time.monotonic())
+        time.sleep(0.005)
+t = threading.Thread(target=other)
+t.start()
+started.wait()
+a = time.monotonic()
+assert fast.mark_ready_local(600000, 0, [1], {{}}) == 0
+b = time.monotonic()
+over.set()
+t.join()
+assert b - a > 0.5, b - a
+print(len([x for x in beats if a + 0.1 < x < b - 0.1]))
+"""
+    out = subprocess.run([sys.executable, "-c", script], capture_output=True, text=True, timeout=60)
+    assert out.returncode == 0, out.stderr
+    assert int(out.stdout) >= 5
 
 
 def test_reduction_stream_option_is_validated(d):
