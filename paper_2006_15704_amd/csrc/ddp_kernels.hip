@@ -557,26 +557,61 @@ __device__ __forceinline__ void store_out32_wave(char* out, int64_t in_byte_off,
     store16u<NT>(wave_base + 1024 + 16 * lane, b);
 }
 
+// OUT_FLAT: a vector that reaches over an end of the segment, elements [lo, hi) of it.  The loads of C
+// replicas are issued before the stores and the adds.  (One element and replica at a time, each load behind
+// the store of the one before: 3000 binary16 elements in eight tensors, R = 8 27 us a synchronization, R = 16
+// 49, R = 64 169; so 17, 27 and 86, with C = 4 19, 28 and 97.)
+// The copy moves bits, not values: a signalling NaN arrives in the bucket as it is.
+template <int DT, int C>
+__device__ __forceinline__ void chunk_copy_edge(void* const* __restrict__ row, int r, uint64_t used, int lo, int hi,
+                                                int64_t off, char* slot, int64_t stride, float (&s)[Fmt<DT>::VEC]) {
+    constexpr int ES = Fmt<DT>::ES;
+    constexpr int VEC = Fmt<DT>::VEC;
+    typedef typename std::conditional<ES == 4, uint32_t, uint16_t>::type bits;
+    bits x[C][VEC];
+#pragma unroll
+    for (int i = 0; i < C; ++i) {
+        const char* base = static_cast<const char*>(row[r + i]) + off;
+        const bool take = ((used >> (r + i)) & 1u) != 0;
+#pragma unroll
+        for (int k = 0; k < VEC; ++k) {
+            x[i][k] = 0;
+            if (take && k >= lo && k < hi) x[i][k] = gload<bits>(base + k * ES);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < C; ++i)
+#pragma unroll
+        for (int k = 0; k < VEC; ++k) {
+            if (k >= lo && k < hi) gstore<bits>(slot + (r + i) * stride + off + k * ES, x[i][k]);
+            s[k] += Fmt<DT>::value(x[i][k]);
+        }
+}
+
+template <int DT>
+__device__ __forceinline__ void copy_edge(void* const* __restrict__ row, int R, uint64_t used, int64_t e, int64_t numel,
+                                          char* slot, int64_t stride, const Scale& sc) {
+    constexpr int ES = Fmt<DT>::ES;
+    constexpr int VEC = Fmt<DT>::VEC;
+    const int lo = e < 0 ? static_cast<int>(-e) : 0;
+    const int hi = numel - e < VEC ? static_cast<int>(numel - e) : VEC;
+    const int64_t off = e * ES;
+    float s[VEC];
+#pragma unroll
+    for (int k = 0; k < VEC; ++k) s[k] = -0.0f;
+    constexpr int C = 8;
+    int r = 0;
+    for (; r + C <= R; r += C) chunk_copy_edge<DT, C>(row, r, used, lo, hi, off, slot, stride, s);
+    for (; r < R; ++r) chunk_copy_edge<DT, 1>(row, r, used, lo, hi, off, slot, stride, s);
+#pragma unroll
+    for (int k = 0; k < VEC; ++k)
+        if (k >= lo && k < hi) Fmt<DT>::store1(slot + R * stride + off + k * ES, apply_scale(sc, s[k]));
+}
+
 template <int DT, int OUT>
 __device__ __forceinline__ void reduce_element(const SegTables& t, int g, int R, int nwrite,
-                                               int64_t idx, bool zero, uint64_t used, const Scale& sc,
-                                               const FlatBuckets& flat, int64_t flat_byte) {
+                                               int64_t idx, bool zero, uint64_t used, const Scale& sc) {
     constexpr int ES = Fmt<DT>::ES;
-    if (OUT == OUT_FLAT) {
-        // the copy moves bits, not values: a signalling NaN arrives in the bucket as it is
-        typedef typename std::conditional<ES == 4, uint32_t, uint16_t>::type bits;
-        char* slot = flat.slab0 + flat_byte + idx * ES;
-        float s = -0.0f;
-        for (int r = 0; r < R; ++r) {
-            bits x = 0;
-            if ((used >> r) & 1u)
-                x = gload<bits>(static_cast<const char*>(t.grad[static_cast<int64_t>(g) * t.R + r]) + idx * ES);
-            gstore<bits>(slot + r * flat.stride, x);
-            s += Fmt<DT>::value(x);
-        }
-        Fmt<DT>::store1(slot + R * flat.stride, apply_scale(sc, s));
-        return;
-    }
     float y = 0.0f;
     if (!zero) {
         float s = -0.0f;
@@ -741,10 +776,12 @@ __device__ __forceinline__ void fused_tile(const SegTables& t, int64_t tile, int
                     if (src_aligned) store16s<NT>(d + off[u], out);
                     else store16u<NT>(d + off[u], out);
                 }
+            } else if constexpr (OUT == OUT_FLAT) {
+                copy_edge<DT>(row, R, used, e[u], numel, slot, flat.stride, sc);
             } else {
                 for (int i = 0; i < VEC; ++i) {
                     const int64_t idx = e[u] + i;
-                    if (idx >= 0 && idx < numel) reduce_element<DT, OUT>(t, g, R, nwrite, idx, zero, used, sc, flat, si.flat_byte);
+                    if (idx >= 0 && idx < numel) reduce_element<DT, OUT>(t, g, R, nwrite, idx, zero, used, sc);
                 }
             }
         }
