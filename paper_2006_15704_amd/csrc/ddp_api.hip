@@ -212,6 +212,18 @@ int64_t launch_traffic(const ddp_ctx* c, int64_t launch_bytes) {
     return launch_bytes * (c->pipeline == DDP_PIPELINE_FUSED ? c->R + 1 : 2 * c->R + 1);
 }
 
+// Staged: whether a launch of up to this many tiles copies and reduces in two kernels.  The one pass sums
+// a tile's replicas in one block, chunk after chunk; with many replicas and few tiles most of the chip
+// idles meanwhile, where the copies run in a block per tile and replica.  One pass / two kernels, us a synchronization, all
+// marks in one call: binary16, 1.6 million elements (400 tiles) R = 16 37 / 36, R = 24 53 / 49, R = 64
+// 146 / 101, 3 million (730) R = 16 61 / 57, R = 24 89 / 77; 100000 R = 64 79 / 26; binary32, 400000
+// (200 tiles) R = 16 22 / 22, R = 24 30 / 29, R = 64 73 / 57, 1.6 million (780) R = 16 51 / 58, R = 24 76 /
+// 80, R = 64 214 / 207, 6 million (2900) R = 32 377 / 403.  One mark per call, 1 MiB buckets: binary16 R = 16 255 / 266 (the
+// host makes one launch more), R = 20 320 / 267, R = 32 449 / 294; binary32 R = 16 351 / 372, R = 32 621 / 496.
+bool split_pass(const ddp_ctx* c, int32_t dtype, int64_t ntiles) {
+    return c->R > 16 && ntiles <= (dtype == DDP_FP32 ? 512 : 1024);
+}
+
 // A model of at most kSmallModelBuckets buckets that move less than this together keeps all of its
 // launches on the backward stream, unless the caller asked for a number of reduction streams or for
 // launches that all go to them (DDP_OPT_TAIL_ON_BACKWARD 0).  Such a
@@ -553,20 +565,21 @@ int32_t launch_range(ddp_ctx* c, int32_t first, int32_t last, Target target) {
         c->open_group = c->timed.size() - 1;
     }
     if (c->timing == 2) c->timed[c->open_group].bucket += 1;   // counts the launches
-    if (c->pipeline == DDP_PIPELINE_STAGED && c->timing == 1) {
-        // pack and reduce as launches of their own, so that each can be stamped
+    const uint32_t tag = static_cast<uint32_t>(c->iteration + 1);
+    if (c->pipeline == DDP_PIPELINE_STAGED && (c->timing == 1 || split_pass(c, bf.dtype, ntiles))) {
+        // pack and reduce as launches of their own; timed one by one, each is stamped
         char* in0 = c->slabs + c->bucket_slab_off[first];
         char* out = c->slabs + static_cast<int64_t>(c->R) * c->slab_stride + c->bucket_slab_off[first];
         // the range of the slab from the first bucket's base to the last one's padded end
         const int64_t nvec = (c->bucket_slab_off[last] - c->bucket_slab_off[first]) / 16 + c->bucket_vecs[last];
         if ((rc = timed_begin(c, DDP_K_PACK, id, st, &slot)) != DDP_OK) return rc;
         HIPCHK(c, ddp::launch_pack(c->tables, tile_base, ntiles, c->slabs, c->slab_stride, c->R,
-                                   d_flags, st));
+                                   d_flags, gate, tag, st));
         if ((rc = timed_end(c, slot, st)) != DDP_OK) return rc;
         if ((rc = timed_begin(c, DDP_K_REDUCE, id, st, &slot)) != DDP_OK) return rc;
         HIPCHK(c, ddp::launch_flat_reduce(bf.dtype, in0, c->slab_stride, out, nvec, c->R, sc,
                                           c->nontemporal != 0,
-                                          occupancy_lds(c, bytes, false), st));
+                                          occupancy_lds(c, bytes, false), gate, tag, sig, st));
         if ((rc = timed_end(c, slot, st)) != DDP_OK) return rc;
     } else {
         const bool staged = c->pipeline == DDP_PIPELINE_STAGED;
@@ -575,7 +588,7 @@ int32_t launch_range(ddp_ctx* c, int32_t first, int32_t last, Target target) {
         HIPCHK(c, ddp::launch_fused_reduce(bf.dtype, c->tables, tile_base, ntiles, c->R,
                                            c->write_all ? c->R : 1, d_flags, c->find_unused != 0, sc,
                                            c->nontemporal != 0, occupancy_lds(c, bytes, staged),
-                                           flat, gate, static_cast<uint32_t>(c->iteration + 1), sig, st));
+                                           flat, gate, tag, sig, st));
         if ((rc = timed_end(c, slot, st)) != DDP_OK) return rc;
     }
     return DDP_OK;

@@ -90,11 +90,23 @@ inline Scale make_scale(int R) {
 void time_next_launch(hipEvent_t start, hipEvent_t stop);
 bool timing_pair_unused();
 
+struct GateRecord;   // below, with the flag-ordering kernels
+
+// gate (may be null): the record of the gate kernel enqueued in front of this
+// launch; if gate->failed_tag == tag the launch does nothing.
+// sig: where (null = nowhere) and with which ordinal the launch's last thread block reports that it
+// has started (OrderState::dispatched)
+struct DispatchSignal {
+    unsigned long long* word;
+    unsigned long long ord;
+};
+
 // K1: gradients -> flat replica slabs for all `nrep` replicas.  local (may be
 // null = every replica used every parameter): one participation mask per
 // segment; bit r = 0: write zeros into replica r's slot and do not read its tensor.
 hipError_t launch_pack(const SegTables& t, int64_t tile_base, int64_t ntiles, char* slab0,
-                       int64_t slab_stride, int nrep, const uint64_t* local, hipStream_t s);
+                       int64_t slab_stride, int nrep, const uint64_t* local,
+                       const GateRecord* gate, uint32_t tag, hipStream_t s);
 
 // K3: averaged slab -> gradient tensors of replicas [0, nrep).  global_used (may
 // be null): per segment, 0 = no replica used the parameter; with keep_unused
@@ -106,7 +118,8 @@ hipError_t launch_unpack(const SegTables& t, int64_t tile_base, int64_t ntiles,
 // K2 (staged): out[v] = scale(sum_r in_r[v]) over nvec 16-byte vectors;
 // in_r = in0 + r*stride.
 hipError_t launch_flat_reduce(int dtype, const char* in0, int64_t stride, char* out, int64_t nvec,
-                              int R, Scale sc, bool nontemporal, unsigned lds, hipStream_t s);
+                              int R, Scale sc, bool nontemporal, unsigned lds,
+                              const GateRecord* gate, uint32_t tag, DispatchSignal sig, hipStream_t s);
 
 // K2 (fused): gather R replicas through the segment table, reduce, scatter to
 // the gradient tensors of replicas [0, nwrite).  local / keep_unused as above
@@ -116,16 +129,6 @@ hipError_t launch_flat_reduce(int dtype, const char* in0, int64_t stride, char* 
 // one pass instead: every replica's gradients are copied into its flat bucket
 // (zeros for a replica that did not use the parameter) and the average goes to
 // the averaged bucket; nwrite and keep_unused do not matter then.
-struct GateRecord;   // below, with the flag-ordering kernels
-
-// gate (may be null): the record of the gate kernel enqueued in front of this
-// launch; if gate->failed_tag == tag the launch does nothing.
-// sig: where (null = nowhere) and with which ordinal the launch's last thread block reports that it
-// has started (OrderState::dispatched)
-struct DispatchSignal {
-    unsigned long long* word;
-    unsigned long long ord;
-};
 hipError_t launch_fused_reduce(int dtype, const SegTables& t, int64_t tile_base, int64_t ntiles,
                                int R, int nwrite, const uint64_t* local, bool keep_unused, Scale sc,
                                bool nontemporal, unsigned lds, FlatBuckets flat,

@@ -181,6 +181,15 @@ __device__ __forceinline__ int classify(int64_t e, int vec, int64_t numel) {
     return (e >= 0 && e + vec <= numel) ? V_FULL : V_EDGE;
 }
 
+// The last block of the grid tells that the launch has been dispatched in full (blocks start
+// in index order): a launch chained behind this one may begin to fill the compute units
+// (reporting a few hundred blocks earlier, to make up for the start-up of the next launch,
+// measured no better; 1024 and more blocks earlier lose the gain).
+__device__ __forceinline__ void signal_dispatch(const DispatchSignal& sig) {
+    if (sig.word != nullptr && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0)
+        __hip_atomic_fetch_max(sig.word, sig.ord, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // ---- K1 / K3: segment copies ---------------------------------------------
 template <int ES>
 __device__ __forceinline__ void copy_tile(const char* __restrict__ src, char* __restrict__ dst,
@@ -225,7 +234,9 @@ __global__ __launch_bounds__(BLOCK) void seg_copy_kernel(SegTables t, int64_t ti
                                                          char* slab0, int64_t slab_stride,
                                                          const uint64_t* __restrict__ local,
                                                          const uint8_t* __restrict__ global_used,
-                                                         int keep_unused) {
+                                                         int keep_unused,
+                                                         const GateRecord* __restrict__ gate, uint32_t tag) {
+    if (PACK && gate != nullptr && gate->failed_tag == tag) return;      // see fused_tile
     const int64_t tile = tile_base + blockIdx.x;
     const int r = blockIdx.y;
     const int g = t.tile_seg[tile];
@@ -432,8 +443,12 @@ __device__ __forceinline__ void chunk_flat(const char* __restrict__ in0, int64_t
 template <int DT, bool NT, int U>
 __global__ __launch_bounds__(BLOCK) void flat_reduce_kernel(const char* __restrict__ in0,
                                                             int64_t stride, char* __restrict__ out,
-                                                            int64_t nvec, int R, Scale sc) {
+                                                            int64_t nvec, int R, Scale sc,
+                                                            const GateRecord* __restrict__ gate,
+                                                            uint32_t tag, DispatchSignal sig) {
     constexpr int VEC = Fmt<DT>::VEC;
+    signal_dispatch(sig);
+    if (gate != nullptr && gate->failed_tag == tag) return;              // see fused_tile
     const int64_t row = blockIdx.x;
     float acc[U][VEC];
     if ((row + 1) * (BLOCK * U) <= nvec) {
@@ -795,12 +810,7 @@ __global__ __launch_bounds__(BLOCK) void fused_reduce_kernel(SegTables t, int64_
                                                              int keep_unused, Scale sc, FlatBuckets flat,
                                                              const GateRecord* __restrict__ gate,
                                                              uint32_t tag, DispatchSignal sig) {
-    // the last block of the grid tells that the launch has been dispatched in full (blocks start
-    // in index order): a launch chained behind this one may begin to fill the compute units
-    // (reporting a few hundred blocks earlier, to make up for the start-up of the next launch,
-    // measured no better; 1024 and more blocks earlier lose the gain)
-    if (sig.word != nullptr && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0)
-        __hip_atomic_fetch_max(sig.word, sig.ord, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    signal_dispatch(sig);
     fused_tile<DT, NT, U, OUT, MASKED>(t, tile_base + blockIdx.x, R, nwrite, local, keep_unused, sc, flat, gate, tag);
 }
 
@@ -1164,10 +1174,11 @@ bool timing_pair_unused() {
 }
 
 hipError_t launch_pack(const SegTables& t, int64_t tile_base, int64_t ntiles, char* slab0,
-                       int64_t slab_stride, int nrep, const uint64_t* local, hipStream_t s) {
+                       int64_t slab_stride, int nrep, const uint64_t* local,
+                       const GateRecord* gate, uint32_t tag, hipStream_t s) {
     if (ntiles <= 0 || nrep <= 0) return hipSuccess;
     dim3 grid(static_cast<unsigned>(ntiles), static_cast<unsigned>(nrep));
-    return launch(seg_copy_kernel<true>, grid, 0u, s, t, tile_base, slab0, slab_stride, local, nullptr, 0);
+    return launch(seg_copy_kernel<true>, grid, 0u, s, t, tile_base, slab0, slab_stride, local, nullptr, 0, gate, tag);
 }
 
 hipError_t launch_unpack(const SegTables& t, int64_t tile_base, int64_t ntiles,
@@ -1176,7 +1187,7 @@ hipError_t launch_unpack(const SegTables& t, int64_t tile_base, int64_t ntiles,
     if (ntiles <= 0 || nrep <= 0) return hipSuccess;
     dim3 grid(static_cast<unsigned>(ntiles), static_cast<unsigned>(nrep));
     const int keep = keep_unused ? 1 : 0;
-    return launch(seg_copy_kernel<false>, grid, 0u, s, t, tile_base, const_cast<char*>(out_slab), int64_t(0), nullptr, global_used, keep);
+    return launch(seg_copy_kernel<false>, grid, 0u, s, t, tile_base, const_cast<char*>(out_slab), int64_t(0), nullptr, global_used, keep, nullptr, 0u);
 }
 
 // Vectors per thread and replica in the reduce kernels: a tile's worth (two), which measured
@@ -1185,20 +1196,22 @@ constexpr int RU = TILE_VECS / BLOCK;
 
 template <int DT>
 static hipError_t flat_reduce_dispatch(bool nt, unsigned lds, hipStream_t s, const char* in0, int64_t stride,
-                                       char* out, int64_t nvec, int R, Scale sc) {
+                                       char* out, int64_t nvec, int R, Scale sc,
+                                       const GateRecord* gate, uint32_t tag, DispatchSignal sig) {
     const int64_t nrows = (nvec + BLOCK * RU - 1) / (BLOCK * RU);
     dim3 grid(static_cast<unsigned>(nrows));
-    if (nt) return launch(flat_reduce_kernel<DT, true, RU>, grid, lds, s, in0, stride, out, nvec, R, sc);
-    return launch(flat_reduce_kernel<DT, false, RU>, grid, lds, s, in0, stride, out, nvec, R, sc);
+    if (nt) return launch(flat_reduce_kernel<DT, true, RU>, grid, lds, s, in0, stride, out, nvec, R, sc, gate, tag, sig);
+    return launch(flat_reduce_kernel<DT, false, RU>, grid, lds, s, in0, stride, out, nvec, R, sc, gate, tag, sig);
 }
 
 hipError_t launch_flat_reduce(int dtype, const char* in0, int64_t stride, char* out, int64_t nvec,
-                              int R, Scale sc, bool nontemporal, unsigned lds, hipStream_t s) {
+                              int R, Scale sc, bool nontemporal, unsigned lds,
+                              const GateRecord* gate, uint32_t tag, DispatchSignal sig, hipStream_t s) {
     if (nvec <= 0) return hipSuccess;
     switch (dtype) {
-        case 0: return flat_reduce_dispatch<0>(nontemporal, lds, s, in0, stride, out, nvec, R, sc);
-        case 1: return flat_reduce_dispatch<1>(nontemporal, lds, s, in0, stride, out, nvec, R, sc);
-        case 2: return flat_reduce_dispatch<2>(nontemporal, lds, s, in0, stride, out, nvec, R, sc);
+        case 0: return flat_reduce_dispatch<0>(nontemporal, lds, s, in0, stride, out, nvec, R, sc, gate, tag, sig);
+        case 1: return flat_reduce_dispatch<1>(nontemporal, lds, s, in0, stride, out, nvec, R, sc, gate, tag, sig);
+        case 2: return flat_reduce_dispatch<2>(nontemporal, lds, s, in0, stride, out, nvec, R, sc, gate, tag, sig);
         default: return hipErrorInvalidValue;
     }
 }

@@ -82,11 +82,12 @@ def test_shifted_replicas_with_binary32_outputs(transport, out_skew):
 
 
 @pytest.mark.parametrize("dtype", [FP32, FP16, BF16])
-@pytest.mark.parametrize("R", [1, 3, 8, 13])
+@pytest.mark.parametrize("R", [1, 3, 8, 13, 17, 64])
 @pytest.mark.parametrize("masked", [False, True])
 def test_staged_buckets_in_one_pass_and_in_two(dtype, R, masked):
     """The staged pipeline copies and reduces a bucket in one pass, or, when its kernels are timed
-    one by one, in two: flat buckets, averages and gradients have the same bits either way."""
+    one by one and in short launches over more than 16 replicas, in two: flat buckets, averages and
+    gradients have the same bits either way."""
     d, harness = lib()
     es = ES[dtype]
     numel = edge_sizes(es)
@@ -118,6 +119,37 @@ def test_staged_buckets_in_one_pass_and_in_two(dtype, R, masked):
                     assert part == expect, f"timing {timing} replica {r} parameter {p}: flat bucket"
         got.append((flat, [grads.download(r, i).tobytes() for r in range(R) for i in range(n)]))
     assert got[0] == got[1]
+
+
+@pytest.mark.parametrize("dtype,tiles", [(FP32, 512), (FP32, 513), (FP16, 1024), (BF16, 1025)])
+@pytest.mark.parametrize("R", [16, 17])
+def test_staged_launches_on_both_sides_of_the_two_pass_limit(dtype, tiles, R):
+    """The longest launch that takes two passes and the shortest that takes one: the sum runs in
+    ascending order and is rounded once, so torch gives the same bits."""
+    d, harness = lib()
+    import torch
+    es = ES[dtype]
+    numel = [tiles * TILE // es - 5]
+    t = {FP32: torch.float32, FP16: torch.float16, BF16: torch.bfloat16}[dtype]
+    grads = harness.DeviceGrads(numel, [dtype], R, fill=0xFF)
+    gen = torch.Generator("cuda")
+    for r in range(R):
+        gen.manual_seed(760 + r)
+        grads.view(r, 0).view(t).normal_(generator=gen)
+    each = [grads.view(r, 0).view(t).clone() for r in range(R)]
+    total = each[0].float()
+    for r in range(1, R):
+        total = total + each[r].float()
+    # (divided on the CPU: by a number, torch multiplies with the reciprocal on the GPU)
+    want = (total.cpu() / torch.full((1,), float(R))).to(t)
+    torch.cuda.synchronize()
+    with harness.Session(grads, 0, 0) as s:
+        s.sync()
+        average = s.bucket_bytes(0, -1).tobytes()
+        flat = [s.bucket_bytes(0, r).tobytes() for r in range(R)]
+    assert grads.download(0, 0).tobytes() == want.view(torch.uint8).numpy().tobytes() == average
+    for r in range(R):
+        assert flat[r] == each[r].view(torch.uint8).cpu().numpy().tobytes()
 
 
 @pytest.mark.parametrize("dtype", [FP32, FP16, BF16])

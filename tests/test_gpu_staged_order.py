@@ -35,8 +35,9 @@ def flag_ordered_session(d, harness, grads, cap, pipeline):
 @pytest.mark.parametrize("dtype", [FP32, FP16, BF16])
 @pytest.mark.parametrize("gate_wait_us", [100000, 0])
 @pytest.mark.parametrize("tail_on_backward", [1, 0])
-def test_staged_launches_wait_for_the_backward_stream(dtype, gate_wait_us, tail_on_backward):
-    staged_launches_wait(dtype, gate_wait_us, tail_on_backward, by_flag=True)
+@pytest.mark.parametrize("R", [3, 17])         # 17: copied and reduced in two passes
+def test_staged_launches_wait_for_the_backward_stream(dtype, gate_wait_us, tail_on_backward, R):
+    staged_launches_wait(dtype, gate_wait_us, tail_on_backward, by_flag=True, R=R)
 
 
 @pytest.mark.parametrize("dtype", [FP32, FP16, BF16])
@@ -46,11 +47,11 @@ def test_staged_launches_ordered_by_events_wait_for_the_backward_stream(dtype, s
     staged_launches_wait(dtype, 100000, tail_on_backward, by_flag=False, streams=streams)
 
 
-def staged_launches_wait(dtype, gate_wait_us, tail_on_backward, by_flag, streams=2):
+def staged_launches_wait(dtype, gate_wait_us, tail_on_backward, by_flag, streams=2, R=3):
     d, harness = lib()
     import torch
     numel = [5, 3000, 3 * 4096 + 7, 8192, 1, 777, 2 * 8192, 4000, 60, 5000]
-    n, R, cap = len(numel), 3, 32 << 10
+    n, cap = len(numel), 32 << 10
     es = 4 if dtype == FP32 else 2
     dtypes = [dtype] * n
     grads = harness.DeviceGrads(numel, dtypes, R, fill=0xFF)
