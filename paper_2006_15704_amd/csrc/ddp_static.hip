@@ -83,37 +83,56 @@ hipError_t upload(unsigned char* dst, const void* src, size_t bytes, hipStream_t
 }
 
 // Whether no tensor that the call writes (replica 0's) shares a byte with any other tensor it reads.
-// Told from the address ranges of whole replicas, in O(n R): each replica's tensors usually come
+// Told from the address ranges of whole replicas: each replica's tensors usually come
 // from one region, and lists for which that does not hold take the path through the flat buckets.
+// Replica 0's own tensors are compared in the order of the list if their addresses ascend or descend in it;
+// else they are sorted, up to kSortedTensors of them, where that costs what the flat path's launches
+// do (host time of a call with shuffled tensors, R = 2, flat / sorted: 300 49 / 23 us, 2000 171 / 175, 20000
+// 1300 / 2046; ascending 20000 flat 1293, sorted 1416, compared in order 1306).
+constexpr size_t kSortedTensors = 2000;
+
+struct AddressRange {
+    uintptr_t first = UINTPTR_MAX, end = 0;      // empty: end == 0
+};
+
 bool writes_are_apart(const ddp::BucketPlan& plan, void* const* grad_ptrs, int32_t R) {
     const size_t n = plan.params.size();
-    std::vector<std::pair<uintptr_t, uintptr_t>> own;     // replica 0's tensors, [first byte, end)
-    uintptr_t lo = 0, hi = 0;
-    own.reserve(n);
+    auto bytes_of = [&](size_t i) { return static_cast<uintptr_t>(plan.params[i].numel) * ddp::elem_size(plan.params[i].dtype); };
+    AddressRange own;
+    bool ascending = true, descending = true;
+    uintptr_t before_first = 0, before_end = 0;
     for (size_t i = 0; i < n; ++i) {
-        const uintptr_t bytes = static_cast<uintptr_t>(plan.params[i].numel) * ddp::elem_size(plan.params[i].dtype);
-        const uintptr_t a = reinterpret_cast<uintptr_t>(grad_ptrs[i]);
+        const uintptr_t bytes = bytes_of(i), a = reinterpret_cast<uintptr_t>(grad_ptrs[i]);
         if (bytes == 0) continue;
-        own.emplace_back(a, a + bytes);
-        if (own.size() == 1 || a < lo) lo = a;
-        if (own.size() == 1 || a + bytes > hi) hi = a + bytes;
-    }
-    std::sort(own.begin(), own.end());
-    for (size_t k = 1; k < own.size(); ++k)
-        if (own[k].first < own[k - 1].second) return false;
-    for (int64_t r = 1; r < R; ++r) {
-        bool any = false;
-        uintptr_t first = 0, end = 0;
-        for (size_t i = 0; i < n; ++i) {
-            const uintptr_t bytes = static_cast<uintptr_t>(plan.params[i].numel) * ddp::elem_size(plan.params[i].dtype);
-            const uintptr_t a = reinterpret_cast<uintptr_t>(grad_ptrs[r * static_cast<int64_t>(n) + static_cast<int64_t>(i)]);
-            if (bytes == 0) continue;
-            if (!any || a < first) first = a;
-            if (!any || a + bytes > end) end = a + bytes;
-            any = true;
+        if (own.end != 0) {
+            ascending = ascending && a >= before_end;
+            descending = descending && a + bytes <= before_first;
         }
-        if (any && !own.empty() && first < hi && lo < end) return false;
+        before_first = a;
+        before_end = a + bytes;
+        own.first = std::min(own.first, a);
+        own.end = std::max(own.end, a + bytes);
     }
+    for (int64_t r = 1; r < R; ++r) {
+        void* const* row = grad_ptrs + r * static_cast<int64_t>(n);
+        AddressRange other;
+        for (size_t i = 0; i < n; ++i) {
+            const uintptr_t bytes = bytes_of(i), a = reinterpret_cast<uintptr_t>(row[i]);
+            if (bytes == 0) continue;
+            other.first = std::min(other.first, a);
+            other.end = std::max(other.end, a + bytes);
+        }
+        if (other.first < own.end && own.first < other.end) return false;
+    }
+    if (ascending || descending) return true;
+    if (n > kSortedTensors) return false;
+    std::vector<std::pair<uintptr_t, uintptr_t>> sorted;     // replica 0's tensors, [first byte, end)
+    sorted.reserve(n);
+    for (size_t i = 0; i < n; ++i)
+        if (bytes_of(i) != 0) sorted.emplace_back(reinterpret_cast<uintptr_t>(grad_ptrs[i]), reinterpret_cast<uintptr_t>(grad_ptrs[i]) + bytes_of(i));
+    std::sort(sorted.begin(), sorted.end());
+    for (size_t k = 1; k < sorted.size(); ++k)
+        if (sorted[k].first < sorted[k - 1].second) return false;
     return true;
 }
 

@@ -206,3 +206,35 @@ def test_static_entry_point_with_tensors_that_share_memory():
         assert both.download(0, R * i).tobytes() == want[i].tobytes(), f"parameter {i}"
         for r in range(1, R):
             assert both.download(0, R * i + r).tobytes() == reps[r][i].tobytes()
+
+
+@pytest.mark.parametrize("order", ["ascending", "descending", "shuffled"])
+@pytest.mark.parametrize("n", [5, 2000, 2001])       # longer unordered lists are not searched for shared memory
+@pytest.mark.parametrize("shared", [False, True])
+def test_static_entry_point_with_tensors_in_any_order_of_addresses(order, n, shared):
+    d, harness = lib()
+    import torch
+    stream = torch.cuda.Stream()
+    rng = np.random.default_rng(50 + n)
+    R, cap = 2, 1 << 20
+    at = {"ascending": list(range(n)), "descending": list(range(n - 1, -1, -1)),
+          "shuffled": [int(p) for p in rng.permutation(n)]}[order]      # parameter i is the at[i]-th in memory
+    stored = [int(x) for x in rng.integers(1, 20, size=n)]
+    if shared:
+        at[n - 1] = at[0]
+    numel = [stored[k] for k in at]
+    reps = inputs(51, stored, R, 1.0, FP32)
+    listed = [[reps[r][k] for k in at] for r in range(R)]
+    want, _, _ = oracle.synchronize(numel, [FP32] * n, cap, listed)
+    grads = harness.DeviceGrads(stored, [FP32] * n, R, align=4, fill=0xFF)
+    for r in range(R):
+        grads.bufs[r].copy_(torch.from_numpy(np.concatenate([np.concatenate(reps[r]).view(np.uint8),
+                                                             np.full(128, 0xFF, np.uint8)])))
+    torch.cuda.synchronize()
+    d.ddp_sync_static(R, 0, stream.cuda_stream, numel, [FP32] * n, [grads.ptr(r, k) for r in range(R) for k in at], cap)
+    stream.synchronize()
+    result = [grads.bufs[r].cpu().numpy() for r in range(R)]
+    for i in range(n):
+        o, b = grads.offsets[at[i]], grads.nbytes(at[i])
+        assert result[0][o:o + b].tobytes() == want[i].tobytes(), f"parameter {i}"
+        assert result[1][o:o + b].tobytes() == listed[1][i].tobytes()
