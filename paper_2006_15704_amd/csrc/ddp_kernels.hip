@@ -229,14 +229,15 @@ __device__ __forceinline__ void copy_tile(const char* __restrict__ src, char* __
 }
 
 // PACK: grad[r][g] -> slab_r + flat_byte[g];  UNPACK: out slab -> grad[r][g].
-template <bool PACK>
+// GATED: the launch has a gate in front of it (PACK only; see fused_tile).
+template <bool PACK, bool GATED>
 __global__ __launch_bounds__(BLOCK) void seg_copy_kernel(SegTables t, int64_t tile_base,
                                                          char* slab0, int64_t slab_stride,
                                                          const uint64_t* __restrict__ local,
                                                          const uint8_t* __restrict__ global_used,
                                                          int keep_unused,
                                                          const GateRecord* __restrict__ gate, uint32_t tag) {
-    if (PACK && gate != nullptr && gate->failed_tag == tag) return;      // see fused_tile
+    if (GATED && gate->failed_tag == tag) return;
     const int64_t tile = tile_base + blockIdx.x;
     const int r = blockIdx.y;
     const int g = t.tile_seg[tile];
@@ -440,15 +441,18 @@ __device__ __forceinline__ void chunk_flat(const char* __restrict__ in0, int64_t
 // Every block handles one row of BLOCK*U consecutive vectors, so blocks stream
 // through memory in launch order (a bounded grid whose blocks loop over distant
 // rows measured slower).
-template <int DT, bool NT, int U>
+// GATED: gate or sig are set (without them the kernel starts without a look at either).
+template <int DT, bool NT, int U, bool GATED>
 __global__ __launch_bounds__(BLOCK) void flat_reduce_kernel(const char* __restrict__ in0,
                                                             int64_t stride, char* __restrict__ out,
                                                             int64_t nvec, int R, Scale sc,
                                                             const GateRecord* __restrict__ gate,
                                                             uint32_t tag, DispatchSignal sig) {
     constexpr int VEC = Fmt<DT>::VEC;
-    signal_dispatch(sig);
-    if (gate != nullptr && gate->failed_tag == tag) return;              // see fused_tile
+    if (GATED) {
+        signal_dispatch(sig);
+        if (gate != nullptr && gate->failed_tag == tag) return;
+    }
     const int64_t row = blockIdx.x;
     float acc[U][VEC];
     if ((row + 1) * (BLOCK * U) <= nvec) {
@@ -1178,7 +1182,7 @@ hipError_t launch_pack(const SegTables& t, int64_t tile_base, int64_t ntiles, ch
                        const GateRecord* gate, uint32_t tag, hipStream_t s) {
     if (ntiles <= 0 || nrep <= 0) return hipSuccess;
     dim3 grid(static_cast<unsigned>(ntiles), static_cast<unsigned>(nrep));
-    return launch(seg_copy_kernel<true>, grid, 0u, s, t, tile_base, slab0, slab_stride, local, nullptr, 0, gate, tag);
+    return launch(gate != nullptr ? seg_copy_kernel<true, true> : seg_copy_kernel<true, false>, grid, 0u, s, t, tile_base, slab0, slab_stride, local, nullptr, 0, gate, tag);
 }
 
 hipError_t launch_unpack(const SegTables& t, int64_t tile_base, int64_t ntiles,
@@ -1187,7 +1191,7 @@ hipError_t launch_unpack(const SegTables& t, int64_t tile_base, int64_t ntiles,
     if (ntiles <= 0 || nrep <= 0) return hipSuccess;
     dim3 grid(static_cast<unsigned>(ntiles), static_cast<unsigned>(nrep));
     const int keep = keep_unused ? 1 : 0;
-    return launch(seg_copy_kernel<false>, grid, 0u, s, t, tile_base, const_cast<char*>(out_slab), int64_t(0), nullptr, global_used, keep, nullptr, 0u);
+    return launch(seg_copy_kernel<false, false>, grid, 0u, s, t, tile_base, const_cast<char*>(out_slab), int64_t(0), nullptr, global_used, keep, nullptr, 0u);
 }
 
 // Vectors per thread and replica in the reduce kernels: a tile's worth (two), which measured
@@ -1200,8 +1204,9 @@ static hipError_t flat_reduce_dispatch(bool nt, unsigned lds, hipStream_t s, con
                                        const GateRecord* gate, uint32_t tag, DispatchSignal sig) {
     const int64_t nrows = (nvec + BLOCK * RU - 1) / (BLOCK * RU);
     dim3 grid(static_cast<unsigned>(nrows));
-    if (nt) return launch(flat_reduce_kernel<DT, true, RU>, grid, lds, s, in0, stride, out, nvec, R, sc, gate, tag, sig);
-    return launch(flat_reduce_kernel<DT, false, RU>, grid, lds, s, in0, stride, out, nvec, R, sc, gate, tag, sig);
+    const bool gated = gate != nullptr || sig.word != nullptr;
+    if (nt) return launch(gated ? flat_reduce_kernel<DT, true, RU, true> : flat_reduce_kernel<DT, true, RU, false>, grid, lds, s, in0, stride, out, nvec, R, sc, gate, tag, sig);
+    return launch(gated ? flat_reduce_kernel<DT, false, RU, true> : flat_reduce_kernel<DT, false, RU, false>, grid, lds, s, in0, stride, out, nvec, R, sc, gate, tag, sig);
 }
 
 hipError_t launch_flat_reduce(int dtype, const char* in0, int64_t stride, char* out, int64_t nvec,
