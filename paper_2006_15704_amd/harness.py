@@ -119,8 +119,7 @@ class Session:
                 B.ddp_set_outputs(self.ctx, [outputs.ptr(0, i) for i in range(outputs.n)])
             self.n_buckets = B.ddp_build_buckets(self.ctx, cap_bytes)
             self.streams_concurrent = bool(B.ddp_get_option(self.ctx, B.DDP_OPT_FLAG_ORDER))
-            if (self.streams_concurrent or streams is not None or same_stream
-                    or pipeline != B.DDP_PIPELINE_FUSED or attempt == 7):
+            if self.streams_concurrent or streams is not None or same_stream or attempt == 7:
                 break
             B.ddp_destroy(self.ctx)
             self.ctx = None

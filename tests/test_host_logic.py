@@ -300,6 +300,28 @@ print(len([x for x in beats if a + 0.1 < x < b - 0.1]))
     assert int(out.stdout) >= 5
 
 
+@pytest.mark.parametrize("pipeline", [0, 1])
+def test_session_tries_streams_until_a_pair_runs_side_by_side(d, pipeline, monkeypatch):
+    """Both pipelines order their launches by flags where the streams allow it, so a session of either
+    takes another pair of streams if the probe says that the first one shares a hardware queue."""
+    from types import SimpleNamespace
+    from paper_2006_15704_amd import harness
+    created, destroyed = [], []
+    fake = SimpleNamespace(**{k: getattr(d.binding, k) for k in dir(d.binding) if k.startswith("DDP_")})
+    fake.ddp_create = lambda R, device, a, b: created.append((a, b)) or len(created)
+    fake.ddp_destroy = destroyed.append
+    fake.ddp_set_option = fake.ddp_register_params = lambda *a: None
+    fake.ddp_build_buckets = lambda ctx, cap: 1
+    fake.ddp_get_option = lambda ctx, option: int(len(created) >= 3)
+    handles = iter(range(1, 100))
+    monkeypatch.setattr(harness, "B", fake)
+    monkeypatch.setattr(harness.torch.cuda, "Stream", lambda device=None: SimpleNamespace(cuda_stream=next(handles)))
+    monkeypatch.setattr(harness.torch.cuda, "synchronize", lambda: None)
+    grads = SimpleNamespace(R=2, device=None, numel=[4], dtype=[0], ptrs=lambda: [0, 0])
+    s = harness.Session(grads, 0, pipeline)
+    assert s.streams_concurrent and s.ctx == 3 and destroyed == [1, 2] and len(set(created)) == 3
+
+
 def test_reduction_stream_option_is_validated(d):
     ctx, _ = plan(d, [4, 4, 4], [0, 0, 0], 0)
     try:
