@@ -211,8 +211,9 @@ typedef struct ddp_ctx ddp_ctx;
 
 /* DDP_PIPELINE_STAGED follows the paper's data flow literally: gradients are
  * copied into flat per-replica bucket buffers (Algorithm 1, autograd_hook),
- * the bucket is reduced (in the same pass over the gradients; with
- * DDP_OPT_TIMING 1 by a kernel of its own, so that both can be stamped), and
+ * the bucket is reduced (in the same pass over the gradients; by a kernel of its
+ * own in short launches over more than 16 replicas, and with DDP_OPT_TIMING 1 so
+ * that both can be stamped), and
  * the averaged bucket is copied back to the gradient tensors by the finalizing
  * step.  DDP_PIPELINE_FUSED computes the
  * same values in one pass per bucket: the kernel gathers each replica's
@@ -268,13 +269,12 @@ int32_t ddp_get_option(ddp_ctx* ctx, int32_t option, int64_t* value);
  *   grad_ptrs     host array of R*n device pointers, row-major [r][i]: replica
  *                 r's gradient of parameter i; contiguous, aligned at least to
  *                 its element size.  16-byte alignment is exploited, not
- *                 required: what matters is that the R tensors of a
- *                 parameter share one address modulo 16 (whatever it is);
- *                 then whole tiles take the unpredicated path (77 % of the HBM
- *                 peak measured on 25 MiB tensors, R = 8).  Replicas that are
- *                 shifted against each other are read with element-aligned
- *                 16-byte loads and cost extra cache lines (62 % measured on
- *                 the same list with the replicas 4 bytes apart modulo 16).
+ *                 required: vectors are cut on replica 0's 16-byte grid, and
+ *                 replicas that are shifted against it are read with
+ *                 element-aligned 16-byte loads, which cost one more cache line
+ *                 per 1 KiB (40 tensors of 25 MiB, R = 8: 79 % of the HBM peak
+ *                 with one address modulo 16 for all replicas of a tensor,
+ *                 78 % with the replicas 4 bytes apart).
  *                 Ignored (may be NULL) on a plan-only context.
  * Errors: n <= 0, null arrays or pointers, unknown dtype -> DDP_ERR_ARG;
  * second call -> DDP_ERR_STATE. */
@@ -347,13 +347,14 @@ int32_t ddp_get_bucket_ptr(const ddp_ctx* ctx, int32_t b, int32_t r, void** ptr)
 /* Algorithm 1, autograd_hook(param_index), with the pending counts of
  * Section 4.2: records that all R replica gradients of `param_id` have been
  * produced by work already enqueued on backward_stream, decrements the
- * bucket's pending count, and launches on reduce_stream (see also
- * DDP_OPT_REDUCE_STREAMS and DDP_OPT_TAIL_ON_BACKWARD), in bucket order,
+ * bucket's pending count, and launches on a reduction stream (which one:
+ * DDP_OPT_REDUCE_STREAMS; DDP_OPT_TAIL_ON_BACKWARD and small models:
+ * backward_stream), in bucket order,
  * every bucket that is complete and whose predecessors have all been launched
  * (Section 3.2.3: no bucket i+1 before bucket i).  A launch first makes
- * reduce_stream wait for backward_stream's work enqueued so far, then copies
+ * its stream wait for backward_stream's work enqueued so far, then copies
  * the bucket's gradients into the flat buffers and reduces them (staged), or
- * runs the one-pass kernel (fused).  Returns after enqueueing.
+ * gathers, reduces and writes them in one pass (fused).  Returns after enqueueing.
  * Errors: buckets not built -> DDP_ERR_STATE; id out of range -> DDP_ERR_ARG;
  * marked twice in one iteration -> DDP_ERR_ALREADY_READY (no state change). */
 int32_t ddp_mark_ready(ddp_ctx* ctx, int32_t param_id);
@@ -364,9 +365,9 @@ int32_t ddp_mark_ready(ddp_ctx* ctx, int32_t param_id);
  * parameter.  A replica that did not contributes zeros to the sum (which is
  * still divided by R) and its tensor is not read.  Participation recorded by
  * ddp_no_sync_accumulate since the last finalize is OR-ed in (Section 3.2.4).
- * ddp_mark_ready(p) is the same call with every used[r] = 1.  At finalize the
- * per-replica flags are copied to the device and reduced with an OR over the
- * replicas (the extra AllReduce on the bitmap); parameters whose global bit is
+ * ddp_mark_ready(p) is the same call with every used[r] = 1.  At finalize a
+ * kernel carries the per-replica flags to the device and reduces them with an OR
+ * over the replicas (the extra AllReduce on the bitmap); parameters whose global bit is
  * 0 keep their gradients with DDP_OPT_FIND_UNUSED, else receive zeros.
  * Errors as for ddp_mark_ready; used == NULL -> DDP_ERR_ARG. */
 int32_t ddp_mark_ready_local(ddp_ctx* ctx, int32_t param_id, const uint8_t* used);
@@ -374,7 +375,8 @@ int32_t ddp_mark_ready_local(ddp_ctx* ctx, int32_t param_id, const uint8_t* used
 /* used[n] (host): the global bitmap of the synchronization closed by the latest
  * ddp_finalize_backward, 1 = at least one replica used the parameter.  When any
  * flag of that iteration was 0 this is the device-computed result (the call
- * waits for the copy that finalize enqueued); otherwise it is all ones. */
+ * waits for the kernel that finalize enqueued, which writes it to host memory);
+ * otherwise it is all ones. */
 int32_t ddp_get_global_used(ddp_ctx* ctx, uint8_t* used);
 
 /* Same as calling ddp_mark_ready for ids[0..count) in order; stops at the
@@ -459,7 +461,9 @@ int32_t ddp_get_kernel_times(ddp_ctx* ctx, int32_t kind, float* ms, int32_t* ids
  * (n, numel, dtype, grad_ptrs: host arrays, copied before the call returns;
  * gradient memory stays the caller's).  Returns the number of buckets.
  *
- * The device tables and the R + 1 flat bucket buffers live in a static device
+ * The device tables and, where the call needs them, the R + 1 flat bucket
+ * buffers (more than 16 replicas, or tensors that may share memory; the limit
+ * below counts them always) live in a static device
  * array of DDP_STATIC_SCRATCH_BYTES that every GPU used through this call holds
  * until the process ends; host tables travel inside kernel arguments.  The call
  * makes no hipMalloc / hipFree / hipHostMalloc and no copy from host memory; all

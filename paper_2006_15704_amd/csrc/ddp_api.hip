@@ -203,9 +203,9 @@ int64_t coalesce_limit(const ddp_ctx* c) { return c->coalesce < 0 ? auto_coalesc
 // A launch is chained to the one in front of it if that one moves at least this many bytes.
 constexpr int64_t kChainMinTraffic = int64_t(160) << 20;
 
-// Whether a launch is one kernel, one that carries the gate check and reports its dispatch: always but
-// for the staged pipeline with its kernels timed one by one.
-bool one_kernel(const ddp_ctx* c) { return c->pipeline == DDP_PIPELINE_FUSED || c->timing != 1; }
+// Whether a launch's kernels carry the gate check and report the dispatch: always but for the staged
+// pipeline with its kernels timed one by one.
+bool carries_gate(const ddp_ctx* c) { return c->pipeline == DDP_PIPELINE_FUSED || c->timing != 1; }
 
 // Bytes that a launch over `launch_bytes` of bucket data moves (the staged pass writes R copies too).
 int64_t launch_traffic(const ddp_ctx* c, int64_t launch_bytes) {
@@ -375,7 +375,7 @@ int32_t create_lane(ddp_ctx* c, int l) {
 // Flags order the launches of the running API call if every reduction stream in use passed
 // the probe.
 bool flags_usable(const ddp_ctx* c) {
-    if (c->flag_order == 0 || !one_kernel(c) || c->d_gate == nullptr) return false;
+    if (c->flag_order == 0 || !carries_gate(c) || c->d_gate == nullptr) return false;
     // (by default the second stream is only used if it passed the probe, see launch_range)
     const int lanes = c->n_streams < 0 ? 1 : c->n_streams;
     for (int l = 0; l < lanes; ++l)
@@ -497,7 +497,7 @@ int32_t launch_range(ddp_ctx* c, int32_t first, int32_t last, Target target) {
     const bool flags_in_use = c->call_by_flag || c->gates_in_iter > 0;
     const bool both_long = c->prev_launch_long && long_launch(c, bytes);
     const bool chained = c->chain_launches != 0 && flags_in_use && c->prev_launch_ord != 0 && c->prev_launch_lane != lane &&
-                         ntiles > 0 && one_kernel(c) &&
+                         ntiles > 0 && carries_gate(c) &&
                          ((c->prev_launch_traffic >= kChainMinTraffic && !both_long) ||
                           (lane < 0 && traffic >= kChainMinTraffic));
     const long long wait_ticks = c->gate_wait_us * c->wall_clock_khz / 1000;
@@ -527,7 +527,7 @@ int32_t launch_range(ddp_ctx* c, int32_t first, int32_t last, Target target) {
         }
         c->lane_ordered[lane] = true;
     }
-    if (c->chain_launches != 0 && (c->call_by_flag || c->gates_in_iter > 0) && ntiles > 0 && one_kernel(c)) {
+    if (c->chain_launches != 0 && (c->call_by_flag || c->gates_in_iter > 0) && ntiles > 0 && carries_gate(c)) {
         // the launch reports when its last block starts, for whatever is chained behind it
         sig.word = &c->d_order->dispatched;
         sig.ord = ++c->launch_ord;
@@ -1383,7 +1383,7 @@ int32_t ddp_get_global_used(ddp_ctx* c, uint8_t* used) {
     if (!c->built) return DDP_ERR_STATE;
     const int32_t n = static_cast<int32_t>(c->plan.params.size());
     if (c->global_on_device) {
-        // what the bitmap kernel computed, brought back by the copy enqueued at finalize
+        // what the bitmap kernel of finalize computed and wrote to host memory
         HIPCHK(c, hipSetDevice(c->device));
         HIPCHK(c, hipEventSynchronize(c->ev_global[(c->iteration - 1) & 1]));
         for (int32_t i = 0; i < n; ++i) used[i] = c->h_global[c->plan.params[i].segment];
