@@ -677,13 +677,15 @@ __device__ __forceinline__ void fused_tile(const SegTables& t, int64_t tile, int
     const char* pre[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) pre[i] = static_cast<const char*>(row[i]);
+    // (behind a gate that gave up this row may be an earlier iteration's: it is not looked at then)
+    const uint64_t mask = MASKED && local != nullptr ? local[g] : 0;
     if (gate_word == tag) return;          // the gate in front of this launch gave up
     const int64_t numel = si.numel;
     const int64_t ltile = tile - si.tile0;
     // participation of the R replicas in this parameter (bit r = replica r used
     // it); without a flag table every replica did
     const uint64_t everyone = R >= 64 ? ~uint64_t(0) : ((uint64_t(1) << R) - 1);
-    const uint64_t used = MASKED && local != nullptr ? local[g] : everyone;
+    const uint64_t used = MASKED && local != nullptr ? mask : everyone;
     if (OUT != OUT_FLAT && used == 0 && keep_unused) return;   // globally unused: the gradients stay as they are
     const bool zero = OUT != OUT_FLAT && used == 0;            // ... or become zeros (flat buckets always do)
     const bool all_used = !MASKED || used == everyone;
