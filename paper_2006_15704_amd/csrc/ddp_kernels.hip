@@ -576,14 +576,16 @@ __device__ __forceinline__ void store_out32_wave(char* out, int64_t in_byte_off,
     store16u<NT>(wave_base + 1024 + 16 * lane, b);
 }
 
-// OUT_FLAT: a vector that reaches over an end of the segment, elements [lo, hi) of it.  The loads of C
-// replicas are issued before the stores and the adds.  (One element and replica at a time, each load behind
-// the store of the one before: 3000 binary16 elements in eight tensors, R = 8 27 us a synchronization, R = 16
-// 49, R = 64 169; so 17, 27 and 86, with C = 4 19, 28 and 97.)
+// A vector that reaches over an end of the segment, elements [lo, hi) of it.  The loads of C replicas are
+// issued before the adds and, with `slot` set (staged pipeline), before the stores to the flat buckets.
+// One element and replica at a time, each load behind the add or the store of the one before: staged, 3000
+// binary16 elements in eight tensors, R = 8 27 us a synchronization, R = 16 49, R = 64 169; so 17, 27 and 86
+// (with C = 4 19, 28 and 97).  Fused, the kernel alone, 2 million elements in a hundred tensors: binary16 R = 8 17.0
+// and 13.0 us, R = 16 30.4 and 23.2, R = 64 120 and 81; binary32 R = 16 30.1 and 26.4, R = 64 128 and 107.
 // The copy moves bits, not values: a signalling NaN arrives in the bucket as it is.
-template <int DT, int C>
-__device__ __forceinline__ void chunk_copy_edge(void* const* __restrict__ row, int r, uint64_t used, int lo, int hi,
-                                                int64_t off, char* slot, int64_t stride, float (&s)[Fmt<DT>::VEC]) {
+template <int DT, int C, bool COPY>
+__device__ __forceinline__ void chunk_edge(void* const* __restrict__ row, int r, uint64_t used, int lo, int hi,
+                                           int64_t off, char* slot, int64_t stride, float (&s)[Fmt<DT>::VEC]) {
     constexpr int ES = Fmt<DT>::ES;
     constexpr int VEC = Fmt<DT>::VEC;
     typedef typename std::conditional<ES == 4, uint32_t, uint16_t>::type bits;
@@ -602,52 +604,39 @@ __device__ __forceinline__ void chunk_copy_edge(void* const* __restrict__ row, i
     for (int i = 0; i < C; ++i)
 #pragma unroll
         for (int k = 0; k < VEC; ++k) {
-            if (k >= lo && k < hi) gstore<bits>(slot + (r + i) * stride + off + k * ES, x[i][k]);
+            if (COPY && k >= lo && k < hi) gstore<bits>(slot + (r + i) * stride + off + k * ES, x[i][k]);
             s[k] += Fmt<DT>::value(x[i][k]);
         }
 }
 
-template <int DT>
-__device__ __forceinline__ void copy_edge(void* const* __restrict__ row, int R, uint64_t used, int64_t e, int64_t numel,
-                                          char* slot, int64_t stride, const Scale& sc) {
+template <int DT, int OUT>
+__device__ __forceinline__ void reduce_edge(const SegTables& t, int g, void* const* __restrict__ row, int R, int nwrite,
+                                            int64_t e, int64_t numel, bool zero, uint64_t used, const Scale& sc,
+                                            char* slot, int64_t stride) {
     constexpr int ES = Fmt<DT>::ES;
     constexpr int VEC = Fmt<DT>::VEC;
     const int lo = e < 0 ? static_cast<int>(-e) : 0;
     const int hi = numel - e < VEC ? static_cast<int>(numel - e) : VEC;
-    const int64_t off = e * ES;
     float s[VEC];
 #pragma unroll
     for (int k = 0; k < VEC; ++k) s[k] = -0.0f;
-    constexpr int C = 8;
-    int r = 0;
-    for (; r + C <= R; r += C) chunk_copy_edge<DT, C>(row, r, used, lo, hi, off, slot, stride, s);
-    for (; r < R; ++r) chunk_copy_edge<DT, 1>(row, r, used, lo, hi, off, slot, stride, s);
-#pragma unroll
-    for (int k = 0; k < VEC; ++k)
-        if (k >= lo && k < hi) Fmt<DT>::store1(slot + R * stride + off + k * ES, apply_scale(sc, s[k]));
-}
-
-template <int DT, int OUT>
-__device__ __forceinline__ void reduce_element(const SegTables& t, int g, int R, int nwrite,
-                                               int64_t idx, bool zero, uint64_t used, const Scale& sc) {
-    constexpr int ES = Fmt<DT>::ES;
-    float y = 0.0f;
     if (!zero) {
-        float s = -0.0f;
-        for (int r = 0; r < R; ++r) {
-            float x = 0.0f;
-            if ((used >> r) & 1u)
-                x = Fmt<DT>::load1(static_cast<const char*>(t.grad[static_cast<int64_t>(g) * t.R + r]) + idx * ES);
-            s += x;
+        int r = 0;
+        for (; r + 8 <= R; r += 8) chunk_edge<DT, 8, OUT == OUT_FLAT>(row, r, used, lo, hi, e * ES, slot, stride, s);
+        for (; r < R; ++r) chunk_edge<DT, 1, OUT == OUT_FLAT>(row, r, used, lo, hi, e * ES, slot, stride, s);
+    }
+#pragma unroll
+    for (int k = 0; k < VEC; ++k) {
+        if (k < lo || k >= hi) continue;
+        const float y = zero ? 0.0f : apply_scale(sc, s[k]);
+        if (OUT == OUT_FLAT) {
+            Fmt<DT>::store1(slot + R * stride + (e + k) * ES, y);
+        } else if (OUT == OUT_BINARY32) {
+            gstore<float>(static_cast<char*>(t.out[g]) + (e + k) * 4, y);
+        } else {
+            for (int w = 0; w < nwrite; ++w) Fmt<DT>::store1(static_cast<char*>(row[w]) + (e + k) * ES, y);
         }
-        y = apply_scale(sc, s);
     }
-    if (OUT == OUT_BINARY32) {
-        gstore<float>(static_cast<char*>(t.out[g]) + idx * 4, y);
-        return;
-    }
-    for (int w = 0; w < nwrite; ++w)
-        Fmt<DT>::store1(static_cast<char*>(t.grad[static_cast<int64_t>(g) * t.R + w]) + idx * ES, y);
 }
 
 // One tile of the fused gather-reduce-scatter.
@@ -797,13 +786,8 @@ __device__ __forceinline__ void fused_tile(const SegTables& t, int64_t tile, int
                     if (src_aligned) store16s<NT>(d + off[u], out);
                     else store16u<NT>(d + off[u], out);
                 }
-            } else if constexpr (OUT == OUT_FLAT) {
-                copy_edge<DT>(row, R, used, e[u], numel, slot, flat.stride, sc);
             } else {
-                for (int i = 0; i < VEC; ++i) {
-                    const int64_t idx = e[u] + i;
-                    if (idx >= 0 && idx < numel) reduce_element<DT, OUT>(t, g, R, nwrite, idx, zero, used, sc);
-                }
+                reduce_edge<DT, OUT>(t, g, row, R, nwrite, e[u], numel, zero, used, sc, slot, flat.stride);
             }
         }
     }
