@@ -462,7 +462,7 @@ int32_t ddp_get_kernel_times(ddp_ctx* ctx, int32_t kind, float* ms, int32_t* ids
  * gradient memory stays the caller's).  Returns the number of buckets.
  *
  * The device tables and, where the call needs them, the R + 1 flat bucket
- * buffers (more than 16 replicas, or tensors that may share memory; the limit
+ * buffers (more than 24 replicas, or tensors that may share memory; the limit
  * below counts them always) live in a static device
  * array of DDP_STATIC_SCRATCH_BYTES that every GPU used through this call holds
  * until the process ends; host tables travel inside kernel arguments.  The call

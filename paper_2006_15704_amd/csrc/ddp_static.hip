@@ -136,12 +136,12 @@ bool writes_are_apart(const ddp::BucketPlan& plan, void* const* grad_ptrs, int32
     return true;
 }
 
-// One block sums all replicas of a tile in turn, and the ends of a 16-bit tensor element by element: with
-// many replicas a short 16-bit list takes longer so than with a copy per replica and a reduction.  us a call
-// in flat buckets / fused: 500 bfloat16 elements in three tensors R = 17 25 / 25, R = 24 26 / 32,
-// R = 32 28 / 40; 400000 binary16 elements in thirty, R = 20 to 32 69 to 82 / 50 to 63, R = 64 (150000)
-// 120 / 110; 700000, R = 16, 72 / 48.  (Binary32 lists are faster fused at every R: R = 64 54 / 46 and 119 / 108.)
-constexpr int32_t kFusedReplicas = 16;
+// One block sums all replicas of a tile in turn: with many replicas a short 16-bit list, whose ends take a
+// lane's worth of elements each, is slower so than with a block per tile and replica for the copies.  us a call in flat
+// buckets / fused: 500 bfloat16 elements in three tensors R = 17 22 to 25 / 19, R = 24 23 to 26 / 23, R = 32 24 to
+// 29 / 28, R = 48 26 to 31 / 39, R = 64 28 to 33 / 49; 100000 in thirty, R = 24 54 / 52, R = 64 (39000) 105 / 110;
+// 400000, R = 24, 61 / 52; binary32, 500 R = 24 24 to 27 / 18, R = 64 29 to 33 / 24, 19000 in thirty, R = 64, 105 / 107.
+constexpr int32_t kFusedReplicas = 24;
 
 #define HIPCHK0(expr)                                                                        \
     do {                                                                                     \

@@ -2,7 +2,7 @@
 is a variant of -- ddp_mark_ready_many + ddp_finalize_backward on a staged
 context -- and against the CPU oracle, bit for bit, on two calls in a row (the
 second with a smaller input, so that what the first call left in the static
-scratch array must not leak into it).  Up to 16 replicas whose tensors lie apart
+scratch array must not leak into it).  Up to 24 replicas whose tensors lie apart
 the call reduces in place; more replicas, and tensors that share memory, go
 through the flat buckets in the array."""
 import numpy as np
@@ -101,7 +101,7 @@ def test_static_entry_point_matches_context_path_twice_in_a_row():
 
 
 @pytest.mark.parametrize("dtype", [FP32, FP16, BF16])
-@pytest.mark.parametrize("R", [16, 17, 64])       # the last that is reduced in place, and flat buckets
+@pytest.mark.parametrize("R", [24, 25, 64])       # the last that is reduced in place, and flat buckets
 def test_static_entry_point_with_many_replicas_on_shrinking_lists(dtype, R):
     """Two calls in a row, the second with fewer and shorter tensors of odd lengths in buckets of other
     sizes: padding and slots that the first one filled lie inside the second one's buckets."""
