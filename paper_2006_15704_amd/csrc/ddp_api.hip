@@ -174,20 +174,23 @@ int32_t fail(ddp_ctx* c, int32_t code, const std::string& msg) {
     } while (0)
 
 // Bytes of unused dynamic LDS per block that leave room for exactly
-// blocks_per_cu blocks on a compute unit.
-// Measured on BERT-large-shaped lists (fp32, launches of the size coalesce_limit
-// gives): a block keeps min(R, 8) x 2 loads per thread in flight, so with few
-// replicas many blocks are needed (R = 2: 77 % of the HBM peak without a cap,
-// 67 % with two blocks; R = 3: 72 % with four, 60 % with two); from R = 5 on two
-// blocks are best or close to it (R = 8: 75.6 % against 73.5 % without a cap and
-// 71.6 % with one block; R = 12: 74.9 % against 71.9 % with one).  For R >= 16
-// one block is 1 to 1.5 points better on lists of large tensors (a block runs
-// several eight-replica phases) but 6 points worse on the ResNet-50 list in
+// blocks_per_cu blocks on a compute unit, for long launches.
+// A block keeps min(R, 8) x 2 loads per thread in flight, so with few
+// replicas many blocks are needed.  The first 101 BERT-large tensors, all marks in one call, us with no cap (five or six blocks by
+// registers) / four blocks / three / two / one: binary32 R = 2 215 / 218 / - / 252 / 326, R = 3 269 / 264 / 310 / 310 / 438,
+// R = 4 346 / 340 / 367 / 366 / 470, R = 5 431 / 423 / 442 / 442 / 574, R = 6 508 / 499 / 492 / 493 / 611, R = 8 662 / 651 / 622 / 622 /
+// 685; bfloat16 R = 2 99 / 99 / 141 / 141, R = 3 135 / 135 / 162 / 162, R = 8 331 / 329 / 307 / 307 / 399, R = 12 479 / 478 / 456 / 456 / 575,
+// R = 16 619 / 620 / 598 / 598 / 658.
+// For R >= 16 one block is about as good on lists of large tensors but 6 points worse on the ResNet-50 list in
 // fp16, whose many small tensors put slow boundary tiles on a unit that then
 // has nothing else to run -- so two it is, also with binary32 outputs next to 16-bit
-// inputs (BERT-large shape in bf16, R = 8, launches of <= 100 MiB: 77.6 % with two or three
-// blocks, 74.8 % with four or none, 74.3 % with five).
-int32_t auto_blocks_per_cu(int32_t R) { return R <= 4 ? 0 : 2; }
+// inputs.
+// copies: the staged pass, which writes as much as it reads (60 BERT-large tensors, us, no cap / three blocks: binary32 R = 2 332 /
+// 337, R = 4 551 / 540, R = 8 1002 / 1009; bfloat16 R = 2 170 / 181, R = 4 278 / 264, R = 8 496 / 503).
+int32_t auto_blocks_per_cu(int32_t R, bool copies) {
+    if (copies) return R == 3 || R == 4 ? 3 : 0;
+    return R <= 2 ? 0 : R <= 5 ? 4 : 2;
+}
 
 // A launch should run for roughly 150 to 300 us: shorter ones pay their start-up
 // and drain, much longer ones lose throughput again.  Bytes of bucket data per
@@ -212,16 +215,15 @@ int64_t launch_traffic(const ddp_ctx* c, int64_t launch_bytes) {
     return launch_bytes * (c->pipeline == DDP_PIPELINE_FUSED ? c->R + 1 : 2 * c->R + 1);
 }
 
-// Staged: whether a launch of up to this many tiles copies and reduces in two kernels.  The one pass sums
+// Staged: whether a launch copies and reduces in two kernels.  The one pass over tiles sums
 // a tile's replicas in one block, chunk after chunk; with many replicas and few tiles most of the chip
-// idles meanwhile, where the copies run in a block per tile and replica.  One pass / two kernels, us a synchronization, all
-// marks in one call: binary16, 1.6 million elements (400 tiles) R = 16 37 / 36, R = 24 53 / 49, R = 64
-// 146 / 101, 3 million (730) R = 16 61 / 57, R = 24 89 / 77; 100000 R = 64 79 / 26; binary32, 400000
-// (200 tiles) R = 16 22 / 22, R = 24 30 / 29, R = 64 73 / 57, 1.6 million (780) R = 16 51 / 58, R = 24 76 /
-// 80, R = 64 214 / 207, 6 million (2900) R = 32 377 / 403.  One mark per call, 1 MiB buckets: binary16 R = 16 255 / 266 (the
-// host makes one launch more), R = 20 320 / 267, R = 32 449 / 294; binary32 R = 16 351 / 372, R = 32 621 / 496.
+// idles meanwhile, where the copies run in a block per tile and replica.  (Still fewer tiles go in slices.)
+// One pass / two kernels, us a synchronization, all marks in one call, sixty tensors: binary32, 384 tiles R = 24 40 / 40,
+// R = 32 53 / 49, R = 64 102 / 87, 512 R = 64 147 / 122; 16 bits, 384 R = 24 48 / 45, R = 64 118 / 97, 512 R = 24 56 / 52,
+// R = 32 74 / 64, R = 64 149 / 117, 1024 R = 32 143 / 144.  R = 16 in one pass is no slower.
 bool split_pass(const ddp_ctx* c, int32_t dtype, int64_t ntiles) {
-    return c->R > 16 && ntiles <= (dtype == DDP_FP32 ? 512 : 1024);
+    const int64_t above = c->nontemporal != 0 ? ddp::slice_tiles(c->R, ddp::elem_size(dtype), true) : 0;
+    return c->R > 16 && ntiles > above && ntiles <= (dtype == DDP_FP32 ? 512 : 1024);
 }
 
 // A model of at most kSmallModelBuckets buckets that move less than this together keeps all of its
@@ -254,17 +256,21 @@ bool long_launch(const ddp_ctx* c, int64_t launch_bytes) {
     return launch_bytes * (c->R + 1) >= c->cap_min_traffic;
 }
 
-// copies: the staged pass, which writes as much as it reads and gains nothing from a cap (ResNet-50,
-// R = 8: 375 us a synchronization with none or four blocks, 384 with two).
-unsigned occupancy_lds(const ddp_ctx* c, int64_t launch_bytes, bool copies) {
-    const int32_t blocks = c->blocks_per_cu >= 0 ? c->blocks_per_cu : copies ? 0 : auto_blocks_per_cu(c->R);
-    if (blocks <= 0 || !long_launch(c, launch_bytes)) return 0;
-    return static_cast<unsigned>((c->lds_per_cu / blocks) & ~int64_t(1023));
-}
-
 unsigned lds_for_blocks(const ddp_ctx* c, int32_t blocks) {
     if (blocks <= 0) return 0;
     return static_cast<unsigned>((c->lds_per_cu / blocks) & ~int64_t(1023));
+}
+
+// Resident blocks of shorter launches (which take tiles): one mark per call, us, no cap / five blocks / three / two: BERT-large, R = 8,
+// 2034 / 2025 / 2034 / 2038, 240 MB in 8 MiB buckets, R = 12, 555 / 553 / 555 / 555, ResNet-50-sized, binary16, R = 16 369 /
+// 366 / 357 / 357; 120 MB, R = 4 230 / 230 / 249 / 249; all marks in one call, 16 MB, R = 8 25.1 / 25.1 / 25.6 / 25.7, R = 16 46.5 / 46.5 /
+// 45.7 / 45.7.
+int32_t short_launch_blocks(int32_t R) { return R <= 4 ? 0 : R < 16 ? 5 : 3; }
+
+unsigned occupancy_lds(const ddp_ctx* c, int64_t launch_bytes, bool copies) {
+    if (c->blocks_per_cu >= 0) return long_launch(c, launch_bytes) ? lds_for_blocks(c, c->blocks_per_cu) : 0;
+    if (long_launch(c, launch_bytes)) return lds_for_blocks(c, auto_blocks_per_cu(c->R, copies));
+    return copies ? 0 : lds_for_blocks(c, short_launch_blocks(c->R));
 }
 
 using ddp::make_scale;
@@ -579,7 +585,7 @@ int32_t launch_range(ddp_ctx* c, int32_t first, int32_t last, Target target) {
         if ((rc = timed_begin(c, DDP_K_REDUCE, id, st, &slot)) != DDP_OK) return rc;
         HIPCHK(c, ddp::launch_flat_reduce(bf.dtype, in0, c->slab_stride, out, nvec, c->R, sc,
                                           c->nontemporal != 0,
-                                          occupancy_lds(c, bytes, false), gate, tag, sig, st));
+                                          long_launch(c, bytes) ? occupancy_lds(c, bytes, false) : 0, gate, tag, sig, st));
         if ((rc = timed_end(c, slot, st)) != DDP_OK) return rc;
     } else {
         const bool staged = c->pipeline == DDP_PIPELINE_STAGED;

@@ -16,6 +16,24 @@ constexpr int BLOCK = 256;
 #endif
 constexpr int TILE_VECS = DDP_TILE_VECS;
 constexpr int TILE_BYTES = TILE_VECS * 16;
+constexpr int MAX_REPLICAS = 64;
+// Short launches cut a tile into slices of one vector per lane of a wave.
+constexpr int SLICE_BYTES = 1024;
+constexpr int SLICES = TILE_BYTES / SLICE_BYTES;
+// Threads that share the elements in vectors reaching over an end of a segment: at most 7 at each end.
+constexpr int EDGE_SLOTS = 16;
+
+// Launches of up to this many tiles take slices (es: bytes of an element).  Fused, the kernel alone, us, tile per block / slices,
+// sixty tensors: binary32 R = 2, 128 tiles 4.0 / 4.1; R = 8, 128 4.8 / 4.6, 192 4.9 / 5.0, 256 6.0 / 6.8; R = 16, 128 6.7 / 6.6, 192 7.3 /
+// 7.3, 256 9.1 / 9.8; R = 32, 128 10.7 / 9.8, 192 11.8 / 11.6 (two tensors 10.2 / 10.9); R = 64, 128 18.1 / 17.4, 192 20.4 / 22.4; bfloat16 R = 4,
+// 192 5.1 / 4.9; R = 8, 192 5.9 / 5.3, 256 6.8 / 7.1; R = 16, 192 8.4 / 7.7, 256 10.8 / 10.5 (two tensors 9.2 / 9.6); R = 32, 192 13.2 / 12.9, 256
+// 17.5 / 15.2 (15.0 / 16.0); R = 64, 128 21.2 / 19.1, 192 23.3 / 24.4.  Staged, us a synchronization: R = 4, 128 10.5 / 9.9, 256 11.5 / 11.5; R = 8,
+// 256 14.6 / 13.9; R = 16, 256 22.7 / 21.0; R = 32, 256 42 / 36; R = 64, 128 50 / 37 (in two kernels, see split_pass in the host
+// code, 36; 256 62 so, 67 in slices).
+inline int64_t slice_tiles(int R, int es, bool staged) {
+    if (R <= 4 || R > 32) return 128;
+    return staged ? 256 : es == 2 ? 192 : 128;
+}
 
 // Tiles of a segment.  Vectors are cut at 16-byte boundaries of the
 // destination, so a destination that starts `lead_bytes` (< 16) past such a
@@ -47,8 +65,8 @@ struct SegInfo {               // 32 bytes, read with one scalar load
 struct SegTables {
     const SegInfo* seg;        // [G]
     const int32_t* tile_seg;   // [tiles] segment that each tile belongs to
-    void* const* grad;         // [G*R + 8] replica r's gradient of segment g at [g*R+r]; eight
-                               // null entries of padding so that any row can be read 8 wide
+    void* const* grad;         // [G*R + 16] replica r's gradient of segment g at [g*R+r]; sixteen
+                               // null entries of padding so that any row can be read 16 wide
     void* const* out;          // [G] binary32 output tensor of segment g (lower-precision
                                // transport, Section 6.2.3), or null: averages go to the gradients
     int32_t G;

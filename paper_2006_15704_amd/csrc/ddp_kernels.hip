@@ -13,6 +13,7 @@
 
 #include <hip/hip_ext.h>
 
+#include <algorithm>
 #include <cstring>
 #include <mutex>
 #include <set>
@@ -64,6 +65,7 @@ __device__ __forceinline__ u32x4 zero16() {
 // serves such an access with one vector instruction too, so a tensor that sits
 // off the 16-byte grid of its peers costs extra cache lines, not a scalar loop.
 typedef u32x4 u32x4_a2 __attribute__((aligned(2)));
+typedef uint32_t u32_a2 __attribute__((aligned(2)));
 template <bool NT>
 __device__ __forceinline__ u32x4 load16u(const char* p) {
     DDP_GLOBAL const u32x4_a2* q = (DDP_GLOBAL const u32x4_a2*)(p);
@@ -75,6 +77,31 @@ __device__ __forceinline__ void store16u(char* p, u32x4 v) {
     DDP_GLOBAL u32x4_a2* q = (DDP_GLOBAL u32x4_a2*)(p);
     if (NT) __builtin_nontemporal_store(v, q);
     else *q = v;
+}
+
+// Tables, masks and gate records do not change while a kernel runs that reads them here, and a block reads
+// them at uniform addresses: through the constant address space these are scalar loads, which the compiler may
+// also move and merge.  (As plain loads it kept them behind the atomic of signal_dispatch, as vector loads with
+// a v_readfirstlane for every word, and waited for some before it issued the next.)
+// The kernel alone, us, two tensors, plain / scalar: binary32, 512 tiles R = 8 9.5 / 8.4, R = 16 16.2 / 14.0, R = 32
+// 28.6 / 26.0, R = 64 55 / 49; slices, 256 tiles R = 32 17.3 / 12.5, R = 64 32 / 23; bfloat16, 256 tiles R = 16 10.1 / 9.0.
+// The ragged list, R = 8, 198 / 192 us.  Whole tiles in long launches are another matter, see fused_tile.
+#define DDP_CONSTANT __attribute__((address_space(4)))
+template <typename T>
+__device__ __forceinline__ T cload(const T* p) {
+    return *(DDP_CONSTANT const T*)(p);
+}
+__device__ __forceinline__ SegInfo segment(const SegTables& t, int g) {
+    typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
+    static_assert(sizeof(SegInfo) == sizeof(u32x8), "one scalar load");
+    return __builtin_bit_cast(SegInfo, *(DDP_CONSTANT const u32x8*)(t.seg + g));
+}
+struct PointerRow {                        // a segment's R pointers
+    DDP_CONSTANT const uint64_t* p;
+    __device__ __forceinline__ char* operator[](int r) const { return reinterpret_cast<char*>(p[r]); }
+};
+__device__ __forceinline__ PointerRow pointer_row(void* const* table, int g, int R) {
+    return PointerRow{(DDP_CONSTANT const uint64_t*)(table + static_cast<int64_t>(g) * R)};
 }
 
 // ---- element formats ------------------------------------------------------
@@ -237,20 +264,20 @@ __global__ __launch_bounds__(BLOCK) void seg_copy_kernel(SegTables t, int64_t ti
                                                          const uint8_t* __restrict__ global_used,
                                                          int keep_unused,
                                                          const GateRecord* __restrict__ gate, uint32_t tag) {
-    if (GATED && gate->failed_tag == tag) return;
+    if (GATED && cload(&gate->failed_tag) == tag) return;
     const int64_t tile = tile_base + blockIdx.x;
     const int r = blockIdx.y;
-    const int g = t.tile_seg[tile];
-    const SegInfo si = t.seg[g];
+    const int g = cload(t.tile_seg + tile);
+    const SegInfo si = segment(t, g);
     const int64_t numel = si.numel;
     const int64_t ltile = tile - si.tile0;
-    char* grad = static_cast<char*>(t.grad[static_cast<int64_t>(g) * t.R + r]);
+    char* grad = pointer_row(t.grad, g, t.R)[r];
     // PACK: local = participation masks, bit r = 0: the replica did not use the
     // parameter, its slot gets zeros and its tensor is not read.
     // UNPACK: global_used[g] = 0: no replica used the parameter, with keep_unused
     // its gradients are left as they are.
-    const bool zero = PACK && local != nullptr && ((local[g] >> r) & 1u) == 0;
-    if (!PACK && keep_unused && global_used != nullptr && global_used[g] == 0) return;
+    const bool zero = PACK && local != nullptr && ((cload(local + g) >> r) & 1u) == 0;
+    if (!PACK && keep_unused && global_used != nullptr && cload(global_used + g) == 0) return;
     const char* src;
     char* dst;
     if (PACK) {
@@ -393,7 +420,7 @@ __device__ __forceinline__ void sum_interior_pre(const char* const (&pre)[8], in
 // +0 differs from the sum with those +0 in their places only in the sign of a zero in between, and
 // both end in +0 where the sum is zero.
 template <int DT, bool NT, int U>
-__device__ __forceinline__ void sum_interior_used(void* const* __restrict__ row, int64_t byte0, uint64_t used,
+__device__ __forceinline__ void sum_interior_used(PointerRow row, int64_t byte0, uint64_t used,
                                                   const uint32_t (&lane_off)[U],
                                                   float (&acc)[U][Fmt<DT>::VEC]) {
 #pragma unroll
@@ -404,7 +431,7 @@ __device__ __forceinline__ void sum_interior_used(void* const* __restrict__ row,
     auto next = [&](int) {
         const int r = __builtin_ctzll(rest);
         rest &= rest - 1;
-        return static_cast<const char*>(row[r]) + byte0;
+        return row[r] + byte0;
     };
     int left = __popcll(used);
     for (; left >= 8; left -= 8) chunk_interior<DT, NT, 8, U>(next, 0, lane_off, acc);
@@ -451,7 +478,7 @@ __global__ __launch_bounds__(BLOCK) void flat_reduce_kernel(const char* __restri
     constexpr int VEC = Fmt<DT>::VEC;
     if (GATED) {
         signal_dispatch(sig);
-        if (gate != nullptr && gate->failed_tag == tag) return;
+        if (gate != nullptr && cload(&gate->failed_tag) == tag) return;
     }
     const int64_t row = blockIdx.x;
     float acc[U][VEC];
@@ -497,12 +524,12 @@ __global__ __launch_bounds__(BLOCK) void flat_reduce_kernel(const char* __restri
 // load), then all C*U vector loads are issued, then the adds run in order.
 // With `slot` set (staged pipeline) the vectors also go to the replicas' flat buckets.
 template <int DT, bool NT, int C, int U>
-__device__ __forceinline__ void chunk_seg(void* const* __restrict__ row, int r, uint64_t used, bool aligned,
+__device__ __forceinline__ void chunk_seg(PointerRow row, int r, uint64_t used, bool aligned,
                                           const int64_t (&off)[U], const bool (&ok)[U],
                                           float (&acc)[U][Fmt<DT>::VEC], char* slot = nullptr, int64_t stride = 0) {
     const char* base[C];
 #pragma unroll
-    for (int i = 0; i < C; ++i) base[i] = static_cast<const char*>(row[r + i]);
+    for (int i = 0; i < C; ++i) base[i] = row[r + i];
     u32x4 x[C][U];
     // a replica that did not use the parameter contributes +0 in its place in
     // the sum, and its tensor is not read
@@ -576,67 +603,21 @@ __device__ __forceinline__ void store_out32_wave(char* out, int64_t in_byte_off,
     store16u<NT>(wave_base + 1024 + 16 * lane, b);
 }
 
-// A vector that reaches over an end of the segment, elements [lo, hi) of it.  The loads of C replicas are
-// issued before the adds and, with `slot` set (staged pipeline), before the stores to the flat buckets.
-// One element and replica at a time, each load behind the add or the store of the one before: staged, 3000
-// binary16 elements in eight tensors, R = 8 27 us a synchronization, R = 16 49, R = 64 169; so 17, 27 and 86
-// (with C = 4 19, 28 and 97).  Fused, the kernel alone, 2 million elements in a hundred tensors: binary16 R = 8 17.0
-// and 13.0 us, R = 16 30.4 and 23.2, R = 64 120 and 81; binary32 R = 16 30.1 and 26.4, R = 64 128 and 107.
-// The copy moves bits, not values: a signalling NaN arrives in the bucket as it is.
-template <int DT, int C, bool COPY>
-__device__ __forceinline__ void chunk_edge(void* const* __restrict__ row, int r, uint64_t used, int lo, int hi,
-                                           int64_t off, char* slot, int64_t stride, float (&s)[Fmt<DT>::VEC]) {
-    constexpr int ES = Fmt<DT>::ES;
-    constexpr int VEC = Fmt<DT>::VEC;
-    typedef typename std::conditional<ES == 4, uint32_t, uint16_t>::type bits;
-    bits x[C][VEC];
-#pragma unroll
-    for (int i = 0; i < C; ++i) {
-        const char* base = static_cast<const char*>(row[r + i]) + off;
-        const bool take = ((used >> (r + i)) & 1u) != 0;
-#pragma unroll
-        for (int k = 0; k < VEC; ++k) {
-            x[i][k] = 0;
-            if (take && k >= lo && k < hi) x[i][k] = gload<bits>(base + k * ES);
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < C; ++i)
-#pragma unroll
-        for (int k = 0; k < VEC; ++k) {
-            if (COPY && k >= lo && k < hi) gstore<bits>(slot + (r + i) * stride + off + k * ES, x[i][k]);
-            s[k] += Fmt<DT>::value(x[i][k]);
-        }
-}
-
-template <int DT, int OUT>
-__device__ __forceinline__ void reduce_edge(const SegTables& t, int g, void* const* __restrict__ row, int R, int nwrite,
-                                            int64_t e, int64_t numel, bool zero, uint64_t used, const Scale& sc,
-                                            char* slot, int64_t stride) {
-    constexpr int ES = Fmt<DT>::ES;
-    constexpr int VEC = Fmt<DT>::VEC;
-    const int lo = e < 0 ? static_cast<int>(-e) : 0;
-    const int hi = numel - e < VEC ? static_cast<int>(numel - e) : VEC;
-    float s[VEC];
-#pragma unroll
-    for (int k = 0; k < VEC; ++k) s[k] = -0.0f;
-    if (!zero) {
-        int r = 0;
-        for (; r + 8 <= R; r += 8) chunk_edge<DT, 8, OUT == OUT_FLAT>(row, r, used, lo, hi, e * ES, slot, stride, s);
-        for (; r < R; ++r) chunk_edge<DT, 1, OUT == OUT_FLAT>(row, r, used, lo, hi, e * ES, slot, stride, s);
-    }
-#pragma unroll
-    for (int k = 0; k < VEC; ++k) {
-        if (k < lo || k >= hi) continue;
-        const float y = zero ? 0.0f : apply_scale(sc, s[k]);
-        if (OUT == OUT_FLAT) {
-            Fmt<DT>::store1(slot + R * stride + (e + k) * ES, y);
-        } else if (OUT == OUT_BINARY32) {
-            gstore<float>(static_cast<char*>(t.out[g]) + (e + k) * 4, y);
-        } else {
-            for (int w = 0; w < nwrite; ++w) Fmt<DT>::store1(static_cast<char*>(row[w]) + (e + k) * ES, y);
-        }
-    }
+// The elements of a block's part [e0, e0 + span) of a segment that lie in vectors reaching over an end of
+// the segment: the first `head` elements of the segment and the `tail` elements from `last` on, at most
+// VEC - 1 each.
+struct EdgeElements {
+    int head, tail;
+    int64_t last;
+};
+template <int VEC>
+__device__ __forceinline__ EdgeElements edge_elements(int64_t e0, int span, int64_t numel) {
+    const int64_t rest = numel - e0;                       // elements from the part's start on, at least 1
+    EdgeElements ed;
+    ed.last = e0 + rest / VEC * VEC;                       // first element of the vector with the segment's end
+    ed.head = e0 < 0 ? static_cast<int>(rest < VEC ? numel : VEC + e0) : 0;
+    ed.tail = rest < span && ed.last >= 0 ? static_cast<int>(numel - ed.last) : 0;
+    return ed;
 }
 
 // One tile of the fused gather-reduce-scatter.
@@ -656,21 +637,33 @@ __device__ __forceinline__ void fused_tile(const SegTables& t, int64_t tile, int
                                            const GateRecord* __restrict__ gate = nullptr, uint32_t tag = 0) {
     constexpr int ES = Fmt<DT>::ES;
     constexpr int VEC = Fmt<DT>::VEC;
-    const uint32_t gate_word = gate != nullptr ? gate->failed_tag : ~tag;
-    const int g = t.tile_seg[tile];
+    constexpr int SPAN = BLOCK * U * VEC;           // elements of a tile
+    static_assert(BLOCK * U == TILE_VECS, "a block takes a tile");
+    typedef typename std::conditional<ES == 4, uint32_t, uint16_t>::type bits;
+    extern __shared__ __align__(16) uint32_t shared_words[];
+    bits* const edge = reinterpret_cast<bits*>(shared_words);      // [R][EDGE_SLOTS]
+    const uint32_t gate_word = gate != nullptr ? cload(&gate->failed_tag) : ~tag;
     // Everything that depends on g alone is fetched together: the segment
     // record and the first eight replica pointers (the pointer table is padded
     // so that eight entries can always be read).
-    void* const* __restrict__ row = t.grad + static_cast<int64_t>(g) * t.R;   // this segment's R pointers
-    const SegInfo si = t.seg[g];
+    // Which of the three accesses are scalar loads decides when a block's first gradient loads go out, and long
+    // launches of whole tiles are sensitive to that (a block that starts sooner is not always better: the
+    // memory system is full, and how the blocks' requests interleave in it changes).  The first 101 BERT-large tensors, us, all
+    // plain / tile map plain, others scalar / all scalar, the best cap on resident blocks each: binary32 R = 3 264 / - / -,
+    // R = 4 338 / 352 / 350, R = 8 617 / 617 / 631, R = 16 (60 tensors) 852 / 866 / 864; bfloat16 R = 2 112 / 102 / 98, R = 3 146 / 132 / 134, R = 4
+    // 165 / 167 / 176, R = 8 319 / 314 / 306, R = 12 451 / 450 / 453, R = 16 590 / 594 / 597; binary32 averages of BERT-large 1144 / 1138 /
+    // 1126; staged (pointers plain in every case: chunk_copy) binary32 R = 4 540 / - / 529, R = 2 332 / - / 336, bfloat16 R = 2 170 / - / 174.
+    const int g = OUT == OUT_BINARY32 ? cload(t.tile_seg + tile) : t.tile_seg[tile];
+    const PointerRow row = pointer_row(t.grad, g, t.R);
+    const SegInfo si = ES == 2 ? segment(t, g) : t.seg[g];
     const char* pre[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) pre[i] = static_cast<const char*>(row[i]);
+    for (int i = 0; i < 8; ++i)
+        pre[i] = ES == 2 ? row[i] : static_cast<const char*>(t.grad[static_cast<int64_t>(g) * t.R + i]);
     // (behind a gate that gave up this row may be an earlier iteration's: it is not looked at then)
-    const uint64_t mask = MASKED && local != nullptr ? local[g] : 0;
+    const uint64_t mask = MASKED && local != nullptr ? cload(local + g) : 0;
     if (gate_word == tag) return;          // the gate in front of this launch gave up
     const int64_t numel = si.numel;
-    const int64_t ltile = tile - si.tile0;
     // participation of the R replicas in this parameter (bit r = replica r used
     // it); without a flag table every replica did
     const uint64_t everyone = R >= 64 ? ~uint64_t(0) : ((uint64_t(1) << R) - 1);
@@ -681,75 +674,94 @@ __device__ __forceinline__ void fused_tile(const SegTables& t, int64_t tile, int
     // replica 0's tensor -- or the slot in the flat bucket -- starts this many elements past a 16-byte boundary
     const int sh = (OUT == OUT_FLAT ? static_cast<int>(si.flat_byte & 15) : si.lead_bytes()) / ES;
     const bool src_aligned = si.congruent();   // every replica's tensor sits at the same offset modulo 16
-    char* const outp = OUT == OUT_BINARY32 ? static_cast<char*>(t.out[g]) : nullptr;
+    char* const outp = OUT == OUT_BINARY32 ? pointer_row(t.out, g, 1)[0] : nullptr;
     char* const slot = OUT == OUT_FLAT ? flat.slab0 + si.flat_byte : nullptr;
-    const int64_t e_tile = ltile * (TILE_BYTES / ES) - sh;
+    const int64_t e0 = (tile - si.tile0) * SPAN - sh;
 
     // The whole tile is inside the segment.  Where the replicas sit
     // modulo 16 does not matter: vectors are cut on replica 0's 16-byte grid, the other replicas (and
     // a binary32 output tensor that is off the grid) are accessed with element-aligned vectors.  90
     // densely packed tensors of odd sizes, R = 8, 120 MB each, replicas 4 bytes apart modulo 16: 235 us
     // when such tiles took the predicated path below, 203 us here (5.3 TB/s; 5.9 when congruent).
-    if (e_tile >= 0 && e_tile + TILE_BYTES / ES <= numel) {
-        const int64_t tile_byte = e_tile * ES;
-#pragma unroll 1
-        for (int step = 0; step < TILE_VECS / (BLOCK * U); ++step) {
-            uint32_t lane_off[U];
-            float acc[U][VEC];
+    if (e0 >= 0 && e0 + SPAN <= numel) {
+        const int64_t byte0 = e0 * ES;
+        uint32_t lane_off[U];
+        float acc[U][VEC];
 #pragma unroll
-            for (int u = 0; u < U; ++u) lane_off[u] = ((step * U + u) * BLOCK + threadIdx.x) * 16u;
-            if constexpr (OUT == OUT_FLAT) {
+        for (int u = 0; u < U; ++u) {
+            lane_off[u] = (u * BLOCK + threadIdx.x) * 16u;
+            // (kept as they are, so that the second vector's loads take the base + offset form too, not 64-bit additions)
+            if (OUT != OUT_FLAT) asm volatile("" : "+v"(lane_off[u]));
+        }
+        if constexpr (OUT == OUT_FLAT) {
 #pragma unroll
-                for (int u = 0; u < U; ++u)
+            for (int u = 0; u < U; ++u)
 #pragma unroll
-                    for (int i = 0; i < VEC; ++i) acc[u][i] = -0.0f;
-                char* const place = slot + tile_byte;
-                int r = 0;
-                for (; r + 8 <= R; r += 8) chunk_copy<DT, NT, 8, U>(row, r, used, tile_byte, place + r * flat.stride, flat.stride, lane_off, acc);
-                if (r + 4 <= R) { chunk_copy<DT, NT, 4, U>(row, r, used, tile_byte, place + r * flat.stride, flat.stride, lane_off, acc); r += 4; }
-                if (r + 2 <= R) { chunk_copy<DT, NT, 2, U>(row, r, used, tile_byte, place + r * flat.stride, flat.stride, lane_off, acc); r += 2; }
-                if (r < R) chunk_copy<DT, NT, 1, U>(row, r, used, tile_byte, place + r * flat.stride, flat.stride, lane_off, acc);
-                // the averaged bucket is read again by the write-back
+                for (int i = 0; i < VEC; ++i) acc[u][i] = -0.0f;
+            char* const place = slot + byte0;
+            void* const* __restrict__ const rows = t.grad + static_cast<int64_t>(g) * t.R;
+            int r = 0;
+            for (; r + 8 <= R; r += 8) chunk_copy<DT, NT, 8, U>(rows, r, used, byte0, place + r * flat.stride, flat.stride, lane_off, acc);
+            if (r + 4 <= R) { chunk_copy<DT, NT, 4, U>(rows, r, used, byte0, place + r * flat.stride, flat.stride, lane_off, acc); r += 4; }
+            if (r + 2 <= R) { chunk_copy<DT, NT, 2, U>(rows, r, used, byte0, place + r * flat.stride, flat.stride, lane_off, acc); r += 2; }
+            if (r < R) chunk_copy<DT, NT, 1, U>(rows, r, used, byte0, place + r * flat.stride, flat.stride, lane_off, acc);
+            // the averaged bucket is read again by the write-back
 #pragma unroll
-                for (int u = 0; u < U; ++u) store16(place + R * flat.stride + lane_off[u], scaled<DT>(sc, acc[u]));
+            for (int u = 0; u < U; ++u) store16(place + R * flat.stride + lane_off[u], scaled<DT>(sc, acc[u]));
+            return;
+        }
+        if (all_used)
+            sum_interior_pre<DT, NT, U>(
+                pre, byte0, [&](int r) { return row[r] + byte0; }, R, lane_off, acc);
+        else if constexpr (MASKED)
+            sum_interior_used<DT, NT, U>(row, byte0, used, lane_off, acc);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (OUT == OUT_BINARY32) {
+                float y[VEC];
+#pragma unroll
+                for (int i = 0; i < VEC; ++i) y[i] = apply_scale(sc, acc[u][i]);
+                if constexpr (OUT == OUT_BINARY32) store_out32_wave<DT, NT>(outp, byte0 + lane_off[u], y);
                 continue;
             }
-            if (all_used)
-                sum_interior_pre<DT, NT, U>(
-                    pre, tile_byte, [&](int r) { return static_cast<const char*>(row[r]) + tile_byte; }, R,
-                    lane_off, acc);
-            else if constexpr (MASKED)
-                sum_interior_used<DT, NT, U>(row, tile_byte, used, lane_off, acc);
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (OUT == OUT_BINARY32) {
-                    float y[VEC];
-#pragma unroll
-                    for (int i = 0; i < VEC; ++i) y[i] = apply_scale(sc, acc[u][i]);
-                    if constexpr (OUT == OUT_BINARY32) store_out32_wave<DT, NT>(outp, tile_byte + lane_off[u], y);
-                    continue;
-                }
-                const u32x4 out = scaled<DT>(sc, acc[u]);
-                store16s<NT>(const_cast<char*>(pre[0]) + tile_byte + lane_off[u], out);
-                for (int w = 1; w < nwrite; ++w)
-                    store16u<NT>(static_cast<char*>(row[w]) + tile_byte + lane_off[u], out);
-            }
+            const u32x4 out = scaled<DT>(sc, acc[u]);
+            store16s<NT>(const_cast<char*>(pre[0]) + byte0 + lane_off[u], out);
+            for (int w = 1; w < nwrite; ++w)
+                store16u<NT>(row[w] + byte0 + lane_off[u], out);
         }
         return;
     }
 
-#pragma unroll 1
-    for (int step = 0; step < TILE_VECS / (BLOCK * U); ++step) {
-        int64_t e[U], off[U];
-        int kind[U];
-        bool ok[U];
+    if (e0 >= numel) return;
+    // The ends of the segment, element by element: sixteen threads to a replica fetch them ahead of the
+    // vectors, all replicas at once, and put them side by side in LDS behind those, where they are summed in
+    // ascending order.  When the lane that owned such a vector fetched its elements itself, behind the
+    // vectors and eight replicas at a time, a launch of 128 tiles with two tensors took, bfloat16, R = 8 10.6 us
+    // and 6.1 so, R = 24 25 and 12, R = 64 60 and 26; binary32 R = 24 14.2 and 11.6, R = 64 33 and 26.
+    const EdgeElements ed = edge_elements<VEC>(e0, SPAN, numel);
+    const int nedge = ed.head + ed.tail;
+    const int slot_k = threadIdx.x % EDGE_SLOTS, slot_r = threadIdx.x / EDGE_SLOTS;
+    const int64_t edge_el = slot_k < ed.head ? slot_k : ed.last + (slot_k - ed.head);
+    constexpr int EDGE_LOADS = MAX_REPLICAS * EDGE_SLOTS / BLOCK;
+    bits edge_x[EDGE_LOADS];
+    if (!zero && slot_k < nedge) {
+#pragma unroll
+        for (int i = 0; i < EDGE_LOADS; ++i) {
+            const int r = slot_r + i * (BLOCK / EDGE_SLOTS);
+            edge_x[i] = 0;
+            if (r < R && ((used >> r) & 1u)) edge_x[i] = gload<bits>(row[r] + edge_el * ES);
+        }
+    }
+    {
+        int64_t off[U];
+        bool full[U], ok[U];
         float acc[U][VEC];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            e[u] = e_tile + static_cast<int64_t>((step * U + u) * BLOCK + threadIdx.x) * VEC;
-            kind[u] = classify(e[u], VEC, numel);
-            ok[u] = kind[u] == V_FULL && !zero;
-            off[u] = e[u] * ES;
+            const int64_t e = e0 + static_cast<int64_t>(u * BLOCK + threadIdx.x) * VEC;
+            full[u] = e >= 0 && e + VEC <= numel;
+            ok[u] = full[u] && !zero;
+            off[u] = e * ES;
 #pragma unroll
             for (int i = 0; i < VEC; ++i) acc[u][i] = -0.0f;
         }
@@ -766,29 +778,52 @@ __device__ __forceinline__ void fused_tile(const SegTables& t, int64_t tile, int
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            if (kind[u] == V_NONE) continue;
-            if (kind[u] == V_FULL) {
-                float y[VEC];
+            if (!full[u]) continue;
+            float y[VEC];
 #pragma unroll
-                for (int i = 0; i < VEC; ++i) y[i] = zero ? 0.0f : apply_scale(sc, acc[u][i]);
-                if (OUT == OUT_BINARY32) {
-                    if constexpr (OUT == OUT_BINARY32) store_out32<DT, NT>(outp, off[u], y, si.out_congruent());
-                    continue;
-                }
-                if (OUT == OUT_FLAT) {
-                    store16(slot + R * flat.stride + off[u], Fmt<DT>::narrow(y));
-                    continue;
-                }
-                const u32x4 out = zero ? zero16() : Fmt<DT>::narrow(y);
-                store16s<NT>(static_cast<char*>(row[0]) + off[u], out);
-                for (int w = 1; w < nwrite; ++w) {
-                    char* d = static_cast<char*>(t.grad[static_cast<int64_t>(g) * t.R + w]);
-                    if (src_aligned) store16s<NT>(d + off[u], out);
-                    else store16u<NT>(d + off[u], out);
-                }
-            } else {
-                reduce_edge<DT, OUT>(t, g, row, R, nwrite, e[u], numel, zero, used, sc, slot, flat.stride);
+            for (int i = 0; i < VEC; ++i) y[i] = zero ? 0.0f : apply_scale(sc, acc[u][i]);
+            if (OUT == OUT_BINARY32) {
+                if constexpr (OUT == OUT_BINARY32) store_out32<DT, NT>(outp, off[u], y, si.out_congruent());
+                continue;
             }
+            if (OUT == OUT_FLAT) {
+                store16(slot + R * flat.stride + off[u], Fmt<DT>::narrow(y));
+                continue;
+            }
+            const u32x4 out = zero ? zero16() : Fmt<DT>::narrow(y);
+            store16s<NT>(row[0] + off[u], out);
+            for (int w = 1; w < nwrite; ++w) {
+                char* d = row[w];
+                if (src_aligned) store16s<NT>(d + off[u], out);
+                else store16u<NT>(d + off[u], out);
+            }
+        }
+    }
+    if (nedge == 0) return;
+    if (!zero && slot_k < nedge) {
+#pragma unroll
+        for (int i = 0; i < EDGE_LOADS; ++i) {
+            const int r = slot_r + i * (BLOCK / EDGE_SLOTS);
+            if (r < R) {
+                edge[r * EDGE_SLOTS + slot_k] = edge_x[i];
+                // (the copy moves bits, not values: a signalling NaN arrives in the bucket as it is)
+                if (OUT == OUT_FLAT) gstore<bits>(slot + r * flat.stride + edge_el * ES, edge_x[i]);
+            }
+        }
+    }
+    __syncthreads();
+    // (every sixteen threads sum the same elements, so that the threads of replica w's write there)
+    if (slot_k < nedge && (slot_r == 0 || slot_r < nwrite)) {
+        float s = -0.0f;
+        if (!zero)
+            for (int r = 0; r < R; ++r) s += Fmt<DT>::value(edge[r * EDGE_SLOTS + slot_k]);
+        const float y = zero ? 0.0f : apply_scale(sc, s);
+        if (OUT == OUT_FLAT) {
+            if (slot_r == 0) Fmt<DT>::store1(slot + R * flat.stride + edge_el * ES, y);
+        } else if (OUT == OUT_BINARY32) {
+            if (slot_r == 0) gstore<float>(outp + edge_el * 4, y);
+        } else {
+            for (int w = slot_r; w < nwrite; w += BLOCK / EDGE_SLOTS) Fmt<DT>::store1(row[w] + edge_el * ES, y);
         }
     }
 }
@@ -802,6 +837,151 @@ __global__ __launch_bounds__(BLOCK) void fused_reduce_kernel(SegTables t, int64_
                                                              uint32_t tag, DispatchSignal sig) {
     signal_dispatch(sig);
     fused_tile<DT, NT, U, OUT, MASKED>(t, tile_base + blockIdx.x, R, nwrite, local, keep_unused, sc, flat, gate, tag);
+}
+
+// A short launch.  It has fewer blocks than fill the chip and runs as long as one of them, whose time is the
+// chain of its memory accesses: the tables, then a round of loads for every eight replicas, then the ends of
+// segments.  So a block owns one slice of a tile here, 1 KiB of every replica (eight times the blocks); its four
+// waves fetch C replicas each, all of them under way at once, and meet in LDS, where thread i sums dword i of
+// the slice over the replicas in ascending order.  (C: R / 4, rounded up, at most.)
+// The kernel alone, us, a tile per block / slices: one tile of two tensors, bfloat16, R = 24 19 / 4.1, R = 64 44 / 5.7
+// (before the ends of segments were fetched together), sixty tensors, 64 tiles, binary32 R = 8 4.6 / 4.1, R = 32 9.8 / 6.2,
+// R = 64 17.5 / 12.1, bfloat16 R = 8 5.6 / 4.4, R = 16 7.8 / 5.7, R = 64 20.7 / 13.7.
+// Per byte a slice costs more than a tile (a whole wave per KiB of a replica, 4-byte stores): slice_tiles() has
+// the line.  Half as long slices, two replicas per load instruction, took three times as long.
+template <int DT, int C, int OUT, bool MASKED>
+__global__ __launch_bounds__(BLOCK) void slice_reduce_kernel(SegTables t, int64_t tile_base, int R, int nwrite,
+                                                             const uint64_t* __restrict__ local, int keep_unused,
+                                                             Scale sc, FlatBuckets flat,
+                                                             const GateRecord* __restrict__ gate, uint32_t tag,
+                                                             DispatchSignal sig) {
+    constexpr int ES = Fmt<DT>::ES;
+    constexpr int VEC = Fmt<DT>::VEC;
+    constexpr int WORDS = SLICE_BYTES / 4;          // dwords of a slice, one per thread
+    constexpr int EPW = 4 / ES;                     // elements of a dword
+    typedef typename std::conditional<ES == 4, uint32_t, uint16_t>::type bits;
+    static_assert(WORDS == BLOCK && SLICE_BYTES == 64 * 16, "one dword per thread, one vector per lane");
+    extern __shared__ __align__(16) uint32_t shared_words[];
+    uint32_t* const gathered = shared_words;       // [R][WORDS]
+    signal_dispatch(sig);
+    const uint32_t gate_word = gate != nullptr ? cload(&gate->failed_tag) : ~tag;
+    const int64_t tile = tile_base + blockIdx.x / SLICES;
+    const int g = cload(t.tile_seg + tile);
+    const PointerRow row = pointer_row(t.grad, g, t.R);
+    const SegInfo si = segment(t, g);
+    const uint64_t mask = MASKED && local != nullptr ? cload(local + g) : 0;
+    if (gate_word == tag) return;
+    const int64_t numel = si.numel;
+    const int sh = (OUT == OUT_FLAT ? static_cast<int>(si.flat_byte & 15) : si.lead_bytes()) / ES;
+    // the slice holds the elements [e0, e0 + SLICE_BYTES / ES) as far as they exist
+    const int64_t e0 = (tile - si.tile0) * (TILE_BYTES / ES) + static_cast<int>(blockIdx.x % SLICES) * (SLICE_BYTES / ES) - sh;
+    if (e0 >= numel) return;
+    const uint64_t everyone = R >= 64 ? ~uint64_t(0) : ((uint64_t(1) << R) - 1);
+    const uint64_t used = MASKED && local != nullptr ? mask : everyone;
+    if (OUT != OUT_FLAT && used == 0 && keep_unused) return;
+    char* const slot = OUT == OUT_FLAT ? flat.slab0 + si.flat_byte : nullptr;
+    // the ends of the segment, element by element, sixteen threads to a replica
+    const EdgeElements ed = edge_elements<VEC>(e0, SLICE_BYTES / ES, numel);
+    const int nedge = ed.head + ed.tail;
+    const int slot_k = threadIdx.x % EDGE_SLOTS, slot_r = threadIdx.x / EDGE_SLOTS;
+    const int64_t edge_el = slot_k < ed.head ? slot_k : ed.last + (slot_k - ed.head);
+    bits edge_x[C / 4];
+    if (slot_k < nedge) {
+#pragma unroll
+        for (int i = 0; i < C / 4; ++i) {
+            const int r = slot_r + i * (BLOCK / EDGE_SLOTS);
+            edge_x[i] = 0;
+            if (r < R && ((used >> r) & 1u)) edge_x[i] = gload<bits>(row[r] + edge_el * ES);
+        }
+    }
+    {
+        // wave w takes Q consecutive replicas; their pointers come in one or two scalar loads (which may reach
+        // into the padding behind the table), and all Q loads are issued before the first is waited for
+        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+        const int Q = (R + 3) / 4, first = wave * Q, count = min(Q, R - first);
+        const int64_t e = e0 + lane * VEC;
+        const bool full = e >= 0 && e + VEC <= numel;
+        const int64_t off = e * ES;
+        if (count > 0) {
+            const char* base[C];
+#pragma unroll
+            for (int i = 0; i < C; ++i) base[i] = row[first + i];
+            u32x4 x[C];
+#pragma unroll
+            for (int i = 0; i < C; ++i) {
+                x[i] = zero16();
+                if (i < count && ((used >> (first + i)) & 1u) && full) x[i] = load16u<true>(base[i] + off);
+            }
+#pragma unroll
+            for (int i = 0; i < C; ++i) {
+                if (i < count && full) {
+                    *reinterpret_cast<u32x4*>(&gathered[(first + i) * WORDS + lane * 4]) = x[i];
+                    if (OUT == OUT_FLAT) store16s<true>(slot + (first + i) * flat.stride + off, x[i]);
+                }
+            }
+        }
+    }
+    if (slot_k < nedge) {
+#pragma unroll
+        for (int i = 0; i < C / 4; ++i) {
+            const int r = slot_r + i * (BLOCK / EDGE_SLOTS);
+            if (r < R) {
+                reinterpret_cast<bits*>(gathered)[r * (SLICE_BYTES / ES) + static_cast<int>(edge_el - e0)] = edge_x[i];
+                if (OUT == OUT_FLAT) gstore<bits>(slot + r * flat.stride + edge_el * ES, edge_x[i]);
+            }
+        }
+    }
+    __syncthreads();
+    float acc[EPW];
+#pragma unroll
+    for (int k = 0; k < EPW; ++k) acc[k] = -0.0f;
+    int r = 0;
+    for (; r + 8 <= R; r += 8) {
+        uint32_t w[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) w[i] = gathered[(r + i) * WORDS + threadIdx.x];
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int k = 0; k < EPW; ++k) acc[k] += Fmt<DT>::value(EPW == 1 ? w[i] : k == 0 ? w[i] & 0xFFFFu : w[i] >> 16);
+    }
+    for (; r < R; ++r) {
+        const uint32_t w = gathered[r * WORDS + threadIdx.x];
+#pragma unroll
+        for (int k = 0; k < EPW; ++k) acc[k] += Fmt<DT>::value(EPW == 1 ? w : k == 0 ? w & 0xFFFFu : w >> 16);
+    }
+    const bool zero = OUT != OUT_FLAT && used == 0;
+    const int64_t e = e0 + static_cast<int>(threadIdx.x) * EPW;
+    float y[EPW];
+    bool in[EPW];
+    bool all = true;
+#pragma unroll
+    for (int k = 0; k < EPW; ++k) {
+        y[k] = zero ? 0.0f : apply_scale(sc, acc[k]);
+        in[k] = e + k >= 0 && e + k < numel;
+        all = all && in[k];
+    }
+    if (OUT == OUT_BINARY32) {
+        char* const out = pointer_row(t.out, g, 1)[0];
+#pragma unroll
+        for (int k = 0; k < EPW; ++k)
+            if (in[k]) gstore<float>(out + (e + k) * 4, y[k]);
+        return;
+    }
+    uint32_t word = 0;
+    if constexpr (ES == 4) word = __float_as_uint(y[0]);
+    else word = Fmt<DT>::down(y[0]) | (Fmt<DT>::down(y[EPW - 1]) << 16);
+    const int writes = OUT == OUT_FLAT ? 1 : nwrite;
+    for (int w = 0; w < writes; ++w) {
+        char* const out = (OUT == OUT_FLAT ? slot + R * flat.stride : row[w]) + e * ES;
+        if (all) {
+            gstore<u32_a2>(out, word);
+        } else {
+#pragma unroll
+            for (int k = 0; k < EPW; ++k)
+                if (in[k]) gstore<bits>(out + k * ES, static_cast<bits>(k == 0 ? word : word >> 16));
+        }
+    }
 }
 
 // ---- stream ordering through device flags ------------------------------------
@@ -908,8 +1088,10 @@ __global__ __launch_bounds__(BLOCK) void repair_kernel(SegTables t, OrderState* 
         const GateRecord r = rec[b];
         if (r.failed_tag != tag || r.dtype != DT) continue;
         if (blockIdx.x == 0 && threadIdx.x == 0) st->repaired += 1;   // (repair launches run one after the other)
-        for (int64_t i = blockIdx.x; i < r.ntiles; i += gridDim.x)
+        for (int64_t i = blockIdx.x; i < r.ntiles; i += gridDim.x) {
+            __syncthreads();       // the tile before is done with its elements in LDS
             fused_tile<DT, NT, U, OUT, true>(t, r.tile_base + i, R, nwrite, local, keep_unused, sc, flat);
+        }
     }
 }
 
@@ -1013,10 +1195,10 @@ template <bool STREAM>
 __global__ __launch_bounds__(BLOCK) void accumulate_kernel(SegTables t, void* const* __restrict__ micro) {
     const int64_t tile = blockIdx.x;
     const int r = blockIdx.y;
-    const int g = t.tile_seg[tile];
-    const SegInfo si = t.seg[g];
-    const char* src = static_cast<const char*>(micro[static_cast<int64_t>(g) * t.R + r]);
-    char* dst = static_cast<char*>(t.grad[static_cast<int64_t>(g) * t.R + r]);
+    const int g = cload(t.tile_seg + tile);
+    const SegInfo si = segment(t, g);
+    const char* src = pointer_row(micro, g, t.R)[r];
+    char* dst = pointer_row(t.grad, g, t.R)[r];
     if (src == nullptr) return;
     const int64_t numel = si.numel;
     const int64_t ltile = tile - si.tile0;
@@ -1207,14 +1389,29 @@ hipError_t launch_flat_reduce(int dtype, const char* in0, int64_t stride, char* 
     }
 }
 
+// What the ends of segments take (fused_tile).
+static unsigned edge_lds(int R) { return static_cast<unsigned>(R * EDGE_SLOTS * sizeof(uint32_t)); }
+
 template <int DT, int OUT, bool MASKED>
 static hipError_t fused_launch(bool nt, int64_t ntiles, unsigned lds, hipStream_t s,
                                const SegTables& t, int64_t tile_base, int R, int nwrite,
                                const uint64_t* local, int keep, Scale sc, FlatBuckets flat,
                                const GateRecord* gate, uint32_t tag, DispatchSignal sig) {
     dim3 grid(static_cast<unsigned>(ntiles));
+    lds = std::max(lds, edge_lds(R));
     if (nt) return launch(fused_reduce_kernel<DT, true, RU, OUT, MASKED>, grid, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
     return launch(fused_reduce_kernel<DT, false, RU, OUT, MASKED>, grid, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
+}
+
+template <int DT, int OUT, bool MASKED>
+static hipError_t slice_launch(int64_t ntiles, hipStream_t s, const SegTables& t, int64_t tile_base, int R, int nwrite,
+                               const uint64_t* local, int keep, Scale sc, FlatBuckets flat,
+                               const GateRecord* gate, uint32_t tag, DispatchSignal sig) {
+    const dim3 grid(static_cast<unsigned>(ntiles * SLICES));
+    const unsigned lds = static_cast<unsigned>(R * SLICE_BYTES);
+    // (registers and code for sixteen replicas a wave cost 20 % where four will do)
+    if (R <= 16) return launch(slice_reduce_kernel<DT, 4, OUT, MASKED>, grid, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
+    return launch(slice_reduce_kernel<DT, MAX_REPLICAS / 4, OUT, MASKED>, grid, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
 }
 
 template <int DT, int OUT>
@@ -1222,6 +1419,12 @@ static hipError_t fused_dispatch(bool nt, int64_t ntiles, unsigned lds, hipStrea
                                  const SegTables& t, int64_t tile_base, int R, int nwrite,
                                  const uint64_t* local, int keep, Scale sc, FlatBuckets flat,
                                  const GateRecord* gate, uint32_t tag, DispatchSignal sig) {
+    // (without the hint every launch takes tiles, so that both kernels can be had at any size)
+    if (nt && ntiles <= slice_tiles(R, Fmt<DT>::ES, OUT == OUT_FLAT)) {
+        if (local == nullptr)
+            return slice_launch<DT, OUT, false>(ntiles, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
+        return slice_launch<DT, OUT, true>(ntiles, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
+    }
     // (the staged pass reads its masks through chunk_copy's one branch per replica: 329 us with either
     // instance, ResNet-50, R = 8, all marks in one call)
     if constexpr (OUT != OUT_FLAT)
@@ -1297,8 +1500,8 @@ static hipError_t repair_dispatch(bool nt, int blocks, hipStream_t s, const SegT
                                   const GateRecord* rec, int nb, uint32_t tag, int R, int nwrite,
                                   const uint64_t* local, int keep, Scale sc, FlatBuckets flat) {
     const dim3 grid(static_cast<unsigned>(blocks));
-    if (nt) return launch(repair_kernel<DT, true, RU, OUT>, grid, 0u, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc, flat);
-    return launch(repair_kernel<DT, false, RU, OUT>, grid, 0u, s, t, st, rec, nb, tag, R, nwrite, local, keep, sc, flat);
+    if (nt) return launch(repair_kernel<DT, true, RU, OUT>, grid, edge_lds(R), s, t, st, rec, nb, tag, R, nwrite, local, keep, sc, flat);
+    return launch(repair_kernel<DT, false, RU, OUT>, grid, edge_lds(R), s, t, st, rec, nb, tag, R, nwrite, local, keep, sc, flat);
 }
 
 hipError_t launch_repair(int dtype, const SegTables& t, OrderState* st, const GateRecord* rec, int nb, uint32_t tag,

@@ -136,13 +136,6 @@ bool writes_are_apart(const ddp::BucketPlan& plan, void* const* grad_ptrs, int32
     return true;
 }
 
-// One block sums all replicas of a tile in turn: with many replicas a short 16-bit list, whose ends take a
-// lane's worth of elements each, is slower so than with a block per tile and replica for the copies.  us a call in flat
-// buckets / fused: 500 bfloat16 elements in three tensors R = 17 22 to 25 / 19, R = 24 23 to 26 / 23, R = 32 24 to
-// 29 / 28, R = 48 26 to 31 / 39, R = 64 28 to 33 / 49; 100000 in thirty, R = 24 54 / 52, R = 64 (39000) 105 / 110;
-// 400000, R = 24, 61 / 52; binary32, 500 R = 24 24 to 27 / 18, R = 64 29 to 33 / 24, 19000 in thirty, R = 64, 105 / 107.
-constexpr int32_t kFusedReplicas = 24;
-
 #define HIPCHK0(expr)                                                                        \
     do {                                                                                     \
         hipError_t e_ = (expr);                                                              \
@@ -230,13 +223,15 @@ extern "C" int32_t ddp_sync_static(int32_t R, int32_t device, void* stream, int3
 
     const int64_t ntiles = ht.tile0[n];
     const ddp::Scale sc = ddp::make_scale(R);
-    if (R <= kFusedReplicas && writes_are_apart(plan, grad_ptrs, R)) {
+    if (writes_are_apart(plan, grad_ptrs, R)) {
         // Nobody sees the flat buckets of this call, so the averages go straight into replica 0's
         // tensors: (R + 1) b bytes in one launch per run of buckets of one element type, instead of a
         // fill, the copies, a reduction per bucket and the write-back, (4 R + 5) b in all.  The bits are
         // the same.  A tensor that is written while another block still reads it (one tensor under two
         // parameters or as two replicas) must not be seen half averaged: such lists go on below.
-        // The first 48 ResNet-50 tensors, R = 4: 37 -> 25 us a call; 2e6 elements, R = 2: 50 -> 20.
+        // The first 48 ResNet-50 tensors, R = 4: 37 -> 25 us a call; 2e6 elements, R = 2: 50 -> 20.  Many
+        // replicas (host arrays ready, flat buckets / so): R = 17, 500 bfloat16 elements in three tensors 18 / 9.0; R = 32,
+        // 100000 in thirty 32 / 20; R = 64, 500 22 / 10, 39000 in thirty 46 / 34; binary32, R = 64, 100000 56 / 33.
         for (int32_t b = 0; b < nb;) {       // in bucket order (Section 3.2.3)
             int32_t e = b + 1;
             while (e < nb && plan.buckets[e].dtype == plan.buckets[b].dtype) ++e;

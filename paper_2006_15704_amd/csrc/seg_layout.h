@@ -17,7 +17,7 @@ struct HostTables {
     int64_t slab_stride = 0;                // bytes of one replica's slab (all buckets), multiple of 4096
     std::vector<int64_t> tile0;             // [G + 1] first tile of every segment
     std::vector<SegInfo> seg;               // [G]
-    std::vector<void*> grad;                // [G * R + 8], see SegTables::grad
+    std::vector<void*> grad;                // [G * R + 16], see SegTables::grad
     std::vector<int32_t> tile_seg;          // [tile0[G]]
     std::vector<void*> out;                 // [G] binary32 output tensors (empty without outputs)
 };
@@ -43,7 +43,7 @@ inline void build_host_tables(const BucketPlan& plan, void* const* grad_ptrs, in
 
     h.tile0.assign(n + 1, 0);
     h.seg.assign(n, SegInfo{});
-    h.grad.assign(static_cast<size_t>(R) * n + 8, nullptr);
+    h.grad.assign(static_cast<size_t>(R) * n + 16, nullptr);
     h.out.assign(out_ptrs ? n : 0, nullptr);
     for (int32_t b = 0; b < nb; ++b) {
         const BucketInfo& bk = plan.buckets[b];
