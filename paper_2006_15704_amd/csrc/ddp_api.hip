@@ -5,6 +5,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <chrono>
 #include <cstdio>
 #include <cstring>
 #include <string>
@@ -100,14 +101,20 @@ struct ddp_ctx {
     uint64_t* h_masks[2] = {nullptr, nullptr};   // pinned copies of local_cur, by iteration parity; see stage_masks
     bool masks_in_flight[2] = {false, false};    // kernels of an earlier iteration may still read h_masks
     int64_t masks_claimed_iter = -1;             // iteration for which h_masks was waited for
-    void** d_micro = nullptr;
-    void** h_micro = nullptr;                // pinned
+    void** d_micro = nullptr;                // [R * n, rounded up to an even number]
+    // Pinned: kMicroSlots tables of micro-step pointers, used in turn, and behind them the ordinal of the latest
+    // table that the device has read (written by pointer_copy_kernel).
+    static constexpr int kMicroSlots = 4;
+    void** h_micro = nullptr;
+    int64_t micro_table = 0;                 // pointers of one table
+    unsigned long long micro_ticket = 0;     // ordinal of the latest call's table
+    unsigned long long* micro_done() const { return reinterpret_cast<unsigned long long*>(h_micro + kMicroSlots * micro_table); }
     void** d_emit = nullptr;
     void** h_emit = nullptr;                 // pinned
     int64_t emit_cap = 0;                    // pointers
     std::vector<hipEvent_t> ev_ready;        // one per bucket
-    hipEvent_t ev_done = nullptr, ev_micro = nullptr, ev_emit = nullptr;
-    bool micro_in_flight = false, emit_in_flight = false;
+    hipEvent_t ev_done = nullptr, ev_emit = nullptr;
+    bool emit_in_flight = false;
 
     std::vector<std::pair<int32_t, int32_t>> log_running, log_closed;
     std::vector<int32_t> order_running, order_closed;   // ready marks in the order they came (the trace)
@@ -733,7 +740,7 @@ void release_device(ddp_ctx* c) {
     }
     drop_timed(c);
     release_build(c);
-    for (hipEvent_t* e : {&c->ev_done, &c->ev_micro, &c->ev_emit, &c->ev_global[0], &c->ev_global[1]})
+    for (hipEvent_t* e : {&c->ev_done, &c->ev_emit, &c->ev_global[0], &c->ev_global[1]})
         if (*e) { (void)hipEventDestroy(*e); *e = nullptr; }
     if (c->d_order_mem) (void)hipFree(c->d_order_mem);
     c->d_order_mem = nullptr; c->d_order = nullptr; c->d_probe = nullptr;
@@ -795,7 +802,6 @@ int32_t ddp_create(ddp_ctx** out, int32_t R, int32_t device, void* reduce_stream
         if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_done, kOrderEvent);
         for (hipEvent_t& ev : c->ev_global)
             if (e == hipSuccess) e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_micro, hipEventDisableTiming);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_emit, hipEventDisableTiming);
         int cus = 0;
         if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device);
@@ -1081,8 +1087,12 @@ static int32_t build_internal(ddp_ctx* c, uint64_t cap_bytes, const std::vector<
         if (n > ddp::kMasksByValue)
             for (uint64_t*& m : c->h_masks)
                 HIPCHK(c, hipHostMalloc(reinterpret_cast<void**>(&m), sizeof(uint64_t) * n, hipHostMallocDefault));
-        HIPCHK(c, hipMalloc(reinterpret_cast<void**>(&c->d_micro), sizeof(void*) * R * n));
-        HIPCHK(c, hipHostMalloc(reinterpret_cast<void**>(&c->h_micro), sizeof(void*) * R * n, hipHostMallocDefault));
+        c->micro_table = round_up(R * n, 2);
+        const size_t micro_bytes = sizeof(void*) * static_cast<size_t>(c->micro_table);
+        HIPCHK(c, hipMalloc(reinterpret_cast<void**>(&c->d_micro), micro_bytes));
+        HIPCHK(c, hipHostMalloc(reinterpret_cast<void**>(&c->h_micro), micro_bytes * ddp_ctx::kMicroSlots + sizeof(unsigned long long), hipHostMallocDefault));
+        std::memset(c->h_micro, 0, micro_bytes * ddp_ctx::kMicroSlots + sizeof(unsigned long long));
+        c->micro_ticket = 0;
         HIPCHK(c, hipMalloc(reinterpret_cast<void**>(&c->d_gate), sizeof(ddp::GateRecord) * (nb + 1) * ddp_ctx::kGateRows));
         HIPCHK(c, hipMemset(c->d_gate, 0, sizeof(ddp::GateRecord) * (nb + 1) * ddp_ctx::kGateRows));
         c->gates_in_iter = 0;
@@ -1137,7 +1147,6 @@ int32_t ddp_rebuild_buckets(ddp_ctx* c, uint64_t cap_bytes) {
             c->global_on_device = false;
         }
         drop_timed(c);
-        c->micro_in_flight = false;
         c->masks_in_flight[0] = c->masks_in_flight[1] = false;
         c->masks_claimed_iter = -1;
     }
@@ -1423,6 +1432,21 @@ int32_t ddp_get_launch_log(const ddp_ctx* c, int32_t which, int32_t* bucket_ids,
     return DDP_OK;
 }
 
+// The table that the next micro-step will use was last used kMicroSlots calls ago: the device must have read it.
+// (A word in pinned memory that the copying kernel writes instead of an event: that costs the stream a packet with a
+// signal and the host 4 us a record.)  A bounded look, then the stream is waited for.
+static int32_t await_micro_slot(ddp_ctx* c) {
+    if (c->micro_ticket < ddp_ctx::kMicroSlots) return DDP_OK;
+    const unsigned long long need = c->micro_ticket + 1 - ddp_ctx::kMicroSlots;
+    const auto until = std::chrono::steady_clock::now() + std::chrono::milliseconds(100);
+    while (__atomic_load_n(c->micro_done(), __ATOMIC_ACQUIRE) < need)
+        if (std::chrono::steady_clock::now() >= until) {
+            HIPCHK(c, hipStreamSynchronize(c->backward));
+            break;
+        }
+    return DDP_OK;
+}
+
 int32_t ddp_no_sync_accumulate(ddp_ctx* c, void* const* micro) {
     if (!c) return DDP_ERR_ARG;
     if (!c->built) return fail(c, DDP_ERR_STATE, "ddp_no_sync_accumulate before ddp_build_buckets");
@@ -1441,12 +1465,16 @@ int32_t ddp_no_sync_accumulate(ddp_ctx* c, void* const* micro) {
                 return fail(c, DDP_ERR_ARG, "ddp_no_sync_accumulate: pointer not aligned to its element size");
         }
     HIPCHK(c, hipSetDevice(c->device));
-    if (c->micro_in_flight) HIPCHK(c, hipEventSynchronize(c->ev_micro));
+    void** const table = c->h_micro + static_cast<int64_t>((c->micro_ticket + 1) % ddp_ctx::kMicroSlots) * c->micro_table;
+    {
+        const int32_t rcw = await_micro_slot(c);
+        if (rcw != DDP_OK) return rcw;
+    }
     // a parameter at a time: its row of the table is written in one go (R = 32, 1600 tensors: 82 us of
     // host time a call when every pointer went to a cache line of its own, 44 so)
     for (int32_t i = 0; i < n; ++i) {
         const int32_t segment = c->plan.params[i].segment;
-        void** row = c->h_micro + segment * R;
+        void** row = table + segment * R;
         uint64_t used = 0;
         for (int64_t r = 0; r < R; ++r) {
             void* const p = micro[r * n + i];
@@ -1455,9 +1483,8 @@ int32_t ddp_no_sync_accumulate(ddp_ctx* c, void* const* micro) {
         }
         c->micro_used[segment] = used;
     }
-    HIPCHK(c, hipMemcpyAsync(c->d_micro, c->h_micro, sizeof(void*) * R * n, hipMemcpyHostToDevice, c->backward));
-    HIPCHK(c, hipEventRecord(c->ev_micro, c->backward));
-    c->micro_in_flight = true;
+    HIPCHK(c, ddp::launch_pointer_copy(c->d_micro, table, c->micro_table, c->micro_done(), c->micro_ticket + 1, c->backward));
+    ++c->micro_ticket;
     size_t slot;
     int32_t rc;
     if ((rc = timed_begin(c, DDP_K_ACCUMULATE, -1, c->backward, &slot)) != DDP_OK) return rc;

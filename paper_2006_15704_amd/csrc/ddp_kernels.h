@@ -238,6 +238,10 @@ hipError_t launch_mask_write(uint64_t* dst, const uint64_t* masks, int count, co
 hipError_t launch_bitmap_or(uint64_t* local, uint8_t* global, uint8_t* host_global, const uint64_t* masks, int G,
                             hipStream_t s);
 
+// dst[0 .. count) = src[0 .. count) (pinned memory; 16-byte aligned both, count even), then *done = ticket (pinned).
+hipError_t launch_pointer_copy(void** dst, void* const* src, int64_t count, unsigned long long* done, unsigned long long ticket,
+                               hipStream_t s);
+
 // K4: grad[r][g] += micro[g*R + r] for all segments and replicas (laid out as SegTables::grad, so that
 // a block fetches both pointers at once)
 // (null micro pointers are skipped).  ntiles = tile0[G].

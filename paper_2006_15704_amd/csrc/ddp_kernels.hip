@@ -1209,6 +1209,29 @@ __global__ __launch_bounds__(BLOCK) void accumulate_kernel(SegTables t, void* co
     }
 }
 
+// The pointers of a micro-step go from pinned memory to the table that accumulate_kernel reads, and `done`
+// (pinned) tells the host with which call's it is through, so that the host may write there again.  One block: the last of its
+// reads has returned when its threads have met, so the store needs no release (which would write the cache back).  Bound by the way to host memory and back, about
+// 2 us; every thread keeps four 16-byte loads under way.
+// A copy of the runtime's and an event behind it took 2.9 and 4 us of the host, the wait for the event 7 when it had
+// just passed, and 10 us of the stream: ResNet-50 in bfloat16, R = 8, 196 -> 193 us a micro-step; 234 tensors, R = 5, 57 -> 50;
+// four micro-steps and the reduction of 84000 elements, R = 16, 270 -> 239.
+__global__ __launch_bounds__(1024) void pointer_copy_kernel(u32x4* __restrict__ dst, const u32x4* __restrict__ src, int64_t nvec,
+                                                            unsigned long long* done, unsigned long long ticket) {
+    constexpr int U = 4;
+    for (int64_t i0 = threadIdx.x; i0 < nvec; i0 += 1024 * U) {
+        u32x4 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (i0 + u * 1024 < nvec) v[u] = src[i0 + u * 1024];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (i0 + u * 1024 < nvec) dst[i0 + u * 1024] = v[u];
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store(done, ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // ---- global participation bitmap ---------------------------------------------
 // Up to kMasksByValue masks reach the device inside kernel arguments instead of by
 // a staged copy, which takes the host three times as long and the stream a copy packet with a hand-over
@@ -1539,6 +1562,14 @@ hipError_t launch_probe(unsigned long long* word, unsigned long long value, long
     hipError_t e = after_launch();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(probe_write_kernel, dim3(1), dim3(64), 0, writer, word, value);
+    return after_launch();
+}
+
+hipError_t launch_pointer_copy(void** dst, void* const* src, int64_t count, unsigned long long* done, unsigned long long ticket,
+                               hipStream_t s) {
+    if (count % 2 != 0) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(pointer_copy_kernel, dim3(1), dim3(1024), 0, s, reinterpret_cast<u32x4*>(dst),
+                       reinterpret_cast<const u32x4*>(src), count / 2, done, ticket);
     return after_launch();
 }
 
