@@ -230,9 +230,11 @@ def ddp_get_bucket_ptr(ctx, b: int, r: int) -> int:
     return p.value or 0
 
 
-# The calls made once per parameter go through a small CPython module (plain
-# argument passing, a tenth of the interpreter time of a ctypes call); it is
-# built together with the library.
+# The calls made once per parameter, and those that take a list with an entry per
+# parameter or tensor, go through a small CPython module (plain argument passing, a
+# tenth of the interpreter time of numpy and a ctypes call); it is built together with
+# the library.  A list it does not take (anything but plain ints) it leaves to the
+# conversions below, by returning None.
 import importlib.util as _ilu
 
 _fast_path = os.path.join(_HERE, "_ddp_fastcall.so")
@@ -241,9 +243,16 @@ if not os.path.exists(_fast_path):
 _spec = _ilu.spec_from_file_location("_ddp_fastcall", _fast_path)
 _fast = _ilu.module_from_spec(_spec)
 _spec.loader.exec_module(_fast)
-_fast.bind(C.cast(_lib.ddp_mark_ready, _vp).value, C.cast(_lib.ddp_finalize_backward, _vp).value,
-           C.cast(_lib.ddp_mark_ready_local, _vp).value, _i32)
+_mark, _finalize, _mark_local, _many, _accumulate, _static = (
+    C.cast(f, _vp).value for f in (_lib.ddp_mark_ready, _lib.ddp_finalize_backward, _lib.ddp_mark_ready_local,
+                                   _lib.ddp_mark_ready_many, _lib.ddp_no_sync_accumulate, _lib.ddp_sync_static))
+_fast.bind(_mark, _finalize, _mark_local, _i32, _many, _accumulate, _static)
 _fast_mark, _fast_finalize, _fast_mark_local = _fast.mark_ready, _fast.finalize_backward, _fast.mark_ready_local
+_fast_many, _fast_accumulate, _fast_static = _fast.mark_ready_many, _fast.no_sync_accumulate, _fast.sync_static
+
+
+def _address(ctx):
+    return ctx.value if type(ctx) is _vp else None
 
 
 def ddp_mark_ready(ctx, param_id: int) -> None:
@@ -266,6 +275,11 @@ def ddp_get_global_used(ctx, n: int) -> np.ndarray:
 
 
 def ddp_mark_ready_many(ctx, ids) -> None:
+    status = _fast_many(_address(ctx), ids)
+    if status is not None:
+        if status < 0:
+            _check(ctx, status)
+        return
     arr = _i32_array(ids)
     _check(ctx, _lib.ddp_mark_ready_many(ctx, _as(arr, _i32), len(arr)))
 
@@ -305,6 +319,11 @@ def ddp_get_launch_log(ctx, which: int = 1):
 
 
 def ddp_no_sync_accumulate(ctx, micro_grad_ptrs: Sequence[Optional[int]]) -> None:
+    status = _fast_accumulate(_address(ctx), micro_grad_ptrs)
+    if status is not None:
+        if status < 0:
+            _check(ctx, status)
+        return
     arr = _ptr_array(micro_grad_ptrs)
     _check(ctx, _lib.ddp_no_sync_accumulate(ctx, _as(arr, _vp)))
 
@@ -338,6 +357,9 @@ def ddp_sync_static(R: int, device: int, stream: int, numel: Sequence[int], dtyp
                     grad_ptrs: Sequence[int], cap_bytes: int) -> int:
     """One whole synchronization without a context and without device-memory
     allocation; returns the number of buckets."""
+    status = _fast_static(R, device, stream, numel, dtype, grad_ptrs, cap_bytes)
+    if status is not None:
+        return _check(None, status)
     ne, dt, gp = _i64_array(numel), _i32_array(dtype), _ptr_array(grad_ptrs)
     if len(gp) != R * len(ne):
         raise ValueError(f"grad_ptrs has {len(gp)} entries, expected R*n = {R * len(ne)}")

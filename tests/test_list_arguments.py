@@ -1,0 +1,78 @@
+"""Lists of plain ints are converted in C, everything else with numpy: the same calls are accepted, with the same
+results and the same errors, whichever way a list goes."""
+import numpy as np
+import pytest
+
+import paper_2006_15704_amd as d
+
+
+def context(n=5, R=2):
+    ctx = d.ddp_create(R, d.DDP_DEVICE_NONE)
+    d.ddp_register_params(ctx, [10 + i for i in range(n)], [0] * n, None)
+    d.ddp_build_buckets(ctx, 100)
+    return ctx
+
+
+FORMS = [list, tuple, lambda v: np.array(v), lambda v: np.array(v, dtype=np.int64), lambda v: [np.int32(x) for x in v],
+         lambda v: [float(x) for x in v], lambda v: range(4, -1, -1)]
+
+
+@pytest.mark.parametrize("form", FORMS)
+def test_ids_in_any_form(form):
+    ctx = context()
+    d.ddp_mark_ready_many(ctx, form([4, 3, 2, 1, 0]))
+    assert d.ddp_get_ready_order(ctx, 0) == [4, 3, 2, 1, 0]
+    d.ddp_finalize_backward(ctx)
+    d.ddp_mark_ready_many(ctx, form([4, 3, 2, 1, 0])[:0])
+    d.ddp_mark_ready_many(ctx, [True, 0])
+    assert d.ddp_get_ready_order(ctx, 0) == [1, 0]
+    d.ddp_destroy(ctx)
+
+
+@pytest.mark.parametrize("ids,error", [([7], d.DdpError), ([-1], d.DdpError), ([1, 1], d.DdpError), ([1 << 31], OverflowError),
+                                       ([-(1 << 31) - 1], OverflowError), ([1 << 80], OverflowError), (["x"], ValueError)])
+def test_refused_ids(ids, error):
+    for form in (list, tuple):
+        ctx = context()
+        with pytest.raises(error):
+            d.ddp_mark_ready_many(ctx, form(ids))
+        d.ddp_destroy(ctx)
+
+
+def test_null_contexts():
+    for ctx in (None, d.binding.C.c_void_p()):
+        with pytest.raises(d.DdpError):
+            d.ddp_mark_ready_many(ctx, [0])
+        with pytest.raises(d.DdpError):
+            d.ddp_no_sync_accumulate(ctx, [0])
+
+
+def test_pointers():
+    ctx = context()
+    for ptrs in ([None] * 10, [0] * 10, tuple([256, None] * 5), np.zeros(10, dtype=np.uint64), [(1 << 64) - 4] * 10):
+        with pytest.raises(d.DdpError) as e:       # nothing is computed without a device
+            d.ddp_no_sync_accumulate(ctx, ptrs)
+        assert e.value.code == d.DDP_ERR_NO_DEVICE
+    for ptrs in ([-1] * 10, [1 << 64] * 10):
+        with pytest.raises(OverflowError):
+            d.ddp_no_sync_accumulate(ctx, ptrs)
+    d.ddp_destroy(ctx)
+
+
+def test_context_free_call():
+    """What is refused before a device is touched."""
+    big = 1 << 30
+    for form in (list, tuple, lambda v: np.array(v, dtype=np.int64)):
+        with pytest.raises(d.DdpError) as e:
+            d.ddp_sync_static(2, 0, 0, form([big]), [0], form([256, 256]), 100)
+        assert e.value.code == d.DDP_ERR_UNSUPPORTED
+        with pytest.raises(d.DdpError) as e:
+            d.ddp_sync_static(2, 0, 0, form([8]), [7], form([256, 256]), 100)
+        assert e.value.code == d.DDP_ERR_ARG
+        with pytest.raises(d.DdpError) as e:
+            d.ddp_sync_static(2, 0, 0, form([8]), [0], form([256, 2]), d.DDP_CAP_WHOLE_MODEL)
+        assert e.value.code == d.DDP_ERR_ARG
+        with pytest.raises(ValueError):
+            d.ddp_sync_static(2, 0, 0, form([8]), [0], form([256]), 100)
+    with pytest.raises(OverflowError):
+        d.ddp_sync_static(2, 0, 0, [8], [0], [-1, 256], 100)
