@@ -157,6 +157,15 @@ struct ddp_ctx {
     }
     int64_t safe_iteration = 0;                   // everything enqueued before this iteration is known to be done
     uint64_t seq_issued = 0;                      // sequence numbers announced so far
+    // Whether the GPU waits for the host (see kEarlyTraffic): the number of an announcement that is also
+    // written to h_progress (pinned), 0 = none outstanding, and when it was enqueued; launches and bytes that may
+    // still go to the backward stream on the strength of the last look; announcements of the running iteration that
+    // came late, launches placed.
+    unsigned long long* h_progress = nullptr;
+    uint64_t progress_wait = 0;
+    std::chrono::steady_clock::time_point progress_since;
+    int32_t early_credit = 0, late_looks = 0, early_launches = 0;
+    int64_t early_bytes = 0;
     uint64_t probe_value = 0;
     uint64_t call_seq = 0;                        // the number announced for the running API call
     bool call_by_flag = false;                    // the running API call orders its launches by flag
@@ -316,9 +325,12 @@ void drop_timed(ddp_ctx* c) {
     c->open_group = static_cast<size_t>(-1);
 }
 
+void look_at_progress(ddp_ctx* c);
+
 // A new API call begins: whatever the caller enqueued on the backward stream
 // since the last call has to be ordered before the launches of this one.
 void new_call(ddp_ctx* c) {
+    look_at_progress(c);
     c->call_by_flag = false;
     c->ordered_in_call = false;
     c->backward_idle_in_call = false;
@@ -396,11 +408,51 @@ bool flags_usable(const ddp_ctx* c) {
     return true;
 }
 
+// A short launch on a reduction stream costs the host three launches (announcement, gate, kernel, 3 us each), on the
+// backward stream one, but there it holds the backward pass up for its own time.  That does not matter while the GPU
+// waits for the host anyway.  So the announcement of a short launch is shown to the host as well, and if it shows
+// within kPromptUs, which takes a backward stream with nothing left to run, the next short launches of the iteration go to
+// the backward stream, kEarlyLaunches of them that move kEarlyBytes (50 us of the GPU) at most; then one is announced again.  A
+// stream that is busy with the backward pass does not get there in time, and after kLateLooks announcements (and one for
+// every four launches placed) that came late no more are shown.
+// One mark per call, us a synchronization, without / with (a process has faster launches or slower ones): ResNet-50 in 1 MiB buckets, binary16, R = 16,
+// 374 to 480 / 285 to 330; 19 MB in 62 buckets, binary32, R = 24, 434 to 566 / 283 to 315; 40 MB in 13, bfloat16, R = 4, 118 to 126 / 84; 23 MB in 5, R = 8,
+// 102 to 112 / 76; every replica written, 17 MB in 12, R = 8, 176 / 113.  Exposed under 10 us of backward work a parameter, ResNet-50 in 1 MiB
+// buckets, fused 96 to 119 / 93 to 126, staged 139 / 135 to 158 (with the bucket's mark in place of kPromptUs, which lets the GPU be up to a bucket
+// behind, 125 / 182 and 155 / 235).
+constexpr int64_t kEarlyTraffic = int64_t(64) << 20, kEarlyBytes = int64_t(256) << 20;
+constexpr int32_t kEarlyLaunches = 16, kLateLooks = 2, kPromptUs = 8;
+
+void look_at_progress(ddp_ctx* c) {
+    if (c->progress_wait == 0) return;
+    const bool reached = __atomic_load_n(c->h_progress, __ATOMIC_RELAXED) >= c->progress_wait;
+    const bool late = std::chrono::steady_clock::now() - c->progress_since > std::chrono::microseconds(kPromptUs);
+    if (!reached && !late) return;
+    c->progress_wait = 0;
+    if (late) {
+        ++c->late_looks;
+    } else {
+        c->early_credit = kEarlyLaunches;
+        c->early_bytes = kEarlyBytes;
+    }
+}
+
+// Whether the launch at hand goes to the backward stream on the strength of the last look.
+bool take_early(ddp_ctx* c, int64_t traffic) {
+    look_at_progress(c);
+    if (c->early_credit == 0) return false;
+    c->early_bytes -= traffic;
+    if (--c->early_credit == 0 || c->early_bytes < 0) c->early_credit = 0;
+    ++c->early_launches;
+    return true;
+}
+
 // Order the launches of the running API call after the gradient-producing work enqueued so
 // far: one look at the backward stream, and at most one announcement or event on it, serves
 // every bucket the call launches (the caller cannot enqueue anything in the middle of a call).
 // If the backward stream has already drained there is nothing to wait for.
-int32_t order_call(ddp_ctx* c, int32_t first) {
+// look: the host will want to know when the stream gets there.
+int32_t order_call(ddp_ctx* c, int32_t first, bool look) {
     if (c->ordered_in_call) return DDP_OK;
     // (a stream that is being captured into a graph cannot be queried: treat it as busy)
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
@@ -416,7 +468,12 @@ int32_t order_call(ddp_ctx* c, int32_t first) {
             // a one-block kernel instead of an event record (which stalls the stream
             // for about 12 us here)
             c->call_seq = ++c->seq_issued;
-            HIPCHK(c, ddp::launch_announce(c->d_order, c->call_seq, c->backward));
+            const bool show = look && c->late_looks <= kLateLooks + c->early_launches / 4;
+            HIPCHK(c, ddp::launch_announce(c->d_order, c->call_seq, show ? c->h_progress : nullptr, c->backward));
+            if (show) {
+                c->progress_wait = c->call_seq;
+                c->progress_since = std::chrono::steady_clock::now();
+            }
             c->call_by_flag = true;
         } else {
             HIPCHK(c, hipEventRecord(c->ev_ready[first], c->backward));
@@ -469,8 +526,12 @@ int32_t launch_range(ddp_ctx* c, int32_t first, int32_t last, Target target) {
     const int32_t id = first + 65536 * (last - first);
     int lane = -1;                    // -1: the backward stream
     hipStream_t st = c->backward;
+    const bool may_be_early = target == Target::kLane && c->n_streams < 0 && c->tail_on_backward != 0 && traffic <= kEarlyTraffic &&
+                              flags_usable(c);
     if (target == Target::kLane && c->n_streams < 0 && c->tail_on_backward != 0 && c->small_model) {
         // stays on the backward stream
+    } else if (may_be_early && take_early(c, traffic)) {
+        // ... and so does this launch
     } else if (target == Target::kLane) {
         // Short launches gain from a neighbour on a second stream (start-up and drain of one
         // overlap with the other); launches long enough for the cap on resident blocks lose
@@ -489,7 +550,7 @@ int32_t launch_range(ddp_ctx* c, int32_t first, int32_t last, Target target) {
     const ddp::GateRecord* gate = nullptr;
     ddp::DispatchSignal sig{nullptr, 0};
     if (lane >= 0 && (!c->lane_ordered[lane] || c->call_by_flag)) {
-        const int32_t rc = order_call(c, first);
+        const int32_t rc = order_call(c, first, may_be_early);
         if (rc != DDP_OK) return rc;
     }
     // Chained launches.  With flag ordering in use (so the streams are known to run side by
@@ -604,6 +665,7 @@ int32_t launch_range(ddp_ctx* c, int32_t first, int32_t last, Target target) {
                                            flat, gate, tag, sig, st));
         if ((rc = timed_end(c, slot, st)) != DDP_OK) return rc;
     }
+    look_at_progress(c);
     return DDP_OK;
 }
 
@@ -672,7 +734,7 @@ int32_t flush_deferred(ddp_ctx* c) {
     // share goes out first, ahead of the backward stream's own launches.
     bool partner = false;
     if (closing && ranges.size() > 1 && c->chain_launches != 0 && c->reduce != c->backward && flags_usable(c)) {
-        const int32_t rc = order_call(c, ranges[0].first);
+        const int32_t rc = order_call(c, ranges[0].first, false);
         if (rc != DDP_OK) return rc;
         partner = c->call_by_flag;
     }
@@ -744,6 +806,8 @@ void release_device(ddp_ctx* c) {
         if (*e) { (void)hipEventDestroy(*e); *e = nullptr; }
     if (c->d_order_mem) (void)hipFree(c->d_order_mem);
     c->d_order_mem = nullptr; c->d_order = nullptr; c->d_probe = nullptr;
+    if (c->h_progress) (void)hipHostFree(c->h_progress);
+    c->h_progress = nullptr;
     if (c->d_emit) (void)hipFree(c->d_emit);
     if (c->h_emit) (void)hipHostFree(c->h_emit);
     c->d_emit = nullptr; c->h_emit = nullptr;
@@ -809,6 +873,8 @@ int32_t ddp_create(ddp_ctx** out, int32_t R, int32_t device, void* reduce_stream
         const size_t order_bytes = sizeof(ddp::OrderState) + 2 * sizeof(unsigned long long);
         if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&c->d_order_mem), order_bytes);
         if (e == hipSuccess) e = hipMemset(c->d_order_mem, 0, order_bytes);
+        if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void**>(&c->h_progress), sizeof(unsigned long long), hipHostMallocDefault);
+        if (e == hipSuccess) *c->h_progress = 0;
         if (e == hipSuccess) e = hipDeviceSynchronize();
         if (e != hipSuccess) {
             std::string msg = std::string("ddp_create: ") + hipGetErrorString(e);
@@ -1388,6 +1454,8 @@ int32_t ddp_finalize_backward(ddp_ctx* c) {
     c->launches_in_iter = 0;
     c->gates_in_iter = 0;
     c->prev_launch_ord = 0;
+    c->progress_wait = 0;
+    c->early_credit = c->late_looks = c->early_launches = 0;
     ++c->iteration;
     c->tracker.new_iteration();
     return DDP_OK;

@@ -185,7 +185,8 @@ struct GateRecord {                 // one per bucket, used by the launch whose 
 
 // backward stream: ready_seq = seq.  (Everything enqueued before it on that stream has
 // ended, and is visible device-wide, by the time the kernel that stores the number runs.)
-hipError_t launch_announce(OrderState* st, unsigned long long seq, hipStream_t s);
+// host (may be null): a word in pinned memory that receives the number as well, for the host to see.
+hipError_t launch_announce(OrderState* st, unsigned long long seq, unsigned long long* host, hipStream_t s);
 
 // The way back at the end of an iteration.  Reduction stream `lane`, behind its last bucket
 // launch: lane_done[lane] = tag.  Backward stream: wait (at most wait_ticks) until lane_done[l]

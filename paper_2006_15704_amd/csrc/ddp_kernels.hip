@@ -998,9 +998,12 @@ constexpr uint32_t MAX_GATE_POLLS = 1u << 22;
 // concurrently running reduce kernel's lines (measured: 11 us per announcement
 // next to a BERT-sized reduction) -- just device-wide atomicity and visibility,
 // which relaxed agent-scope atomics give.
-__global__ __launch_bounds__(64) void announce_kernel(OrderState* st, unsigned long long seq) {
-    if (threadIdx.x == 0)
+// host: pinned word that receives the number too, or null.
+__global__ __launch_bounds__(64) void announce_kernel(OrderState* st, unsigned long long seq, unsigned long long* host) {
+    if (threadIdx.x == 0) {
         __hip_atomic_store(&st->ready_seq, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (host != nullptr) __hip_atomic_store(host, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
 }
 
 // One wave; lane 0 polls.  Both bounds (wall-clock ticks and the poll count) end
@@ -1487,8 +1490,8 @@ hipError_t launch_fused_reduce(int dtype, const SegTables& t, int64_t tile_base,
     }
 }
 
-hipError_t launch_announce(OrderState* st, unsigned long long seq, hipStream_t s) {
-    hipLaunchKernelGGL(announce_kernel, dim3(1), dim3(64), 0, s, st, seq);
+hipError_t launch_announce(OrderState* st, unsigned long long seq, unsigned long long* host, hipStream_t s) {
+    hipLaunchKernelGGL(announce_kernel, dim3(1), dim3(64), 0, s, st, seq, host);
     return after_launch();
 }
 

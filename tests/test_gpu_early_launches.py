@@ -1,0 +1,61 @@
+"""Short launches that go to the backward stream while the GPU waits for the host, next to others on the reduction
+streams: gradients that the backward stream is still producing, at once or late, are reduced as they will be."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("pipeline", [0, 1])
+@pytest.mark.parametrize("delays_us", [(0,), (0, 0, 0, 0, 0, 0, 0, 0, 400), (20,)])
+def test_many_short_launches_marked_one_by_one(pipeline, delays_us):
+    import torch
+    import paper_2006_15704_amd as d
+    from paper_2006_15704_amd import harness
+    n, R, cap = 60, 5, 4096
+    numel = [700 + 13 * i for i in range(n)]                  # a bucket each
+    grads = harness.DeviceGrads(numel, [0] * n, R, fill=0xFF)
+    source = harness.DeviceGrads(numel, [0] * n, R)
+    with harness.Session(grads, cap, pipeline) as s:
+        for it in range(3):
+            reps = [workloads.gaussian_replica(960 + it, r, 0, numel, 1e-2, 0) for r in range(R)]
+            want, _, wlog = oracle.synchronize(numel, [0] * n, cap, reps)
+            for r in range(R):
+                source.upload_replica(r, reps[r])
+            torch.cuda.synchronize()
+            src = source.ptrs()
+            for k, p in enumerate(range(n - 1, -1, -1)):
+                d.ddp_synth_backward(s.ctx, [p], [delays_us[k % len(delays_us)] * 1000], src, mark=False)
+                d.ddp_mark_ready(s.ctx, p)
+            d.ddp_finalize_backward(s.ctx)
+            d.ddp_synchronize(s.ctx)
+            assert d.ddp_get_launch_log(s.ctx, 1) == wlog
+            assert d.ddp_get_option(s.ctx, d.DDP_STAT_REPAIRED_LAUNCHES) == 0
+            for p in range(n):
+                assert grads.download(0, p).tobytes() == np.asarray(want[p]).tobytes(), f"iteration {it} parameter {p}"
+
+
+@pytest.mark.parametrize("pipeline", [0, 1])
+def test_many_short_launches_without_a_backward_pass(pipeline):
+    import torch
+    import paper_2006_15704_amd as d
+    from paper_2006_15704_amd import harness
+    n, R, cap = 90, 8, 4096
+    numel = [900 + 7 * i for i in range(n)]
+    reps = [workloads.gaussian_replica(970, r, 0, numel, 1e-2, 0) for r in range(R)]
+    want, _, _ = oracle.synchronize(numel, [0] * n, cap, reps)
+    grads = harness.DeviceGrads(numel, [0] * n, R, fill=0xFF)
+    with harness.Session(grads, cap, pipeline) as s:
+        for it in range(4):
+            for r in range(R):
+                grads.upload_replica(r, reps[r])
+            torch.cuda.synchronize()
+            for p in range(n - 1, -1, -1):
+                d.ddp_mark_ready(s.ctx, p)
+            d.ddp_finalize_backward(s.ctx)
+            d.ddp_synchronize(s.ctx)
+            for p in range(n):
+                assert grads.download(0, p).tobytes() == np.asarray(want[p]).tobytes(), f"iteration {it} parameter {p}"
