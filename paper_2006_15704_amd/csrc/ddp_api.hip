@@ -330,7 +330,7 @@ void look_at_progress(ddp_ctx* c);
 // A new API call begins: whatever the caller enqueued on the backward stream
 // since the last call has to be ordered before the launches of this one.
 void new_call(ddp_ctx* c) {
-    look_at_progress(c);
+    if (c->progress_wait != 0) look_at_progress(c);
     c->call_by_flag = false;
     c->ordered_in_call = false;
     c->backward_idle_in_call = false;
