@@ -84,7 +84,8 @@ typedef struct ddp_ctx ddp_ctx;
                                      before its first bucket launch to just after its last (kind
                                      DDP_K_ITERATION); 0: off.  Read with ddp_get_kernel_times */
 #define DDP_OPT_NONTEMPORAL    5  /* any time: 1 (default) = read-once inputs are loaded, and the
-                                     averages stored, with the non-temporal hint; 0 = plain */
+                                     averages stored, with the non-temporal hint; 0 = plain, and no
+                                     launch counts as short (a thread block per 8 KiB tile at any size) */
 #define DDP_OPT_EMIT_BUSY_BLOCKS 8 /* any time: ddp_synth_backward's delay kernel.  0 (default): one
                                      thread block that sleeps between clock polls; n > 0: n blocks
                                      that do arithmetic between polls, so that the delay loads the
@@ -117,7 +118,10 @@ typedef struct ddp_ctx ddp_ctx;
                                      of buckets less one at most 16) unless
                                      DDP_OPT_TAIL_ON_BACKWARD is 0: its launches stay on
                                      backward_stream, where each takes less than the way to another
-                                     stream and back.
+                                     stream and back.  (With the same two options at their
+                                     defaults, launches that move at most 64 MiB also stay there while the
+                                     GPU is seen to wait for the host, up to 16 of them or 256 MiB at
+                                     a time.)
                                      The launches of an iteration take the streams in turn: the
                                      caller's reduce_stream first, then streams the library creates
                                      (default priority).  This is the one-GPU form of Section 3.3's
@@ -134,9 +138,10 @@ typedef struct ddp_ctx ddp_ctx;
                                      unit fill the memory system; more only interleave more request
                                      streams at the DRAM channels and throughput drops.  0 = no cap
                                      (wave slots decide: 8).  Default -1 =
-                                     chosen from R: no cap up to R = 4 (few loads per block), else 2;
-                                     none for the staged pipeline's launches, which write as much as
-                                     they read */
+                                     chosen from R: no cap up to R = 2 (few loads per block), 4 up to
+                                     R = 5, else 2, and in launches below DDP_OPT_REDUCE_CAP_MIN_BYTES 5
+                                     from R = 5 on and 3 from R = 16 on; staged pipeline (its
+                                     launches write as much as they read): 3 for R = 3 and 4, else none */
 #define DDP_OPT_REDUCE_CAP_MIN_BYTES 14 /* any time: the cap applies to launches that move at least this
                                      many bytes, counted as (R + 1) x the launch's bucket bytes in
                                      both pipelines (measured at R = 8: it gains 1 to 2.5 points of
@@ -212,7 +217,7 @@ typedef struct ddp_ctx ddp_ctx;
 /* DDP_PIPELINE_STAGED follows the paper's data flow literally: gradients are
  * copied into flat per-replica bucket buffers (Algorithm 1, autograd_hook),
  * the bucket is reduced (in the same pass over the gradients; by a kernel of its
- * own in short launches over more than 16 replicas, and with DDP_OPT_TIMING 1 so
+ * own in launches of a few MiB over more than 16 replicas, and with DDP_OPT_TIMING 1 so
  * that both can be stamped), and
  * the averaged bucket is copied back to the gradient tensors by the finalizing
  * step.  DDP_PIPELINE_FUSED computes the
@@ -462,7 +467,7 @@ int32_t ddp_get_kernel_times(ddp_ctx* ctx, int32_t kind, float* ms, int32_t* ids
  * gradient memory stays the caller's).  Returns the number of buckets.
  *
  * The device tables and, where the call needs them, the R + 1 flat bucket
- * buffers (more than 24 replicas, or tensors that may share memory; the limit
+ * buffers (tensors that may share memory; the limit
  * below counts them always) live in a static device
  * array of DDP_STATIC_SCRATCH_BYTES that every GPU used through this call holds
  * until the process ends; host tables travel inside kernel arguments.  The call

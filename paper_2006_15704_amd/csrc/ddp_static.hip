@@ -193,7 +193,8 @@ extern "C" int32_t ddp_sync_static(int32_t R, int32_t device, void* stream, int3
 
     // layout of the scratch array: [segment records | pointer rows | tile map | pad to 256 | R + 1 slabs]
     const size_t seg_bytes = sizeof(ddp::SegInfo) * static_cast<size_t>(n);
-    const size_t ptr_bytes = sizeof(void*) * ht.grad.size();
+    // (eight entries of padding: a row that is read sixteen wide reaches into the tile map and the slabs behind it)
+    const size_t ptr_bytes = sizeof(void*) * (static_cast<size_t>(R) * static_cast<size_t>(n) + 8);
     const size_t map_bytes = sizeof(int32_t) * ht.tile_seg.size();
     const size_t table_bytes = static_cast<size_t>(ddp::round_up_to(static_cast<int64_t>(seg_bytes + ptr_bytes + map_bytes), 256));
     const size_t slab_bytes = static_cast<size_t>(ht.slab_stride) * static_cast<size_t>(R + 1);

@@ -2,8 +2,8 @@
 is a variant of -- ddp_mark_ready_many + ddp_finalize_backward on a staged
 context -- and against the CPU oracle, bit for bit, on two calls in a row (the
 second with a smaller input, so that what the first call left in the static
-scratch array must not leak into it).  Up to 24 replicas whose tensors lie apart
-the call reduces in place; more replicas, and tensors that share memory, go
+scratch array must not leak into it).  Replicas whose tensors lie apart
+the call reduces in place; tensors that share memory go
 through the flat buckets in the array."""
 import numpy as np
 import pytest
