@@ -141,7 +141,7 @@ typedef struct ddp_ctx ddp_ctx;
                                      chosen from R: no cap up to R = 2 (few loads per block), 4 up to
                                      R = 5, else 2, and in launches below DDP_OPT_REDUCE_CAP_MIN_BYTES 5
                                      from R = 5 on and 3 from R = 16 on; staged pipeline (its
-                                     launches write as much as they read): 3 for R = 3 and 4, else none */
+                                     launches write as much as they read): 3 for R = 4, else none */
 #define DDP_OPT_REDUCE_CAP_MIN_BYTES 14 /* any time: the cap applies to launches that move at least this
                                      many bytes, counted as (R + 1) x the launch's bucket bytes in
                                      both pipelines (measured at R = 8: it gains 1 to 2.5 points of

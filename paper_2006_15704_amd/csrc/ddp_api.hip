@@ -202,9 +202,10 @@ int32_t fail(ddp_ctx* c, int32_t code, const std::string& msg) {
 // has nothing else to run -- so two it is, also with binary32 outputs next to 16-bit
 // inputs.
 // copies: the staged pass, which writes as much as it reads (60 BERT-large tensors, us, no cap / three blocks: binary32 R = 2 332 /
-// 337, R = 4 551 / 540, R = 8 1002 / 1009; bfloat16 R = 2 170 / 181, R = 4 278 / 264, R = 8 496 / 503).
+// 337, R = 3 440 / 496, R = 4 551 / 540, R = 8 1002 / 1009; bfloat16 R = 2 170 / 181, R = 3 219 / 236, R = 4 278 / 264, R = 8 496 / 503).
+// Three replicas are read by a round of two and one of one, so that a block has fewer loads under way than with four.
 int32_t auto_blocks_per_cu(int32_t R, bool copies) {
-    if (copies) return R == 3 || R == 4 ? 3 : 0;
+    if (copies) return R == 4 ? 3 : 0;
     return R <= 2 ? 0 : R <= 5 ? 4 : 2;
 }
 
