@@ -139,9 +139,9 @@ typedef struct ddp_ctx ddp_ctx;
                                      streams at the DRAM channels and throughput drops.  0 = no cap
                                      (wave slots decide: 8).  Default -1 =
                                      chosen from R: no cap up to R = 2 (few loads per block), 4 up to
-                                     R = 5, else 2, and in launches below DDP_OPT_REDUCE_CAP_MIN_BYTES 5
-                                     from R = 5 on and 3 from R = 16 on; staged pipeline (its
-                                     launches write as much as they read): 3 for R = 4, else none */
+                                     R = 5, else 2, and in launches below DDP_OPT_REDUCE_CAP_MIN_BYTES 4
+                                     from R = 5 on and 2 from R = 16 on; staged pipeline (its
+                                     launches write as much as they read): 2 for R = 4, else none */
 #define DDP_OPT_REDUCE_CAP_MIN_BYTES 14 /* any time: the cap applies to launches that move at least this
                                      many bytes, counted as (R + 1) x the launch's bucket bytes in
                                      both pipelines (measured at R = 8: it gains 1 to 2.5 points of
@@ -150,7 +150,7 @@ typedef struct ddp_ctx ddp_ctx;
                                      launch and gains 2.5 points).  Default 360 MiB (40 MiB of bucket
                                      data at R = 8) */
 #define DDP_OPT_ACCUMULATE_BLOCKS_PER_CU 16 /* any time: likewise for the accumulate kernel (two loads
-                                     and a store per vector; registers allow 8 blocks).  Default 5 */
+                                     and a store per vector; registers allow 8 blocks).  Default 4 */
 #define DDP_OPT_TAIL_ON_BACKWARD 17 /* any time between iterations: 1 (default) = the buckets launched by
                                      the API call that completes an iteration (the call after which
                                      the last bucket is launchable: every gradient exists, nothing

@@ -65,7 +65,7 @@ struct ddp_ctx {
     int32_t blocks_per_cu = -1;                   // reduce kernels: resident blocks per compute unit (0 = no cap,
                                                   // -1 = chosen from R, see auto_blocks_per_cu)
     int64_t cap_min_traffic = int64_t(360) << 20; // ... applied to launches that move at least this many bytes
-    int32_t acc_blocks_per_cu = 5;                // accumulate kernel: likewise
+    int32_t acc_blocks_per_cu = 4;                // accumulate kernel: likewise
     int64_t lds_per_cu = 160 * 1024;              // read from the device at creation
 
     bool registered = false, built = false;
@@ -189,23 +189,23 @@ int32_t fail(ddp_ctx* c, int32_t code, const std::string& msg) {
             return fail((c), DDP_ERR_HIP, std::string(#expr) + ": " + hipGetErrorString(e_)); \
     } while (0)
 
-// Bytes of unused dynamic LDS per block that leave room for exactly
-// blocks_per_cu blocks on a compute unit, for long launches.
+// Resident blocks per compute unit for long launches (lds_for_blocks turns them into LDS per block).
 // A block keeps min(R, 8) x 2 loads per thread in flight, so with few
-// replicas many blocks are needed.  The first 101 BERT-large tensors, all marks in one call, us with no cap (five or six blocks by
-// registers) / four blocks / three / two / one: binary32 R = 2 215 / 218 / - / 252 / 326, R = 3 269 / 264 / 310 / 310 / 438,
-// R = 4 346 / 340 / 367 / 366 / 470, R = 5 431 / 423 / 442 / 442 / 574, R = 6 508 / 499 / 492 / 493 / 611, R = 8 662 / 651 / 622 / 622 /
-// 685; bfloat16 R = 2 99 / 99 / 141 / 141, R = 3 135 / 135 / 162 / 162, R = 8 331 / 329 / 307 / 307 / 399, R = 12 479 / 478 / 456 / 456 / 575,
-// R = 16 619 / 620 / 598 / 598 / 658.
+// replicas many blocks are needed.  The first 101 BERT-large tensors, all marks in one call, us with no cap (five blocks by
+// registers) / four blocks / three / two: binary32 R = 3 271 / 265 / 276 / 309, R = 4 345 / 339 / 334 / 368, R = 5 430 / 423 / 414 /
+// 442, R = 6 506 / 498 / 485 / 494, R = 8 663 / 652 / 634 / 623, R = 16 (60 tensors) 867 / 860 / 854 / 823; bfloat16 R = 3 132 / 132 / 138 / 163,
+// R = 4 166 / 167 / 166 / 202, R = 8 327 / 327 / 320 / 315, R = 12 475 / 476 / 468 / 451, R = 16 624 / 624 / 620 / 596.
+// (R = 2, no cap / four / two / one: binary32 215 / 218 / 252 / 326, bfloat16 99 / 99 / 141; R = 8 with one 685 and 399.)
 // For R >= 16 one block is about as good on lists of large tensors but 6 points worse on the ResNet-50 list in
 // fp16, whose many small tensors put slow boundary tiles on a unit that then
 // has nothing else to run -- so two it is, also with binary32 outputs next to 16-bit
 // inputs.
-// copies: the staged pass, which writes as much as it reads (60 BERT-large tensors, us, no cap / three blocks: binary32 R = 2 332 /
-// 337, R = 3 440 / 496, R = 4 551 / 540, R = 8 1002 / 1009; bfloat16 R = 2 170 / 181, R = 3 219 / 236, R = 4 278 / 264, R = 8 496 / 503).
+// copies: the staged pass, which writes as much as it reads (60 BERT-large tensors, us, no cap / three blocks / two: binary32 R = 2 332 /
+// - / 338, R = 3 440 / - / 496, R = 4 551 / 540 / 540, R = 8 1002 / - / 1009; bfloat16 R = 2 170 / - / 181, R = 3 219 / - / 236, R = 4 278 / 272 /
+// 264, R = 8 496 / - / 503).
 // Three replicas are read by a round of two and one of one, so that a block has fewer loads under way than with four.
 int32_t auto_blocks_per_cu(int32_t R, bool copies) {
-    if (copies) return R == 4 ? 3 : 0;
+    if (copies) return R == 4 ? 2 : 0;
     return R <= 2 ? 0 : R <= 5 ? 4 : 2;
 }
 
@@ -274,15 +274,14 @@ bool long_launch(const ddp_ctx* c, int64_t launch_bytes) {
 }
 
 unsigned lds_for_blocks(const ddp_ctx* c, int32_t blocks) {
-    if (blocks <= 0) return 0;
-    return static_cast<unsigned>((c->lds_per_cu / blocks) & ~int64_t(1023));
+    return static_cast<unsigned>(ddp::lds_for_blocks(c->lds_per_cu, blocks));
 }
 
-// Resident blocks of shorter launches (which take tiles): one mark per call, us, no cap / five blocks / three / two: BERT-large, R = 8,
-// 2034 / 2025 / 2034 / 2038, 240 MB in 8 MiB buckets, R = 12, 555 / 553 / 555 / 555, ResNet-50-sized, binary16, R = 16 369 /
-// 366 / 357 / 357; 120 MB, R = 4 230 / 230 / 249 / 249; all marks in one call, 16 MB, R = 8 25.1 / 25.1 / 25.6 / 25.7, R = 16 46.5 / 46.5 /
-// 45.7 / 45.7.
-int32_t short_launch_blocks(int32_t R) { return R <= 4 ? 0 : R < 16 ? 5 : 3; }
+// Resident blocks of shorter launches (which take tiles): one mark per call, us, no cap / four blocks / two: BERT-large, R = 8,
+// 2034 / 2025 / 2038, 240 MB in 8 MiB buckets, R = 12, 555 / 553 / 555, ResNet-50-sized, binary16, R = 16 369 /
+// 366 / 357; 120 MB, R = 4 230 / 230 / 249; all marks in one call, 16 MB, R = 8 25.1 / 25.0 / 25.5 (bfloat16 25.4 / 25.5 / 26.7), R = 16 46.5 / 46.5 /
+// 45.7.  Three blocks lie between four and two.
+int32_t short_launch_blocks(int32_t R) { return R <= 4 ? 0 : R < 16 ? 4 : 2; }
 
 unsigned occupancy_lds(const ddp_ctx* c, int64_t launch_bytes, bool copies) {
     if (c->blocks_per_cu >= 0) return long_launch(c, launch_bytes) ? lds_for_blocks(c, c->blocks_per_cu) : 0;

@@ -23,6 +23,22 @@ constexpr int SLICES = TILE_BYTES / SLICE_BYTES;
 // Threads that share the elements in vectors reaching over an end of a segment: at most 7 at each end.
 constexpr int EDGE_SLOTS = 16;
 
+// Dynamic LDS per block that leaves room for exactly `blocks` blocks on a compute unit with lds_per_cu bytes.  The hardware hands
+// LDS out in units of 1280 bytes: an allocation between two of them takes the next one up.  (Rounded down to KiB
+// instead, a third of 160 KiB left room for two blocks and a fifth for four.)
+constexpr int64_t LDS_UNIT = 1280;
+constexpr int64_t lds_for_blocks(int64_t lds_per_cu, int blocks) {
+    return blocks <= 0 ? 0 : lds_per_cu / blocks / LDS_UNIT * LDS_UNIT;
+}
+constexpr bool lds_holds_exactly(int64_t lds_per_cu, int blocks) {
+    const int64_t taken = (lds_for_blocks(lds_per_cu, blocks) + LDS_UNIT - 1) / LDS_UNIT * LDS_UNIT;
+    return taken * blocks <= lds_per_cu && taken * (blocks + 1) > lds_per_cu;
+}
+// (eight blocks of four waves fill a unit's wave slots)
+static_assert(lds_holds_exactly(160 * 1024, 1) && lds_holds_exactly(160 * 1024, 2) && lds_holds_exactly(160 * 1024, 3) &&
+              lds_holds_exactly(160 * 1024, 4) && lds_holds_exactly(160 * 1024, 5) && lds_holds_exactly(160 * 1024, 6) &&
+              lds_holds_exactly(160 * 1024, 7) && lds_holds_exactly(160 * 1024, 8), "a cap is the number of blocks it says");
+
 // Launches of up to this many tiles take slices (es: bytes of an element).  Fused, the kernel alone, us, tile per block / slices,
 // sixty tensors: binary32 R = 2, 128 tiles 4.0 / 4.1; R = 8, 128 4.8 / 4.6, 192 4.9 / 5.0, 256 6.0 / 6.8; R = 16, 128 6.7 / 6.6, 192 7.3 /
 // 7.3, 256 9.1 / 9.8; R = 32, 128 10.7 / 9.8, 192 11.8 / 11.6 (two tensors 10.2 / 10.9); R = 64, 128 18.1 / 17.4, 192 20.4 / 22.4; bfloat16 R = 4,
