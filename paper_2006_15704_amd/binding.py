@@ -164,6 +164,7 @@ def ddp_create(R: int, device: int, reduce_stream: int = 0, backward_stream: int
     _check(None, _lib.ddp_create(C.byref(handle), R, device, _vp(reduce_stream or None),
                                  _vp(backward_stream or None)))
     _replicas[handle.value] = int(R)
+    _nparams.pop(handle.value, None)
     return handle
 
 
@@ -319,12 +320,16 @@ def ddp_get_launch_log(ctx, which: int = 1):
 
 
 def ddp_no_sync_accumulate(ctx, micro_grad_ptrs: Sequence[Optional[int]]) -> None:
-    status = _fast_accumulate(_address(ctx), micro_grad_ptrs)
+    address = _address(ctx)
+    need = _replicas.get(address, 0) * _nparams.get(address, 0)      # the library reads that many pointers
+    status = _fast_accumulate(address, micro_grad_ptrs, need)
     if status is not None:
         if status < 0:
             _check(ctx, status)
         return
     arr = _ptr_array(micro_grad_ptrs)
+    if len(arr) < need:
+        raise ValueError(f"micro_grad_ptrs has {len(arr)} entries, expected R*n = {need}")
     _check(ctx, _lib.ddp_no_sync_accumulate(ctx, _as(arr, _vp)))
 
 

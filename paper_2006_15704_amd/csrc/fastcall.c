@@ -207,17 +207,23 @@ static PyObject* mark_ready_many(PyObject* self, PyObject* const* args, Py_ssize
     return PyLong_FromLong((long)status);
 }
 
-/* no_sync_accumulate(ctx_address, pointers) -> status or None, as above.
+/* no_sync_accumulate(ctx_address, pointers, need) -> status or None, as above; a list of fewer than `need` pointers, which the
+ * library would read, is left to the caller too.
  * (1170 pointers: 50 us a call through numpy and ctypes, 22 so.) */
 static PyObject* no_sync_accumulate(PyObject* self, PyObject* const* args, Py_ssize_t nargs) {
-    if (nargs != 2 || g_accumulate == NULL) {
-        PyErr_SetString(PyExc_TypeError, "no_sync_accumulate(ctx_address, pointers) after bind()");
+    if (nargs != 3 || g_accumulate == NULL) {
+        PyErr_SetString(PyExc_TypeError, "no_sync_accumulate(ctx_address, pointers, need) after bind()");
         return NULL;
     }
     Py_ssize_t n = 0;
+    const Py_ssize_t need = PyLong_AsSsize_t(args[2]);
+    if (need == -1 && PyErr_Occurred()) return NULL;
     if (!PyLong_CheckExact(args[0])) Py_RETURN_NONE;
     void** ptrs = (void**)plain_ints(args[1], 8, 1, &n);
-    if (ptrs == NULL) Py_RETURN_NONE;
+    if (ptrs == NULL || n < need) {
+        PyMem_RawFree(ptrs);
+        Py_RETURN_NONE;
+    }
     void* ctx = PyLong_AsVoidPtr(args[0]);
     int32_t status;
     Py_BEGIN_ALLOW_THREADS

@@ -59,6 +59,20 @@ def test_pointers():
     d.ddp_destroy(ctx)
 
 
+@pytest.mark.parametrize("form", [list, tuple, lambda v: np.array(v, dtype=np.uint64), lambda v: [np.uint64(x) for x in v], iter])
+def test_pointer_lists_of_other_lengths(form):
+    """A list with an entry too few is refused before the library reads past its end; further entries are not read."""
+    ctx = context(n=5, R=2)
+    for length in (0, 1, 5, 9):
+        with pytest.raises(ValueError):
+            d.ddp_no_sync_accumulate(ctx, form([256] * length))
+    for length in (10, 11):
+        with pytest.raises(d.DdpError) as e:
+            d.ddp_no_sync_accumulate(ctx, form([256] * length))
+        assert e.value.code == d.DDP_ERR_NO_DEVICE
+    d.ddp_destroy(ctx)
+
+
 def test_context_free_call():
     """What is refused before a device is touched."""
     big = 1 << 30
