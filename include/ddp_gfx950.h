@@ -257,7 +257,7 @@ int32_t ddp_set_option(ddp_ctx* ctx, int32_t option, int64_t value);
  * gives 1 if launches of the next iteration on a reduction stream would be
  * ordered through device flags (the option allows it, the buckets are built, every
  * reduction stream in use passed the concurrency probe, and not the staged
- * pipeline with DDP_OPT_TIMING 1), else 0.  Also reads DDP_STAT_REPAIRED_LAUNCHES below.  Unknown option ->
+ * pipeline with DDP_OPT_TIMING 1), else 0.  Also reads DDP_STAT_REPAIRED_LAUNCHES and DDP_STAT_EARLY_LAUNCHES below.  Unknown option ->
  * DDP_ERR_ARG. */
 int32_t ddp_get_option(ddp_ctx* ctx, int32_t option, int64_t* value);
 
@@ -266,6 +266,11 @@ int32_t ddp_get_option(ddp_ctx* ctx, int32_t option, int64_t* value);
  * the context's outstanding work first).  A number that keeps growing says that
  * DDP_OPT_GATE_WAIT_US is too short for this backward pass. */
 #define DDP_STAT_REPAIRED_LAUNCHES 100
+
+/* Read-only through ddp_get_option: the number of short bucket launches that stayed
+ * on backward_stream because the GPU was seen to wait for the host
+ * (DDP_OPT_REDUCE_STREAMS), since ddp_create.  Waits for nothing. */
+#define DDP_STAT_EARLY_LAUNCHES 101
 
 /* Algorithm 1, constructor loop over net.parameters(): registers n parameters
  * in registration order (index = position in net.parameters()).

@@ -166,6 +166,7 @@ struct ddp_ctx {
     std::chrono::steady_clock::time_point progress_since;
     int32_t early_credit = 0, late_looks = 0, early_launches = 0;
     int64_t early_bytes = 0;
+    int64_t early_total = 0;                      // launches placed since ddp_create
     uint64_t probe_value = 0;
     uint64_t call_seq = 0;                        // the number announced for the running API call
     bool call_by_flag = false;                    // the running API call orders its launches by flag
@@ -444,6 +445,7 @@ bool take_early(ddp_ctx* c, int64_t traffic) {
     c->early_bytes -= traffic;
     if (--c->early_credit == 0 || c->early_bytes < 0) c->early_credit = 0;
     ++c->early_launches;
+    ++c->early_total;
     return true;
 }
 
@@ -1006,6 +1008,7 @@ int32_t ddp_get_option(ddp_ctx* c, int32_t option, int64_t* value) {
             *value = n;
             return DDP_OK;
         }
+        case DDP_STAT_EARLY_LAUNCHES: *value = c->early_total; return DDP_OK;
         case DDP_OPT_PIPELINE: *value = c->pipeline; return DDP_OK;
         case DDP_OPT_WRITE_ALL: *value = c->write_all; return DDP_OK;
         case DDP_OPT_TIMING: *value = c->timing; return DDP_OK;

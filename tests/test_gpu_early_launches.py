@@ -38,6 +38,42 @@ def test_many_short_launches_marked_one_by_one(pipeline, delays_us):
                 assert grads.download(0, p).tobytes() == np.asarray(want[p]).tobytes(), f"iteration {it} parameter {p}"
 
 
+def iterations(options, n, delay_us, count):
+    """Launches placed early in `count` iterations of n buckets marked one by one, delay_us of backward work in front of each."""
+    import paper_2006_15704_amd as d
+    from paper_2006_15704_amd import harness
+    grads = harness.DeviceGrads([900] * n, [0] * n, 8, fill=0)
+    with harness.Session(grads, 3600, 1) as s:
+        for option, value in options(d):
+            d.ddp_set_option(s.ctx, option, value)
+        for _ in range(count):
+            for p in range(n - 1, -1, -1):
+                if delay_us:
+                    d.ddp_synth_backward(s.ctx, [p], [delay_us * 1000], mark=False)
+                d.ddp_mark_ready(s.ctx, p)
+            d.ddp_finalize_backward(s.ctx)
+            d.ddp_synchronize(s.ctx)
+        return d.ddp_get_option(s.ctx, d.DDP_STAT_EARLY_LAUNCHES), s.streams_concurrent
+
+
+def test_launches_stay_on_the_backward_stream_while_the_gpu_waits():
+    early, by_flags = iterations(lambda d: [], 90, 0, 20)
+    if not by_flags:
+        pytest.skip("no stream runs next to the backward stream here")
+    assert early >= 20 * 90 // 4          # (a slow host misses some)
+
+
+def test_launches_leave_the_backward_stream_while_it_is_busy():
+    early, _ = iterations(lambda d: [], 60, 200, 4)
+    assert early <= 4 * 60 // 4           # (a host that was held up for 200 us finds the stream idle)
+
+
+@pytest.mark.parametrize("options", [lambda d: [(d.DDP_OPT_TAIL_ON_BACKWARD, 0)], lambda d: [(d.DDP_OPT_REDUCE_STREAMS, 2)],
+                                     lambda d: [(d.DDP_OPT_FLAG_ORDER, 0)]])
+def test_no_early_launches_where_the_caller_chose_streams_or_events(options):
+    assert iterations(options, 60, 0, 3)[0] == 0
+
+
 @pytest.mark.parametrize("pipeline", [0, 1])
 def test_many_short_launches_without_a_backward_pass(pipeline):
     import torch
