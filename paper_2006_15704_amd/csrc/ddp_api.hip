@@ -530,16 +530,19 @@ int32_t launch_range(ddp_ctx* c, int32_t first, int32_t last, Target target) {
     hipStream_t st = c->backward;
     const bool may_be_early = target == Target::kLane && c->n_streams < 0 && c->tail_on_backward != 0 && traffic <= kEarlyTraffic &&
                               flags_usable(c);
+    bool early = false;
     if (target == Target::kLane && c->n_streams < 0 && c->tail_on_backward != 0 && c->small_model) {
         // stays on the backward stream
     } else if (may_be_early && take_early(c, traffic)) {
-        // ... and so does this launch
+        early = true;                 // ... and so does this launch
     } else if (target == Target::kLane) {
         // Short launches gain from a neighbour on a second stream (start-up and drain of one
         // overlap with the other); launches long enough for the cap on resident blocks lose
         // when two of them share the memory system, so by default those stay on one stream.
         const int lanes = c->n_streams < 0 ? (!long_launch(c, bytes) && c->lane[1] && c->lane_concurrent[1] ? 2 : 1) : c->n_streams;
         lane = static_cast<int>(c->launches_in_iter++ % lanes);
+        // (short launches next to this one would take long to run: they look again first)
+        if (traffic >= kChainMinTraffic) c->early_credit = 0;
     } else if (target == Target::kPartner) {
         lane = 0;
     }
@@ -569,11 +572,12 @@ int32_t launch_range(ddp_ctx* c, int32_t first, int32_t last, Target target) {
     // chained, they lose 1.5 to 3 points against one stream (R = 16 and 32, binary32
     // outputs).  A launch on the backward stream is chained whenever it moves 160 MiB itself:
     // with back-to-back iterations it would otherwise run next to the iteration's first
-    // launches for all of its time.
+    // launches for all of its time.  An early launch never is: what comes behind it on the backward stream
+    // is the rest of the backward pass, which would wait for the launch in front of it too.
     const bool flags_in_use = c->call_by_flag || c->gates_in_iter > 0;
     const bool both_long = c->prev_launch_long && long_launch(c, bytes);
     const bool chained = c->chain_launches != 0 && flags_in_use && c->prev_launch_ord != 0 && c->prev_launch_lane != lane &&
-                         ntiles > 0 && carries_gate(c) &&
+                         ntiles > 0 && carries_gate(c) && !early &&
                          ((c->prev_launch_traffic >= kChainMinTraffic && !both_long) ||
                           (lane < 0 && traffic >= kChainMinTraffic));
     const long long wait_ticks = c->gate_wait_us * c->wall_clock_khz / 1000;

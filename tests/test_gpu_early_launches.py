@@ -75,6 +75,40 @@ def test_no_early_launches_where_the_caller_chose_streams_or_events(options):
 
 
 @pytest.mark.parametrize("pipeline", [0, 1])
+def test_the_backward_stream_is_not_held_behind_a_long_launch(pipeline):
+    """Short launches, one of more than 160 MiB that is stuck on a busy reduction stream, short launches: the backward
+    stream gets past the latter while the long one has yet to start."""
+    import torch
+    import paper_2006_15704_amd as d
+    from paper_2006_15704_amd import harness
+    R, cap = 2, 4096
+    numel = [1000] * 5 + [15 << 20] + [1000] * 4                    # (R + 1) x 60 MiB
+    n = len(numel)
+    grads = harness.DeviceGrads(numel, [0] * n, R, fill=0)
+    marker = harness.DeviceGrads([16], [0], R, fill=0)
+    with harness.Session(grads, cap, pipeline) as s, \
+            harness.Session(marker, cap, 1, streams=(s.backward_stream, s.reduce_stream)) as delay:
+        if not s.streams_concurrent:
+            pytest.skip("no stream runs next to the backward stream here")
+        d.ddp_set_option(s.ctx, d.DDP_OPT_REDUCE_CAP_MIN_BYTES, 160 << 20)      # so that it takes the caller's reduction stream
+        for it in range(6):
+            free, past = torch.cuda.Event(), torch.cuda.Event()
+            d.ddp_synth_backward(delay.ctx, [0], [60_000_000], mark=False)      # the reduction stream is busy for 60 ms
+            free.record(s.reduce_stream)
+            for p in range(n - 1, 0, -1):
+                d.ddp_mark_ready(s.ctx, p)
+            past.record(s.backward_stream)
+            past.synchronize()
+            held = free.query()
+            d.ddp_mark_ready(s.ctx, 0)
+            d.ddp_finalize_backward(s.ctx)
+            d.ddp_synchronize(s.ctx)
+            d.ddp_synchronize(delay.ctx)
+            assert not held, f"iteration {it}"
+        assert d.ddp_get_option(s.ctx, d.DDP_STAT_EARLY_LAUNCHES) > 0
+
+
+@pytest.mark.parametrize("pipeline", [0, 1])
 def test_many_short_launches_without_a_backward_pass(pipeline):
     import torch
     import paper_2006_15704_amd as d
