@@ -416,23 +416,28 @@ bool flags_usable(const ddp_ctx* c) {
 // the backward stream, kEarlyLaunches of them that move kEarlyBytes (50 us of the GPU) at most; then one is announced again.  A
 // stream that is busy with the backward pass does not get there in time, and after kLateLooks announcements (and one for
 // every four launches placed) that came late no more are shown.
-// One mark per call, us a synchronization, without / with (a process has faster launches or slower ones): ResNet-50 in 1 MiB buckets, binary16, R = 16,
-// 374 to 480 / 285 to 330; 19 MB in 62 buckets, binary32, R = 24, 434 to 566 / 283 to 315; 40 MB in 13, bfloat16, R = 4, 118 to 126 / 84; 23 MB in 5, R = 8,
-// 102 to 112 / 76; every replica written, 17 MB in 12, R = 8, 176 / 113.  Exposed under 10 us of backward work a parameter, ResNet-50 in 1 MiB
-// buckets, fused 96 to 119 / 93 to 126, staged 139 / 135 to 158 (with the bucket's mark in place of kPromptUs, which lets the GPU be up to a bucket
-// behind, 125 / 182 and 155 / 235).
+// One mark per call, us a synchronization, without / with (several processes, whose launches take the host more or less time): ResNet-50
+// in 1 MiB buckets, binary16, R = 16, 404 to 503 / 283 to 343; 19 MB in 62 buckets, binary32, R = 24, 470 to 589 / 317 to 319; 40 MB in 13,
+// bfloat16, R = 4, 100 to 135 / 86 to 94; 23 MB in 5, R = 8, 89 to 115 / 78 to 85; every replica written, 17 MB in 12, R = 8, 187 to 193 / 116
+// to 123; 90 buckets of 900 elements with participation masks, R = 8, 1090 to 1500 / 670 to 880.  Exposed under 10 us of backward work a parameter,
+// ResNet-50 in 1 MiB buckets, fused 96 to 122 / 94 to 134, staged 152 to 163 / 143 to 164 (with the bucket's mark in place of kPromptUs,
+// which lets the GPU be up to a bucket behind, 125 / 182 and 155 / 235).
 constexpr int64_t kEarlyTraffic = int64_t(64) << 20, kEarlyBytes = int64_t(256) << 20;
-constexpr int32_t kEarlyLaunches = 16, kLateLooks = 2, kPromptUs = 8;
+constexpr int32_t kEarlyLaunches = 16, kLateLooks = 3, kPromptUs = 8;
 
+// The host looks behind every launch of its own.  A number that is there within kPromptUs came in time, one
+// that is not there after kPromptUs comes late; one that is there by then but was last looked for before says
+// nothing of the stream, only that the host took long, and counts as neither.
 void look_at_progress(ddp_ctx* c) {
     if (c->progress_wait == 0) return;
-    const bool reached = __atomic_load_n(c->h_progress, __ATOMIC_RELAXED) >= c->progress_wait;
+    // (the clock first: what is not there yet a little later was not there then)
     const bool late = std::chrono::steady_clock::now() - c->progress_since > std::chrono::microseconds(kPromptUs);
+    const bool reached = __atomic_load_n(c->h_progress, __ATOMIC_RELAXED) >= c->progress_wait;
     if (!reached && !late) return;
     c->progress_wait = 0;
-    if (late) {
+    if (!reached) {
         ++c->late_looks;
-    } else {
+    } else if (!late) {
         c->early_credit = kEarlyLaunches;
         c->early_bytes = kEarlyBytes;
     }
@@ -441,9 +446,10 @@ void look_at_progress(ddp_ctx* c) {
 // Whether the launch at hand goes to the backward stream on the strength of the last look.
 bool take_early(ddp_ctx* c, int64_t traffic) {
     look_at_progress(c);
+    if (c->early_credit != 0 && traffic > c->early_bytes) c->early_credit = 0;
     if (c->early_credit == 0) return false;
     c->early_bytes -= traffic;
-    if (--c->early_credit == 0 || c->early_bytes < 0) c->early_credit = 0;
+    --c->early_credit;
     ++c->early_launches;
     ++c->early_total;
     return true;
@@ -470,7 +476,7 @@ int32_t order_call(ddp_ctx* c, int32_t first, bool look) {
             // a one-block kernel instead of an event record (which stalls the stream
             // for about 12 us here)
             c->call_seq = ++c->seq_issued;
-            const bool show = look && c->late_looks <= kLateLooks + c->early_launches / 4;
+            const bool show = look && c->late_looks < kLateLooks + c->early_launches / 4;
             HIPCHK(c, ddp::launch_announce(c->d_order, c->call_seq, show ? c->h_progress : nullptr, c->backward));
             if (show) {
                 c->progress_wait = c->call_seq;
@@ -602,6 +608,7 @@ int32_t launch_range(ddp_ctx* c, int32_t first, int32_t last, Target target) {
                                        chained ? c->prev_launch_ord : 0ull, chained ? wait_ticks : 0, st));
             gate = rec;
             ++c->gates_in_iter;
+            look_at_progress(c);
         } else if (!c->backward_idle_in_call) {
             HIPCHK(c, hipStreamWaitEvent(st, c->call_event, 0));
         }
@@ -631,6 +638,7 @@ int32_t launch_range(ddp_ctx* c, int32_t first, int32_t last, Target target) {
         HIPCHK(c, ddp::launch_mask_write(c->d_local + seg_begin, masks, seg_end - seg_begin,
                                          gate, static_cast<uint32_t>(c->iteration + 1), st));
         d_flags = c->d_local;
+        look_at_progress(c);
     }
     const ddp::Scale sc = make_scale(c->R);
     size_t slot;
@@ -655,6 +663,7 @@ int32_t launch_range(ddp_ctx* c, int32_t first, int32_t last, Target target) {
         if ((rc = timed_begin(c, DDP_K_PACK, id, st, &slot)) != DDP_OK) return rc;
         HIPCHK(c, ddp::launch_pack(c->tables, tile_base, ntiles, c->slabs, c->slab_stride, c->R,
                                    d_flags, gate, tag, st));
+        look_at_progress(c);
         if ((rc = timed_end(c, slot, st)) != DDP_OK) return rc;
         if ((rc = timed_begin(c, DDP_K_REDUCE, id, st, &slot)) != DDP_OK) return rc;
         HIPCHK(c, ddp::launch_flat_reduce(bf.dtype, in0, c->slab_stride, out, nvec, c->R, sc,

@@ -38,8 +38,9 @@ def test_many_short_launches_marked_one_by_one(pipeline, delays_us):
                 assert grads.download(0, p).tobytes() == np.asarray(want[p]).tobytes(), f"iteration {it} parameter {p}"
 
 
-def iterations(options, n, delay_us, count):
-    """Launches placed early in `count` iterations of n buckets marked one by one, delay_us of backward work in front of each."""
+def iterations(options, n, delay_us, count, flags=None):
+    """Launches placed early in `count` iterations of n buckets marked one by one, delay_us of backward work in front of each;
+    flags: which of the eight replicas took part."""
     import paper_2006_15704_amd as d
     from paper_2006_15704_amd import harness
     grads = harness.DeviceGrads([900] * n, [0] * n, 8, fill=0)
@@ -50,14 +51,18 @@ def iterations(options, n, delay_us, count):
             for p in range(n - 1, -1, -1):
                 if delay_us:
                     d.ddp_synth_backward(s.ctx, [p], [delay_us * 1000], mark=False)
-                d.ddp_mark_ready(s.ctx, p)
+                if flags is None:
+                    d.ddp_mark_ready(s.ctx, p)
+                else:
+                    d.ddp_mark_ready_local(s.ctx, p, flags)
             d.ddp_finalize_backward(s.ctx)
             d.ddp_synchronize(s.ctx)
         return d.ddp_get_option(s.ctx, d.DDP_STAT_EARLY_LAUNCHES), s.streams_concurrent
 
 
-def test_launches_stay_on_the_backward_stream_while_the_gpu_waits():
-    early, by_flags = iterations(lambda d: [], 90, 0, 20)
+@pytest.mark.parametrize("flags", [None, [1, 1, 1, 0, 1, 1, 1, 1]])      # (with masks the host makes a launch more a bucket)
+def test_launches_stay_on_the_backward_stream_while_the_gpu_waits(flags):
+    early, by_flags = iterations(lambda d: [], 90, 0, 20, flags)
     if not by_flags:
         pytest.skip("no stream runs next to the backward stream here")
     assert early >= 20 * 90 // 4          # (a slow host misses some)
