@@ -139,13 +139,16 @@ typedef struct ddp_ctx ddp_ctx;
                                      streams at the DRAM channels and throughput drops.  0 = no cap
                                      (wave slots decide: 8).  Default -1 =
                                      chosen from R: no cap up to R = 2 (few loads per block), 4 up to
-                                     R = 5, else 2, and in launches below DDP_OPT_REDUCE_CAP_MIN_BYTES 4
-                                     from R = 5 on and 2 from R = 16 on; staged pipeline (its
+                                     R = 5, else 2, and in launches below DDP_OPT_REDUCE_CAP_MIN_BYTES, unless
+                                     that was set, 4 from R = 5 on and 2 from R = 16 on; staged pipeline (its
                                      launches write as much as they read): 2 for R = 4, else none */
-#define DDP_OPT_REDUCE_CAP_MIN_BYTES 14 /* any time: the cap applies to launches that move at least this
+#define DDP_OPT_REDUCE_CAP_MIN_BYTES 14 /* any time: launches that move at least this
                                      many bytes, counted as (R + 1) x the launch's bucket bytes in
-                                     both pipelines (measured at R = 8: it gains 1 to 2.5 points of
-                                     HBM peak from 50 MiB of bucket data up and loses 1.5 to 3 on
+                                     both pipelines, are long ones: a cap set with
+                                     DDP_OPT_REDUCE_BLOCKS_PER_CU applies to them only, and so does the cap
+                                     chosen from R once this option has been set (left at its default,
+                                     shorter launches are capped too, at more blocks; measured at R = 8: two blocks gain 1 to 2.5 points of
+                                     HBM peak from 50 MiB of bucket data up and lose 1.5 to 3 on
                                      launches of 25 MiB and less; at R = 16 and 32 a 25 MiB bucket is already a long
                                      launch and gains 2.5 points).  Default 360 MiB (40 MiB of bucket
                                      data at R = 8) */

@@ -65,6 +65,7 @@ struct ddp_ctx {
     int32_t blocks_per_cu = -1;                   // reduce kernels: resident blocks per compute unit (0 = no cap,
                                                   // -1 = chosen from R, see auto_blocks_per_cu)
     int64_t cap_min_traffic = int64_t(360) << 20; // ... applied to launches that move at least this many bytes
+    bool cap_min_set = false;                     // ... by the caller's choice: shorter launches have no cap then
     int32_t acc_blocks_per_cu = 4;                // accumulate kernel: likewise
     int64_t lds_per_cu = 160 * 1024;              // read from the device at creation
 
@@ -287,7 +288,7 @@ int32_t short_launch_blocks(int32_t R) { return R <= 4 ? 0 : R < 16 ? 4 : 2; }
 unsigned occupancy_lds(const ddp_ctx* c, int64_t launch_bytes, bool copies) {
     if (c->blocks_per_cu >= 0) return long_launch(c, launch_bytes) ? lds_for_blocks(c, c->blocks_per_cu) : 0;
     if (long_launch(c, launch_bytes)) return lds_for_blocks(c, auto_blocks_per_cu(c->R, copies));
-    return copies ? 0 : lds_for_blocks(c, short_launch_blocks(c->R));
+    return copies || c->cap_min_set ? 0 : lds_for_blocks(c, short_launch_blocks(c->R));
 }
 
 using ddp::make_scale;
@@ -958,6 +959,7 @@ int32_t ddp_set_option(ddp_ctx* c, int32_t option, int64_t value) {
         case DDP_OPT_REDUCE_CAP_MIN_BYTES:
             if (value < 0) return fail(c, DDP_ERR_ARG, "bad size");
             c->cap_min_traffic = value;
+            c->cap_min_set = true;
             return DDP_OK;
         case DDP_OPT_TAIL_ON_BACKWARD:
             c->tail_on_backward = value != 0;
