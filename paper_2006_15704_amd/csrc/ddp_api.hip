@@ -103,13 +103,17 @@ struct ddp_ctx {
     bool masks_in_flight[2] = {false, false};    // kernels of an earlier iteration may still read h_masks
     int64_t masks_claimed_iter = -1;             // iteration for which h_masks was waited for
     void** d_micro = nullptr;                // [R * n, rounded up to an even number]
-    // Pinned: kMicroSlots tables of micro-step pointers, used in turn, and behind them the ordinal of the latest
-    // table that the device has read (written by pointer_copy_kernel).
-    static constexpr int kMicroSlots = 4;
+    // Pinned: micro_slots tables of micro-step pointers, used in turn, and behind them the ordinal of the latest
+    // table that the device has read (written by pointer_copy_kernel).  Two keep the device busy: the host fills one while
+    // the other has yet to be read (four micro-steps and the reduction, R = 2, four tensors, 37 us with one, 31.0 with
+    // two, 31.6 with four; R = 32, 1600 tensors 1887 / 1876 / 1873; R = 64, 8000 tensors 19.5 ms with any).  Tables of at most
+    // kSmallMicroTable bytes are four, so that the host of a short step is not held up by one that ran late.
+    static constexpr size_t kSmallMicroTable = 64 * 1024;
+    int micro_slots = 2;
     void** h_micro = nullptr;
     int64_t micro_table = 0;                 // pointers of one table
     unsigned long long micro_ticket = 0;     // ordinal of the latest call's table
-    unsigned long long* micro_done() const { return reinterpret_cast<unsigned long long*>(h_micro + kMicroSlots * micro_table); }
+    unsigned long long* micro_done() const { return reinterpret_cast<unsigned long long*>(h_micro + micro_slots * micro_table); }
     void** d_emit = nullptr;
     void** h_emit = nullptr;                 // pinned
     int64_t emit_cap = 0;                    // pointers
@@ -1173,9 +1177,11 @@ static int32_t build_internal(ddp_ctx* c, uint64_t cap_bytes, const std::vector<
                 HIPCHK(c, hipHostMalloc(reinterpret_cast<void**>(&m), sizeof(uint64_t) * n, hipHostMallocDefault));
         c->micro_table = round_up(R * n, 2);
         const size_t micro_bytes = sizeof(void*) * static_cast<size_t>(c->micro_table);
+        c->micro_slots = micro_bytes <= ddp_ctx::kSmallMicroTable ? 4 : 2;
+        const size_t pinned_bytes = micro_bytes * static_cast<size_t>(c->micro_slots) + sizeof(unsigned long long);
         HIPCHK(c, hipMalloc(reinterpret_cast<void**>(&c->d_micro), micro_bytes));
-        HIPCHK(c, hipHostMalloc(reinterpret_cast<void**>(&c->h_micro), micro_bytes * ddp_ctx::kMicroSlots + sizeof(unsigned long long), hipHostMallocDefault));
-        std::memset(c->h_micro, 0, micro_bytes * ddp_ctx::kMicroSlots + sizeof(unsigned long long));
+        HIPCHK(c, hipHostMalloc(reinterpret_cast<void**>(&c->h_micro), pinned_bytes, hipHostMallocDefault));
+        std::memset(c->h_micro, 0, pinned_bytes);
         c->micro_ticket = 0;
         HIPCHK(c, hipMalloc(reinterpret_cast<void**>(&c->d_gate), sizeof(ddp::GateRecord) * (nb + 1) * ddp_ctx::kGateRows));
         HIPCHK(c, hipMemset(c->d_gate, 0, sizeof(ddp::GateRecord) * (nb + 1) * ddp_ctx::kGateRows));
@@ -1518,12 +1524,12 @@ int32_t ddp_get_launch_log(const ddp_ctx* c, int32_t which, int32_t* bucket_ids,
     return DDP_OK;
 }
 
-// The table that the next micro-step will use was last used kMicroSlots calls ago: the device must have read it.
+// The table that the next micro-step will use was last used micro_slots calls ago: the device must have read it.
 // (A word in pinned memory that the copying kernel writes instead of an event: that costs the stream a packet with a
 // signal and the host 4 us a record.)  A bounded look, then the stream is waited for.
 static int32_t await_micro_slot(ddp_ctx* c) {
-    if (c->micro_ticket < ddp_ctx::kMicroSlots) return DDP_OK;
-    const unsigned long long need = c->micro_ticket + 1 - ddp_ctx::kMicroSlots;
+    if (c->micro_ticket < static_cast<unsigned long long>(c->micro_slots)) return DDP_OK;
+    const unsigned long long need = c->micro_ticket + 1 - static_cast<unsigned long long>(c->micro_slots);
     const auto until = std::chrono::steady_clock::now() + std::chrono::milliseconds(100);
     while (__atomic_load_n(c->micro_done(), __ATOMIC_ACQUIRE) < need)
         if (std::chrono::steady_clock::now() >= until) {
@@ -1551,7 +1557,7 @@ int32_t ddp_no_sync_accumulate(ddp_ctx* c, void* const* micro) {
                 return fail(c, DDP_ERR_ARG, "ddp_no_sync_accumulate: pointer not aligned to its element size");
         }
     HIPCHK(c, hipSetDevice(c->device));
-    void** const table = c->h_micro + static_cast<int64_t>((c->micro_ticket + 1) % ddp_ctx::kMicroSlots) * c->micro_table;
+    void** const table = c->h_micro + static_cast<int64_t>((c->micro_ticket + 1) % static_cast<unsigned long long>(c->micro_slots)) * c->micro_table;
     {
         const int32_t rcw = await_micro_slot(c);
         if (rcw != DDP_OK) return rcw;

@@ -7,7 +7,7 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("R,n", [(1, 1), (3, 5), (64, 33)])
+@pytest.mark.parametrize("R,n", [(1, 1), (3, 5), (64, 33), (64, 140)])      # (the last: two tables instead of four)
 @pytest.mark.parametrize("delay_us", [0, 300])
 def test_tables_of_many_micro_steps(R, n, delay_us):
     import torch
