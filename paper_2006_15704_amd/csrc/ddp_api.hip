@@ -210,8 +210,14 @@ int32_t fail(ddp_ctx* c, int32_t code, const std::string& msg) {
 // - / 338, R = 3 440 / - / 496, R = 4 551 / 540 / 540, R = 8 1002 / - / 1009; bfloat16 R = 2 170 / - / 181, R = 3 219 / - / 236, R = 4 278 / 272 /
 // 264, R = 8 496 / - / 503).
 // Three replicas are read by a round of two and one of one, so that a block has fewer loads under way than with four.
-int32_t auto_blocks_per_cu(int32_t R, bool copies) {
+// write_all: every replica is written, too, and few replicas do best with few blocks (one launch of 900 MiB, us, no cap / four blocks / three /
+// two: binary32 R = 2 201 / 197 / 199 / 216, R = 3 238 / 236 / 226 / 227, R = 4 263 / 266 / 262 / 247, R = 5 276 / 279 / 276 / 262, R = 8 300 / 302 /
+// 305 / 306, R = 12 319 / 319 / 319 / 325, R = 16 330 / 329 / 328 / 337; bfloat16 R = 2 199 / 199 / 201 / 235, R = 3 241 / 241 / 228 / 233, R = 4 261 /
+// 260 / 259 / 251, R = 5 278 / 278 / 281 / 264, R = 8 296 / 296 / 299 / 295, R = 12 321 / 321 / 325 / 324, R = 16 331 / 331 / 332 / 338; sixty
+// BERT-large tensors, binary32 R = 4 412 / 418 / 412 / 385, R = 8 849 / 852 / 835 / 851, bfloat16 R = 8 420 / 421 / 426 / 415).
+int32_t auto_blocks_per_cu(int32_t R, bool copies, bool write_all) {
     if (copies) return R == 4 ? 2 : 0;
+    if (write_all) return R >= 3 && R < 12 ? 2 : 0;
     return R <= 2 ? 0 : R <= 5 ? 4 : 2;
 }
 
@@ -291,7 +297,7 @@ int32_t short_launch_blocks(int32_t R) { return R <= 4 ? 0 : R < 16 ? 4 : 2; }
 
 unsigned occupancy_lds(const ddp_ctx* c, int64_t launch_bytes, bool copies) {
     if (c->blocks_per_cu >= 0) return long_launch(c, launch_bytes) ? lds_for_blocks(c, c->blocks_per_cu) : 0;
-    if (long_launch(c, launch_bytes)) return lds_for_blocks(c, auto_blocks_per_cu(c->R, copies));
+    if (long_launch(c, launch_bytes)) return lds_for_blocks(c, auto_blocks_per_cu(c->R, copies, c->write_all));
     return copies || c->cap_min_set ? 0 : lds_for_blocks(c, short_launch_blocks(c->R));
 }
 
