@@ -142,7 +142,8 @@ typedef struct ddp_ctx ddp_ctx;
                                      R = 5, else 2, and in launches below DDP_OPT_REDUCE_CAP_MIN_BYTES, unless
                                      that was set, 4 from R = 5 on and 2 from R = 16 on; staged pipeline (its
                                      launches write as much as they read): 2 for R = 4, else none;
-                                     DDP_OPT_WRITE_ALL: 2 for R = 3 to 11, else none, in long launches */
+                                     DDP_OPT_WRITE_ALL: none in long launches for R <= 2 and
+                                     R = 12 to 15, else 2 */
 #define DDP_OPT_REDUCE_CAP_MIN_BYTES 14 /* any time: launches that move at least this
                                      many bytes, counted as (R + 1) x the launch's bucket bytes in
                                      both pipelines, are long ones: a cap set with

@@ -214,10 +214,12 @@ int32_t fail(ddp_ctx* c, int32_t code, const std::string& msg) {
 // two: binary32 R = 2 201 / 197 / 199 / 216, R = 3 238 / 236 / 226 / 227, R = 4 263 / 266 / 262 / 247, R = 5 276 / 279 / 276 / 262, R = 8 300 / 302 /
 // 305 / 306, R = 12 319 / 319 / 319 / 325, R = 16 330 / 329 / 328 / 337; bfloat16 R = 2 199 / 199 / 201 / 235, R = 3 241 / 241 / 228 / 233, R = 4 261 /
 // 260 / 259 / 251, R = 5 278 / 278 / 281 / 264, R = 8 296 / 296 / 299 / 295, R = 12 321 / 321 / 325 / 324, R = 16 331 / 331 / 332 / 338; sixty
-// BERT-large tensors, binary32 R = 4 412 / 418 / 412 / 385, R = 8 849 / 852 / 835 / 851, bfloat16 R = 8 420 / 421 / 426 / 415).
+// BERT-large tensors, binary32 R = 4 412 / 418 / 412 / 385, R = 8 849 / 852 / 835 / 851, R = 10 1067 / 1093 / 1063 / 1049, R = 12 1301 / 1314 / 1307 / 1294,
+// R = 16 1756 / 1760 / 1748 / 1748, R = 32 3623 / 3627 / 3609 / 3528; bfloat16 R = 8 420 / 421 / 426 / 415, R = 10 530 / 530 / 535 / 524, R = 12 647 / 647 / 656 /
+// 647, R = 14 755 / 755 / 762 / 766, R = 16 870 / 871 / 876 / 886, R = 32 1812 / 1810 / 1807 / 1786).
 int32_t auto_blocks_per_cu(int32_t R, bool copies, bool write_all) {
     if (copies) return R == 4 ? 2 : 0;
-    if (write_all) return R >= 3 && R < 12 ? 2 : 0;
+    if (write_all) return R <= 2 || (R >= 12 && R < 16) ? 0 : 2;
     return R <= 2 ? 0 : R <= 5 ? 4 : 2;
 }
 

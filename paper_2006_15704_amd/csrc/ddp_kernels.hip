@@ -630,7 +630,8 @@ __device__ __forceinline__ EdgeElements edge_elements(int64_t e0, int span, int6
 // registers: the first 101 BERT-large tensors with masks compiled in / left out, binary16,
 // R = 16, one mark per call 681 / 677 us a synchronization; bfloat16, R = 8, 329 / 327, and with
 // the averages to every replica 627.5 / 626.5.
-template <int DT, bool NT, int U, int OUT, bool MASKED>
+// FORM: see table_form.
+template <int DT, bool NT, int U, int OUT, bool MASKED, int FORM = 0>
 __device__ __forceinline__ void fused_tile(const SegTables& t, int64_t tile, int R, int nwrite,
                                            const uint64_t* __restrict__ local, int keep_unused,
                                            const Scale& sc, const FlatBuckets& flat,
@@ -653,13 +654,14 @@ __device__ __forceinline__ void fused_tile(const SegTables& t, int64_t tile, int
     // R = 4 338 / 352 / 350, R = 8 617 / 617 / 631, R = 16 (60 tensors) 852 / 866 / 864; bfloat16 R = 2 112 / 102 / 98, R = 3 146 / 132 / 134, R = 4
     // 165 / 167 / 176, R = 8 319 / 314 / 306, R = 12 451 / 450 / 453, R = 16 590 / 594 / 597; binary32 averages of BERT-large 1144 / 1138 /
     // 1126; staged (pointers plain in every case: chunk_copy) binary32 R = 4 540 / - / 529, R = 2 332 / - / 336, bfloat16 R = 2 170 / - / 174.
-    const int g = OUT == OUT_BINARY32 ? cload(t.tile_seg + tile) : t.tile_seg[tile];
+    constexpr bool PLAIN = ES == 4 || FORM == 2 || (OUT == OUT_BINARY32 && FORM == 1);
+    const int g = OUT == OUT_BINARY32 && !PLAIN ? cload(t.tile_seg + tile) : t.tile_seg[tile];
     const PointerRow row = pointer_row(t.grad, g, t.R);
-    const SegInfo si = ES == 2 ? segment(t, g) : t.seg[g];
+    const SegInfo si = PLAIN ? t.seg[g] : segment(t, g);
     const char* pre[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i)
-        pre[i] = ES == 2 ? row[i] : static_cast<const char*>(t.grad[static_cast<int64_t>(g) * t.R + i]);
+        pre[i] = PLAIN ? static_cast<const char*>(t.grad[static_cast<int64_t>(g) * t.R + i]) : row[i];
     // (behind a gate that gave up this row may be an earlier iteration's: it is not looked at then)
     const uint64_t mask = MASKED && local != nullptr ? cload(local + g) : 0;
     if (gate_word == tag) return;          // the gate in front of this launch gave up
@@ -691,7 +693,7 @@ __device__ __forceinline__ void fused_tile(const SegTables& t, int64_t tile, int
         for (int u = 0; u < U; ++u) {
             lane_off[u] = (u * BLOCK + threadIdx.x) * 16u;
             // (kept as they are, so that the second vector's loads take the base + offset form too, not 64-bit additions)
-            if (OUT != OUT_FLAT) asm volatile("" : "+v"(lane_off[u]));
+            if (OUT == OUT_BINARY32 || (OUT == OUT_GRAD && FORM != 1)) asm volatile("" : "+v"(lane_off[u]));
         }
         if constexpr (OUT == OUT_FLAT) {
 #pragma unroll
@@ -712,7 +714,9 @@ __device__ __forceinline__ void fused_tile(const SegTables& t, int64_t tile, int
         }
         if (all_used)
             sum_interior_pre<DT, NT, U>(
-                pre, byte0, [&](int r) { return row[r] + byte0; }, R, lane_off, acc);
+                pre, byte0, [&](int r) {
+                    return (FORM == 2 ? static_cast<const char*>(t.grad[static_cast<int64_t>(g) * t.R + r]) : row[r]) + byte0;
+                }, R, lane_off, acc);
         else if constexpr (MASKED)
             sum_interior_used<DT, NT, U>(row, byte0, used, lane_off, acc);
 #pragma unroll
@@ -828,7 +832,7 @@ __device__ __forceinline__ void fused_tile(const SegTables& t, int64_t tile, int
     }
 }
 
-template <int DT, bool NT, int U, int OUT, bool MASKED>
+template <int DT, bool NT, int U, int OUT, bool MASKED, int FORM = 0>
 __global__ __launch_bounds__(BLOCK) void fused_reduce_kernel(SegTables t, int64_t tile_base, int R,
                                                              int nwrite,
                                                              const uint64_t* __restrict__ local,
@@ -836,7 +840,7 @@ __global__ __launch_bounds__(BLOCK) void fused_reduce_kernel(SegTables t, int64_
                                                              const GateRecord* __restrict__ gate,
                                                              uint32_t tag, DispatchSignal sig) {
     signal_dispatch(sig);
-    fused_tile<DT, NT, U, OUT, MASKED>(t, tile_base + blockIdx.x, R, nwrite, local, keep_unused, sc, flat, gate, tag);
+    fused_tile<DT, NT, U, OUT, MASKED, FORM>(t, tile_base + blockIdx.x, R, nwrite, local, keep_unused, sc, flat, gate, tag);
 }
 
 // A short launch.  It has fewer blocks than fill the chip and runs as long as one of them, whose time is the
@@ -1420,6 +1424,28 @@ hipError_t launch_flat_reduce(int dtype, const char* in0, int64_t stride, char* 
 // What the ends of segments take (fused_tile).
 static unsigned edge_lds(int R) { return static_cast<unsigned>(R * EDGE_SLOTS * sizeof(uint32_t)); }
 
+// How a launch of tiles without masks reads its tables (FORM of fused_tile), which decides when a block's loads go out: whether a
+// block's first pointers, its segment and its tile's entry come by scalar or by plain loads, and likewise the pointers of
+// replicas 8 and up; and whether the lanes' offsets are kept for the base + offset form.  Long launches are a few percent
+// faster with one or the other, see fused_tile, and no form is the best for every R; sixty BERT-large tensors unless noted, us.
+// 2: everything plain, from two full rounds of eight replicas on.  One launch, 0 or 1 / 2: binary32 R = 16 835 / 816, R = 24 1259 / 1218, R = 32
+// 1658 / 1614 (R = 12 615 / 638, R = 14 726 / 723); bfloat16 R = 16 407 / 398, R = 24 613 / 597, R = 32 806 / 791 (R = 10 255 / 281, R = 12 300 / 316,
+// R = 14 354 / 365); binary32 averages R = 16 431 / 427, R = 24 652 / 639, R = 32 858 / 843 (R = 14 379 / 384).  One mark per call, 25 MiB buckets:
+// binary32 R = 16 848 / 842, R = 24 1253 / 1243, R = 32 1635 / 1626.
+// 1, binary32 averages: first loads plain, further pointers scalar.  2000 MiB, 0 / 1: R = 2 447 / 454, R = 3 424 / 410, R = 4 410 / 390, R = 5 402 /
+// 376, R = 6 384 / 394, R = 8 353 / 370, R = 9 355 / 382, R = 10 359 / 368, R = 11 364 / 360, R = 14 375 / 360.
+// 1, binary32 gradients of which every replica is written: offsets left to the compiler.  2000 MiB, 0 / 1: R = 2 464 / 450, R = 3 506 / 508, R = 4
+// 557 / 571, R = 5 583 / 583, R = 6 618 / 600, R = 7 652 / 642, R = 8 682 / 677, R = 10 699 / 670 (25 MiB buckets, one mark per call, 541 / 555), R = 16 742 / 741 (2 is no better).  (One replica
+// written, R = 2, 323 / 339; 16 bits, every replica, R = 4 557 / 575.)
+// Shorter launches keep 0: there the loads that come sooner count (150 MiB, 0 / 2, binary32 averages, R = 16 29.1 / 29.8, R = 32 32.0 / 33.6; 0 / 1, R = 5
+// 31.0 / 31.7; every replica written, R = 64, 67.2 / 68.2).
+static int table_form(int es, int out, int R, int nwrite, int64_t ntiles) {
+    if (ntiles * TILE_BYTES * (R + 1) < (int64_t(400) << 20)) return 0;
+    if (out == OUT_BINARY32) return R >= 16 ? 2 : (R >= 3 && R <= 5) || R >= 11 ? 1 : 0;
+    if (nwrite == 1) return R >= 16 ? 2 : 0;
+    return es == 4 && (R < 3 || (R > 5 && R <= 8)) ? 1 : 0;
+}
+
 template <int DT, int OUT, bool MASKED>
 static hipError_t fused_launch(bool nt, int64_t ntiles, unsigned lds, hipStream_t s,
                                const SegTables& t, int64_t tile_base, int R, int nwrite,
@@ -1427,6 +1453,14 @@ static hipError_t fused_launch(bool nt, int64_t ntiles, unsigned lds, hipStream_
                                const GateRecord* gate, uint32_t tag, DispatchSignal sig) {
     dim3 grid(static_cast<unsigned>(ntiles));
     lds = std::max(lds, edge_lds(R));
+    if constexpr (!MASKED && OUT != OUT_FLAT) {
+        const int form = nt ? table_form(Fmt<DT>::ES, OUT, R, nwrite, ntiles) : 0;
+        if constexpr (OUT == OUT_BINARY32 || Fmt<DT>::ES == 4)
+            if (form == 1)
+                return launch(fused_reduce_kernel<DT, true, RU, OUT, false, 1>, grid, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
+        if (form == 2)
+            return launch(fused_reduce_kernel<DT, true, RU, OUT, false, 2>, grid, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
+    }
     if (nt) return launch(fused_reduce_kernel<DT, true, RU, OUT, MASKED>, grid, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
     return launch(fused_reduce_kernel<DT, false, RU, OUT, MASKED>, grid, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
 }

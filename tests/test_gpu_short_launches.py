@@ -148,3 +148,43 @@ def test_launches_on_both_sides_of_the_limit(pipeline, dtype, R, tiles):
             # (divided on the CPU: by a number, torch multiplies with the reciprocal on the GPU)
             want = (total.cpu() / torch.full((1,), float(R))).to(t)
             assert grads.download(0, i).tobytes() == want.view(torch.uint8).numpy().tobytes(), f"{tiles + extra} tiles, parameter {i}"
+
+
+@pytest.mark.parametrize("long_launch", [0, 1])
+@pytest.mark.parametrize("dtype", [FP32, FP16, BF16])
+@pytest.mark.parametrize("R", [1, 2, 3, 5, 6, 10, 11, 15, 16, 17, 24, 64])
+def test_whole_tiles_with_tables_in_every_form(dtype, R, long_launch):
+    """Launches above the limit for slices, whole tiles and ends: how the tables of a long one (400 MiB) are read depends on the number
+    of replicas, on the output's type and on how many replicas are written.  The reference sums and divides in binary32 in the same order."""
+    import torch
+    d, harness = lib()
+    es = ES[dtype]
+    ttype = {FP32: torch.float32, FP16: torch.float16, BF16: torch.bfloat16}[dtype]
+    t = TILE // es
+    numel = [(51200 // (R + 1) if long_launch else 130) * t + 5, 1, 70 * t - 3, t, 90 * t + 1, 33]
+    n = len(numel)
+    grads = harness.DeviceGrads(numel, [dtype] * n, R, skew=[es * (3 * i % 8) for i in range(n)],
+                                replica_skew=[es * (5 * r % (16 // es)) for r in range(R)], fill=0)
+    gen = torch.Generator("cuda")
+    gen.manual_seed(R)
+    inputs = [[torch.randn(k, generator=gen, device="cuda").to(ttype) for k in numel] for _ in range(R)]
+    want = []
+    for i in range(n):
+        s = inputs[0][i].float()
+        for r in range(1, R):
+            s = s + inputs[r][i].float()
+        want.append(s / torch.full_like(s, float(R)))
+    for write_all, binary32 in ((False, False), (True, False), (False, True)):
+        if binary32 and dtype == FP32:
+            continue
+        for r in range(R):
+            for i in range(n):
+                grads.view(r, i).copy_(inputs[r][i].view(torch.uint8))
+        outputs = harness.DeviceGrads(numel, [FP32] * n, 1, fill=0xFF) if binary32 else None
+        with harness.Session(grads, 1 << 40, FUSED, write_all, outputs=outputs) as s:
+            s.sync()
+        for r in range(R if write_all else 1):
+            for i in range(n):
+                expect = want[i] if binary32 else want[i].to(ttype)
+                got = (outputs if binary32 else grads).view(r, i)
+                assert torch.equal(got, expect.view(torch.uint8)), f"replica {r} parameter {i} write_all {write_all}"
