@@ -1433,17 +1433,20 @@ static unsigned edge_lds(int R) { return static_cast<unsigned>(R * EDGE_SLOTS * 
 // R = 14 354 / 365); binary32 averages R = 16 431 / 427, R = 24 652 / 639, R = 32 858 / 843 (R = 14 379 / 384).  One mark per call, 25 MiB buckets:
 // binary32 R = 16 848 / 842, R = 24 1253 / 1243, R = 32 1635 / 1626.
 // 1, binary32 averages: first loads plain, further pointers scalar.  2000 MiB, 0 / 1: R = 2 447 / 454, R = 3 424 / 410, R = 4 410 / 390, R = 5 402 /
-// 376, R = 6 384 / 394, R = 8 353 / 370, R = 9 355 / 382, R = 10 359 / 368, R = 11 364 / 360, R = 14 375 / 360.
+// 376, R = 6 384 / 394, R = 8 353 / 370, R = 9 355 / 382, R = 10 359 / 368, R = 11 364 / 360 (binary16 317 / 323), R = 14 375 / 360.
 // 1, binary32 gradients of which every replica is written: offsets left to the compiler.  2000 MiB, 0 / 1: R = 2 464 / 450, R = 3 506 / 508, R = 4
 // 557 / 571, R = 5 583 / 583, R = 6 618 / 600, R = 7 652 / 642, R = 8 682 / 677, R = 10 699 / 670 (25 MiB buckets, one mark per call, 541 / 555), R = 16 742 / 741 (2 is no better).  (One replica
 // written, R = 2, 323 / 339; 16 bits, every replica, R = 4 557 / 575.)
+// binary16 keeps 0 from sixteen replicas on: its conversions leave the loads of 2 no room (60 tensors, one launch of 4 GB, 0 / 2, R = 16 655 / 720, R = 32
+// 656 / 704; with binary32 averages R = 16 672 / 782, R = 32 682 / 829).
 // Shorter launches keep 0: there the loads that come sooner count (150 MiB, 0 / 2, binary32 averages, R = 16 29.1 / 29.8, R = 32 32.0 / 33.6; 0 / 1, R = 5
-// 31.0 / 31.7; every replica written, R = 64, 67.2 / 68.2).
-static int table_form(int es, int out, int R, int nwrite, int64_t ntiles) {
-    if (ntiles * TILE_BYTES * (R + 1) < (int64_t(400) << 20)) return 0;
-    if (out == OUT_BINARY32) return R >= 16 ? 2 : (R >= 3 && R <= 5) || R >= 11 ? 1 : 0;
-    if (nwrite == 1) return R >= 16 ? 2 : 0;
-    return es == 4 && (R < 3 || (R > 5 && R <= 8)) ? 1 : 0;
+// 31.0 / 31.7; every replica written, R = 64, 67.2 / 68.2; one replica, 470 MiB, R = 24, binary32 80.1 / 81.3, bfloat16 80.9 / 82.3; 950 MiB, 25 MiB buckets, R = 32, 166 / 163
+// and 167 / 164).
+static int table_form(int dtype, int out, int R, int nwrite, int64_t ntiles) {
+    if (ntiles * TILE_BYTES * (R + 1) < (int64_t(600) << 20)) return 0;
+    if (R >= 16 && nwrite == 1) return dtype == 1 ? 0 : 2;
+    if (out == OUT_BINARY32) return (R >= 3 && R <= 5) || R >= 12 ? 1 : 0;
+    return dtype == 0 && nwrite > 1 && (R < 3 || (R > 5 && R <= 8)) ? 1 : 0;
 }
 
 template <int DT, int OUT, bool MASKED>
@@ -1454,12 +1457,13 @@ static hipError_t fused_launch(bool nt, int64_t ntiles, unsigned lds, hipStream_
     dim3 grid(static_cast<unsigned>(ntiles));
     lds = std::max(lds, edge_lds(R));
     if constexpr (!MASKED && OUT != OUT_FLAT) {
-        const int form = nt ? table_form(Fmt<DT>::ES, OUT, R, nwrite, ntiles) : 0;
+        const int form = nt ? table_form(DT, OUT, R, nwrite, ntiles) : 0;
         if constexpr (OUT == OUT_BINARY32 || Fmt<DT>::ES == 4)
             if (form == 1)
                 return launch(fused_reduce_kernel<DT, true, RU, OUT, false, 1>, grid, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
-        if (form == 2)
-            return launch(fused_reduce_kernel<DT, true, RU, OUT, false, 2>, grid, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
+        if constexpr (DT != 1)
+            if (form == 2)
+                return launch(fused_reduce_kernel<DT, true, RU, OUT, false, 2>, grid, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
     }
     if (nt) return launch(fused_reduce_kernel<DT, true, RU, OUT, MASKED>, grid, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
     return launch(fused_reduce_kernel<DT, false, RU, OUT, MASKED>, grid, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);

@@ -154,14 +154,14 @@ def test_launches_on_both_sides_of_the_limit(pipeline, dtype, R, tiles):
 @pytest.mark.parametrize("dtype", [FP32, FP16, BF16])
 @pytest.mark.parametrize("R", [1, 2, 3, 5, 6, 10, 11, 15, 16, 17, 24, 64])
 def test_whole_tiles_with_tables_in_every_form(dtype, R, long_launch):
-    """Launches above the limit for slices, whole tiles and ends: how the tables of a long one (400 MiB) are read depends on the number
+    """Launches above the limit for slices, whole tiles and ends: how the tables of a long one (600 MiB) are read depends on the number
     of replicas, on the output's type and on how many replicas are written.  The reference sums and divides in binary32 in the same order."""
     import torch
     d, harness = lib()
     es = ES[dtype]
     ttype = {FP32: torch.float32, FP16: torch.float16, BF16: torch.bfloat16}[dtype]
     t = TILE // es
-    numel = [(51200 // (R + 1) if long_launch else 130) * t + 5, 1, 70 * t - 3, t, 90 * t + 1, 33]
+    numel = [(77000 // (R + 1) if long_launch else 130) * t + 5, 1, 70 * t - 3, t, 90 * t + 1, 33]
     n = len(numel)
     grads = harness.DeviceGrads(numel, [dtype] * n, R, skew=[es * (3 * i % 8) for i in range(n)],
                                 replica_skew=[es * (5 * r % (16 // es)) for r in range(R)], fill=0)
