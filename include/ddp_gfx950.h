@@ -133,7 +133,7 @@ typedef struct ddp_ctx ddp_ctx;
                                      unchanged */
 #define DDP_OPT_REDUCE_BLOCKS_PER_CU 13 /* any time: cap on the thread blocks of the reduce kernels that
                                      are resident on one compute unit at a time (an LDS allocation
-                                     the kernels do not touch enforces it).  A block keeps R x 2
+                                     beyond what the kernels use enforces it).  A block keeps R x 2
                                      16-byte loads per thread in flight, so two or three blocks per
                                      unit fill the memory system; more only interleave more request
                                      streams at the DRAM channels and throughput drops.  0 = no cap

@@ -85,7 +85,7 @@ __device__ __forceinline__ void store16u(char* p, u32x4 v) {
 // a v_readfirstlane for every word, and waited for some before it issued the next.)
 // The kernel alone, us, two tensors, plain / scalar: binary32, 512 tiles R = 8 9.5 / 8.4, R = 16 16.2 / 14.0, R = 32
 // 28.6 / 26.0, R = 64 55 / 49; slices, 256 tiles R = 32 17.3 / 12.5, R = 64 32 / 23; bfloat16, 256 tiles R = 16 10.1 / 9.0.
-// The ragged list, R = 8, 198 / 192 us.  Whole tiles in long launches are another matter, see fused_tile.
+// The ragged list, R = 8, 199 / 197 us.  Whole tiles in long launches are another matter, see fused_tile.
 #define DDP_CONSTANT __attribute__((address_space(4)))
 template <typename T>
 __device__ __forceinline__ T cload(const T* p) {
@@ -653,7 +653,7 @@ __device__ __forceinline__ void fused_tile(const SegTables& t, int64_t tile, int
     // plain / tile map plain, others scalar / all scalar, the best cap on resident blocks each: binary32 R = 3 264 / - / -,
     // R = 4 338 / 352 / 350, R = 8 617 / 617 / 631, R = 16 (60 tensors) 852 / 866 / 864; bfloat16 R = 2 112 / 102 / 98, R = 3 146 / 132 / 134, R = 4
     // 165 / 167 / 176, R = 8 319 / 314 / 306, R = 12 451 / 450 / 453, R = 16 590 / 594 / 597; binary32 averages of BERT-large 1144 / 1138 /
-    // 1126; staged (pointers plain in every case: chunk_copy) binary32 R = 4 540 / - / 529, R = 2 332 / - / 336, bfloat16 R = 2 170 / - / 174.
+    // 1126 (further forms for long launches: table_form); staged (pointers plain in every case: chunk_copy) binary32 R = 4 540 / - / 529, R = 2 332 / - / 336, bfloat16 R = 2 170 / - / 174.
     constexpr bool PLAIN = ES == 4 || FORM == 2 || (OUT == OUT_BINARY32 && FORM == 1);
     const int g = OUT == OUT_BINARY32 && !PLAIN ? cload(t.tile_seg + tile) : t.tile_seg[tile];
     const PointerRow row = pointer_row(t.grad, g, t.R);
@@ -1324,8 +1324,8 @@ inline hipError_t after_launch() { return hipGetLastError(); }
 // Every kernel here streams through HBM and needs only a few resident blocks per
 // CU to keep the memory system full; more blocks mean more interleaved request
 // streams at the DRAM channels and measurably less throughput.  `lds` bytes of
-// dynamic LDS that no kernel touches cap the number of resident blocks
-// (a CU has 160 KiB of LDS): 0 = no cap.
+// dynamic LDS cap the number of resident blocks (a CU has 160 KiB of LDS): 0 = no cap.  For the kernels that keep
+// data there it is a required minimum, too: edge_lds(R) for whole tiles and repairs, R * SLICE_BYTES for slices.
 constexpr unsigned kLdsNoOptIn = 64 * 1024;
 constexpr unsigned kLdsPerUnit = 160 * 1024;     // gfx950
 
