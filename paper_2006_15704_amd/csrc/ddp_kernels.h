@@ -113,7 +113,7 @@ inline Scale make_scale(int R) {
 
 // All segment launches cover the tiles [tile_base, tile_base + ntiles) of the
 // global tile numbering (tile0 / tile_seg).  `lds` in K2 and K4: bytes of
-// dynamic LDS per block that the kernels do not use; they cap the number of
+// dynamic LDS per block, beyond what the kernels use; they cap the number of
 // blocks resident on a compute unit (0 = no cap).  The copy kernels K1 and K3
 // keep one or two loads per thread in flight and want every block they can get.
 
