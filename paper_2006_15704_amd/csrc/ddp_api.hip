@@ -102,7 +102,7 @@ struct ddp_ctx {
     uint64_t* h_masks[2] = {nullptr, nullptr};   // pinned copies of local_cur, by iteration parity; see stage_masks
     bool masks_in_flight[2] = {false, false};    // kernels of an earlier iteration may still read h_masks
     int64_t masks_claimed_iter = -1;             // iteration for which h_masks was waited for
-    void** d_micro = nullptr;                // [R * n, rounded up to an even number]
+    void** d_micro = nullptr;                // [R * n, rounded up to an even number], and a word for pointer_copy_kernel
     // Pinned: micro_slots tables of micro-step pointers, used in turn, and behind them the ordinal of the latest
     // table that the device has read (written by pointer_copy_kernel).  Two keep the device busy: the host fills one while
     // the other has yet to be read (four micro-steps and the reduction, R = 2, four tensors, 37 us with one, 31.0 with
@@ -1187,7 +1187,8 @@ static int32_t build_internal(ddp_ctx* c, uint64_t cap_bytes, const std::vector<
         const size_t micro_bytes = sizeof(void*) * static_cast<size_t>(c->micro_table);
         c->micro_slots = micro_bytes <= ddp_ctx::kSmallMicroTable ? 4 : 2;
         const size_t pinned_bytes = micro_bytes * static_cast<size_t>(c->micro_slots) + sizeof(unsigned long long);
-        HIPCHK(c, hipMalloc(reinterpret_cast<void**>(&c->d_micro), micro_bytes));
+        HIPCHK(c, hipMalloc(reinterpret_cast<void**>(&c->d_micro), micro_bytes + sizeof(unsigned long long)));
+        HIPCHK(c, hipMemset(c->d_micro + c->micro_table, 0, sizeof(unsigned long long)));
         HIPCHK(c, hipHostMalloc(reinterpret_cast<void**>(&c->h_micro), pinned_bytes, hipHostMallocDefault));
         std::memset(c->h_micro, 0, pinned_bytes);
         c->micro_ticket = 0;
@@ -1583,7 +1584,8 @@ int32_t ddp_no_sync_accumulate(ddp_ctx* c, void* const* micro) {
         }
         c->micro_used[segment] = used;
     }
-    HIPCHK(c, ddp::launch_pointer_copy(c->d_micro, table, c->micro_table, c->micro_done(), c->micro_ticket + 1, c->backward));
+    HIPCHK(c, ddp::launch_pointer_copy(c->d_micro, table, c->micro_table, reinterpret_cast<unsigned*>(c->d_micro + c->micro_table),
+                                       c->micro_done(), c->micro_ticket + 1, c->backward));
     ++c->micro_ticket;
     size_t slot;
     int32_t rc;

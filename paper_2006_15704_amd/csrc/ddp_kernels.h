@@ -256,8 +256,9 @@ hipError_t launch_bitmap_or(uint64_t* local, uint8_t* global, uint8_t* host_glob
                             hipStream_t s);
 
 // dst[0 .. count) = src[0 .. count) (pinned memory; 16-byte aligned both, count even), then *done = ticket (pinned).
-hipError_t launch_pointer_copy(void** dst, void* const* src, int64_t count, unsigned long long* done, unsigned long long ticket,
-                               hipStream_t s);
+// arrived: a word in device memory that is 0 between launches; they run one after the other on one stream.
+hipError_t launch_pointer_copy(void** dst, void* const* src, int64_t count, unsigned* arrived, unsigned long long* done,
+                               unsigned long long ticket, hipStream_t s);
 
 // K4: grad[r][g] += micro[g*R + r] for all segments and replicas (laid out as SegTables::grad, so that
 // a block fetches both pointers at once)

@@ -1219,16 +1219,23 @@ __global__ __launch_bounds__(BLOCK) void accumulate_kernel(SegTables t, void* co
 }
 
 // The pointers of a micro-step go from pinned memory to the table that accumulate_kernel reads, and `done`
-// (pinned) tells the host with which call's it is through, so that the host may write there again.  One block: the last of its
-// reads has returned when its threads have met, so the store needs no release (which would write the cache back).  Bound by the way to host memory and back, about
-// 2 us; every thread keeps four 16-byte loads under way.
+// (pinned) tells the host with which call's it is through, so that the host may write there again.  The last of a block's
+// reads has returned when its threads have met, so neither the count of blocks that are through (`arrived`, 0 between
+// launches) nor the store needs a release (which would write the cache back).  Bound by the way to host memory and back, about
+// 2 us; every thread keeps four 16-byte loads under way, a block takes 64 KiB a round, and a table takes as many blocks, up to 32.
 // A copy of the runtime's and an event behind it took 2.9 and 4 us of the host, the wait for the event 7 when it had
 // just passed, and 10 us of the stream: ResNet-50 in bfloat16, R = 8, 196 -> 193 us a micro-step; 234 tensors, R = 5, 57 -> 50;
-// four micro-steps and the reduction of 84000 elements, R = 16, 270 -> 239.
-__global__ __launch_bounds__(1024) void pointer_copy_kernel(u32x4* __restrict__ dst, const u32x4* __restrict__ src, int64_t nvec,
-                                                            unsigned long long* done, unsigned long long ticket) {
-    constexpr int U = 4;
-    for (int64_t i0 = threadIdx.x; i0 < nvec; i0 += 1024 * U) {
+// four micro-steps and the reduction of 84000 elements, R = 16, 270 -> 239.  Large tables (pointers ready in an array, us a micro-step, the
+// runtime's copy / one block / so): R = 64, 2000 tensors 401 / 447 / 379, 8000 1662 / 1851 / 1622; R = 32, 1600 tensors 521 / 533 / 511 (the
+// kernel alone 40 / 12).
+// MANY: more than one block.  (A table that one block takes is spared the count: R = 2, four tensors, 6.2 us a micro-step, 7.8 with it.)
+constexpr int POINTER_COPY_LOADS = 4, POINTER_COPY_BLOCKS = 32;
+template <bool MANY>
+__global__ __launch_bounds__(1024) void pointer_copy_kernel(u32x4* __restrict__ dst, const u32x4* __restrict__ src, int64_t nvec, int blocks,
+                                                            unsigned* arrived, unsigned long long* done, unsigned long long ticket) {
+    constexpr int U = POINTER_COPY_LOADS;
+    for (int64_t i0 = (MANY ? static_cast<int64_t>(blockIdx.x) * 1024 * U : 0) + threadIdx.x; i0 < nvec;
+         i0 += static_cast<int64_t>(MANY ? blocks : 1) * 1024 * U) {
         u32x4 v[U];
 #pragma unroll
         for (int u = 0; u < U; ++u)
@@ -1238,7 +1245,12 @@ __global__ __launch_bounds__(1024) void pointer_copy_kernel(u32x4* __restrict__ 
             if (i0 + u * 1024 < nvec) dst[i0 + u * 1024] = v[u];
     }
     __syncthreads();
-    if (threadIdx.x == 0) __hip_atomic_store(done, ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (threadIdx.x != 0) return;
+    if (MANY) {
+        if (__hip_atomic_fetch_add(arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 < static_cast<unsigned>(blocks)) return;
+        __hip_atomic_store(arrived, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __hip_atomic_store(done, ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // ---- global participation bitmap ---------------------------------------------
@@ -1608,11 +1620,13 @@ hipError_t launch_probe(unsigned long long* word, unsigned long long value, long
     return after_launch();
 }
 
-hipError_t launch_pointer_copy(void** dst, void* const* src, int64_t count, unsigned long long* done, unsigned long long ticket,
-                               hipStream_t s) {
+hipError_t launch_pointer_copy(void** dst, void* const* src, int64_t count, unsigned* arrived, unsigned long long* done,
+                               unsigned long long ticket, hipStream_t s) {
     if (count % 2 != 0) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(pointer_copy_kernel, dim3(1), dim3(1024), 0, s, reinterpret_cast<u32x4*>(dst),
-                       reinterpret_cast<const u32x4*>(src), count / 2, done, ticket);
+    const int64_t nvec = count / 2, round = 1024 * POINTER_COPY_LOADS;
+    const int64_t blocks = std::min<int64_t>(std::max<int64_t>((nvec + round - 1) / round, 1), POINTER_COPY_BLOCKS);
+    hipLaunchKernelGGL(blocks > 1 ? pointer_copy_kernel<true> : pointer_copy_kernel<false>, dim3(static_cast<unsigned>(blocks)), dim3(1024), 0, s,
+                       reinterpret_cast<u32x4*>(dst), reinterpret_cast<const u32x4*>(src), nvec, static_cast<int>(blocks), arrived, done, ticket);
     return after_launch();
 }
 
