@@ -561,7 +561,10 @@ int32_t launch_range(ddp_ctx* c, int32_t first, int32_t last, Target target) {
         const int lanes = c->n_streams < 0 ? (!long_launch(c, bytes) && c->lane[1] && c->lane_concurrent[1] ? 2 : 1) : c->n_streams;
         lane = static_cast<int>(c->launches_in_iter++ % lanes);
         // (short launches next to this one would take long to run: they look again first)
-        if (traffic >= kChainMinTraffic) c->early_credit = 0;
+        if (traffic >= kChainMinTraffic) {
+            c->early_credit = 0;
+            c->progress_wait = 0;     // (an announcement in front of it says nothing of what comes behind)
+        }
     } else if (target == Target::kPartner) {
         lane = 0;
     }
