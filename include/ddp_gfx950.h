@@ -190,11 +190,8 @@ typedef struct ddp_ctx ddp_ctx;
                                      backward_stream once every gradient exists, so results never depend
                                      on a wait succeeding.  The way back at ddp_finalize_backward is
                                      ordered likewise: each reduction stream stores the iteration's
-                                     number behind its last launch and one kernel on backward_stream
-                                     waits (bounded) for those numbers, followed by waits for events of
-                                     the same streams, which have fired by then (a wait for an event
-                                     that has yet to fire is handed over slowly on this system when it
-                                     was enqueued long before).  Streams that share a hardware queue cannot
+                                     number behind its last launch, and backward_stream waits for the
+                                     value.  Streams that share a hardware queue cannot
                                      run a gate and its announcement concurrently; ddp_create (and
                                      DDP_OPT_REDUCE_STREAMS) probe for that with a bounded test and such
                                      streams keep events.  0: events always */

@@ -185,12 +185,9 @@ struct OrderState {
                                     //    later gates of the iteration give up at once
     uint32_t repaired;              // launches redone by repair launches since the context was created
     uint32_t pad1[30];
-    unsigned long long lane_done[16];   // per reduction stream: the latest iteration tag whose launches
-                                        //    on that stream have all ended (monotonic)
     unsigned long long dispatched;      // ordinal of the latest gated bucket launch whose last thread block
     unsigned long long pad2[15];        //    has started (monotonic): the launch is draining or done
 };
-constexpr int kOrderLanes = 16;
 
 struct GateRecord {                 // one per bucket, used by the launch whose first bucket it is
     int32_t tile_base;              // tile range of the launch
@@ -204,17 +201,12 @@ struct GateRecord {                 // one per bucket, used by the launch whose 
 // host (may be null): a word in pinned memory that receives the number as well, for the host to see.
 hipError_t launch_announce(OrderState* st, unsigned long long seq, unsigned long long* host, hipStream_t s);
 
-// The way back at the end of an iteration.  Reduction stream `lane`, behind its last bucket
-// launch: lane_done[lane] = tag.  Backward stream: wait (at most wait_ticks) until lane_done[l]
-// >= tag for every l in lane_mask.  The join only spares the backward stream a wait for an
-// event that has not fired yet (slow on this system when the wait was enqueued long before):
-// the events of the same streams are recorded before the done kernels and waited for after
-// the join kernel, so a join that gives up changes nothing but the time.
 // backward stream, in front of a bucket launch that needs no gate there: the scheduling wait alone
 hipError_t launch_chain_wait(OrderState* st, unsigned long long chain_ord, long long chain_ticks, hipStream_t s);
-hipError_t launch_done(OrderState* st, int lane, unsigned long long tag, hipStream_t s);
-hipError_t launch_join(OrderState* st, uint32_t lane_mask, unsigned long long tag, long long wait_ticks,
-                       hipStream_t s);
+
+// The way back at the end of an iteration: on a reduction stream, behind its last bucket launch, *word = tag
+// (host memory that a stream can wait on, hipStreamWaitValue64).
+hipError_t launch_done(unsigned long long* word, unsigned long long tag, hipStream_t s);
 
 // reduction stream: wait (at most wait_ticks of the device wall clock) until
 // ready_seq >= need; on failure fill *rec, tag *row_summary (the record behind the last bucket's

@@ -89,6 +89,45 @@ def test_flag_ordered_launches_wait_for_the_backward_stream(dtype, streams, gate
         assert repaired == 0
 
 
+@pytest.mark.parametrize("streams", [-1, 1, 2, 3, 8])
+@pytest.mark.parametrize("gate_wait_us", [100000, 0])
+def test_work_behind_finalize_sees_the_launches_of_every_reduction_stream(streams, gate_wait_us):
+    """The reductions are longer than the calls that enqueue them, five iterations follow each other without the
+    host waiting, and each one's results are read, and its gradients overwritten, on the backward stream at once.
+    With a gate wait of 0 an iteration's numbers come before the previous iteration's on the other streams."""
+    d, harness = lib()
+    import torch
+    numel = [400000 + 4096 * (k % 3) + k for k in range(24)]
+    n, R, cap, rounds = len(numel), 4, 2 << 20, 5
+    dtypes = [FP32] * n
+    grads = harness.DeviceGrads(numel, dtypes, R, fill=0)
+    reps = [workloads.gaussian_replica(660, r, 0, numel, 1.0, FP32) for r in range(R)]
+    src = harness.DeviceGrads(numel, dtypes, R)
+    for r in range(R):
+        src.upload_replica(r, reps[r])
+    want, _, wlog = oracle.synchronize(numel, dtypes, cap, reps)[:3]
+    keep = harness.DeviceGrads(numel, dtypes, rounds, fill=0)
+    torch.cuda.synchronize()
+    with session_with_flags(d, harness, grads, cap, streams) as s:
+        d.ddp_set_option(s.ctx, d.DDP_OPT_GATE_WAIT_US, gate_wait_us)
+        for it in range(rounds):
+            with torch.cuda.stream(s.backward_stream):
+                for r in range(R):
+                    grads.bufs[r].copy_(src.bufs[r], non_blocking=True)
+            for p in range(n - 1, -1, -1):
+                d.ddp_mark_ready(s.ctx, p)
+            d.ddp_finalize_backward(s.ctx)
+            assert d.ddp_get_launch_log(s.ctx, 1) == wlog
+            with torch.cuda.stream(s.backward_stream):
+                keep.bufs[it].copy_(grads.bufs[0], non_blocking=True)
+                grads.bufs[0].fill_(0xFF)
+        d.ddp_synchronize(s.ctx)
+        torch.cuda.synchronize()
+    for it in range(rounds):
+        for i in range(n):
+            assert keep.download(it, i).tobytes() == want[i].tobytes(), f"iteration {it} parameter {i}"
+
+
 @pytest.mark.parametrize("find_unused", [False, True])
 @pytest.mark.parametrize("gate_wait_us", [100000, 0])
 def test_flag_ordering_with_partial_participation_and_all_writers(find_unused, gate_wait_us):
