@@ -431,9 +431,11 @@ int32_t ddp_get_launch_log(const ddp_ctx* ctx, int32_t which, int32_t* bucket_id
  *   micro_grad_ptrs  host array of R*n device pointers, [r][i]; a NULL entry
  *                    means parameter i produced no gradient in this micro-step.
  * The micro buffers may be reused once work enqueued on backward_stream after
- * this call has started (stream order).  Asynchronous, but a call waits until the
- * device has read the pointers of the call before the last (of the fourth-last, where 8 R n bytes are at
- * most 64 KiB).  They travel through pinned memory that ddp_build_buckets allocates for so many tables of 8 R n bytes. */
+ * this call has started (stream order).  Asynchronous.  The pointers travel in the launch's arguments if R n of them, or, where
+ * every replica's tensors lie at the same distances from each other and are present alike, R + n are at most
+ * 448.  Longer lists travel through pinned memory that ddp_build_buckets allocates for a few tables of 8 R n bytes: a call then
+ * waits until the device has read the pointers of the call before the last (of the fourth-last, where such a table takes at
+ * most 64 KiB). */
 int32_t ddp_no_sync_accumulate(ddp_ctx* ctx, void* const* micro_grad_ptrs);
 
 /* used[n] (host): 1 if the parameter received a gradient through

@@ -1579,6 +1579,76 @@ static int32_t await_micro_slot(ddp_ctx* c) {
     return DDP_OK;
 }
 
+// How a micro-step's pointers reach the device: in the arguments of the launch where they fit, as they are or, where
+// every replica's tensors lie alike (views into one buffer per replica, say), as R bases and n distances; else as a table.
+enum class MicroForm { kTable, kWords, kRegular };
+
+// Fills `words` (kMicroByValue of them) for the two forms that travel by value, and micro_used.
+static MicroForm micro_words(ddp_ctx* c, void* const* micro, uint64_t* words) {
+    const int64_t R = c->R, n = static_cast<int64_t>(c->plan.params.size());
+    if (R + n > ddp::kMicroByValue) return MicroForm::kTable;
+    int64_t first = 0;
+    while (first < n && micro[first] == nullptr) ++first;
+    bool regular = first < n;
+    for (int64_t r = 0; regular && r < R; ++r) {
+        void* const* const row = micro + r * n;
+        const uintptr_t shift = reinterpret_cast<uintptr_t>(row[first]) - reinterpret_cast<uintptr_t>(micro[first]);
+        regular = row[first] != nullptr;
+        for (int64_t i = 0; regular && i < n; ++i)
+            regular = micro[i] == nullptr ? row[i] == nullptr
+                                          : row[i] != nullptr && reinterpret_cast<uintptr_t>(row[i]) == reinterpret_cast<uintptr_t>(micro[i]) + shift;
+        words[r] = reinterpret_cast<uintptr_t>(row[first]);
+    }
+    if (regular) {
+        const uint64_t everyone = everyone_mask(c);
+        for (int64_t i = 0; i < n; ++i) {
+            const int32_t segment = c->plan.params[i].segment;
+            words[R + segment] = micro[i] ? reinterpret_cast<uintptr_t>(micro[i]) - reinterpret_cast<uintptr_t>(micro[first]) : ddp::kMicroAbsent;
+            c->micro_used[segment] = micro[i] ? everyone : 0;
+        }
+        return MicroForm::kRegular;
+    }
+    if (R * n > ddp::kMicroByValue) return MicroForm::kTable;
+    for (int64_t i = 0; i < n; ++i) {
+        const int32_t segment = c->plan.params[i].segment;
+        uint64_t used = 0;
+        for (int64_t r = 0; r < R; ++r) {
+            void* const p = micro[r * n + i];
+            words[segment * R + r] = p ? reinterpret_cast<uintptr_t>(p) : ddp::kMicroAbsent;
+            used |= static_cast<uint64_t>(p != nullptr) << r;
+        }
+        c->micro_used[segment] = used;
+    }
+    return MicroForm::kWords;
+}
+
+// Brings a micro-step's pointers to d_micro, through the next of the pinned tables, and notes micro_used.
+static int32_t send_micro_table(ddp_ctx* c, void* const* micro) {
+    const int64_t R = c->R, n = static_cast<int64_t>(c->plan.params.size());
+    void** const table = c->h_micro + static_cast<int64_t>((c->micro_ticket + 1) % static_cast<unsigned long long>(c->micro_slots)) * c->micro_table;
+    {
+        const int32_t rcw = await_micro_slot(c);
+        if (rcw != DDP_OK) return rcw;
+    }
+    // a parameter at a time: its row of the table is written in one go (R = 32, 1600 tensors: 82 us of
+    // host time a call when every pointer went to a cache line of its own, 44 so)
+    for (int64_t i = 0; i < n; ++i) {
+        const int32_t segment = c->plan.params[i].segment;
+        void** row = table + segment * R;
+        uint64_t used = 0;
+        for (int64_t r = 0; r < R; ++r) {
+            void* const p = micro[r * n + i];
+            row[r] = p;
+            used |= static_cast<uint64_t>(p != nullptr) << r;
+        }
+        c->micro_used[segment] = used;
+    }
+    HIPCHK(c, ddp::launch_pointer_copy(c->d_micro, table, c->micro_table, reinterpret_cast<unsigned*>(c->d_micro + c->micro_table),
+                                       c->micro_done(), c->micro_ticket + 1, c->backward));
+    ++c->micro_ticket;
+    return DDP_OK;
+}
+
 int32_t ddp_no_sync_accumulate(ddp_ctx* c, void* const* micro) {
     if (!c) return DDP_ERR_ARG;
     if (!c->built) return fail(c, DDP_ERR_STATE, "ddp_no_sync_accumulate before ddp_build_buckets");
@@ -1597,32 +1667,22 @@ int32_t ddp_no_sync_accumulate(ddp_ctx* c, void* const* micro) {
                 return fail(c, DDP_ERR_ARG, "ddp_no_sync_accumulate: pointer not aligned to its element size");
         }
     HIPCHK(c, hipSetDevice(c->device));
-    void** const table = c->h_micro + static_cast<int64_t>((c->micro_ticket + 1) % static_cast<unsigned long long>(c->micro_slots)) * c->micro_table;
-    {
-        const int32_t rcw = await_micro_slot(c);
-        if (rcw != DDP_OK) return rcw;
+    uint64_t words[ddp::kMicroByValue];
+    const MicroForm form = micro_words(c, micro, words);
+    if (form == MicroForm::kTable) {
+        const int32_t rct = send_micro_table(c, micro);
+        if (rct != DDP_OK) return rct;
     }
-    // a parameter at a time: its row of the table is written in one go (R = 32, 1600 tensors: 82 us of
-    // host time a call when every pointer went to a cache line of its own, 44 so)
-    for (int32_t i = 0; i < n; ++i) {
-        const int32_t segment = c->plan.params[i].segment;
-        void** row = table + segment * R;
-        uint64_t used = 0;
-        for (int64_t r = 0; r < R; ++r) {
-            void* const p = micro[r * n + i];
-            row[r] = p;
-            used |= static_cast<uint64_t>(p != nullptr) << r;
-        }
-        c->micro_used[segment] = used;
-    }
-    HIPCHK(c, ddp::launch_pointer_copy(c->d_micro, table, c->micro_table, reinterpret_cast<unsigned*>(c->d_micro + c->micro_table),
-                                       c->micro_done(), c->micro_ticket + 1, c->backward));
-    ++c->micro_ticket;
     size_t slot;
     int32_t rc;
+    const unsigned lds = lds_for_blocks(c, c->acc_blocks_per_cu);
     if ((rc = timed_begin(c, DDP_K_ACCUMULATE, -1, c->backward, &slot)) != DDP_OK) return rc;
-    HIPCHK(c, ddp::launch_accumulate(c->tables, c->h_tile0[n], c->R, c->d_micro,
-                                     lds_for_blocks(c, c->acc_blocks_per_cu), c->backward));
+    if (form == MicroForm::kTable)
+        HIPCHK(c, ddp::launch_accumulate(c->tables, c->h_tile0[n], c->R, c->d_micro, lds, c->backward));
+    else
+        HIPCHK(c, ddp::launch_accumulate_by_value(c->tables, c->h_tile0[n], c->R, words,
+                                                  static_cast<int>(form == MicroForm::kRegular ? R + n : R * n),
+                                                  form == MicroForm::kRegular, lds, c->backward));
     if ((rc = timed_end(c, slot, c->backward)) != DDP_OK) return rc;
     for (int32_t i = 0; i < n; ++i) {
         const int32_t segment = c->plan.params[i].segment;

@@ -252,11 +252,18 @@ hipError_t launch_bitmap_or(uint64_t* local, uint8_t* global, uint8_t* host_glob
 hipError_t launch_pointer_copy(void** dst, void* const* src, int64_t count, unsigned* arrived, unsigned long long* done,
                                unsigned long long ticket, hipStream_t s);
 
-// K4: grad[r][g] += micro[g*R + r] for all segments and replicas (laid out as SegTables::grad, so that
-// a block fetches both pointers at once)
-// (null micro pointers are skipped).  ntiles = tile0[G].
+// K4: grad[r][g] += micro gradient for all segments and replicas (null micro pointers are skipped).  ntiles = tile0[G].
+// micro: a table in device memory, replica r's pointer of segment g at [g*R + r] (laid out as SegTables::grad, so that
+// a block fetches both pointers at once) ...
 hipError_t launch_accumulate(const SegTables& t, int64_t ntiles, int R, void* const* micro,
                              unsigned lds, hipStream_t s);
+
+// ... or words that travel in the launch's arguments: the table itself, or with `regular` the addresses of R bases
+// followed by the distances of the G segments from them (kMicroAbsent: a segment without a gradient).
+constexpr int kMicroByValue = 448;
+constexpr uint64_t kMicroAbsent = uint64_t(1) << 63;
+hipError_t launch_accumulate_by_value(const SegTables& t, int64_t ntiles, int R, const uint64_t* words, int count, bool regular,
+                                      unsigned lds, hipStream_t s);
 
 // K6: a kernel that waits `ticks` of the device wall clock (bounded; skipped for
 // ticks <= 0), followed by a kernel that copies src_r -> dst_r (nelem elements

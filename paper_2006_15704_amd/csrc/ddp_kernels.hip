@@ -1184,13 +1184,33 @@ __device__ __forceinline__ void accumulate_tile(const char* __restrict__ src, ch
     }
 }
 
-template <bool STREAM>
-__global__ __launch_bounds__(BLOCK) void accumulate_kernel(SegTables t, void* const* __restrict__ micro) {
+// Where a block finds its micro-gradient: in a table in device memory, or in the launch's arguments.
+struct MicroTable {
+    void* const* row0;
+    __device__ __forceinline__ const char* operator()(int g, int r, int R) const { return pointer_row(row0, g, R)[r]; }
+};
+// The arguments save the kernel that brings a table to the device and its hand-over, 4.7 us of the stream, and one of two launches
+// of the host; 512 bytes of them cost the host no more than none, 3.5 KiB 1.4 us.  Us a micro-step, table / arguments:
+// R = 2, four tensors 6.7 / 4.2, R = 8, forty 11.2 / 8.4, R = 4, 175 16.2 / 13.6, R = 16, 87 24.4 / 22.5 (all bound by the list's way
+// through Python); four micro-steps and the reduction, R = 8, sixty tensors 57.6 / 48.3, R = 16, 200 tensors of 10 MB 328 / 314; ResNet-50
+// in bfloat16, R = 8 194.0 / 192.7.
+template <int N>
+struct MicroWords {
+    uint64_t w[N];
+    int32_t regular;           // w: R bases and a distance for each segment; else the table itself
+    __device__ __forceinline__ const char* operator()(int g, int r, int R) const {
+        const uint64_t a = regular ? w[r] : 0, d = regular ? w[R + g] : w[g * R + r];
+        return d == kMicroAbsent ? nullptr : reinterpret_cast<const char*>(a + d);
+    }
+};
+
+template <bool STREAM, typename Micro>
+__global__ __launch_bounds__(BLOCK) void accumulate_kernel(SegTables t, Micro micro) {
     const int64_t tile = blockIdx.x;
     const int r = blockIdx.y;
     const int g = cload(t.tile_seg + tile);
     const SegInfo si = segment(t, g);
-    const char* src = pointer_row(micro, g, t.R)[r];
+    const char* src = micro(g, r, t.R);
     char* dst = pointer_row(t.grad, g, t.R)[r];
     if (src == nullptr) return;
     const int64_t numel = si.numel;
@@ -1329,7 +1349,7 @@ constexpr unsigned kLdsPerUnit = 160 * 1024;     // gfx950
 thread_local hipEvent_t g_time_start = nullptr, g_time_stop = nullptr;
 
 template <typename... KArgs, typename... Args>
-static hipError_t launch(void (*kernel)(KArgs...), dim3 grid, unsigned lds, hipStream_t s, Args... args) {
+static hipError_t launch(void (*kernel)(KArgs...), dim3 grid, unsigned lds, hipStream_t s, const Args&... args) {
     if (lds > kLdsNoOptIn) {
         // allocations above 64 KiB must be allowed per kernel; once is enough
         // (per device: the attribute belongs to the kernel's code object on the current device)
@@ -1608,8 +1628,8 @@ hipError_t launch_pointer_copy(void** dst, void* const* src, int64_t count, unsi
 
 constexpr int64_t kStreamedGradients = int64_t(368) << 20;
 
-hipError_t launch_accumulate(const SegTables& t, int64_t ntiles, int R, void* const* micro,
-                             unsigned lds, hipStream_t s) {
+template <typename Micro>
+static hipError_t accumulate_launch(const SegTables& t, int64_t ntiles, int R, const Micro& micro, unsigned lds, hipStream_t s) {
     if (ntiles <= 0 || R <= 0) return hipSuccess;
     dim3 grid(static_cast<unsigned>(ntiles), static_cast<unsigned>(R));
     // Up to about one and a half times the last-level cache (256 MiB) enough of the gradients is still
@@ -1622,8 +1642,29 @@ hipError_t launch_accumulate(const SegTables& t, int64_t ntiles, int R, void* co
     // small tensors take the hint early and are no worse for it (two micro-steps and the reduction, real
     // bytes / whole tiles compared with the threshold: R = 64, 800 tensors of 500 bfloat16 404 / 390 us,
     // of 100 binary32 185 / 188; R = 32, 2000 of 500 bfloat16 442 / 429; R = 8, 8000 of 100 bfloat16 405 / 417).
-    if (ntiles * R * int64_t(TILE_BYTES) > kStreamedGradients) return launch(accumulate_kernel<true>, grid, lds, s, t, micro);
-    return launch(accumulate_kernel<false>, grid, lds, s, t, micro);
+    if (ntiles * R * int64_t(TILE_BYTES) > kStreamedGradients) return launch(accumulate_kernel<true, Micro>, grid, lds, s, t, micro);
+    return launch(accumulate_kernel<false, Micro>, grid, lds, s, t, micro);
+}
+
+hipError_t launch_accumulate(const SegTables& t, int64_t ntiles, int R, void* const* micro, unsigned lds, hipStream_t s) {
+    return accumulate_launch(t, ntiles, R, MicroTable{micro}, lds, s);
+}
+
+template <int N>
+static hipError_t accumulate_words(const SegTables& t, int64_t ntiles, int R, const uint64_t* words, int count, bool regular,
+                                   unsigned lds, hipStream_t s) {
+    MicroWords<N> m;
+    std::memcpy(m.w, words, sizeof(uint64_t) * count);
+    m.regular = regular ? 1 : 0;
+    return accumulate_launch(t, ntiles, R, m, lds, s);
+}
+
+hipError_t launch_accumulate_by_value(const SegTables& t, int64_t ntiles, int R, const uint64_t* words, int count, bool regular,
+                                      unsigned lds, hipStream_t s) {
+    if (count > kMicroByValue) return hipErrorInvalidValue;
+    if (count <= 64) return accumulate_words<64>(t, ntiles, R, words, count, regular, lds, s);
+    if (count <= 192) return accumulate_words<192>(t, ntiles, R, words, count, regular, lds, s);
+    return accumulate_words<kMicroByValue>(t, ntiles, R, words, count, regular, lds, s);
 }
 
 hipError_t launch_mask_write(uint64_t* dst, const uint64_t* masks, int count, const GateRecord* gate, uint32_t tag,
