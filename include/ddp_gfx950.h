@@ -477,9 +477,10 @@ int32_t ddp_get_kernel_times(ddp_ctx* ctx, int32_t kind, float* ms, int32_t* ids
  * (n, numel, dtype, grad_ptrs: host arrays, copied before the call returns;
  * gradient memory stays the caller's).  Returns the number of buckets.
  *
- * The device tables and, where the call needs them, the R + 1 flat bucket
+ * The device tables, unless they are short enough (448 eight-byte words: 2 n + R where the replicas' tensors lie at the
+ * same distances from each other, else n (R + 1)) to travel in the reduction's own arguments, and, where the call needs them, the R + 1 flat bucket
  * buffers (tensors that may share memory; the limit
- * below counts them always) live in a static device
+ * below counts tables and buffers always) live in a static device
  * array of DDP_STATIC_SCRATCH_BYTES that every GPU used through this call holds
  * until the process ends; host tables travel inside kernel arguments.  The call
  * makes no hipMalloc / hipFree / hipHostMalloc and no copy from host memory; all

@@ -169,6 +169,21 @@ hipError_t launch_fused_reduce(int dtype, const SegTables& t, int64_t tile_base,
                                const GateRecord* gate, uint32_t tag, DispatchSignal sig, hipStream_t s);
 // (with t.out set -- 16-bit gradients, binary32 averages written to t.out -- nwrite must be 1)
 
+// K2 (fused) without tables in device memory: they travel in the launch's arguments, as `count` words.
+//   [0, n)           numel | congruent() << 31 | tile0 << 32 of every segment
+//   then, as they are: the R pointers of every segment;
+//   or, `regular`:     R bases and every segment's distance from them.
+// (gradients of one type, all replicas take part, replica 0 receives the averages)
+constexpr int kTableWords = 448;
+struct WordTables {
+    const uint64_t* words;
+    int32_t n;
+    bool regular;
+    int count(int R) const { return regular ? 2 * n + R : n * (R + 1); }
+};
+hipError_t launch_fused_reduce_by_value(int dtype, const WordTables& t, int64_t tile_base, int64_t ntiles, int R, Scale sc,
+                                        hipStream_t s);
+
 // ---- stream ordering through device flags -------------------------------------
 // A bucket launch on a reduction stream must come after the backward-stream work
 // that produces its gradients (Section 3.2.3).  Instead of an event pair per

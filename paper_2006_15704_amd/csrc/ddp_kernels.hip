@@ -103,6 +103,51 @@ struct PointerRow {                        // a segment's R pointers
 __device__ __forceinline__ PointerRow pointer_row(void* const* table, int g, int R) {
     return PointerRow{(DDP_CONSTANT const uint64_t*)(table + static_cast<int64_t>(g) * R)};
 }
+__device__ __forceinline__ int segment_of(const SegTables& t, int64_t tile) { return cload(t.tile_seg + tile); }
+__device__ __forceinline__ PointerRow gradients_of(const SegTables& t, int g) { return pointer_row(t.grad, g, t.R); }
+
+// Tables that travel in the launch's arguments (WordTables has the layout).  There is no tile map: a wave compares the first
+// tiles of 64 segments with its own at a time.
+template <int N>
+struct ArgTables {
+    uint64_t w[N + 16];                    // (a row is read up to sixteen entries wide)
+    int32_t n, R;
+    int32_t at, step;                      // the pointers of segment g start at w[at + g * step] ...
+    int32_t dist;                          // ... and, if this is not 0, lie w[dist + g] further on
+};
+template <int N>
+struct ArgRow {
+    const ArgTables<N>& t;
+    int at;
+    uint64_t dist;
+    __device__ __forceinline__ char* operator[](int r) const { return reinterpret_cast<char*>(t.w[at + r] + dist); }
+};
+template <int N>
+__device__ __forceinline__ int segment_of(const ArgTables<N>& t, int64_t tile) {
+    const int lane = threadIdx.x & 63;
+    int before = 0;
+    for (int g = 0; g < t.n; g += 64) {
+        const int i = min(g + lane, t.n - 1);
+        const bool starts = g + lane < t.n && static_cast<int64_t>(t.w[i] >> 32) <= tile;
+        before += __popcll(__ballot(starts));
+    }
+    return __builtin_amdgcn_readfirstlane(before - 1);     // (segments without elements share the next one's first tile)
+}
+template <int N>
+__device__ __forceinline__ ArgRow<N> gradients_of(const ArgTables<N>& t, int g) {
+    return ArgRow<N>{t, t.at + g * t.step, t.dist != 0 ? t.w[t.dist + g] : 0};
+}
+template <int N>
+__device__ __forceinline__ SegInfo segment(const ArgTables<N>& t, int g) {
+    const uint64_t w = t.w[g];
+    SegInfo si;
+    si.numel = static_cast<uint32_t>(w) & 0x7FFFFFFFu;
+    si.tile0 = static_cast<int64_t>(w >> 32);
+    si.flat_byte = 0;
+    si.param = 0;
+    si.flags = (static_cast<uint32_t>(w) >> 31 ? 0x100 : 0) | static_cast<int>(reinterpret_cast<uintptr_t>(gradients_of(t, g)[0]) & 15u) << 16;
+    return si;
+}
 
 // ---- element formats ------------------------------------------------------
 template <int DT> struct Fmt;
@@ -523,8 +568,8 @@ __global__ __launch_bounds__(BLOCK) void flat_reduce_kernel(const char* __restri
 // and lanes are predicated.  The C pointers are fetched first (one scalar
 // load), then all C*U vector loads are issued, then the adds run in order.
 // With `slot` set (staged pipeline) the vectors also go to the replicas' flat buckets.
-template <int DT, bool NT, int C, int U>
-__device__ __forceinline__ void chunk_seg(PointerRow row, int r, uint64_t used, bool aligned,
+template <int DT, bool NT, int C, int U, typename Row>
+__device__ __forceinline__ void chunk_seg(const Row& row, int r, uint64_t used, bool aligned,
                                           const int64_t (&off)[U], const bool (&ok)[U],
                                           float (&acc)[U][Fmt<DT>::VEC], char* slot = nullptr, int64_t stride = 0) {
     const char* base[C];
@@ -631,8 +676,8 @@ __device__ __forceinline__ EdgeElements edge_elements(int64_t e0, int span, int6
 // R = 16, one mark per call 681 / 677 us a synchronization; bfloat16, R = 8, 329 / 327, and with
 // the averages to every replica 627.5 / 626.5.
 // FORM: see table_form.
-template <int DT, bool NT, int U, int OUT, bool MASKED, int FORM = 0>
-__device__ __forceinline__ void fused_tile(const SegTables& t, int64_t tile, int R, int nwrite,
+template <int DT, bool NT, int U, int OUT, bool MASKED, int FORM = 0, typename Tables = SegTables>
+__device__ __forceinline__ void fused_tile(const Tables& t, int64_t tile, int R, int nwrite,
                                            const uint64_t* __restrict__ local, int keep_unused,
                                            const Scale& sc, const FlatBuckets& flat,
                                            const GateRecord* __restrict__ gate = nullptr, uint32_t tag = 0) {
@@ -654,14 +699,21 @@ __device__ __forceinline__ void fused_tile(const SegTables& t, int64_t tile, int
     // R = 4 338 / 352 / 350, R = 8 617 / 617 / 631, R = 16 (60 tensors) 852 / 866 / 864; bfloat16 R = 2 112 / 102 / 98, R = 3 146 / 132 / 134, R = 4
     // 165 / 167 / 176, R = 8 319 / 314 / 306, R = 12 451 / 450 / 453, R = 16 590 / 594 / 597; binary32 averages of BERT-large 1144 / 1138 /
     // 1126 (further forms for long launches: table_form); staged (pointers plain in every case: chunk_copy) binary32 R = 4 540 / - / 529, R = 2 332 / - / 336, bfloat16 R = 2 170 / - / 174.
-    constexpr bool PLAIN = ES == 4 || FORM == 2 || (OUT == OUT_BINARY32 && FORM == 1);
-    const int g = OUT == OUT_BINARY32 && !PLAIN ? cload(t.tile_seg + tile) : t.tile_seg[tile];
-    const PointerRow row = pointer_row(t.grad, g, t.R);
-    const SegInfo si = PLAIN ? t.seg[g] : segment(t, g);
+    constexpr bool IN_MEMORY = std::is_same<Tables, SegTables>::value;
+    constexpr bool PLAIN = IN_MEMORY && (ES == 4 || FORM == 2 || (OUT == OUT_BINARY32 && FORM == 1));
+    int g;
+    if constexpr (IN_MEMORY) g = OUT == OUT_BINARY32 && !PLAIN ? cload(t.tile_seg + tile) : t.tile_seg[tile];
+    else g = segment_of(t, tile);
+    const auto row = gradients_of(t, g);
+    SegInfo si;
+    if constexpr (PLAIN) si = t.seg[g];
+    else si = segment(t, g);
     const char* pre[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-        pre[i] = PLAIN ? static_cast<const char*>(t.grad[static_cast<int64_t>(g) * t.R + i]) : row[i];
+    for (int i = 0; i < 8; ++i) {
+        if constexpr (PLAIN) pre[i] = static_cast<const char*>(t.grad[static_cast<int64_t>(g) * t.R + i]);
+        else pre[i] = row[i];
+    }
     // (behind a gate that gave up this row may be an earlier iteration's: it is not looked at then)
     const uint64_t mask = MASKED && local != nullptr ? cload(local + g) : 0;
     if (gate_word == tag) return;          // the gate in front of this launch gave up
@@ -676,7 +728,8 @@ __device__ __forceinline__ void fused_tile(const SegTables& t, int64_t tile, int
     // replica 0's tensor -- or the slot in the flat bucket -- starts this many elements past a 16-byte boundary
     const int sh = (OUT == OUT_FLAT ? static_cast<int>(si.flat_byte & 15) : si.lead_bytes()) / ES;
     const bool src_aligned = si.congruent();   // every replica's tensor sits at the same offset modulo 16
-    char* const outp = OUT == OUT_BINARY32 ? pointer_row(t.out, g, 1)[0] : nullptr;
+    char* outp = nullptr;
+    if constexpr (OUT == OUT_BINARY32) outp = pointer_row(t.out, g, 1)[0];
     char* const slot = OUT == OUT_FLAT ? flat.slab0 + si.flat_byte : nullptr;
     const int64_t e0 = (tile - si.tile0) * SPAN - sh;
 
@@ -715,7 +768,8 @@ __device__ __forceinline__ void fused_tile(const SegTables& t, int64_t tile, int
         if (all_used)
             sum_interior_pre<DT, NT, U>(
                 pre, byte0, [&](int r) {
-                    return (FORM == 2 ? static_cast<const char*>(t.grad[static_cast<int64_t>(g) * t.R + r]) : row[r]) + byte0;
+                    if constexpr (FORM == 2) return static_cast<const char*>(t.grad[static_cast<int64_t>(g) * t.R + r]) + byte0;
+                    else return static_cast<const char*>(row[r]) + byte0;
                 }, R, lane_off, acc);
         else if constexpr (MASKED)
             sum_interior_used<DT, NT, U>(row, byte0, used, lane_off, acc);
@@ -832,8 +886,8 @@ __device__ __forceinline__ void fused_tile(const SegTables& t, int64_t tile, int
     }
 }
 
-template <int DT, bool NT, int U, int OUT, bool MASKED, int FORM = 0>
-__global__ __launch_bounds__(BLOCK) void fused_reduce_kernel(SegTables t, int64_t tile_base, int R,
+template <int DT, bool NT, int U, int OUT, bool MASKED, int FORM = 0, typename Tables = SegTables>
+__global__ __launch_bounds__(BLOCK) void fused_reduce_kernel(Tables t, int64_t tile_base, int R,
                                                              int nwrite,
                                                              const uint64_t* __restrict__ local,
                                                              int keep_unused, Scale sc, FlatBuckets flat,
@@ -853,8 +907,8 @@ __global__ __launch_bounds__(BLOCK) void fused_reduce_kernel(SegTables t, int64_
 // R = 64 17.5 / 12.1, bfloat16 R = 8 5.6 / 4.4, R = 16 7.8 / 5.7, R = 64 20.7 / 13.7.
 // Per byte a slice costs more than a tile (a whole wave per KiB of a replica, 4-byte stores): slice_tiles() has
 // the line.  Half as long slices, two replicas per load instruction, took three times as long.
-template <int DT, int C, int OUT, bool MASKED>
-__global__ __launch_bounds__(BLOCK) void slice_reduce_kernel(SegTables t, int64_t tile_base, int R, int nwrite,
+template <int DT, int C, int OUT, bool MASKED, typename Tables = SegTables>
+__global__ __launch_bounds__(BLOCK) void slice_reduce_kernel(Tables t, int64_t tile_base, int R, int nwrite,
                                                              const uint64_t* __restrict__ local, int keep_unused,
                                                              Scale sc, FlatBuckets flat,
                                                              const GateRecord* __restrict__ gate, uint32_t tag,
@@ -870,8 +924,8 @@ __global__ __launch_bounds__(BLOCK) void slice_reduce_kernel(SegTables t, int64_
     signal_dispatch(sig);
     const uint32_t gate_word = gate != nullptr ? cload(&gate->failed_tag) : ~tag;
     const int64_t tile = tile_base + blockIdx.x / SLICES;
-    const int g = cload(t.tile_seg + tile);
-    const PointerRow row = pointer_row(t.grad, g, t.R);
+    const int g = segment_of(t, tile);
+    const auto row = gradients_of(t, g);
     const SegInfo si = segment(t, g);
     const uint64_t mask = MASKED && local != nullptr ? cload(local + g) : 0;
     if (gate_word == tag) return;
@@ -965,7 +1019,7 @@ __global__ __launch_bounds__(BLOCK) void slice_reduce_kernel(SegTables t, int64_
         in[k] = e + k >= 0 && e + k < numel;
         all = all && in[k];
     }
-    if (OUT == OUT_BINARY32) {
+    if constexpr (OUT == OUT_BINARY32) {
         char* const out = pointer_row(t.out, g, 1)[0];
 #pragma unroll
         for (int k = 0; k < EPW; ++k)
@@ -1542,6 +1596,46 @@ hipError_t launch_fused_reduce(int dtype, const SegTables& t, int64_t tile_base,
         case 0: return fused_dispatch<0, OUT_GRAD>(nontemporal, ntiles, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
         case 1: return fused_dispatch<1, OUT_GRAD>(nontemporal, ntiles, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
         case 2: return fused_dispatch<2, OUT_GRAD>(nontemporal, ntiles, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+template <int DT, int N>
+static hipError_t value_launch(const WordTables& words, int64_t tile_base, int64_t ntiles, int R, Scale sc, hipStream_t s) {
+    ArgTables<N> t;
+    std::memcpy(t.w, words.words, sizeof(uint64_t) * words.count(R));
+    t.n = words.n;
+    t.R = R;
+    t.at = words.n;
+    t.step = words.regular ? 0 : R;
+    t.dist = words.regular ? words.n + R : 0;
+    const FlatBuckets flat{nullptr, 0};
+    const DispatchSignal sig{nullptr, 0};
+    if (ntiles > slice_tiles(R, Fmt<DT>::ES, false))
+        return launch(fused_reduce_kernel<DT, true, RU, OUT_GRAD, false, 0, ArgTables<N>>, dim3(static_cast<unsigned>(ntiles)), edge_lds(R), s,
+                      t, tile_base, R, 1, nullptr, 0, sc, flat, nullptr, 0u, sig);
+    const dim3 grid(static_cast<unsigned>(ntiles * SLICES));
+    const unsigned lds = static_cast<unsigned>(R * SLICE_BYTES);
+    if (R <= 16) return launch(slice_reduce_kernel<DT, 4, OUT_GRAD, false, ArgTables<N>>, grid, lds, s, t, tile_base, R, 1, nullptr, 0, sc, flat, nullptr, 0u, sig);
+    return launch(slice_reduce_kernel<DT, MAX_REPLICAS / 4, OUT_GRAD, false, ArgTables<N>>, grid, lds, s, t, tile_base, R, 1, nullptr, 0, sc, flat, nullptr, 0u, sig);
+}
+
+template <int DT>
+static hipError_t value_dispatch(const WordTables& t, int64_t tile_base, int64_t ntiles, int R, Scale sc, hipStream_t s) {
+    const int count = t.count(R);
+    if (count <= 128) return value_launch<DT, 128>(t, tile_base, ntiles, R, sc, s);
+    if (count <= 256) return value_launch<DT, 256>(t, tile_base, ntiles, R, sc, s);
+    return value_launch<DT, kTableWords>(t, tile_base, ntiles, R, sc, s);
+}
+
+hipError_t launch_fused_reduce_by_value(int dtype, const WordTables& t, int64_t tile_base, int64_t ntiles, int R, Scale sc,
+                                        hipStream_t s) {
+    if (ntiles <= 0) return hipSuccess;
+    if (t.n <= 0 || R <= 0 || R > MAX_REPLICAS || t.count(R) > kTableWords) return hipErrorInvalidValue;
+    switch (dtype) {
+        case 0: return value_dispatch<0>(t, tile_base, ntiles, R, sc, s);
+        case 1: return value_dispatch<1>(t, tile_base, ntiles, R, sc, s);
+        case 2: return value_dispatch<2>(t, tile_base, ntiles, R, sc, s);
         default: return hipErrorInvalidValue;
     }
 }

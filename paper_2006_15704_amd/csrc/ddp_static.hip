@@ -95,7 +95,7 @@ struct AddressRange {
     uintptr_t first = UINTPTR_MAX, end = 0;      // empty: end == 0
 };
 
-bool writes_are_apart(const ddp::BucketPlan& plan, void* const* grad_ptrs, int32_t R) {
+bool writes_are_apart(const ddp::BucketPlan& plan, void* const* grad_ptrs, int32_t R, const uintptr_t* shift) {
     const size_t n = plan.params.size();
     auto bytes_of = [&](size_t i) { return static_cast<uintptr_t>(plan.params[i].numel) * ddp::elem_size(plan.params[i].dtype); };
     AddressRange own;
@@ -116,7 +116,8 @@ bool writes_are_apart(const ddp::BucketPlan& plan, void* const* grad_ptrs, int32
     for (int64_t r = 1; r < R; ++r) {
         void* const* row = grad_ptrs + r * static_cast<int64_t>(n);
         AddressRange other;
-        for (size_t i = 0; i < n; ++i) {
+        if (shift != nullptr && own.end != 0) other = AddressRange{own.first + shift[r], own.end + shift[r]};
+        else for (size_t i = 0; i < n; ++i) {
             const uintptr_t bytes = bytes_of(i), a = reinterpret_cast<uintptr_t>(row[i]);
             if (bytes == 0) continue;
             other.first = std::min(other.first, a);
@@ -133,6 +134,23 @@ bool writes_are_apart(const ddp::BucketPlan& plan, void* const* grad_ptrs, int32
     std::sort(sorted.begin(), sorted.end());
     for (size_t k = 1; k < sorted.size(); ++k)
         if (sorted[k].first < sorted[k - 1].second) return false;
+    return true;
+}
+
+// Whether every replica's tensors lie alike (views into one buffer per replica, say): shift[r] = what those of replica r lie
+// further on than replica 0's.  Tensors without elements do not count.
+bool replicas_alike(const ddp::BucketPlan& plan, void* const* grad_ptrs, int32_t R, uintptr_t* shift, int64_t* base) {
+    const int64_t n = static_cast<int64_t>(plan.params.size());
+    int64_t b = 0;
+    while (b < n && plan.params[b].numel == 0) ++b;
+    if (b == n) return false;
+    *base = b;
+    for (int64_t r = 0; r < R; ++r) {
+        void* const* row = grad_ptrs + r * n;
+        shift[r] = reinterpret_cast<uintptr_t>(row[b]) - reinterpret_cast<uintptr_t>(grad_ptrs[b]);
+        for (int64_t i = b + 1; i < n; ++i)
+            if (reinterpret_cast<uintptr_t>(row[i]) != reinterpret_cast<uintptr_t>(grad_ptrs[i]) + shift[r] && plan.params[i].numel != 0) return false;
+    }
     return true;
 }
 
@@ -183,19 +201,23 @@ extern "C" int32_t ddp_sync_static(int32_t R, int32_t device, void* stream, int3
         for (int32_t i = 0; i < n; ++i) {
             const void* p = grad_ptrs[r * n + i];
             if (numel[i] > 0 && !p) return fail_without_context(DDP_ERR_ARG, "ddp_sync_static: null gradient pointer");
-            if (reinterpret_cast<uintptr_t>(p) % static_cast<uintptr_t>(ddp::elem_size(dtype[i])) != 0)
+            if ((reinterpret_cast<uintptr_t>(p) & static_cast<uintptr_t>(ddp::elem_size(dtype[i]) - 1)) != 0)
                 return fail_without_context(DDP_ERR_ARG, "ddp_sync_static: gradient pointer not aligned to its element size");
         }
     plan.assign(cap_bytes, nullptr);
     ddp::HostTables ht;
-    ddp::build_host_tables(plan, grad_ptrs, R, ht);
+    uintptr_t shift_of[DDP_MAX_REPLICAS];
+    int64_t first = 0;
+    const uintptr_t* const shift = replicas_alike(plan, grad_ptrs, R, shift_of, &first) ? shift_of : nullptr;
+    ddp::build_layout(plan, grad_ptrs, R, ht, nullptr, shift);
     const int32_t nb = static_cast<int32_t>(plan.buckets.size());
+    const int64_t ntiles = ht.tile0[n];
 
     // layout of the scratch array: [segment records | pointer rows | tile map | pad to 256 | R + 1 slabs]
     const size_t seg_bytes = sizeof(ddp::SegInfo) * static_cast<size_t>(n);
     // (eight entries of padding: a row that is read sixteen wide reaches into the tile map and the slabs behind it)
     const size_t ptr_bytes = sizeof(void*) * (static_cast<size_t>(R) * static_cast<size_t>(n) + 8);
-    const size_t map_bytes = sizeof(int32_t) * ht.tile_seg.size();
+    const size_t map_bytes = sizeof(int32_t) * static_cast<size_t>(ntiles);
     const size_t table_bytes = static_cast<size_t>(ddp::round_up_to(static_cast<int64_t>(seg_bytes + ptr_bytes + map_bytes), 256));
     const size_t slab_bytes = static_cast<size_t>(ht.slab_stride) * static_cast<size_t>(R + 1);
     if (table_bytes + slab_bytes > DDP_STATIC_SCRATCH_BYTES)
@@ -205,9 +227,55 @@ extern "C" int32_t ddp_sync_static(int32_t R, int32_t device, void* stream, int3
 
     hipStream_t s = static_cast<hipStream_t>(stream);
     HIPCHK0(hipSetDevice(device));
+    const ddp::Scale sc = ddp::make_scale(R);
+
+    // Nobody sees the flat buckets of this call, so the averages go straight into replica 0's
+    // tensors: (R + 1) b bytes in one launch per run of buckets of one element type, instead of a
+    // fill, the copies, a reduction per bucket and the write-back, (4 R + 5) b in all.  The bits are
+    // the same.  A tensor that is written while another block still reads it (one tensor under two
+    // parameters or as two replicas) must not be seen half averaged: such lists take the flat buckets.
+    // The first 48 ResNet-50 tensors, R = 4: 37 -> 25 us a call; 2e6 elements, R = 2: 50 -> 20.  Many
+    // replicas (host arrays ready, flat buckets / so): R = 17, 500 bfloat16 elements in three tensors 18 / 9.0; R = 32,
+    // 100000 in thirty 32 / 20; R = 64, 500 22 / 10, 39000 in thirty 46 / 34; binary32, R = 64, 100000 56 / 33.
+    const bool in_place = writes_are_apart(plan, grad_ptrs, R, shift);
+    auto for_each_run = [&](auto launch_tiles) -> hipError_t {       // in bucket order (Section 3.2.3)
+        for (int32_t b = 0; b < nb;) {
+            int32_t e = b + 1;
+            while (e < nb && plan.buckets[e].dtype == plan.buckets[b].dtype) ++e;
+            const int64_t tile0 = ht.tile0[plan.buckets[b].seg_begin];
+            const int64_t tile1 = e < nb ? ht.tile0[plan.buckets[e].seg_begin] : ntiles;
+            const hipError_t err = launch_tiles(plan.buckets[b].dtype, tile0, tile1 - tile0);
+            if (err != hipSuccess) return err;
+            b = e;
+        }
+        return hipSuccess;
+    };
+    // Tables of up to 448 words travel in the arguments of the kernel that uses them: 2 n + R words where the replicas lie
+    // alike, else n (R + 1).  (Written to the scratch array they take a launch for every 3 KiB, each of 3.8 us of the host, and as many
+    // hand-overs.)  Us a call, written / by value: R = 2, four tensors 6.1 / 4.5; R = 24, 24 tensors 15.3 / 10.2, 44 25.2 / 14.2; R = 16, 20
+    // tensors 12.3 / 7.7; R = 64, 59 tensors 70 / 38 (the list's way through Python is 35 of them); the first 48 ResNet-50 tensors, R = 4,
+    // 11.6 / 7.3 (16.1 / 7.3 in another process); 2e6 elements, R = 2 10.8 / 6.7.
+    ddp::WordTables by_value{nullptr, n, shift != nullptr};
+    if (in_place && by_value.count(R) <= ddp::kTableWords) {
+        uint64_t words[ddp::kTableWords];
+        by_value.words = words;
+        const uintptr_t base0 = reinterpret_cast<uintptr_t>(grad_ptrs[first]);
+        for (int32_t g = 0; g < n; ++g) {
+            const ddp::SegInfo& si = ht.seg[g];          // (numel < 2^24, the scratch array's limit)
+            words[g] = static_cast<uint64_t>(si.numel) | static_cast<uint64_t>(si.congruent() ? 1 : 0) << 31 | static_cast<uint64_t>(si.tile0) << 32;
+            if (shift != nullptr) words[n + R + g] = reinterpret_cast<uintptr_t>(grad_ptrs[si.param]) - base0;
+            else for (int64_t r = 0; r < R; ++r) words[n + static_cast<int64_t>(g) * R + r] = reinterpret_cast<uintptr_t>(grad_ptrs[r * n + si.param]);
+        }
+        for (int32_t r = 0; shift != nullptr && r < R; ++r) words[n + r] = base0 + shift[r];
+        HIPCHK0(for_each_run([&](int32_t dt, int64_t tile0, int64_t count) {
+            return ddp::launch_fused_reduce_by_value(dt, by_value, tile0, count, R, sc, s);
+        }));
+        return nb;
+    }
+
     unsigned char* base = nullptr;
     HIPCHK0(scratch_on(device, &base));
-
+    ddp::build_host_tables(plan, grad_ptrs, R, ht);
     std::vector<unsigned char> host(seg_bytes + ptr_bytes + map_bytes);
     std::memcpy(host.data(), ht.seg.data(), seg_bytes);
     std::memcpy(host.data() + seg_bytes, ht.grad.data(), ptr_bytes);
@@ -222,27 +290,11 @@ extern "C" int32_t ddp_sync_static(int32_t R, int32_t device, void* stream, int3
     t.R = R;
     char* slabs = reinterpret_cast<char*>(base + table_bytes);
 
-    const int64_t ntiles = ht.tile0[n];
-    const ddp::Scale sc = ddp::make_scale(R);
-    if (writes_are_apart(plan, grad_ptrs, R)) {
-        // Nobody sees the flat buckets of this call, so the averages go straight into replica 0's
-        // tensors: (R + 1) b bytes in one launch per run of buckets of one element type, instead of a
-        // fill, the copies, a reduction per bucket and the write-back, (4 R + 5) b in all.  The bits are
-        // the same.  A tensor that is written while another block still reads it (one tensor under two
-        // parameters or as two replicas) must not be seen half averaged: such lists go on below.
-        // The first 48 ResNet-50 tensors, R = 4: 37 -> 25 us a call; 2e6 elements, R = 2: 50 -> 20.  Many
-        // replicas (host arrays ready, flat buckets / so): R = 17, 500 bfloat16 elements in three tensors 18 / 9.0; R = 32,
-        // 100000 in thirty 32 / 20; R = 64, 500 22 / 10, 39000 in thirty 46 / 34; binary32, R = 64, 100000 56 / 33.
-        for (int32_t b = 0; b < nb;) {       // in bucket order (Section 3.2.3)
-            int32_t e = b + 1;
-            while (e < nb && plan.buckets[e].dtype == plan.buckets[b].dtype) ++e;
-            const int64_t tile0 = ht.tile0[plan.buckets[b].seg_begin];
-            const int64_t tile1 = e < nb ? ht.tile0[plan.buckets[e].seg_begin] : ntiles;
-            HIPCHK0(ddp::launch_fused_reduce(plan.buckets[b].dtype, t, tile0, tile1 - tile0, R, 1, nullptr, false, sc,
-                                             true, 0, ddp::FlatBuckets{nullptr, 0}, nullptr, 0,
-                                             ddp::DispatchSignal{nullptr, 0}, s));
-            b = e;
-        }
+    if (in_place) {
+        HIPCHK0(for_each_run([&](int32_t dt, int64_t tile0, int64_t count) {
+            return ddp::launch_fused_reduce(dt, t, tile0, count, R, 1, nullptr, false, sc, true, 0, ddp::FlatBuckets{nullptr, 0}, nullptr, 0,
+                                            ddp::DispatchSignal{nullptr, 0}, s);
+        }));
         return nb;
     }
     // The array keeps what the previous call left in it.  The flat buckets are

@@ -24,10 +24,12 @@ struct HostTables {
 
 inline int64_t round_up_to(int64_t x, int64_t a) { return (x + a - 1) / a * a; }
 
+// Slab layout, tile numbering and segment records.
 // grad_ptrs: [R][n] in registration order (the layout of ddp_register_params).
 // out_ptrs: [n] binary32 output tensors in registration order, or null.
-inline void build_host_tables(const BucketPlan& plan, void* const* grad_ptrs, int R, HostTables& h,
-                              void* const* out_ptrs = nullptr) {
+// shift: [R] or null: what replica r's tensors lie further on in memory than replica 0's, where that is the same for all of them.
+inline void build_layout(const BucketPlan& plan, void* const* grad_ptrs, int R, HostTables& h, void* const* out_ptrs = nullptr,
+                         const uintptr_t* shift = nullptr) {
     const int32_t n = static_cast<int32_t>(plan.params.size());
     const int32_t nb = static_cast<int32_t>(plan.buckets.size());
     h.bucket_slab_off.resize(nb);
@@ -40,10 +42,11 @@ inline void build_host_tables(const BucketPlan& plan, void* const* grad_ptrs, in
         off = round_up_to(off + h.bucket_vecs[b] * 16, 256);
     }
     h.slab_stride = round_up_to(off > 0 ? off : 256, 4096);
+    bool shifted = shift == nullptr;            // some replica may lie elsewhere modulo 16 than replica 0
+    for (int r = 0; r < R && !shifted; ++r) shifted = (shift[r] & 15u) != 0;
 
     h.tile0.assign(n + 1, 0);
     h.seg.assign(n, SegInfo{});
-    h.grad.assign(static_cast<size_t>(R) * n + 16, nullptr);
     h.out.assign(out_ptrs ? n : 0, nullptr);
     for (int32_t b = 0; b < nb; ++b) {
         const BucketInfo& bk = plan.buckets[b];
@@ -57,12 +60,11 @@ inline void build_host_tables(const BucketPlan& plan, void* const* grad_ptrs, in
             // flat slab and each replica's gradient tensor
             int lead = static_cast<int>(flat_byte & 15);
             const uintptr_t a0 = reinterpret_cast<uintptr_t>(grad_ptrs[i]);
+            lead = std::max(lead, static_cast<int>(a0 & 15u));
             bool cong = true;
-            for (int64_t r = 0; r < R; ++r) {
-                void* ptr = grad_ptrs[r * n + i];
-                const uintptr_t a = reinterpret_cast<uintptr_t>(ptr);
-                h.grad[static_cast<size_t>(g) * R + r] = ptr;
-                if (static_cast<int>(a & 15u) > lead) lead = static_cast<int>(a & 15u);
+            for (int64_t r = 1; shifted && r < R; ++r) {
+                const uintptr_t a = reinterpret_cast<uintptr_t>(grad_ptrs[r * n + i]);
+                lead = std::max(lead, static_cast<int>(a & 15u));
                 cong = cong && ((a ^ a0) & 15u) == 0;
             }
             h.tile0[g + 1] = h.tile0[g] + tiles_for(p.numel, es, lead);
@@ -78,6 +80,16 @@ inline void build_host_tables(const BucketPlan& plan, void* const* grad_ptrs, in
             }
         }
     }
+}
+
+// ... and the two tables that grow with R n and with the bytes.
+inline void build_host_tables(const BucketPlan& plan, void* const* grad_ptrs, int R, HostTables& h,
+                              void* const* out_ptrs = nullptr) {
+    build_layout(plan, grad_ptrs, R, h, out_ptrs);
+    const int32_t n = static_cast<int32_t>(plan.params.size());
+    h.grad.assign(static_cast<size_t>(R) * n + 16, nullptr);
+    for (int32_t g = 0; g < n; ++g)
+        for (int64_t r = 0; r < R; ++r) h.grad[static_cast<size_t>(g) * R + r] = grad_ptrs[r * n + h.seg[g].param];
     h.tile_seg.resize(static_cast<size_t>(h.tile0[n]));
     for (int32_t g = 0; g < n; ++g)
         for (int64_t tl = h.tile0[g]; tl < h.tile0[g + 1]; ++tl) h.tile_seg[tl] = g;

@@ -238,3 +238,45 @@ def test_static_entry_point_with_tensors_in_any_order_of_addresses(order, n, sha
         o, b = grads.offsets[at[i]], grads.nbytes(at[i])
         assert result[0][o:o + b].tobytes() == want[i].tobytes(), f"parameter {i}"
         assert result[1][o:o + b].tobytes() == listed[1][i].tobytes()
+
+
+# Tables that travel in the launch's arguments: n (R + 1) words, or 2 n + R where the replicas lie alike; sizes on both sides of
+# the 128, 256 and 448 words that an instance of the kernel holds, of slices, and of 64 segments.
+@pytest.mark.parametrize("alike,R,n", [(False, 1, 64), (False, 1, 65), (False, 3, 64), (False, 3, 65), (False, 7, 56), (False, 7, 57),
+                                       (False, 64, 6), (False, 64, 7), (False, 1, 224), (True, 2, 63), (True, 2, 64), (True, 16, 120),
+                                       (True, 17, 120), (True, 64, 192), (True, 64, 193), (True, 8, 220), (True, 8, 221), (True, 5, 1)])
+@pytest.mark.parametrize("large", [False, True])
+def test_static_entry_point_with_tables_in_every_form(alike, R, n, large):
+    d, harness = lib()
+    import torch
+    stream = torch.cuda.Stream()
+    rng = np.random.default_rng(1000 * R + n + large)
+    numel = [int(x) for x in rng.integers(1, 40, size=n)]
+    dtypes = [int(t) for t in np.sort(rng.integers(0, 3, size=n))]
+    if n > 4:
+        numel[2] = numel[n - 1] = 0               # tensors without elements, also at the end
+    if large:
+        numel[0], numel[n // 2] = 100003 if R < 40 else 30011, 3 * 4096
+    cap = 4096
+    reps = [[workloads.gaussian_grad(70, r, 0, p, numel[p], 1.0, dtypes[p]) for p in range(n)] for r in range(R)]
+    want, _, _ = oracle.synchronize(numel, dtypes, cap, reps)
+    gaps = rng.integers(0, 5, size=(1 if alike else R, n)) * 4
+    grads = [harness.DeviceGrads(numel, dtypes, 1, align=4, skew=[int(x) for x in gaps[0 if alike else r]],
+                                 replica_skew=[4 * (r % 4)], fill=0xFF) for r in range(R)]
+    for r in range(R):
+        raw = np.full(grads[r].bufs[0].numel(), 0xFF, dtype=np.uint8)
+        for i in range(n):
+            o = grads[r].offsets[i] + grads[r].replica_skew[0]
+            raw[o:o + grads[r].nbytes(i)] = reps[r][i].view(np.uint8)
+        grads[r].bufs[0].copy_(torch.from_numpy(raw))
+    ptrs = [grads[r].ptr(0, i) if numel[i] else None for r in range(R) for i in range(n)]
+    torch.cuda.synchronize()
+    for _ in range(1 if R > 1 else 2):                    # (R = 1: the average is the tensor itself)
+        d.ddp_sync_static(R, 0, stream.cuda_stream, numel, dtypes, ptrs, cap)
+    stream.synchronize()
+    for r in range(R):
+        raw = grads[r].bufs[0].cpu().numpy()
+        for i in range(n):
+            o = grads[r].offsets[i] + grads[r].replica_skew[0]
+            x = want[i] if r == 0 else reps[r][i]
+            assert raw[o:o + grads[r].nbytes(i)].tobytes() == x.tobytes(), f"replica {r} parameter {i}"
