@@ -665,18 +665,24 @@ int32_t launch_range(ddp_ctx* c, int32_t first, int32_t last, Target target) {
     // Participation masks travel to the device only for launches that hold a
     // zero bit (a replica that did not use a parameter, or a parameter nobody
     // marked); everything else runs without a mask table.
-    const uint64_t* d_flags = nullptr;
+    ddp::Masks masks;
+    uint64_t mask_words[ddp::kMaskWords];
     bool need_flags = false;
     for (int32_t b = first; b <= last; ++b) need_flags = need_flags || c->bucket_zero[b] != 0;
-    if (need_flags) {
+    const bool two_kernels = c->pipeline == DDP_PIPELINE_STAGED && (c->timing == 1 || split_pass(c, bf.dtype, ntiles));
+    if (need_flags && !two_kernels && ddp::masks_fit(c->R, seg_end - seg_begin)) {
+        ddp::pack_masks(c->local_cur.data() + seg_begin, seg_end - seg_begin, c->R, mask_words);
+        masks.words = mask_words;
+        masks.first = seg_begin;
+    } else if (need_flags) {
         // After the ordering above the stream is also behind the previous iteration's readers of
         // the table (or its gate gave up and nothing is written).
-        const uint64_t* masks;
-        const int32_t rcm = stage_masks(c, seg_begin, seg_end, &masks);
+        const uint64_t* host;
+        const int32_t rcm = stage_masks(c, seg_begin, seg_end, &host);
         if (rcm != DDP_OK) return rcm;
-        HIPCHK(c, ddp::launch_mask_write(c->d_local + seg_begin, masks, seg_end - seg_begin,
+        HIPCHK(c, ddp::launch_mask_write(c->d_local + seg_begin, host, seg_end - seg_begin,
                                          gate, static_cast<uint32_t>(c->iteration + 1), st));
-        d_flags = c->d_local;
+        masks.table = c->d_local;
         look_at_progress(c);
     }
     const ddp::Scale sc = make_scale(c->R);
@@ -693,7 +699,7 @@ int32_t launch_range(ddp_ctx* c, int32_t first, int32_t last, Target target) {
     }
     if (c->timing == 2) c->timed[c->open_group].bucket += 1;   // counts the launches
     const uint32_t tag = static_cast<uint32_t>(c->iteration + 1);
-    if (c->pipeline == DDP_PIPELINE_STAGED && (c->timing == 1 || split_pass(c, bf.dtype, ntiles))) {
+    if (two_kernels) {
         // pack and reduce as launches of their own; timed one by one, each is stamped
         char* in0 = c->slabs + c->bucket_slab_off[first];
         char* out = c->slabs + static_cast<int64_t>(c->R) * c->slab_stride + c->bucket_slab_off[first];
@@ -701,7 +707,7 @@ int32_t launch_range(ddp_ctx* c, int32_t first, int32_t last, Target target) {
         const int64_t nvec = (c->bucket_slab_off[last] - c->bucket_slab_off[first]) / 16 + c->bucket_vecs[last];
         if ((rc = timed_begin(c, DDP_K_PACK, id, st, &slot)) != DDP_OK) return rc;
         HIPCHK(c, ddp::launch_pack(c->tables, tile_base, ntiles, c->slabs, c->slab_stride, c->R,
-                                   d_flags, gate, tag, st));
+                                   masks.table, gate, tag, st));
         look_at_progress(c);
         if ((rc = timed_end(c, slot, st)) != DDP_OK) return rc;
         if ((rc = timed_begin(c, DDP_K_REDUCE, id, st, &slot)) != DDP_OK) return rc;
@@ -714,7 +720,7 @@ int32_t launch_range(ddp_ctx* c, int32_t first, int32_t last, Target target) {
         const ddp::FlatBuckets flat{staged ? c->slabs : nullptr, staged ? c->slab_stride : 0};
         if ((rc = timed_begin(c, DDP_K_REDUCE, id, st, &slot)) != DDP_OK) return rc;
         HIPCHK(c, ddp::launch_fused_reduce(bf.dtype, c->tables, tile_base, ntiles, c->R,
-                                           c->write_all ? c->R : 1, d_flags, c->find_unused != 0, sc,
+                                           c->write_all ? c->R : 1, masks, c->find_unused != 0, sc,
                                            c->nontemporal != 0, occupancy_lds(c, bytes, staged),
                                            flat, gate, tag, sig, st));
         if ((rc = timed_end(c, slot, st)) != DDP_OK) return rc;
@@ -1461,12 +1467,15 @@ int32_t ddp_finalize_backward(ddp_ctx* c) {
             // The bitmap step of Section 4.2: the host bitmap goes to the device
             // with the launch that ORs it over the replicas, which yields the
             // parameters that somebody used.
-            const uint64_t* masks;
-            const int32_t rc = stage_masks(c, 0, n, &masks);
-            if (rc != DDP_OK) return rc;
-            HIPCHK(c, ddp::launch_bitmap_or(c->d_local, c->d_global, c->h_global, masks, n, c->backward));
+            const uint64_t* masks = c->local_cur.data();
+            const bool by_value = ddp::masks_fit(c->R, n);
+            if (!by_value) {
+                const int32_t rc = stage_masks(c, 0, n, &masks);
+                if (rc != DDP_OK) return rc;
+            }
+            HIPCHK(c, ddp::launch_bitmap_or(c->d_local, c->d_global, c->h_global, masks, n, c->R, c->backward));
             HIPCHK(c, hipEventRecord(c->ev_global[c->iteration & 1], c->backward));
-            c->masks_in_flight[c->iteration & 1] = n > ddp::kMasksByValue;
+            c->masks_in_flight[c->iteration & 1] = n > ddp::kMasksByValue;     // (of this launch, or of a bucket's)
         }
         const bool staged = c->pipeline == DDP_PIPELINE_STAGED;
         if (c->gates_in_iter > 0) {

@@ -155,8 +155,22 @@ hipError_t launch_flat_reduce(int dtype, const char* in0, int64_t stride, char* 
                               int R, Scale sc, bool nontemporal, unsigned lds,
                               const GateRecord* gate, uint32_t tag, DispatchSignal sig, hipStream_t s);
 
+// Participation masks (bit r: replica r used the parameter) of the segments of a launch: none = every replica used every
+// parameter; a table in device memory with one for every segment; or words that travel in the launch's arguments, a
+// mask in the lowest 8, 16, 32 or 64 bits that hold R, those of segment `first` first.
+constexpr int kMaskWords = 96;
+struct Masks {
+    const uint64_t* table = nullptr;
+    const uint64_t* words = nullptr;
+    int first = 0;
+};
+inline int mask_shift(int R) { return R <= 8 ? 3 : R <= 16 ? 4 : R <= 32 ? 5 : 6; }
+inline bool masks_fit(int R, int64_t count) { return (count << mask_shift(R)) <= int64_t(kMaskWords) * 64; }
+// words[0 .. kMaskWords) = masks[0 .. count), packed.
+void pack_masks(const uint64_t* masks, int count, int R, uint64_t* words);
+
 // K2 (fused): gather R replicas through the segment table, reduce, scatter to
-// the gradient tensors of replicas [0, nwrite).  local / keep_unused as above
+// the gradient tensors of replicas [0, nwrite).  keep_unused as above
 // (a replica with bit 0 contributes +0 and is not read; a parameter nobody
 // used is skipped with keep_unused, else written as zeros).
 // With flat.slab0 set (staged pipeline) the launch does K1's and K2's work in
@@ -164,7 +178,7 @@ hipError_t launch_flat_reduce(int dtype, const char* in0, int64_t stride, char* 
 // (zeros for a replica that did not use the parameter) and the average goes to
 // the averaged bucket; nwrite and keep_unused do not matter then.
 hipError_t launch_fused_reduce(int dtype, const SegTables& t, int64_t tile_base, int64_t ntiles,
-                               int R, int nwrite, const uint64_t* local, bool keep_unused, Scale sc,
+                               int R, int nwrite, const Masks& masks, bool keep_unused, Scale sc,
                                bool nontemporal, unsigned lds, FlatBuckets flat,
                                const GateRecord* gate, uint32_t tag, DispatchSignal sig, hipStream_t s);
 // (with t.out set -- 16-bit gradients, binary32 averages written to t.out -- nwrite must be 1)
@@ -258,8 +272,8 @@ hipError_t launch_mask_write(uint64_t* dst, const uint64_t* masks, int count, co
                              hipStream_t s);
 
 // For g < G: local[g] = masks[g], global[g] = host_global[g] = OR of its bits (the bitmap AllReduce of
-// Section 4.2).  masks as above; host_global: pinned.
-hipError_t launch_bitmap_or(uint64_t* local, uint8_t* global, uint8_t* host_global, const uint64_t* masks, int G,
+// Section 4.2).  masks as above, of R replicas; host_global: pinned.
+hipError_t launch_bitmap_or(uint64_t* local, uint8_t* global, uint8_t* host_global, const uint64_t* masks, int G, int R,
                             hipStream_t s);
 
 // dst[0 .. count) = src[0 .. count) (pinned memory; 16-byte aligned both, count even), then *done = ticket (pinned).

@@ -149,6 +149,34 @@ __device__ __forceinline__ SegInfo segment(const ArgTables<N>& t, int g) {
     return si;
 }
 
+// Where a launch's participation masks are (Masks).  In the arguments they spare it the kernel that writes them to the table:
+// one launch of three or four less for the host (3.8 us), and a hand-over on the stream (2.5 us) in front of the reduction.
+// One mark per call, us a synchronization, table / arguments: ResNet-50, R = 8, 0.7 of the flags set 140 / 134; 300000 elements in forty 32 KiB
+// buckets, R = 8 348 / 165 to 210; bfloat16, 6 MB in seven buckets, R = 4 85 / 47 to 60; 2 MiB buckets, R = 8 82 / 58 to 68; a tenth of the parameters
+// never marked, R = 4, 0.4 MB 18.9 / 14.2; all marks in one call, binary16, R = 8, 20 MB 36.6 / 33.1.
+struct NoMasks {
+    static constexpr bool ANY = false;
+    __device__ __forceinline__ bool present() const { return false; }
+    __device__ __forceinline__ uint64_t of(int) const { return 0; }
+};
+struct MaskTable {
+    static constexpr bool ANY = true;
+    const uint64_t* local;                 // null: every replica used every parameter
+    __device__ __forceinline__ bool present() const { return local != nullptr; }
+    __device__ __forceinline__ uint64_t of(int g) const { return cload(local + g); }
+};
+struct MaskWords {
+    static constexpr bool ANY = true;
+    uint64_t m[kMaskWords];
+    int32_t first, shift;
+    __device__ __forceinline__ bool present() const { return true; }
+    __device__ __forceinline__ uint64_t of(int g) const {
+        const int bit = (g - first) << shift;
+        const uint64_t w = m[bit >> 6];
+        return shift == 6 ? w : (w >> (bit & 63)) & ((uint64_t(1) << (1 << shift)) - 1);
+    }
+};
+
 // ---- element formats ------------------------------------------------------
 template <int DT> struct Fmt;
 
@@ -670,15 +698,15 @@ __device__ __forceinline__ EdgeElements edge_elements(int64_t e0, int span, int6
 // not touch gradients that may still be incomplete; the repair launch redoes it.
 // The gate word is fetched together with the tile's tables (one round of scalar
 // loads, not one more in front of them) and looked at before any gradient is.
-// MASKED = local may be set.  Most launches have no masks, and the chunks of 1 to 8
+// Masks: most launches have none (NoMasks), and the chunks of 1 to 8
 // replicas that sum_interior_used adds make the code a third longer, at the same
 // registers: the first 101 BERT-large tensors with masks compiled in / left out, binary16,
 // R = 16, one mark per call 681 / 677 us a synchronization; bfloat16, R = 8, 329 / 327, and with
 // the averages to every replica 627.5 / 626.5.
 // FORM: see table_form.
-template <int DT, bool NT, int U, int OUT, bool MASKED, int FORM = 0, typename Tables = SegTables>
+template <int DT, bool NT, int U, int OUT, typename Masks, int FORM = 0, typename Tables = SegTables>
 __device__ __forceinline__ void fused_tile(const Tables& t, int64_t tile, int R, int nwrite,
-                                           const uint64_t* __restrict__ local, int keep_unused,
+                                           const Masks& masks, int keep_unused,
                                            const Scale& sc, const FlatBuckets& flat,
                                            const GateRecord* __restrict__ gate = nullptr, uint32_t tag = 0) {
     constexpr int ES = Fmt<DT>::ES;
@@ -714,14 +742,16 @@ __device__ __forceinline__ void fused_tile(const Tables& t, int64_t tile, int R,
         if constexpr (PLAIN) pre[i] = static_cast<const char*>(t.grad[static_cast<int64_t>(g) * t.R + i]);
         else pre[i] = row[i];
     }
-    // (behind a gate that gave up this row may be an earlier iteration's: it is not looked at then)
-    const uint64_t mask = MASKED && local != nullptr ? cload(local + g) : 0;
+    // (behind a gate that gave up this row of a table may be an earlier iteration's: it is not looked at then)
+    constexpr bool MASKED = Masks::ANY;
+    const bool masked = masks.present();
+    const uint64_t mask = masked ? masks.of(g) : 0;
     if (gate_word == tag) return;          // the gate in front of this launch gave up
     const int64_t numel = si.numel;
     // participation of the R replicas in this parameter (bit r = replica r used
     // it); without a flag table every replica did
     const uint64_t everyone = R >= 64 ? ~uint64_t(0) : ((uint64_t(1) << R) - 1);
-    const uint64_t used = MASKED && local != nullptr ? mask : everyone;
+    const uint64_t used = masked ? mask : everyone;
     if (OUT != OUT_FLAT && used == 0 && keep_unused) return;   // globally unused: the gradients stay as they are
     const bool zero = OUT != OUT_FLAT && used == 0;            // ... or become zeros (flat buckets always do)
     const bool all_used = !MASKED || used == everyone;
@@ -886,15 +916,13 @@ __device__ __forceinline__ void fused_tile(const Tables& t, int64_t tile, int R,
     }
 }
 
-template <int DT, bool NT, int U, int OUT, bool MASKED, int FORM = 0, typename Tables = SegTables>
+template <int DT, bool NT, int U, int OUT, typename Masks, int FORM = 0, typename Tables = SegTables>
 __global__ __launch_bounds__(BLOCK) void fused_reduce_kernel(Tables t, int64_t tile_base, int R,
-                                                             int nwrite,
-                                                             const uint64_t* __restrict__ local,
-                                                             int keep_unused, Scale sc, FlatBuckets flat,
+                                                             int nwrite, Masks masks, int keep_unused, Scale sc, FlatBuckets flat,
                                                              const GateRecord* __restrict__ gate,
                                                              uint32_t tag, DispatchSignal sig) {
     signal_dispatch(sig);
-    fused_tile<DT, NT, U, OUT, MASKED, FORM>(t, tile_base + blockIdx.x, R, nwrite, local, keep_unused, sc, flat, gate, tag);
+    fused_tile<DT, NT, U, OUT, Masks, FORM>(t, tile_base + blockIdx.x, R, nwrite, masks, keep_unused, sc, flat, gate, tag);
 }
 
 // A short launch.  It has fewer blocks than fill the chip and runs as long as one of them, whose time is the
@@ -907,10 +935,9 @@ __global__ __launch_bounds__(BLOCK) void fused_reduce_kernel(Tables t, int64_t t
 // R = 64 17.5 / 12.1, bfloat16 R = 8 5.6 / 4.4, R = 16 7.8 / 5.7, R = 64 20.7 / 13.7.
 // Per byte a slice costs more than a tile (a whole wave per KiB of a replica, 4-byte stores): slice_tiles() has
 // the line.  Half as long slices, two replicas per load instruction, took three times as long.
-template <int DT, int C, int OUT, bool MASKED, typename Tables = SegTables>
+template <int DT, int C, int OUT, typename Masks, typename Tables = SegTables>
 __global__ __launch_bounds__(BLOCK) void slice_reduce_kernel(Tables t, int64_t tile_base, int R, int nwrite,
-                                                             const uint64_t* __restrict__ local, int keep_unused,
-                                                             Scale sc, FlatBuckets flat,
+                                                             Masks masks, int keep_unused, Scale sc, FlatBuckets flat,
                                                              const GateRecord* __restrict__ gate, uint32_t tag,
                                                              DispatchSignal sig) {
     constexpr int ES = Fmt<DT>::ES;
@@ -927,7 +954,8 @@ __global__ __launch_bounds__(BLOCK) void slice_reduce_kernel(Tables t, int64_t t
     const int g = segment_of(t, tile);
     const auto row = gradients_of(t, g);
     const SegInfo si = segment(t, g);
-    const uint64_t mask = MASKED && local != nullptr ? cload(local + g) : 0;
+    const bool masked = masks.present();
+    const uint64_t mask = masked ? masks.of(g) : 0;
     if (gate_word == tag) return;
     const int64_t numel = si.numel;
     const int sh = (OUT == OUT_FLAT ? static_cast<int>(si.flat_byte & 15) : si.lead_bytes()) / ES;
@@ -935,7 +963,7 @@ __global__ __launch_bounds__(BLOCK) void slice_reduce_kernel(Tables t, int64_t t
     const int64_t e0 = (tile - si.tile0) * (TILE_BYTES / ES) + static_cast<int>(blockIdx.x % SLICES) * (SLICE_BYTES / ES) - sh;
     if (e0 >= numel) return;
     const uint64_t everyone = R >= 64 ? ~uint64_t(0) : ((uint64_t(1) << R) - 1);
-    const uint64_t used = MASKED && local != nullptr ? mask : everyone;
+    const uint64_t used = masked ? mask : everyone;
     if (OUT != OUT_FLAT && used == 0 && keep_unused) return;
     char* const slot = OUT == OUT_FLAT ? flat.slab0 + si.flat_byte : nullptr;
     // the ends of the segment, element by element, sixteen threads to a replica
@@ -1135,7 +1163,7 @@ __global__ __launch_bounds__(BLOCK) void repair_kernel(SegTables t, OrderState* 
         if (blockIdx.x == 0 && threadIdx.x == 0) st->repaired += 1;   // (repair launches run one after the other)
         for (int64_t i = blockIdx.x; i < r.ntiles; i += gridDim.x) {
             __syncthreads();       // the tile before is done with its elements in LDS
-            fused_tile<DT, NT, U, OUT, true>(t, r.tile_base + i, R, nwrite, local, keep_unused, sc, flat);
+            fused_tile<DT, NT, U, OUT>(t, r.tile_base + i, R, nwrite, MaskTable{local}, keep_unused, sc, flat);
         }
     }
 }
@@ -1317,14 +1345,20 @@ __global__ __launch_bounds__(1024) void pointer_copy_kernel(u32x4* __restrict__ 
 // on each side.  ResNet-50, R = 8, 0.7 of the flags set, one mark per call: 502 us a synchronization
 // with copies, flag bytes, the predicated path for every such tile and marks that pass a numpy array
 // through ctypes; 149 us with masks, sum_interior_used and marks in C.
-struct MaskPayload { uint64_t m[kMasksByValue]; };
+struct MaskPayload {
+    uint64_t m[kMasksByValue];
+    __device__ __forceinline__ uint64_t of(int i) const { return m[i]; }
+};
 
 // More are read from pinned memory, by one launch whatever their number.  A tenth of the parameters
 // never marked, R = 4, all marks in one call, us a synchronization with staged copies / a launch of
 // arguments for every 384 masks / pinned memory: 500 parameters 51 / 38 / 25, 1000 61 / 50 / 33,
 // 4000 114 / 155 / 82, 20000 404 / 683 / 345.  (Pinned memory for fewer than 384 is no faster than
 // arguments, 24 / 24, and has the host wait for the iteration before the last.)
-struct MaskPointer { const uint64_t* m; };
+struct MaskPointer {
+    const uint64_t* m;
+    __device__ __forceinline__ uint64_t of(int i) const { return m[i]; }
+};
 
 // rows [0, count) of one launch; a launch whose gate gave up reads no masks, and its rows may still
 // be read by the previous iteration's repair launch
@@ -1333,7 +1367,7 @@ __global__ __launch_bounds__(BLOCK) void mask_write_kernel(uint64_t* __restrict_
                                                            const GateRecord* __restrict__ gate, uint32_t tag) {
     if (gate != nullptr && gate->failed_tag == tag) return;
     const int i = blockIdx.x * BLOCK + threadIdx.x;
-    if (i < count) dst[i] = p.m[i];
+    if (i < count) dst[i] = p.of(i);
 }
 
 // The one-GPU form of the extra AllReduce on the unused-parameter bitmap
@@ -1344,7 +1378,7 @@ __global__ __launch_bounds__(BLOCK) void bitmap_or_kernel(uint64_t* __restrict__
                                                           uint8_t* __restrict__ host_global, Masks p, int count) {
     const int g = blockIdx.x * BLOCK + threadIdx.x;
     if (g >= count) return;
-    const uint64_t mask = p.m[g];
+    const uint64_t mask = p.of(g);
     const uint8_t any = mask != 0 ? 1 : 0;
     local[g] = mask;
     global[g] = any;
@@ -1519,58 +1553,72 @@ static int table_form(int dtype, int out, int R, int nwrite, int64_t ntiles) {
     return dtype == 0 && nwrite > 1 && (R < 3 || (R > 5 && R <= 8)) ? 1 : 0;
 }
 
-template <int DT, int OUT, bool MASKED>
+template <int DT, int OUT, typename M>
 static hipError_t fused_launch(bool nt, int64_t ntiles, unsigned lds, hipStream_t s,
                                const SegTables& t, int64_t tile_base, int R, int nwrite,
-                               const uint64_t* local, int keep, Scale sc, FlatBuckets flat,
+                               const M& masks, int keep, Scale sc, FlatBuckets flat,
                                const GateRecord* gate, uint32_t tag, DispatchSignal sig) {
     dim3 grid(static_cast<unsigned>(ntiles));
     lds = std::max(lds, edge_lds(R));
-    if constexpr (!MASKED && OUT != OUT_FLAT) {
+    if constexpr (!M::ANY && OUT != OUT_FLAT) {
         const int form = nt ? table_form(DT, OUT, R, nwrite, ntiles) : 0;
         if constexpr (OUT == OUT_BINARY32 || Fmt<DT>::ES == 4)
             if (form == 1)
-                return launch(fused_reduce_kernel<DT, true, RU, OUT, false, 1>, grid, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
+                return launch(fused_reduce_kernel<DT, true, RU, OUT, M, 1>, grid, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
         if constexpr (DT != 1)
             if (form == 2)
-                return launch(fused_reduce_kernel<DT, true, RU, OUT, false, 2>, grid, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
+                return launch(fused_reduce_kernel<DT, true, RU, OUT, M, 2>, grid, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
     }
-    if (nt) return launch(fused_reduce_kernel<DT, true, RU, OUT, MASKED>, grid, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
-    return launch(fused_reduce_kernel<DT, false, RU, OUT, MASKED>, grid, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
+    if (nt) return launch(fused_reduce_kernel<DT, true, RU, OUT, M>, grid, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
+    return launch(fused_reduce_kernel<DT, false, RU, OUT, M>, grid, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
 }
 
-template <int DT, int OUT, bool MASKED>
+template <int DT, int OUT, typename M>
 static hipError_t slice_launch(int64_t ntiles, hipStream_t s, const SegTables& t, int64_t tile_base, int R, int nwrite,
-                               const uint64_t* local, int keep, Scale sc, FlatBuckets flat,
+                               const M& masks, int keep, Scale sc, FlatBuckets flat,
                                const GateRecord* gate, uint32_t tag, DispatchSignal sig) {
     const dim3 grid(static_cast<unsigned>(ntiles * SLICES));
     const unsigned lds = static_cast<unsigned>(R * SLICE_BYTES);
     // (registers and code for sixteen replicas a wave cost 20 % where four will do)
-    if (R <= 16) return launch(slice_reduce_kernel<DT, 4, OUT, MASKED>, grid, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
-    return launch(slice_reduce_kernel<DT, MAX_REPLICAS / 4, OUT, MASKED>, grid, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
+    if (R <= 16) return launch(slice_reduce_kernel<DT, 4, OUT, M>, grid, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
+    return launch(slice_reduce_kernel<DT, MAX_REPLICAS / 4, OUT, M>, grid, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
 }
 
 template <int DT, int OUT>
 static hipError_t fused_dispatch(bool nt, int64_t ntiles, unsigned lds, hipStream_t s,
                                  const SegTables& t, int64_t tile_base, int R, int nwrite,
-                                 const uint64_t* local, int keep, Scale sc, FlatBuckets flat,
+                                 const Masks& masks, int keep, Scale sc, FlatBuckets flat,
                                  const GateRecord* gate, uint32_t tag, DispatchSignal sig) {
     // (without the hint every launch takes tiles, so that both kernels can be had at any size)
-    if (nt && ntiles <= slice_tiles(R, Fmt<DT>::ES, OUT == OUT_FLAT)) {
-        if (local == nullptr)
-            return slice_launch<DT, OUT, false>(ntiles, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
-        return slice_launch<DT, OUT, true>(ntiles, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
+    const bool slices = nt && ntiles <= slice_tiles(R, Fmt<DT>::ES, OUT == OUT_FLAT);
+    auto with = [&](const auto& m) {
+        if (slices) return slice_launch<DT, OUT>(ntiles, s, t, tile_base, R, nwrite, m, keep, sc, flat, gate, tag, sig);
+        return fused_launch<DT, OUT>(nt, ntiles, lds, s, t, tile_base, R, nwrite, m, keep, sc, flat, gate, tag, sig);
+    };
+    if (masks.words != nullptr) {
+        MaskWords m;
+        std::memcpy(m.m, masks.words, sizeof(m.m));
+        m.first = masks.first;
+        m.shift = mask_shift(R);
+        return with(m);
     }
     // (the staged pass reads its masks through chunk_copy's one branch per replica: 329 us with either
     // instance, ResNet-50, R = 8, all marks in one call)
-    if constexpr (OUT != OUT_FLAT)
-        if (local == nullptr)
-            return fused_launch<DT, OUT, false>(nt, ntiles, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
-    return fused_launch<DT, OUT, true>(nt, ntiles, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
+    if (masks.table == nullptr && (OUT != OUT_FLAT || slices)) {
+        if constexpr (OUT != OUT_FLAT) return with(NoMasks{});
+        else return slice_launch<DT, OUT>(ntiles, s, t, tile_base, R, nwrite, NoMasks{}, keep, sc, flat, gate, tag, sig);
+    }
+    return with(MaskTable{masks.table});
+}
+
+void pack_masks(const uint64_t* masks, int count, int R, uint64_t* words) {
+    const int shift = mask_shift(R);
+    std::memset(words, 0, sizeof(uint64_t) * kMaskWords);
+    for (int k = 0; k < count; ++k) words[(k << shift) >> 6] |= masks[k] << ((k << shift) & 63);
 }
 
 hipError_t launch_fused_reduce(int dtype, const SegTables& t, int64_t tile_base, int64_t ntiles,
-                               int R, int nwrite, const uint64_t* local, bool keep_unused, Scale sc,
+                               int R, int nwrite, const Masks& masks, bool keep_unused, Scale sc,
                                bool nontemporal, unsigned lds, FlatBuckets flat,
                                const GateRecord* gate, uint32_t tag, DispatchSignal sig, hipStream_t s) {
     if (ntiles <= 0) return hipSuccess;
@@ -1579,23 +1627,23 @@ hipError_t launch_fused_reduce(int dtype, const SegTables& t, int64_t tile_base,
         // 16-bit gradients, binary32 averages to separate tensors
         if (nwrite != 1 || flat.slab0 != nullptr) return hipErrorInvalidValue;
         switch (dtype) {
-            case 1: return fused_dispatch<1, OUT_BINARY32>(nontemporal, ntiles, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
-            case 2: return fused_dispatch<2, OUT_BINARY32>(nontemporal, ntiles, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
+            case 1: return fused_dispatch<1, OUT_BINARY32>(nontemporal, ntiles, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
+            case 2: return fused_dispatch<2, OUT_BINARY32>(nontemporal, ntiles, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
             default: return hipErrorInvalidValue;
         }
     }
     if (flat.slab0 != nullptr) {
         switch (dtype) {
-            case 0: return fused_dispatch<0, OUT_FLAT>(nontemporal, ntiles, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
-            case 1: return fused_dispatch<1, OUT_FLAT>(nontemporal, ntiles, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
-            case 2: return fused_dispatch<2, OUT_FLAT>(nontemporal, ntiles, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
+            case 0: return fused_dispatch<0, OUT_FLAT>(nontemporal, ntiles, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
+            case 1: return fused_dispatch<1, OUT_FLAT>(nontemporal, ntiles, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
+            case 2: return fused_dispatch<2, OUT_FLAT>(nontemporal, ntiles, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
             default: return hipErrorInvalidValue;
         }
     }
     switch (dtype) {
-        case 0: return fused_dispatch<0, OUT_GRAD>(nontemporal, ntiles, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
-        case 1: return fused_dispatch<1, OUT_GRAD>(nontemporal, ntiles, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
-        case 2: return fused_dispatch<2, OUT_GRAD>(nontemporal, ntiles, lds, s, t, tile_base, R, nwrite, local, keep, sc, flat, gate, tag, sig);
+        case 0: return fused_dispatch<0, OUT_GRAD>(nontemporal, ntiles, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
+        case 1: return fused_dispatch<1, OUT_GRAD>(nontemporal, ntiles, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
+        case 2: return fused_dispatch<2, OUT_GRAD>(nontemporal, ntiles, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
         default: return hipErrorInvalidValue;
     }
 }
@@ -1612,12 +1660,12 @@ static hipError_t value_launch(const WordTables& words, int64_t tile_base, int64
     const FlatBuckets flat{nullptr, 0};
     const DispatchSignal sig{nullptr, 0};
     if (ntiles > slice_tiles(R, Fmt<DT>::ES, false))
-        return launch(fused_reduce_kernel<DT, true, RU, OUT_GRAD, false, 0, ArgTables<N>>, dim3(static_cast<unsigned>(ntiles)), edge_lds(R), s,
-                      t, tile_base, R, 1, nullptr, 0, sc, flat, nullptr, 0u, sig);
+        return launch(fused_reduce_kernel<DT, true, RU, OUT_GRAD, NoMasks, 0, ArgTables<N>>, dim3(static_cast<unsigned>(ntiles)), edge_lds(R), s,
+                      t, tile_base, R, 1, NoMasks{}, 0, sc, flat, nullptr, 0u, sig);
     const dim3 grid(static_cast<unsigned>(ntiles * SLICES));
     const unsigned lds = static_cast<unsigned>(R * SLICE_BYTES);
-    if (R <= 16) return launch(slice_reduce_kernel<DT, 4, OUT_GRAD, false, ArgTables<N>>, grid, lds, s, t, tile_base, R, 1, nullptr, 0, sc, flat, nullptr, 0u, sig);
-    return launch(slice_reduce_kernel<DT, MAX_REPLICAS / 4, OUT_GRAD, false, ArgTables<N>>, grid, lds, s, t, tile_base, R, 1, nullptr, 0, sc, flat, nullptr, 0u, sig);
+    if (R <= 16) return launch(slice_reduce_kernel<DT, 4, OUT_GRAD, NoMasks, ArgTables<N>>, grid, lds, s, t, tile_base, R, 1, NoMasks{}, 0, sc, flat, nullptr, 0u, sig);
+    return launch(slice_reduce_kernel<DT, MAX_REPLICAS / 4, OUT_GRAD, NoMasks, ArgTables<N>>, grid, lds, s, t, tile_base, R, 1, NoMasks{}, 0, sc, flat, nullptr, 0u, sig);
 }
 
 template <int DT>
@@ -1775,10 +1823,18 @@ hipError_t launch_mask_write(uint64_t* dst, const uint64_t* masks, int count, co
     return after_launch();
 }
 
-hipError_t launch_bitmap_or(uint64_t* local, uint8_t* global, uint8_t* host_global, const uint64_t* masks, int G,
+hipError_t launch_bitmap_or(uint64_t* local, uint8_t* global, uint8_t* host_global, const uint64_t* masks, int G, int R,
                             hipStream_t s) {
     if (G <= 0) return hipSuccess;
     const dim3 grid((G + BLOCK - 1) / BLOCK);
+    if (masks_fit(R, G)) {
+        MaskWords p;
+        pack_masks(masks, G, R, p.m);
+        p.first = 0;
+        p.shift = mask_shift(R);
+        hipLaunchKernelGGL(bitmap_or_kernel<MaskWords>, grid, dim3(BLOCK), 0, s, local, global, host_global, p, G);
+        return after_launch();
+    }
     if (G > kMasksByValue) {
         hipLaunchKernelGGL(bitmap_or_kernel<MaskPointer>, grid, dim3(BLOCK), 0, s, local, global, host_global, MaskPointer{masks}, G);
         return after_launch();

@@ -394,3 +394,26 @@ def test_masks_of_consecutive_iterations(pipeline, n):
     for it in range(iterations):
         for p in range(n):
             assert keep.download(it, p).tobytes() == want[it][0][0][p].tobytes(), f"iteration {it} parameter {p}"
+
+
+# Masks that travel in a launch's arguments: 8, 16, 32 or 64 bits a segment, on both sides of the 96 words there are, of the
+# changes of width, and of the 384 masks that one launch writes to the table.  One bucket, and a few.
+@pytest.mark.parametrize("R,n", [(1, 768), (2, 769), (8, 768), (9, 384), (9, 385), (16, 100), (17, 192), (17, 193), (32, 60),
+                                 (33, 96), (33, 97), (64, 96), (64, 97)])
+@pytest.mark.parametrize("pipeline", [STAGED, FUSED])
+def test_masks_in_every_form(R, n, pipeline):
+    rng = np.random.default_rng(R * 1000 + n)
+    numel = [int(x) for x in rng.integers(1, 30, size=n)]
+    if n <= 100:
+        numel[n // 2] = 3 * 2048 + 5
+    dtypes = [BF16 if R % 2 else FP32] * n
+    reps = [[workloads.gaussian_grad(590, r, 0, p, numel[p], 1e-2, dtypes[p]) for p in range(n)] for r in range(R)]
+    flag = rng.random((n, R)) < 0.6
+    flag[5] = False
+    marks = [(p, [int(u) for u in flag[p]]) for p in range(n - 1, -1, -1)]
+    for r in range(R):
+        for p in range(n):
+            if not flag[p, r]:
+                poison(reps[r][p], dtypes[p])
+    for cap in (1 << 30, 2000):
+        check_against_oracle(numel, dtypes, reps, marks, cap, pipeline, False, bool(R % 3))
