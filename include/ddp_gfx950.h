@@ -96,11 +96,14 @@ typedef struct ddp_ctx ddp_ctx;
                                      element type share ONE launch per kernel as long as the launch
                                      stays within `value` bytes of bucket data (INT64_MAX: no
                                      limit); order and results are unchanged.  0 = one launch per
-                                     bucket.  Default -1 = chosen from R so that a launch runs for
-                                     roughly 150 to 300 us (400 MiB for R <= 2, 240 MiB up to 4,
-                                     100 MiB up to 8, 70 MiB up to 16, else 50 MiB; measured: short
-                                     launches pay a fixed start-up and drain cost each, much longer
-                                     ones lose throughput again) */
+                                     bucket.  Default -1 = chosen from R (400 MiB for R <= 2, 240 MiB up
+                                     to 4, 100 MiB up to 8, 70 MiB up to 16, else 50 MiB; twice that for
+                                     R up to 16 but 4 where the fused pipeline writes the averages to
+                                     replica 0's gradient tensors alone; what is left of a run of
+                                     buckets joins its last launch if it is at most a quarter of the
+                                     limit; measured: short launches pay a fixed start-up and drain
+                                     cost each, much longer ones lose throughput again).  A launch
+                                     hold (DDP_OPT_LAUNCH_HOLD) counts the limits before doubling */
 #define DDP_OPT_FIND_UNUSED   11  /* any time between iterations: the paper's find_unused_parameters
                                      knob.  1 = gradients of parameters that no replica used in the
                                      iteration (the global bitmap of Section 4.2 says so) are left

@@ -225,16 +225,37 @@ int32_t auto_blocks_per_cu(int32_t R, bool copies, bool write_all) {
     return R <= 2 ? 0 : R <= 5 ? 4 : 2;
 }
 
-// A launch should run for roughly 150 to 300 us: shorter ones pay their start-up
-// and drain, much longer ones lose throughput again.  Bytes of bucket data per
-// launch that gave the best rate: R = 2: 400 MiB (67 -> 77 % with no cap),
-// R = 4: 240 MiB (76.5 -> 79 %), R = 8: 100 MiB, R = 16: 70 MiB, R = 32: 50 MiB.
+// Bytes of bucket data up to which buckets that become launchable together share a launch: a launch pays its start-up and drain, and
+// very long ones lose a little throughput again.  Lists of 5 to 6 GB in all, us, limits of MiB: R = 2 binary32 400 941, 800
+// 933, 1600 941, bfloat16 969, 957, 961; R = 3 240 463, 480 452; R = 4 240 974, 480 970, 960 975, bfloat16 960, 959, 973, binary16 986, 990, 996; R = 5
+// 100 645, 200 636, 400 640; R = 6 100 666, 200 644; R = 8 100 960, 200 948, 400 950, 800 961, bfloat16 986, 966, 961; R = 16 70 980, 140 972, 280 973; R = 24, 4 GB, 50
+// 653, 100 657; R = 32 50 965, 100 960; R = 64 50 805, 100 808; BERT-large, R = 8 100 1958, 200 1934, 400 1935, 800 1946.
+// Launches that write more do not gain from twice the bytes: every replica written, R = 4 240 775, 480 778; staged, R = 8 100 1148, 200 1155,
+// R = 16 70 1160, 140 1172; binary32 averages, R = 8 100 711, 200 712, R = 16 70 724, 140 731.
 int64_t auto_coalesce(int32_t R) {
     const int64_t mib = int64_t(1) << 20;
     return (R <= 2 ? 400 : R <= 4 ? 240 : R <= 8 ? 100 : R <= 16 ? 70 : 50) * mib;
 }
 
+// What a launch hold fills a launch with, and 0 = no sharing.
 int64_t coalesce_limit(const ddp_ctx* c) { return c->coalesce < 0 ? auto_coalesce(c->R) : c->coalesce; }
+
+int64_t launch_limit(const ddp_ctx* c) {
+    const bool one_writer = c->pipeline == DDP_PIPELINE_FUSED && !c->write_all && c->out_ptrs.empty();
+    const bool twice = c->coalesce < 0 && one_writer && c->R != 4 && c->R <= 16;
+    return coalesce_limit(c) * (twice ? 2 : 1);
+}
+
+// What is left of a run of buckets goes out with its last launch if it is at most a quarter of the limit that the library chose: a
+// launch of its own would be mostly start-up and drain, on another stream and with the way back from it.  One launch of 1.1 /
+// 1.25 / 1.5 times the limit (of the former limits for one writer) against two, %: binary32 R = 2 -3.9 / -2.0 / -1.2, R = 4 -2.8 / -1.4 / -0.6, R = 8 -4.9 /
+// -3.1 / -2.3, R = 16 -2.9 / -1.8 / -0.8, R = 32 -1.8 / -0.7 / +0.3; binary32 averages R = 2 -3.1 / -1.8 / +0.3, R = 8 -4.9 / -5.2 / -2.2, R = 32 -1.8 / -0.9 / +0.1;
+// staged R = 2 -1.7 / -0.7 / +0.4 (bfloat16 -1.1 / +0.6 / +2.5), R = 4 -2.2 / -1.1 / -0.8, R = 8 -1.6 / -0.2 / +0.6, R = 16 -1.3 / -0.1 / +0.4; every
+// replica written R = 4 -2.4 / -2.3 / -0.3, R = 8 -1.8 / -1.5 / +0.7, R = 16 -1.4 / -1.0 / -0.1.  The ragged list, R = 8, 114 MiB, 188.5 / 179.5 us.
+int64_t last_launch_limit(const ddp_ctx* c) {
+    const int64_t limit = launch_limit(c);
+    return c->coalesce < 0 ? limit + limit / 4 : limit;
+}
 
 // A launch is chained to the one in front of it if that one moves at least this many bytes.
 constexpr int64_t kChainMinTraffic = int64_t(160) << 20;
@@ -774,15 +795,17 @@ int32_t flush_deferred(ddp_ctx* c) {
     size_t i = 0;
     while (i < todo.size()) {
         size_t j = i;
-        const int64_t limit = coalesce_limit(c);
+        const int64_t limit = launch_limit(c);
         if (limit > 0) {
-            uint64_t bytes = c->plan.buckets[todo[i]].bytes();
-            while (j + 1 < todo.size() && todo[j + 1] == todo[j] + 1 &&
-                   c->plan.buckets[todo[j + 1]].dtype == c->plan.buckets[todo[i]].dtype &&
-                   bytes + c->plan.buckets[todo[j + 1]].bytes() <= static_cast<uint64_t>(limit)) {
-                bytes += c->plan.buckets[todo[j + 1]].bytes();
-                ++j;
-            }
+            // the run of consecutive buckets of one type that starts here
+            size_t end = i + 1;
+            uint64_t bytes = c->plan.buckets[todo[i]].bytes(), run = bytes;
+            while (end < todo.size() && todo[end] == todo[end - 1] + 1 && c->plan.buckets[todo[end]].dtype == c->plan.buckets[todo[i]].dtype)
+                run += c->plan.buckets[todo[end++]].bytes();
+            if (run <= static_cast<uint64_t>(last_launch_limit(c))) j = end - 1;
+            else
+                while (j + 1 < end && bytes + c->plan.buckets[todo[j + 1]].bytes() <= static_cast<uint64_t>(limit))
+                    bytes += c->plan.buckets[todo[++j]].bytes();
         }
         ranges.emplace_back(todo[i], todo[j]);
         i = j + 1;
@@ -1077,7 +1100,7 @@ int32_t ddp_get_option(ddp_ctx* c, int32_t option, int64_t* value) {
         case DDP_OPT_TIMING: *value = c->timing; return DDP_OK;
         case DDP_OPT_FIND_UNUSED: *value = c->find_unused; return DDP_OK;
         case DDP_OPT_REDUCE_STREAMS: *value = c->n_streams; return DDP_OK;
-        case DDP_OPT_COALESCE: *value = coalesce_limit(c); return DDP_OK;
+        case DDP_OPT_COALESCE: *value = launch_limit(c); return DDP_OK;
         case DDP_OPT_TAIL_ON_BACKWARD: *value = c->tail_on_backward; return DDP_OK;
         case DDP_OPT_GATE_WAIT_US: *value = c->gate_wait_us; return DDP_OK;
         case DDP_OPT_LAUNCH_HOLD: *value = c->hold_marks; return DDP_OK;

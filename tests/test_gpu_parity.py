@@ -404,6 +404,35 @@ def test_coalesced_launches_keep_order_results_and_cover_every_bucket(pipeline):
         assert grads.download(0, p).tobytes() == want[p].tobytes(), f"parameter {p}"
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("R,pipeline,write_all,launches", [
+    (8, FUSED, False, [250]), (8, FUSED, False, [200, 51]), (8, FUSED, False, [200, 200, 200]), (8, STAGED, False, [125]), (8, STAGED, False, [100, 26]),
+    (8, FUSED, True, [125]), (8, FUSED, True, [100, 26]), (4, FUSED, False, [300]), (4, FUSED, False, [240, 61]),
+    (17, FUSED, False, [62]), (17, FUSED, False, [50, 13])])
+def test_buckets_share_launches_up_to_the_limit_chosen_for_them(R, pipeline, write_all, launches):
+    """One tensor of 1 MiB in each bucket; the last launch of a run may be a quarter longer."""
+    import torch
+    d, harness = lib()
+    n = sum(launches)
+    grads = harness.DeviceGrads([1 << 18] * n, [FP32] * n, R)
+    for r in range(R):
+        grads.bufs[r][:n << 20].view(torch.float32).fill_(float(r + 1))
+    torch.cuda.synchronize()
+    with harness.Session(grads, 1 << 20, pipeline, write_all) as s:
+        assert s.n_buckets == n
+        d.ddp_set_option(s.ctx, d.DDP_OPT_TIMING, 1)
+        d.ddp_mark_ready_many(s.ctx, list(range(n - 1, -1, -1)))
+        d.ddp_finalize_backward(s.ctx)
+        d.ddp_synchronize(s.ctx)
+        _, ids = d.ddp_get_kernel_times(s.ctx, d.DDP_K_REDUCE)
+    assert [int(i) // 65536 + 1 for i in ids] == launches
+    assert [int(i) % 65536 for i in ids] == [sum(launches[:k]) for k in range(len(launches))]
+    mean = np.float32(R * (R + 1) // 2) / np.float32(R)
+    for r in range(R):
+        want = mean if r == 0 or write_all else np.float32(r + 1)
+        assert bool((grads.bufs[r][:n << 20].view(torch.float32) == float(want)).all()), f"replica {r}"
+
+
 # ---- kernel time stamps ------------------------------------------------------------------------
 @pytest.mark.gpu
 @pytest.mark.parametrize("pipeline", [STAGED, FUSED])
