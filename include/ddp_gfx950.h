@@ -141,12 +141,13 @@ typedef struct ddp_ctx ddp_ctx;
                                      unit fill the memory system; more only interleave more request
                                      streams at the DRAM channels and throughput drops.  0 = no cap
                                      (wave slots decide: 8).  Default -1 =
-                                     chosen from R: no cap up to R = 2 (few loads per block), 4 up to
-                                     R = 5, else 2, and in launches below DDP_OPT_REDUCE_CAP_MIN_BYTES, unless
+                                     chosen from R: no cap up to R = 2 (few loads per block), 4 for R = 3 (16-bit
+                                     gradients R = 4, too), 3 up to R = 6 (16-bit averages
+                                     R = 7), else 2, and in launches below DDP_OPT_REDUCE_CAP_MIN_BYTES, unless
                                      that was set, 4 from R = 5 on and 2 from R = 16 on; staged pipeline (its
                                      launches write as much as they read): 2 for R = 4, else none;
                                      DDP_OPT_WRITE_ALL: none in long launches for R <= 2 and
-                                     R = 12 to 15, else 2 */
+                                     R = 12 to 16, 3 for R = 3 in 16 bits, else 2 */
 #define DDP_OPT_REDUCE_CAP_MIN_BYTES 14 /* any time: launches that move at least this
                                      many bytes, counted as (R + 1) x the launch's bucket bytes in
                                      both pipelines, are long ones: a cap set with
@@ -158,7 +159,9 @@ typedef struct ddp_ctx ddp_ctx;
                                      launch and gains 2.5 points).  Default 360 MiB (40 MiB of bucket
                                      data at R = 8) */
 #define DDP_OPT_ACCUMULATE_BLOCKS_PER_CU 16 /* any time: likewise for the accumulate kernel (two loads
-                                     and a store per vector; registers allow 8 blocks).  Default 4 */
+                                     and a store per vector; registers allow 8 blocks).  Default 4; as long as it
+                                     has not been set, 3 where all gradients are 16-bit, and 6 (16-bit: 5) where
+                                     they are 368 MiB or less */
 #define DDP_OPT_TAIL_ON_BACKWARD 17 /* any time between iterations: 1 (default) = the buckets launched by
                                      the API call that completes an iteration (the call after which
                                      the last bucket is launchable: every gradient exists, nothing

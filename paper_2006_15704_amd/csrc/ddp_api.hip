@@ -67,10 +67,12 @@ struct ddp_ctx {
     int64_t cap_min_traffic = int64_t(360) << 20; // ... applied to launches that move at least this many bytes
     bool cap_min_set = false;                     // ... by the caller's choice: shorter launches have no cap then
     int32_t acc_blocks_per_cu = 4;                // accumulate kernel: likewise
+    bool acc_blocks_set = false;                  // ... by the caller's choice, see auto_accumulate_blocks
     int64_t lds_per_cu = 160 * 1024;              // read from the device at creation
 
     bool registered = false, built = false;
     bool small_model = false;                     // set by build_internal, see kSmallModelTraffic
+    bool wide = false;                            // some gradient is binary32
     ddp::BucketPlan plan;
     ddp::ReadyTracker tracker;
     std::vector<void*> grad_ptrs;            // [R][n], registration order
@@ -219,11 +221,28 @@ int32_t fail(ddp_ctx* c, int32_t code, const std::string& msg) {
 // BERT-large tensors, binary32 R = 4 412 / 418 / 412 / 385, R = 8 849 / 852 / 835 / 851, R = 10 1067 / 1093 / 1063 / 1049, R = 12 1301 / 1314 / 1307 / 1294,
 // R = 16 1756 / 1760 / 1748 / 1748, R = 32 3623 / 3627 / 3609 / 3528; bfloat16 R = 8 420 / 421 / 426 / 415, R = 10 530 / 530 / 535 / 524, R = 12 647 / 647 / 656 /
 // 647, R = 14 755 / 755 / 762 / 766, R = 16 870 / 871 / 876 / 886, R = 32 1812 / 1810 / 1807 / 1786).
-int32_t auto_blocks_per_cu(int32_t R, bool copies, bool write_all) {
+// Three blocks, lists of 2.2 GB moved, all marks in one call, us with four blocks / three / two: binary32 R = 4 344 / 341 / 379, R = 5 348 / 340 / 367, R = 6
+// 353 / 341 / 347, R = 7 359 / 348 / 352, R = 8 368 / 354 / 340; bfloat16 R = 4 342 / 346 / 426, R = 5 351 / 342 / 390, R = 6 360 / 347 / 364, R = 7 367 / 353 /
+// 373, R = 8 378 / 370 / 345; binary16 R = 4 346 / 342 / 399 (120 MiB buckets, one mark per call 355 / 359 / 403), R = 5 355 / 342 / 393, R = 6 358 / 346 / 378, R = 7
+// 370 / 354 / 367, R = 8 377 / 363 / 354; binary32 averages R = 4 412 / 428 / 455, R = 5 418 / 415 / 441, R = 6 418 / 414 / 420, R = 7 414 / 413 / 395; every
+// replica written, no cap / three / two: binary32 R = 3 573 / 543 / 544, R = 16 774 / 771 / 796, bfloat16 R = 3 570 / 550 / 579, R = 16 772 / 777 / 791.  Sixty BERT-large
+// tensors, three / two: binary32 R = 6 325 / 328, R = 7 376 / 373, every replica written R = 3 294 / 282; bfloat16 R = 6 164 / 171, R = 7 189 / 196, every replica
+// written R = 3 145 / 148.
+int32_t auto_blocks_per_cu(int32_t R, int es, bool copies, bool write_all, bool out32) {
     if (copies) return R == 4 ? 2 : 0;
-    if (write_all) return R <= 2 || (R >= 12 && R < 16) ? 0 : 2;
-    return R <= 2 ? 0 : R <= 5 ? 4 : 2;
+    if (write_all) return R <= 2 || (R >= 12 && R <= 16) ? 0 : R == 3 && es == 2 ? 3 : 2;
+    if (R <= 2) return 0;
+    if (R == 3 || (R == 4 && es == 2)) return 4;
+    return R <= (out32 || es == 4 ? 6 : 7) ? 3 : 2;
 }
+
+// Resident blocks of the accumulation.  Gradients that go past the caches: four, in 16 bits three; others have less of the memory to wait for
+// and are over sooner, so that more blocks under way count for more.  Us a micro-step of 60 tensors, three / four / five / six / no cap:
+// 2.4 GB of gradients, binary32 R = 2 1169 / 1144 / 1162 / 1183 / 1204, R = 32 1169 / 1170 / 1194 / 1211 / 1243; bfloat16 R = 2 1135 / 1152 / 1168 / 1186 / 1192, R = 8
+// 1132 / 1165 / 1181 / 1204 / 1218; binary16 R = 8 1152 / 1173 / 1185 / 1205 / 1223; 800 MB, binary32 R = 8 394 / 382 / 383 / 392 / 399, bfloat16 370 / 377 / 387 / 392 / 394; 200
+// MB, binary32 R = 2 108 / 103 / 102 / 100 / 101, R = 8 106 / 104 / 104 / 103 / 103, bfloat16 R = 8 101 / 102 / 101 / 102 / 103; 60 MB, binary32 R = 2 34.1 / 33.3 / 32.1 / 30.0 /
+// 29.7, R = 8 34.3 / 32.5 / 31.2 / 30.1 / 29.7, bfloat16 R = 8 31.7 / 30.3 / 30.1 / 29.9 / 29.8.
+int32_t auto_accumulate_blocks(bool streamed, bool wide) { return streamed ? (wide ? 4 : 3) : (wide ? 6 : 5); }
 
 // Bytes of bucket data up to which buckets that become launchable together share a launch: a launch pays its start-up and drain, and
 // very long ones lose a little throughput again.  Lists of 5 to 6 GB in all, us, limits of MiB: R = 2 binary32 400 941, 800
@@ -320,9 +339,9 @@ unsigned lds_for_blocks(const ddp_ctx* c, int32_t blocks) {
 // 45.7.  Three blocks lie between four and two.
 int32_t short_launch_blocks(int32_t R) { return R <= 4 ? 0 : R < 16 ? 4 : 2; }
 
-unsigned occupancy_lds(const ddp_ctx* c, int64_t launch_bytes, bool copies) {
+unsigned occupancy_lds(const ddp_ctx* c, int64_t launch_bytes, int es, bool copies) {
     if (c->blocks_per_cu >= 0) return long_launch(c, launch_bytes) ? lds_for_blocks(c, c->blocks_per_cu) : 0;
-    if (long_launch(c, launch_bytes)) return lds_for_blocks(c, auto_blocks_per_cu(c->R, copies, c->write_all));
+    if (long_launch(c, launch_bytes)) return lds_for_blocks(c, auto_blocks_per_cu(c->R, es, copies, c->write_all, !c->out_ptrs.empty()));
     return copies || c->cap_min_set ? 0 : lds_for_blocks(c, short_launch_blocks(c->R));
 }
 
@@ -734,7 +753,7 @@ int32_t launch_range(ddp_ctx* c, int32_t first, int32_t last, Target target) {
         if ((rc = timed_begin(c, DDP_K_REDUCE, id, st, &slot)) != DDP_OK) return rc;
         HIPCHK(c, ddp::launch_flat_reduce(bf.dtype, in0, c->slab_stride, out, nvec, c->R, sc,
                                           c->nontemporal != 0,
-                                          long_launch(c, bytes) ? occupancy_lds(c, bytes, false) : 0, gate, tag, sig, st));
+                                          long_launch(c, bytes) ? occupancy_lds(c, bytes, ddp::elem_size(bf.dtype), false) : 0, gate, tag, sig, st));
         if ((rc = timed_end(c, slot, st)) != DDP_OK) return rc;
     } else {
         const bool staged = c->pipeline == DDP_PIPELINE_STAGED;
@@ -742,7 +761,7 @@ int32_t launch_range(ddp_ctx* c, int32_t first, int32_t last, Target target) {
         if ((rc = timed_begin(c, DDP_K_REDUCE, id, st, &slot)) != DDP_OK) return rc;
         HIPCHK(c, ddp::launch_fused_reduce(bf.dtype, c->tables, tile_base, ntiles, c->R,
                                            c->write_all ? c->R : 1, masks, c->find_unused != 0, sc,
-                                           c->nontemporal != 0, occupancy_lds(c, bytes, staged),
+                                           c->nontemporal != 0, occupancy_lds(c, bytes, ddp::elem_size(bf.dtype), staged),
                                            flat, gate, tag, sig, st));
         if ((rc = timed_end(c, slot, st)) != DDP_OK) return rc;
     }
@@ -1026,6 +1045,7 @@ int32_t ddp_set_option(ddp_ctx* c, int32_t option, int64_t value) {
         case DDP_OPT_ACCUMULATE_BLOCKS_PER_CU:
             if (value < 0 || value > 16) return fail(c, DDP_ERR_ARG, "blocks per compute unit outside [0, 16]");
             c->acc_blocks_per_cu = static_cast<int32_t>(value);
+            c->acc_blocks_set = true;
             return DDP_OK;
         case DDP_OPT_REDUCE_CAP_MIN_BYTES:
             if (value < 0) return fail(c, DDP_ERR_ARG, "bad size");
@@ -1183,6 +1203,8 @@ static int32_t build_internal(ddp_ctx* c, uint64_t cap_bytes, const std::vector<
     c->bucket_zero.assign(nb, 0);
     c->global_closed.assign(n, 0);
 
+    c->wide = false;
+    for (const ddp::BucketInfo& bk : c->plan.buckets) c->wide = c->wide || bk.dtype == DDP_FP32;
     int64_t total_bytes = 0;
     for (const ddp::BucketInfo& bk : c->plan.buckets) total_bytes += static_cast<int64_t>(bk.bytes());
     c->small_model = nb <= kSmallModelBuckets && int64_t(c->R) * (nb - 1) <= kSmallModelReplicas &&
@@ -1707,7 +1729,8 @@ int32_t ddp_no_sync_accumulate(ddp_ctx* c, void* const* micro) {
     }
     size_t slot;
     int32_t rc;
-    const unsigned lds = lds_for_blocks(c, c->acc_blocks_per_cu);
+    const unsigned lds = lds_for_blocks(c, c->acc_blocks_set ? c->acc_blocks_per_cu
+                                                             : auto_accumulate_blocks(ddp::accumulate_streams(c->h_tile0[n], c->R), c->wide));
     if ((rc = timed_begin(c, DDP_K_ACCUMULATE, -1, c->backward, &slot)) != DDP_OK) return rc;
     if (form == MicroForm::kTable)
         HIPCHK(c, ddp::launch_accumulate(c->tables, c->h_tile0[n], c->R, c->d_micro, lds, c->backward));

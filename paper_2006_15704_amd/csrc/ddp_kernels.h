@@ -281,6 +281,9 @@ hipError_t launch_bitmap_or(uint64_t* local, uint8_t* global, uint8_t* host_glob
 hipError_t launch_pointer_copy(void** dst, void* const* src, int64_t count, unsigned* arrived, unsigned long long* done,
                                unsigned long long ticket, hipStream_t s);
 
+// Whether the gradients' loads and stores of a micro-step carry the non-temporal hint.
+bool accumulate_streams(int64_t ntiles, int R);
+
 // K4: grad[r][g] += micro gradient for all segments and replicas (null micro pointers are skipped).  ntiles = tile0[G].
 // micro: a table in device memory, replica r's pointer of segment g at [g*R + r] (laid out as SegTables::grad, so that
 // a block fetches both pointers at once) ...

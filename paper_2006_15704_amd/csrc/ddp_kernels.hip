@@ -1203,10 +1203,8 @@ __device__ __forceinline__ u32x4 added(u32x4 a, u32x4 b) {
 
 // Bound by HBM: two reads and one write of every byte.
 // STREAM: the gradients' loads and stores carry the non-temporal hint as the micro-step's loads always
-// do (launch_accumulate has the rule).  Four resident blocks (us a micro-step, three / four / five / six: ResNet-50, R = 8,
-// bfloat16 192 / 196 / 201 / 202, binary32 395 / 393 / 400 / 407; four steps of 37 BERT-large tensors, R = 32, and the reduction 15170 /
-// 15155 / 15440 / 15680), two vectors per thread; one or
-// four vectors and replicas in turn block by block were no better.
+// do (launch_accumulate has the rule).  Two vectors per thread; one or four vectors and replicas in turn block by block were
+// no better.  Three to six resident blocks (auto_accumulate_blocks in the host code).
 template <int DT, bool STREAM>
 __device__ __forceinline__ void accumulate_tile(const char* __restrict__ src, char* dst,
                                                 int64_t numel, int64_t ltile) {
@@ -1769,6 +1767,7 @@ hipError_t launch_pointer_copy(void** dst, void* const* src, int64_t count, unsi
 }
 
 constexpr int64_t kStreamedGradients = int64_t(368) << 20;
+bool accumulate_streams(int64_t ntiles, int R) { return ntiles * R * int64_t(TILE_BYTES) > kStreamedGradients; }
 
 template <typename Micro>
 static hipError_t accumulate_launch(const SegTables& t, int64_t ntiles, int R, const Micro& micro, unsigned lds, hipStream_t s) {
@@ -1784,7 +1783,7 @@ static hipError_t accumulate_launch(const SegTables& t, int64_t ntiles, int R, c
     // small tensors take the hint early and are no worse for it (two micro-steps and the reduction, real
     // bytes / whole tiles compared with the threshold: R = 64, 800 tensors of 500 bfloat16 404 / 390 us,
     // of 100 binary32 185 / 188; R = 32, 2000 of 500 bfloat16 442 / 429; R = 8, 8000 of 100 bfloat16 405 / 417).
-    if (ntiles * R * int64_t(TILE_BYTES) > kStreamedGradients) return launch(accumulate_kernel<true, Micro>, grid, lds, s, t, micro);
+    if (accumulate_streams(ntiles, R)) return launch(accumulate_kernel<true, Micro>, grid, lds, s, t, micro);
     return launch(accumulate_kernel<false, Micro>, grid, lds, s, t, micro);
 }
 
