@@ -1714,12 +1714,13 @@ int32_t ddp_no_sync_accumulate(ddp_ctx* c, void* const* micro) {
     if (!micro) return fail(c, DDP_ERR_ARG, "ddp_no_sync_accumulate: null pointer array");
     const int32_t n = static_cast<int32_t>(c->plan.params.size());
     const int64_t R = c->R;
-    for (int64_t r = 0; r < R; ++r)
-        for (int32_t i = 0; i < n; ++i) {
-            const void* p = micro[r * n + i];
-            if (p && reinterpret_cast<uintptr_t>(p) % static_cast<uintptr_t>(ddp::elem_size(c->plan.params[i].dtype)) != 0)
-                return fail(c, DDP_ERR_ARG, "ddp_no_sync_accumulate: pointer not aligned to its element size");
-        }
+    // (one addressing of all replicas' rows at a time: the parameter's size is looked at once)
+    for (int32_t i = 0; i < n; ++i) {
+        uintptr_t any = 0;
+        for (int64_t r = 0; r < R; ++r) any |= reinterpret_cast<uintptr_t>(micro[r * n + i]);
+        if ((any & static_cast<uintptr_t>(ddp::elem_size(c->plan.params[i].dtype) - 1)) != 0)
+            return fail(c, DDP_ERR_ARG, "ddp_no_sync_accumulate: pointer not aligned to its element size");
+    }
     HIPCHK(c, hipSetDevice(c->device));
     uint64_t words[ddp::kMicroByValue];
     const MicroForm form = micro_words(c, micro, words);

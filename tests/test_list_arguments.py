@@ -90,3 +90,46 @@ def test_context_free_call():
             d.ddp_sync_static(2, 0, 0, form([8]), [0], form([256]), 100)
     with pytest.raises(OverflowError):
         d.ddp_sync_static(2, 0, 0, [8], [0], [-1, 256], 100)
+
+
+EDGES = [0, 1, (1 << 15) - 1, 1 << 15, (1 << 30) - 1, 1 << 30, (1 << 31) - 1, 1 << 31, (1 << 32) + 5, (1 << 45) - 3, (1 << 60) - 1, 1 << 60,
+         (1 << 62) + 1, (1 << 63) - 1, 1 << 63, (1 << 64) - 1]
+
+
+@pytest.mark.parametrize("form", [list, tuple])
+def test_values_arrive_as_they_are(form):
+    """Ints of every number of the interpreter's digits, as pointers, sizes and ids."""
+    from ctypes import CFUNCTYPE, POINTER, c_int32, c_int64, c_uint64, c_void_p, cast
+    B = d.binding
+    got = []
+
+    @CFUNCTYPE(c_int32, c_void_p, POINTER(c_uint64))
+    def accumulate(ctx, p):
+        got.append(p[:len(EDGES) + 1])
+        return 0
+
+    @CFUNCTYPE(c_int32, c_void_p, POINTER(c_int32), c_int32)
+    def many(ctx, p, n):
+        got.append(p[:n])
+        return 0
+
+    @CFUNCTYPE(c_int32, c_int32, c_int32, c_void_p, c_int32, POINTER(c_int64), POINTER(c_int32), POINTER(c_uint64), c_uint64)
+    def static(R, device, stream, n, numel, dtype, p, cap):
+        got.append((numel[:n], dtype[:n], p[:R * n]))
+        return 0
+
+    sizes = [v for v in EDGES if v < 1 << 63] + [-1, -(1 << 30), -(1 << 63)]
+    ids = [v for v in EDGES if v < 1 << 31] + [-1, -(1 << 30), -(1 << 31)]
+    address = lambda f: cast(f, c_void_p).value
+    B._fast.bind(B._mark, B._finalize, B._mark_local, c_int32, address(many), address(accumulate), address(static))
+    try:
+        assert B._fast_accumulate(1, form(EDGES + [None]), len(EDGES) + 1) == 0
+        assert B._fast_many(1, form(ids)) == 0
+        assert B._fast_static(1, 0, 0, form(sizes), form(ids[:1] * len(sizes)), form((EDGES * 2)[:len(sizes)]), 0) == 0
+        assert B._fast_many(1, form([1 << 31])) is None and B._fast_many(1, form([-(1 << 31) - 1])) is None
+        assert B._fast_accumulate(1, form([1 << 64] * 17), 17) is None and B._fast_accumulate(1, form([True] * 17), 17) is None
+    finally:
+        B._fast.bind(B._mark, B._finalize, B._mark_local, c_int32, B._many, B._accumulate, B._static)
+    assert got[0] == EDGES + [0]
+    assert got[1] == ids
+    assert got[2] == (sizes, [ids[0]] * len(sizes), (EDGES * 2)[:len(sizes)])
