@@ -99,10 +99,9 @@ struct ddp_ctx {
     bool global_on_device = false;           // closed iteration: the bitmap kernel ran, result in h_global
     uint64_t* d_local = nullptr;             // [G]
     uint8_t* d_global = nullptr;             // [G]
-    uint8_t* h_global = nullptr;             // pinned, written by the bitmap kernel
-    hipEvent_t ev_global[2] = {nullptr, nullptr};   // behind the bitmap step, by iteration parity
+    uint64_t* h_global = nullptr;            // [G], pinned, written by the bitmap kernel: iteration tag * 2 + bit; see await_bitmap
     uint64_t* h_masks[2] = {nullptr, nullptr};   // pinned copies of local_cur, by iteration parity; see stage_masks
-    bool masks_in_flight[2] = {false, false};    // kernels of an earlier iteration may still read h_masks
+    uint64_t masks_in_flight[2] = {0, 0};        // tag of the iteration whose kernels may still read h_masks, 0 = none
     int64_t masks_claimed_iter = -1;             // iteration for which h_masks was waited for
     void** d_micro = nullptr;                // [R * n, rounded up to an even number], and a word for pointer_copy_kernel
     // Pinned: micro_slots tables of micro-step pointers, used in turn, and behind them the ordinal of the latest
@@ -573,16 +572,36 @@ int32_t order_call(ddp_ctx* c, int32_t first, bool look) {
     return DDP_OK;
 }
 
+// Waits until the bitmap step of the iteration with this tag has run: every word it writes for the host carries the tag, so that
+// nothing else has to tell.  (An event behind it took the host 5 us, and the next kernel on the stream started 4 us later
+// for it.)  A bounded look, then the stream is waited for.
+int32_t await_bitmap(ddp_ctx* c, uint64_t tag) {
+    const int32_t n = static_cast<int32_t>(c->plan.params.size());
+    const auto until = std::chrono::steady_clock::now() + std::chrono::milliseconds(100);
+    bool waited = false;
+    for (int32_t g = 0; g < n; ++g)
+        while (__atomic_load_n(c->h_global + g, __ATOMIC_RELAXED) >> 1 < tag) {
+            if (waited) return fail(c, DDP_ERR_HIP, "the bitmap step of the closed iteration has not run");
+            if (std::chrono::steady_clock::now() < until) continue;
+            HIPCHK(c, hipStreamSynchronize(c->backward));
+            waited = true;
+        }
+    return DDP_OK;
+}
+
 // Where a mask launch takes the masks of segments [begin, end) of the running iteration from: up to
 // kMasksByValue go into kernel arguments, more are copied into pinned memory that the kernel reads.
-// All kernels that read an iteration's copy are in front of its bitmap step's event.
+// All kernels that read an iteration's copy are in front of its bitmap step, or are that step.
 int32_t stage_masks(ddp_ctx* c, int begin, int end, const uint64_t** masks) {
     *masks = c->local_cur.data() + begin;
     if (end - begin <= ddp::kMasksByValue) return DDP_OK;
     const int par = static_cast<int>(c->iteration & 1);
     if (c->masks_claimed_iter != c->iteration) {
-        if (c->masks_in_flight[par]) HIPCHK(c, hipEventSynchronize(c->ev_global[par]));
-        c->masks_in_flight[par] = false;
+        if (c->masks_in_flight[par] != 0) {
+            const int32_t rc = await_bitmap(c, c->masks_in_flight[par]);
+            if (rc != DDP_OK) return rc;
+        }
+        c->masks_in_flight[par] = 0;
         c->masks_claimed_iter = c->iteration;
     }
     std::memcpy(c->h_masks[par] + begin, *masks, sizeof(uint64_t) * (end - begin));
@@ -908,7 +927,7 @@ void release_device(ddp_ctx* c) {
     }
     drop_timed(c);
     release_build(c);
-    for (hipEvent_t* e : {&c->ev_done, &c->ev_emit, &c->ev_global[0], &c->ev_global[1]})
+    for (hipEvent_t* e : {&c->ev_done, &c->ev_emit})
         if (*e) { (void)hipEventDestroy(*e); *e = nullptr; }
     if (c->d_order_mem) (void)hipFree(c->d_order_mem);
     c->d_order_mem = nullptr; c->d_order = nullptr; c->d_probe = nullptr;
@@ -970,8 +989,6 @@ int32_t ddp_create(ddp_ctx** out, int32_t R, int32_t device, void* reduce_stream
         if (e == hipSuccess) e = hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, device);
         if (e == hipSuccess && lds >= 64 * 1024) c->lds_per_cu = lds;
         if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_done, kOrderEvent);
-        for (hipEvent_t& ev : c->ev_global)
-            if (e == hipSuccess) e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_emit, hipEventDisableTiming);
         int cus = 0;
         if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device);
@@ -1260,7 +1277,8 @@ static int32_t build_internal(ddp_ctx* c, uint64_t cap_bytes, const std::vector<
 
         HIPCHK(c, hipMalloc(reinterpret_cast<void**>(&c->d_local), sizeof(uint64_t) * n));
         HIPCHK(c, hipMalloc(reinterpret_cast<void**>(&c->d_global), static_cast<size_t>(n) + 16));
-        HIPCHK(c, hipHostMalloc(reinterpret_cast<void**>(&c->h_global), static_cast<size_t>(n), hipHostMallocDefault));
+        HIPCHK(c, hipHostMalloc(reinterpret_cast<void**>(&c->h_global), sizeof(uint64_t) * n, hipHostMallocDefault));
+        std::memset(c->h_global, 0, sizeof(uint64_t) * n);
         if (n > ddp::kMasksByValue)
             for (uint64_t*& m : c->h_masks)
                 HIPCHK(c, hipHostMalloc(reinterpret_cast<void**>(&m), sizeof(uint64_t) * n, hipHostMallocDefault));
@@ -1323,11 +1341,11 @@ int32_t ddp_rebuild_buckets(ddp_ctx* c, uint64_t cap_bytes) {
             if (c->lane[l]) HIPCHK(c, hipStreamSynchronize(c->lane[l]));
         HIPCHK(c, hipStreamSynchronize(c->reduce));
         if (c->global_on_device) {      // keep the closed iteration's bitmap readable
-            for (int32_t i = 0; i < n; ++i) c->global_closed[i] = c->h_global[c->plan.params[i].segment];
+            for (int32_t i = 0; i < n; ++i) c->global_closed[i] = c->h_global[c->plan.params[i].segment] & 1;
             c->global_on_device = false;
         }
         drop_timed(c);
-        c->masks_in_flight[0] = c->masks_in_flight[1] = false;
+        c->masks_in_flight[0] = c->masks_in_flight[1] = 0;
         c->masks_claimed_iter = -1;
     }
     const std::vector<uint8_t> keep_global = c->global_closed, keep_used = c->used_closed;
@@ -1518,9 +1536,8 @@ int32_t ddp_finalize_backward(ddp_ctx* c) {
                 const int32_t rc = stage_masks(c, 0, n, &masks);
                 if (rc != DDP_OK) return rc;
             }
-            HIPCHK(c, ddp::launch_bitmap_or(c->d_local, c->d_global, c->h_global, masks, n, c->R, c->backward));
-            HIPCHK(c, hipEventRecord(c->ev_global[c->iteration & 1], c->backward));
-            c->masks_in_flight[c->iteration & 1] = n > ddp::kMasksByValue;     // (of this launch, or of a bucket's)
+            HIPCHK(c, ddp::launch_bitmap_or(c->d_local, c->d_global, c->h_global, tag, masks, n, c->R, c->backward));
+            if (n > ddp::kMasksByValue) c->masks_in_flight[c->iteration & 1] = tag;     // (of this launch, or of a bucket's)
         }
         const bool staged = c->pipeline == DDP_PIPELINE_STAGED;
         if (c->gates_in_iter > 0) {
@@ -1586,8 +1603,9 @@ int32_t ddp_get_global_used(ddp_ctx* c, uint8_t* used) {
     if (c->global_on_device) {
         // what the bitmap kernel of finalize computed and wrote to host memory
         HIPCHK(c, hipSetDevice(c->device));
-        HIPCHK(c, hipEventSynchronize(c->ev_global[(c->iteration - 1) & 1]));
-        for (int32_t i = 0; i < n; ++i) used[i] = c->h_global[c->plan.params[i].segment];
+        const int32_t rc = await_bitmap(c, static_cast<uint64_t>(c->iteration));      // (the closed iteration's tag)
+        if (rc != DDP_OK) return rc;
+        for (int32_t i = 0; i < n; ++i) used[i] = c->h_global[c->plan.params[i].segment] & 1;
     } else {
         std::memcpy(used, c->global_closed.data(), static_cast<size_t>(n));
     }

@@ -271,9 +271,9 @@ constexpr int kMasksByValue = 384;
 hipError_t launch_mask_write(uint64_t* dst, const uint64_t* masks, int count, const GateRecord* gate, uint32_t tag,
                              hipStream_t s);
 
-// For g < G: local[g] = masks[g], global[g] = host_global[g] = OR of its bits (the bitmap AllReduce of
-// Section 4.2).  masks as above, of R replicas; host_global: pinned.
-hipError_t launch_bitmap_or(uint64_t* local, uint8_t* global, uint8_t* host_global, const uint64_t* masks, int G, int R,
+// For g < G: local[g] = masks[g], global[g] = OR of its bits (the bitmap AllReduce of
+// Section 4.2), host_global[g] = tag * 2 + the same bit.  masks as above, of R replicas; host_global: pinned.
+hipError_t launch_bitmap_or(uint64_t* local, uint8_t* global, uint64_t* host_global, uint64_t tag, const uint64_t* masks, int G, int R,
                             hipStream_t s);
 
 // dst[0 .. count) = src[0 .. count) (pinned memory; 16-byte aligned both, count even), then *done = ticket (pinned).

@@ -1370,17 +1370,17 @@ __global__ __launch_bounds__(BLOCK) void mask_write_kernel(uint64_t* __restrict_
 
 // The one-GPU form of the extra AllReduce on the unused-parameter bitmap
 // (Section 4.2): global[g] = OR over the R replicas of bit r of local[g], for the device (write-back)
-// and for the host (pinned memory, readable behind the event recorded after this launch).
+// and for the host (pinned memory; a word tells by itself whose iteration's it is).
 template <typename Masks>
 __global__ __launch_bounds__(BLOCK) void bitmap_or_kernel(uint64_t* __restrict__ local, uint8_t* __restrict__ global,
-                                                          uint8_t* __restrict__ host_global, Masks p, int count) {
+                                                          uint64_t* __restrict__ host_global, uint64_t tag, Masks p, int count) {
     const int g = blockIdx.x * BLOCK + threadIdx.x;
     if (g >= count) return;
     const uint64_t mask = p.of(g);
     const uint8_t any = mask != 0 ? 1 : 0;
     local[g] = mask;
     global[g] = any;
-    host_global[g] = any;
+    __hip_atomic_store(host_global + g, tag * 2 + any, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // ---- K6: synthetic backward emitter -----------------------------------------
@@ -1822,7 +1822,7 @@ hipError_t launch_mask_write(uint64_t* dst, const uint64_t* masks, int count, co
     return after_launch();
 }
 
-hipError_t launch_bitmap_or(uint64_t* local, uint8_t* global, uint8_t* host_global, const uint64_t* masks, int G, int R,
+hipError_t launch_bitmap_or(uint64_t* local, uint8_t* global, uint64_t* host_global, uint64_t tag, const uint64_t* masks, int G, int R,
                             hipStream_t s) {
     if (G <= 0) return hipSuccess;
     const dim3 grid((G + BLOCK - 1) / BLOCK);
@@ -1831,16 +1831,16 @@ hipError_t launch_bitmap_or(uint64_t* local, uint8_t* global, uint8_t* host_glob
         pack_masks(masks, G, R, p.m);
         p.first = 0;
         p.shift = mask_shift(R);
-        hipLaunchKernelGGL(bitmap_or_kernel<MaskWords>, grid, dim3(BLOCK), 0, s, local, global, host_global, p, G);
+        hipLaunchKernelGGL(bitmap_or_kernel<MaskWords>, grid, dim3(BLOCK), 0, s, local, global, host_global, tag, p, G);
         return after_launch();
     }
     if (G > kMasksByValue) {
-        hipLaunchKernelGGL(bitmap_or_kernel<MaskPointer>, grid, dim3(BLOCK), 0, s, local, global, host_global, MaskPointer{masks}, G);
+        hipLaunchKernelGGL(bitmap_or_kernel<MaskPointer>, grid, dim3(BLOCK), 0, s, local, global, host_global, tag, MaskPointer{masks}, G);
         return after_launch();
     }
     MaskPayload p;
     std::memcpy(p.m, masks, sizeof(uint64_t) * G);
-    hipLaunchKernelGGL(bitmap_or_kernel<MaskPayload>, grid, dim3(BLOCK), 0, s, local, global, host_global, p, G);
+    hipLaunchKernelGGL(bitmap_or_kernel<MaskPayload>, grid, dim3(BLOCK), 0, s, local, global, host_global, tag, p, G);
     return after_launch();
 }
 

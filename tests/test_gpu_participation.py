@@ -417,3 +417,35 @@ def test_masks_in_every_form(R, n, pipeline):
                 poison(reps[r][p], dtypes[p])
     for cap in (1 << 30, 2000):
         check_against_oracle(numel, dtypes, reps, marks, cap, pipeline, False, bool(R % 3))
+
+
+@pytest.mark.parametrize("R,n", [(3, 7), (4, 300), (2, 900), (20, 500)])      # masks in arguments, and in pinned memory
+def test_the_bitmap_read_back_is_that_of_the_closed_iteration(R, n):
+    """Iterations follow each other while the GPU is behind; the bitmap is asked for after some of them."""
+    d, harness = lib()
+    rng = np.random.default_rng(n)
+    numel = [int(x) for x in rng.integers(1, 9, size=n)]
+    grads = harness.DeviceGrads(numel, [FP32] * n, R, fill=0)
+    for r in range(R):
+        grads.upload_replica(r, [np.full(k, r + 1, dtype=np.float32) for k in numel])
+    flags = [rng.random((n, R)) < 0.5 / R for _ in range(6)]
+    with harness.Session(grads, 1 << 20, FUSED) as s:
+        d.ddp_set_option(s.ctx, d.DDP_OPT_FIND_UNUSED, 1)
+        for it, flag in enumerate(flags):
+            d.ddp_synth_backward(s.ctx, [0], [400_000], mark=False)
+            for p in range(n - 1, -1, -1):
+                d.ddp_mark_ready_local(s.ctx, p, [int(u) for u in flag[p]])
+            d.ddp_finalize_backward(s.ctx)
+            if it in (1, 4, 5):
+                assert d.ddp_get_global_used(s.ctx, n).tolist() == flag.any(axis=1).astype(int).tolist(), f"iteration {it}"
+        d.ddp_synchronize(s.ctx)
+    mean = [np.float32(1)] * n                             # replica 0's tensors, updated by every iteration that used them
+    for flag in flags:
+        for p in range(n):
+            if flag[p].any():
+                total = np.float32(0)
+                for r in range(R):
+                    total += (mean[p] if r == 0 else np.float32(r + 1)) if flag[p][r] else np.float32(0)
+                mean[p] = np.float32(total / np.float32(R))
+    for p in range(n):
+        assert (grads.download(0, p) == mean[p]).all(), f"parameter {p}"
