@@ -337,13 +337,23 @@ unsigned lds_for_blocks(const ddp_ctx* c, int32_t blocks) {
 // Resident blocks of shorter launches (which take tiles): one mark per call, us, no cap / four blocks / two: BERT-large, R = 8,
 // 2034 / 2025 / 2038, 240 MB in 8 MiB buckets, R = 12, 555 / 553 / 555, ResNet-50-sized, binary16, R = 16 369 /
 // 366 / 357; 120 MB, R = 4 230 / 230 / 249; all marks in one call, 16 MB, R = 8 25.1 / 25.0 / 25.5 (bfloat16 25.4 / 25.5 / 26.7), R = 16 46.5 / 46.5 /
-// 45.7.  Three blocks lie between four and two.
-int32_t short_launch_blocks(int32_t R) { return R <= 4 ? 0 : R < 16 ? 4 : 2; }
+// 45.7.
+// Binary32 launches that move 200 MiB and more have three (one mark per call; two / three / four blocks): R = 8, BERT-large in 225 MiB
+// launches - / 1972 / 2006, a list in 252 MiB launches - / 202.5 / 201.9, in 72 MiB launches - / 242.7 / 239.7; R = 10, 252 MiB - / 203.7 / 204.2; R = 12, 217 MiB - / 207.5 /
+// 209.0.  Others do not: bfloat16, R = 10 - / 205.2 / 203.8; binary32 averages, R = 8 - / 404 / 402; with masks, ResNet-50, R = 8 - / 127.4 / 124.4; R = 5,
+// 240 MiB - / 204.4 / 202.1; R = 16, 212 MiB 205.0 / 207.9 / -, 108 MiB 219.8 / 223.3 / - (bfloat16 222.2 / 226.6), R = 32 219.2 / 226.7 / -; R = 4, 210 MiB 202.6 with three and 197.8 with
+// no cap.
+constexpr int64_t kThreeBlocksFrom = int64_t(200) << 20;
+int32_t short_launch_blocks(int32_t R, int64_t moved, int es, bool masked) {
+    if (R <= 4) return 0;
+    if (R >= 16) return 2;
+    return R >= 8 && es == 4 && moved >= kThreeBlocksFrom && !masked ? 3 : 4;
+}
 
-unsigned occupancy_lds(const ddp_ctx* c, int64_t launch_bytes, int es, bool copies) {
+unsigned occupancy_lds(const ddp_ctx* c, int64_t launch_bytes, int es, bool copies, bool masked) {
     if (c->blocks_per_cu >= 0) return long_launch(c, launch_bytes) ? lds_for_blocks(c, c->blocks_per_cu) : 0;
     if (long_launch(c, launch_bytes)) return lds_for_blocks(c, auto_blocks_per_cu(c->R, es, copies, c->write_all, !c->out_ptrs.empty()));
-    return copies || c->cap_min_set ? 0 : lds_for_blocks(c, short_launch_blocks(c->R));
+    return copies || c->cap_min_set ? 0 : lds_for_blocks(c, short_launch_blocks(c->R, launch_bytes * (c->R + 1), es, masked));
 }
 
 using ddp::make_scale;
@@ -776,7 +786,7 @@ int32_t launch_range(ddp_ctx* c, int32_t first, int32_t last, Target target) {
         if ((rc = timed_begin(c, DDP_K_REDUCE, id, st, &slot)) != DDP_OK) return rc;
         HIPCHK(c, ddp::launch_flat_reduce(bf.dtype, in0, c->slab_stride, out, nvec, c->R, sc,
                                           c->nontemporal != 0,
-                                          long_launch(c, bytes) ? occupancy_lds(c, bytes, ddp::elem_size(bf.dtype), false) : 0, gate, tag, sig, st));
+                                          long_launch(c, bytes) ? occupancy_lds(c, bytes, ddp::elem_size(bf.dtype), false, need_flags) : 0, gate, tag, sig, st));
         if ((rc = timed_end(c, slot, st)) != DDP_OK) return rc;
     } else {
         const bool staged = c->pipeline == DDP_PIPELINE_STAGED;
@@ -784,7 +794,7 @@ int32_t launch_range(ddp_ctx* c, int32_t first, int32_t last, Target target) {
         if ((rc = timed_begin(c, DDP_K_REDUCE, id, st, &slot)) != DDP_OK) return rc;
         HIPCHK(c, ddp::launch_fused_reduce(bf.dtype, c->tables, tile_base, ntiles, c->R,
                                            c->write_all ? c->R : 1, masks, c->find_unused != 0, sc,
-                                           c->nontemporal != 0, occupancy_lds(c, bytes, ddp::elem_size(bf.dtype), staged),
+                                           c->nontemporal != 0, occupancy_lds(c, bytes, ddp::elem_size(bf.dtype), staged, need_flags),
                                            flat, gate, tag, sig, st));
         if ((rc = timed_end(c, slot, st)) != DDP_OK) return rc;
     }
