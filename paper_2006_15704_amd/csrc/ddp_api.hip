@@ -8,6 +8,7 @@
 #include <chrono>
 #include <cstdio>
 #include <cstring>
+#include <mutex>
 #include <string>
 #include <utility>
 #include <vector>
@@ -423,23 +424,56 @@ int32_t probe_pair(ddp_ctx* c, hipStream_t waiter, hipStream_t other, bool* conc
     return DDP_OK;
 }
 
-// The word that the backward stream waits on for lane l (0 at first).  A device that cannot have one keeps events.
-bool make_done_word(ddp_ctx* c, int l) {
-    int can = 0;
-    if (hipDeviceGetAttribute(&can, hipDeviceAttributeCanUseStreamWaitValue, c->device) != hipSuccess || can == 0) return false;
-    if (c->done_word[l] != nullptr) return true;
-    void* p = nullptr;
-    if (hipExtMallocWithFlags(&p, sizeof(uint64_t), hipMallocSignalMemory) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
+// Words that streams wait on (hipMallocSignalMemory gives them out one at a time, and an allocation takes 30 us): contexts hand
+// theirs on, by device, when their streams have ended; at most kSpareWords are kept.
+constexpr size_t kSpareWords = 32;
+std::mutex g_words_mu;
+std::vector<std::pair<int, uint64_t*>> g_spare_words;
+
+uint64_t* take_word(int device) {
+    {
+        std::lock_guard<std::mutex> lock(g_words_mu);
+        for (size_t k = g_spare_words.size(); k-- > 0;)
+            if (g_spare_words[k].first == device) {
+                uint64_t* const w = g_spare_words[k].second;
+                g_spare_words.erase(g_spare_words.begin() + static_cast<std::ptrdiff_t>(k));
+                __atomic_store_n(w, uint64_t(0), __ATOMIC_SEQ_CST);
+                return w;
+            }
     }
-    if (ddp::launch_done(static_cast<unsigned long long*>(p), 0, c->lane[l]) != hipSuccess || hipStreamSynchronize(c->lane[l]) != hipSuccess) {
+    int can = 0;
+    void* p = nullptr;
+    hipPointerAttribute_t at{};
+    if (hipDeviceGetAttribute(&can, hipDeviceAttributeCanUseStreamWaitValue, device) != hipSuccess || can == 0 ||
+        hipExtMallocWithFlags(&p, sizeof(uint64_t), hipMallocSignalMemory) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    if (hipPointerGetAttributes(&at, p) != hipSuccess || at.type != hipMemoryTypeHost) {      // (the host sets them to 0)
         (void)hipGetLastError();
         (void)hipFree(p);
-        return false;
+        return nullptr;
     }
-    c->done_word[l] = static_cast<uint64_t*>(p);
-    return true;
+    __atomic_store_n(static_cast<uint64_t*>(p), uint64_t(0), __ATOMIC_SEQ_CST);
+    return static_cast<uint64_t*>(p);
+}
+
+// No stream waits for the word or writes it any more.
+void give_word(int device, uint64_t* w) {
+    {
+        std::lock_guard<std::mutex> lock(g_words_mu);
+        if (g_spare_words.size() < kSpareWords) {
+            g_spare_words.emplace_back(device, w);
+            return;
+        }
+    }
+    (void)hipFree(w);
+}
+
+// The word that the backward stream waits on for lane l (0 at first).  A device that cannot have one keeps events.
+bool make_done_word(ddp_ctx* c, int l) {
+    if (c->done_word[l] == nullptr) c->done_word[l] = take_word(c->device);
+    return c->done_word[l] != nullptr;
 }
 
 // Lane l against the backward stream: a gate kernel on a lane that shares the backward
@@ -924,19 +958,21 @@ void release_build(ddp_ctx* c) {
 void release_device(ddp_ctx* c) {
     if (c->plan_only) return;
     (void)hipSetDevice(c->device);
-    if (c->reduce) (void)hipStreamSynchronize(c->reduce);
-    if (c->backward) (void)hipStreamSynchronize(c->backward);
-    if (!c->reduce || !c->backward) (void)hipStreamSynchronize(nullptr);
+    bool ended = true;                 // nothing of the context is under way
+    auto wait = [&](hipStream_t s) { ended = hipStreamSynchronize(s) == hipSuccess && ended; };
+    if (c->reduce) wait(c->reduce);
+    if (c->backward) wait(c->backward);
+    if (!c->reduce || !c->backward) wait(nullptr);
     for (int l = 1; l < ddp_ctx::kMaxLanes; ++l) {
         if (c->lane[l]) {
-            (void)hipStreamSynchronize(c->lane[l]);
+            wait(c->lane[l]);
             (void)hipStreamDestroy(c->lane[l]);
             c->lane[l] = nullptr;
         }
         if (c->ev_join[l]) { (void)hipEventDestroy(c->ev_join[l]); c->ev_join[l] = nullptr; }
     }
     for (uint64_t*& w : c->done_word) {
-        if (w) (void)hipFree(w);
+        if (w && ended) give_word(c->device, w);      // (else it is left alone: a kernel may still write it)
         w = nullptr;
     }
     drop_timed(c);

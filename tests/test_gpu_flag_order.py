@@ -108,24 +108,26 @@ def test_work_behind_finalize_sees_the_launches_of_every_reduction_stream(stream
     want, _, wlog = oracle.synchronize(numel, dtypes, cap, reps)[:3]
     keep = harness.DeviceGrads(numel, dtypes, rounds, fill=0)
     torch.cuda.synchronize()
-    with session_with_flags(d, harness, grads, cap, streams) as s:
-        d.ddp_set_option(s.ctx, d.DDP_OPT_GATE_WAIT_US, gate_wait_us)
+    for context in range(2):          # (the second takes over what the first one's streams waited on)
+        with session_with_flags(d, harness, grads, cap, streams) as s:
+            d.ddp_set_option(s.ctx, d.DDP_OPT_GATE_WAIT_US, gate_wait_us)
+            for it in range(rounds):
+                with torch.cuda.stream(s.backward_stream):
+                    for r in range(R):
+                        grads.bufs[r].copy_(src.bufs[r], non_blocking=True)
+                for p in range(n - 1, -1, -1):
+                    d.ddp_mark_ready(s.ctx, p)
+                d.ddp_finalize_backward(s.ctx)
+                assert d.ddp_get_launch_log(s.ctx, 1) == wlog
+                with torch.cuda.stream(s.backward_stream):
+                    keep.bufs[it].copy_(grads.bufs[0], non_blocking=True)
+                    grads.bufs[0].fill_(0xFF)
+            d.ddp_synchronize(s.ctx)
+            torch.cuda.synchronize()
         for it in range(rounds):
-            with torch.cuda.stream(s.backward_stream):
-                for r in range(R):
-                    grads.bufs[r].copy_(src.bufs[r], non_blocking=True)
-            for p in range(n - 1, -1, -1):
-                d.ddp_mark_ready(s.ctx, p)
-            d.ddp_finalize_backward(s.ctx)
-            assert d.ddp_get_launch_log(s.ctx, 1) == wlog
-            with torch.cuda.stream(s.backward_stream):
-                keep.bufs[it].copy_(grads.bufs[0], non_blocking=True)
-                grads.bufs[0].fill_(0xFF)
-        d.ddp_synchronize(s.ctx)
-        torch.cuda.synchronize()
-    for it in range(rounds):
-        for i in range(n):
-            assert keep.download(it, i).tobytes() == want[i].tobytes(), f"iteration {it} parameter {i}"
+            for i in range(n):
+                assert keep.download(it, i).tobytes() == want[i].tobytes(), f"context {context} iteration {it} parameter {i}"
+            keep.bufs[it].fill_(0)
 
 
 @pytest.mark.parametrize("find_unused", [False, True])
