@@ -84,7 +84,7 @@ struct ddp_ctx {
     int64_t slab_stride = 0;
     std::vector<int64_t> bucket_slab_off;    // byte offset of each bucket inside a slab
     std::vector<int64_t> bucket_vecs;        // 16-byte vectors per bucket (padded)
-    std::vector<int64_t> h_tile0;            // [G+1]
+    std::vector<int64_t> h_tile0, h_slices;  // [G+1], see HostTables
     void* d_tables = nullptr;                // one allocation holding all segment tables
     int32_t* d_tile_seg = nullptr;           // [tiles] segment index of every tile
     ddp::SegTables tables{};
@@ -296,9 +296,9 @@ int64_t launch_traffic(const ddp_ctx* c, int64_t launch_bytes) {
 // One pass / two kernels, us a synchronization, all marks in one call, sixty tensors: binary32, 384 tiles R = 24 40 / 40,
 // R = 32 53 / 49, R = 64 102 / 87, 512 R = 64 147 / 122; 16 bits, 384 R = 24 48 / 45, R = 64 118 / 97, 512 R = 24 56 / 52,
 // R = 32 74 / 64, R = 64 149 / 117, 1024 R = 32 143 / 144.  R = 16 in one pass is no slower.
-bool split_pass(const ddp_ctx* c, int32_t dtype, int64_t ntiles) {
-    const int64_t above = c->nontemporal != 0 ? ddp::slice_tiles(c->R, ddp::elem_size(dtype), true) : 0;
-    return c->R > 16 && ntiles > above && ntiles <= (dtype == DDP_FP32 ? 512 : 1024);
+bool split_pass(const ddp_ctx* c, int32_t dtype, int64_t ntiles, int64_t nslices) {
+    if (c->nontemporal != 0 && ddp::takes_slices(c->R, ddp::elem_size(dtype), true, ntiles, nslices)) return false;
+    return c->R > 16 && ntiles <= (dtype == DDP_FP32 ? 512 : 1024);
 }
 
 // A model of at most kSmallModelBuckets buckets that move less than this together keeps all of its
@@ -669,6 +669,7 @@ int32_t launch_range(ddp_ctx* c, int32_t first, int32_t last, Target target) {
     const int seg_end = bl.seg_begin + static_cast<int>(bl.params.size());
     const int64_t tile_base = c->h_tile0[seg_begin];
     const int64_t ntiles = c->h_tile0[seg_end] - tile_base;
+    const int64_t nslices = c->h_slices[seg_end] - c->h_slices[seg_begin];
     int64_t bytes = 0;
     for (int32_t b = first; b <= last; ++b) bytes += static_cast<int64_t>(c->plan.buckets[b].bytes());
     const int64_t traffic = launch_traffic(c, bytes);
@@ -776,7 +777,7 @@ int32_t launch_range(ddp_ctx* c, int32_t first, int32_t last, Target target) {
     uint64_t mask_words[ddp::kMaskWords];
     bool need_flags = false;
     for (int32_t b = first; b <= last; ++b) need_flags = need_flags || c->bucket_zero[b] != 0;
-    const bool two_kernels = c->pipeline == DDP_PIPELINE_STAGED && (c->timing == 1 || split_pass(c, bf.dtype, ntiles));
+    const bool two_kernels = c->pipeline == DDP_PIPELINE_STAGED && (c->timing == 1 || split_pass(c, bf.dtype, ntiles, nslices));
     if (need_flags && !two_kernels && ddp::masks_fit(c->R, seg_end - seg_begin)) {
         ddp::pack_masks(c->local_cur.data() + seg_begin, seg_end - seg_begin, c->R, mask_words);
         masks.words = mask_words;
@@ -826,7 +827,7 @@ int32_t launch_range(ddp_ctx* c, int32_t first, int32_t last, Target target) {
         const bool staged = c->pipeline == DDP_PIPELINE_STAGED;
         const ddp::FlatBuckets flat{staged ? c->slabs : nullptr, staged ? c->slab_stride : 0};
         if ((rc = timed_begin(c, DDP_K_REDUCE, id, st, &slot)) != DDP_OK) return rc;
-        HIPCHK(c, ddp::launch_fused_reduce(bf.dtype, c->tables, tile_base, ntiles, c->R,
+        HIPCHK(c, ddp::launch_fused_reduce(bf.dtype, c->tables, tile_base, ntiles, nslices, c->R,
                                            c->write_all ? c->R : 1, masks, c->find_unused != 0, sc,
                                            c->nontemporal != 0, occupancy_lds(c, bytes, ddp::elem_size(bf.dtype), staged, need_flags),
                                            flat, gate, tag, sig, st));
@@ -1293,6 +1294,7 @@ static int32_t build_internal(ddp_ctx* c, uint64_t cap_bytes, const std::vector<
         c->bucket_vecs = ht.bucket_vecs;
         c->slab_stride = ht.slab_stride;
         c->h_tile0 = ht.tile0;
+        c->h_slices = ht.slices;
         if (c->h_tile0[n] >= (int64_t(1) << 31)) {
             c->built = false;
             return fail(c, DDP_ERR_UNSUPPORTED, "model too large for one launch grid");

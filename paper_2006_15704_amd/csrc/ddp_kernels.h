@@ -51,6 +51,27 @@ inline int64_t slice_tiles(int R, int es, bool staged) {
     return staged ? 256 : es == 2 ? 192 : 128;
 }
 
+// Slices that hold elements of a segment with `ntiles` tiles (whatever its lead-in).
+inline int64_t slices_for(int64_t numel, int es, int64_t ntiles) {
+    const int64_t most = ntiles * SLICES, n = (numel * es + 15 + SLICE_BYTES - 1) / SLICE_BYTES;
+    return n < most ? n : most;
+}
+
+// Whether a launch takes slices.  The tiles of small tensors are mostly empty, and blocks of empty slices end at once, so for some numbers of
+// replicas the slices that hold something count, up to so many tiles.  (With many replicas an empty block's LDS holds the others
+// up.)  All marks in one call, 240 tensors of 1000 kB in all, us, by tiles -> by slices: staged, binary32 R = 5 10.5 -> 11.2, R = 8 12.6 -> 11.9, R = 12 16.7 ->
+// 14.0, R = 16 19.6 -> 16.0, R = 24 21.2 -> 20.5, bfloat16 R = 5 13.0 -> 12.1, R = 8 15.7 -> 12.8, R = 12 22.0 -> 15.0, R = 16 26.4 -> 17.0, R = 24 24.1 -> 23.3; of 600 kB,
+// R = 32 21.1 -> 21.3 and 24.0 -> 24.2, R = 64 33.6 -> 43.6 and 39.3 -> 51.1.  Fused, 140 of 300 kB / 200 of 300 / 240 of 1000: binary32 R = 12 5.7 -> 5.1 / - / -, R = 16 6.2 ->
+// 5.6 / - / (600 kB) 6.8 -> 7.4, R = 24 7.9 -> 5.8 / 7.9 -> 7.3 / -, bfloat16 R = 12 - / 7.1 -> 5.9 / 7.9 -> 8.5, R = 16 - / 7.5 -> 6.4 / 8.9 -> 9.3, R = 24 - / 9.6 -> 8.4 / 12.2 ->
+// 11.5, R = 8 (1200 kB) 6.9 -> 7.2, R = 32 (600 kB) 12.2 -> 12.7, R = 64 (600 kB) 21.7 -> 29.2.
+inline bool takes_slices(int R, int es, bool staged, int64_t ntiles, int64_t nslices) {
+    const int64_t line = slice_tiles(R, es, staged);
+    if (ntiles <= line) return true;
+    const int least = !staged ? 9 : es == 2 ? 5 : 8;
+    if (R < least || R > 24 || nslices > line * SLICES) return false;
+    return ntiles <= (!staged && R <= 16 ? line * 3 / 2 : line * 4);
+}
+
 // Tiles of a segment.  Vectors are cut at 16-byte boundaries of the
 // destination, so a destination that starts `lead_bytes` (< 16) past such a
 // boundary shifts the grid by that much; the caller passes the largest lead-in
@@ -177,7 +198,8 @@ void pack_masks(const uint64_t* masks, int count, int R, uint64_t* words);
 // one pass instead: every replica's gradients are copied into its flat bucket
 // (zeros for a replica that did not use the parameter) and the average goes to
 // the averaged bucket; nwrite and keep_unused do not matter then.
-hipError_t launch_fused_reduce(int dtype, const SegTables& t, int64_t tile_base, int64_t ntiles,
+// nslices: slices of the range that hold elements, see slices_for.
+hipError_t launch_fused_reduce(int dtype, const SegTables& t, int64_t tile_base, int64_t ntiles, int64_t nslices,
                                int R, int nwrite, const Masks& masks, bool keep_unused, Scale sc,
                                bool nontemporal, unsigned lds, FlatBuckets flat,
                                const GateRecord* gate, uint32_t tag, DispatchSignal sig, hipStream_t s);
@@ -195,7 +217,7 @@ struct WordTables {
     bool regular;
     int count(int R) const { return regular ? 2 * n + R : n * (R + 1); }
 };
-hipError_t launch_fused_reduce_by_value(int dtype, const WordTables& t, int64_t tile_base, int64_t ntiles, int R, Scale sc,
+hipError_t launch_fused_reduce_by_value(int dtype, const WordTables& t, int64_t tile_base, int64_t ntiles, int64_t nslices, int R, Scale sc,
                                         hipStream_t s);
 
 // ---- stream ordering through device flags -------------------------------------

@@ -1583,12 +1583,12 @@ static hipError_t slice_launch(int64_t ntiles, hipStream_t s, const SegTables& t
 }
 
 template <int DT, int OUT>
-static hipError_t fused_dispatch(bool nt, int64_t ntiles, unsigned lds, hipStream_t s,
+static hipError_t fused_dispatch(bool nt, int64_t ntiles, int64_t nslices, unsigned lds, hipStream_t s,
                                  const SegTables& t, int64_t tile_base, int R, int nwrite,
                                  const Masks& masks, int keep, Scale sc, FlatBuckets flat,
                                  const GateRecord* gate, uint32_t tag, DispatchSignal sig) {
     // (without the hint every launch takes tiles, so that both kernels can be had at any size)
-    const bool slices = nt && ntiles <= slice_tiles(R, Fmt<DT>::ES, OUT == OUT_FLAT);
+    const bool slices = nt && takes_slices(R, Fmt<DT>::ES, OUT == OUT_FLAT, ntiles, nslices);
     auto with = [&](const auto& m) {
         if (slices) return slice_launch<DT, OUT>(ntiles, s, t, tile_base, R, nwrite, m, keep, sc, flat, gate, tag, sig);
         return fused_launch<DT, OUT>(nt, ntiles, lds, s, t, tile_base, R, nwrite, m, keep, sc, flat, gate, tag, sig);
@@ -1615,7 +1615,7 @@ void pack_masks(const uint64_t* masks, int count, int R, uint64_t* words) {
     for (int k = 0; k < count; ++k) words[(k << shift) >> 6] |= masks[k] << ((k << shift) & 63);
 }
 
-hipError_t launch_fused_reduce(int dtype, const SegTables& t, int64_t tile_base, int64_t ntiles,
+hipError_t launch_fused_reduce(int dtype, const SegTables& t, int64_t tile_base, int64_t ntiles, int64_t nslices,
                                int R, int nwrite, const Masks& masks, bool keep_unused, Scale sc,
                                bool nontemporal, unsigned lds, FlatBuckets flat,
                                const GateRecord* gate, uint32_t tag, DispatchSignal sig, hipStream_t s) {
@@ -1625,29 +1625,29 @@ hipError_t launch_fused_reduce(int dtype, const SegTables& t, int64_t tile_base,
         // 16-bit gradients, binary32 averages to separate tensors
         if (nwrite != 1 || flat.slab0 != nullptr) return hipErrorInvalidValue;
         switch (dtype) {
-            case 1: return fused_dispatch<1, OUT_BINARY32>(nontemporal, ntiles, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
-            case 2: return fused_dispatch<2, OUT_BINARY32>(nontemporal, ntiles, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
+            case 1: return fused_dispatch<1, OUT_BINARY32>(nontemporal, ntiles, nslices, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
+            case 2: return fused_dispatch<2, OUT_BINARY32>(nontemporal, ntiles, nslices, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
             default: return hipErrorInvalidValue;
         }
     }
     if (flat.slab0 != nullptr) {
         switch (dtype) {
-            case 0: return fused_dispatch<0, OUT_FLAT>(nontemporal, ntiles, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
-            case 1: return fused_dispatch<1, OUT_FLAT>(nontemporal, ntiles, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
-            case 2: return fused_dispatch<2, OUT_FLAT>(nontemporal, ntiles, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
+            case 0: return fused_dispatch<0, OUT_FLAT>(nontemporal, ntiles, nslices, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
+            case 1: return fused_dispatch<1, OUT_FLAT>(nontemporal, ntiles, nslices, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
+            case 2: return fused_dispatch<2, OUT_FLAT>(nontemporal, ntiles, nslices, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
             default: return hipErrorInvalidValue;
         }
     }
     switch (dtype) {
-        case 0: return fused_dispatch<0, OUT_GRAD>(nontemporal, ntiles, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
-        case 1: return fused_dispatch<1, OUT_GRAD>(nontemporal, ntiles, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
-        case 2: return fused_dispatch<2, OUT_GRAD>(nontemporal, ntiles, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
+        case 0: return fused_dispatch<0, OUT_GRAD>(nontemporal, ntiles, nslices, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
+        case 1: return fused_dispatch<1, OUT_GRAD>(nontemporal, ntiles, nslices, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
+        case 2: return fused_dispatch<2, OUT_GRAD>(nontemporal, ntiles, nslices, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
         default: return hipErrorInvalidValue;
     }
 }
 
 template <int DT, int N>
-static hipError_t value_launch(const WordTables& words, int64_t tile_base, int64_t ntiles, int R, Scale sc, hipStream_t s) {
+static hipError_t value_launch(const WordTables& words, int64_t tile_base, int64_t ntiles, int64_t nslices, int R, Scale sc, hipStream_t s) {
     ArgTables<N> t;
     std::memcpy(t.w, words.words, sizeof(uint64_t) * words.count(R));
     t.n = words.n;
@@ -1657,7 +1657,7 @@ static hipError_t value_launch(const WordTables& words, int64_t tile_base, int64
     t.dist = words.regular ? words.n + R : 0;
     const FlatBuckets flat{nullptr, 0};
     const DispatchSignal sig{nullptr, 0};
-    if (ntiles > slice_tiles(R, Fmt<DT>::ES, false))
+    if (!takes_slices(R, Fmt<DT>::ES, false, ntiles, nslices))
         return launch(fused_reduce_kernel<DT, true, RU, OUT_GRAD, NoMasks, 0, ArgTables<N>>, dim3(static_cast<unsigned>(ntiles)), edge_lds(R), s,
                       t, tile_base, R, 1, NoMasks{}, 0, sc, flat, nullptr, 0u, sig);
     const dim3 grid(static_cast<unsigned>(ntiles * SLICES));
@@ -1667,21 +1667,21 @@ static hipError_t value_launch(const WordTables& words, int64_t tile_base, int64
 }
 
 template <int DT>
-static hipError_t value_dispatch(const WordTables& t, int64_t tile_base, int64_t ntiles, int R, Scale sc, hipStream_t s) {
+static hipError_t value_dispatch(const WordTables& t, int64_t tile_base, int64_t ntiles, int64_t nslices, int R, Scale sc, hipStream_t s) {
     const int count = t.count(R);
-    if (count <= 128) return value_launch<DT, 128>(t, tile_base, ntiles, R, sc, s);
-    if (count <= 256) return value_launch<DT, 256>(t, tile_base, ntiles, R, sc, s);
-    return value_launch<DT, kTableWords>(t, tile_base, ntiles, R, sc, s);
+    if (count <= 128) return value_launch<DT, 128>(t, tile_base, ntiles, nslices, R, sc, s);
+    if (count <= 256) return value_launch<DT, 256>(t, tile_base, ntiles, nslices, R, sc, s);
+    return value_launch<DT, kTableWords>(t, tile_base, ntiles, nslices, R, sc, s);
 }
 
-hipError_t launch_fused_reduce_by_value(int dtype, const WordTables& t, int64_t tile_base, int64_t ntiles, int R, Scale sc,
+hipError_t launch_fused_reduce_by_value(int dtype, const WordTables& t, int64_t tile_base, int64_t ntiles, int64_t nslices, int R, Scale sc,
                                         hipStream_t s) {
     if (ntiles <= 0) return hipSuccess;
     if (t.n <= 0 || R <= 0 || R > MAX_REPLICAS || t.count(R) > kTableWords) return hipErrorInvalidValue;
     switch (dtype) {
-        case 0: return value_dispatch<0>(t, tile_base, ntiles, R, sc, s);
-        case 1: return value_dispatch<1>(t, tile_base, ntiles, R, sc, s);
-        case 2: return value_dispatch<2>(t, tile_base, ntiles, R, sc, s);
+        case 0: return value_dispatch<0>(t, tile_base, ntiles, nslices, R, sc, s);
+        case 1: return value_dispatch<1>(t, tile_base, ntiles, nslices, R, sc, s);
+        case 2: return value_dispatch<2>(t, tile_base, ntiles, nslices, R, sc, s);
         default: return hipErrorInvalidValue;
     }
 }

@@ -244,7 +244,8 @@ extern "C" int32_t ddp_sync_static(int32_t R, int32_t device, void* stream, int3
             while (e < nb && plan.buckets[e].dtype == plan.buckets[b].dtype) ++e;
             const int64_t tile0 = ht.tile0[plan.buckets[b].seg_begin];
             const int64_t tile1 = e < nb ? ht.tile0[plan.buckets[e].seg_begin] : ntiles;
-            const hipError_t err = launch_tiles(plan.buckets[b].dtype, tile0, tile1 - tile0);
+            const int64_t nslices = ht.slices[e < nb ? plan.buckets[e].seg_begin : n] - ht.slices[plan.buckets[b].seg_begin];
+            const hipError_t err = launch_tiles(plan.buckets[b].dtype, tile0, tile1 - tile0, nslices);
             if (err != hipSuccess) return err;
             b = e;
         }
@@ -267,8 +268,8 @@ extern "C" int32_t ddp_sync_static(int32_t R, int32_t device, void* stream, int3
             else for (int64_t r = 0; r < R; ++r) words[n + static_cast<int64_t>(g) * R + r] = reinterpret_cast<uintptr_t>(grad_ptrs[r * n + si.param]);
         }
         for (int32_t r = 0; shift != nullptr && r < R; ++r) words[n + r] = base0 + shift[r];
-        HIPCHK0(for_each_run([&](int32_t dt, int64_t tile0, int64_t count) {
-            return ddp::launch_fused_reduce_by_value(dt, by_value, tile0, count, R, sc, s);
+        HIPCHK0(for_each_run([&](int32_t dt, int64_t tile0, int64_t count, int64_t nslices) {
+            return ddp::launch_fused_reduce_by_value(dt, by_value, tile0, count, nslices, R, sc, s);
         }));
         return nb;
     }
@@ -291,8 +292,8 @@ extern "C" int32_t ddp_sync_static(int32_t R, int32_t device, void* stream, int3
     char* slabs = reinterpret_cast<char*>(base + table_bytes);
 
     if (in_place) {
-        HIPCHK0(for_each_run([&](int32_t dt, int64_t tile0, int64_t count) {
-            return ddp::launch_fused_reduce(dt, t, tile0, count, R, 1, ddp::Masks{}, false, sc, true, 0, ddp::FlatBuckets{nullptr, 0}, nullptr, 0,
+        HIPCHK0(for_each_run([&](int32_t dt, int64_t tile0, int64_t count, int64_t nslices) {
+            return ddp::launch_fused_reduce(dt, t, tile0, count, nslices, R, 1, ddp::Masks{}, false, sc, true, 0, ddp::FlatBuckets{nullptr, 0}, nullptr, 0,
                                             ddp::DispatchSignal{nullptr, 0}, s);
         }));
         return nb;

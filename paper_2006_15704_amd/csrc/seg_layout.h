@@ -16,6 +16,7 @@ struct HostTables {
     std::vector<int64_t> bucket_vecs;       // 16-byte vectors per bucket (length padded to 16 bytes)
     int64_t slab_stride = 0;                // bytes of one replica's slab (all buckets), multiple of 4096
     std::vector<int64_t> tile0;             // [G + 1] first tile of every segment
+    std::vector<int64_t> slices;            // [G + 1] slices with elements in front of every segment
     std::vector<SegInfo> seg;               // [G]
     std::vector<void*> grad;                // [G * R + 16], see SegTables::grad
     std::vector<int32_t> tile_seg;          // [tile0[G]]
@@ -46,6 +47,7 @@ inline void build_layout(const BucketPlan& plan, void* const* grad_ptrs, int R, 
     for (int r = 0; r < R && !shifted; ++r) shifted = (shift[r] & 15u) != 0;
 
     h.tile0.assign(n + 1, 0);
+    h.slices.assign(n + 1, 0);
     h.seg.assign(n, SegInfo{});
     h.out.assign(out_ptrs ? n : 0, nullptr);
     for (int32_t b = 0; b < nb; ++b) {
@@ -68,6 +70,7 @@ inline void build_layout(const BucketPlan& plan, void* const* grad_ptrs, int R, 
                 cong = cong && ((a ^ a0) & 15u) == 0;
             }
             h.tile0[g + 1] = h.tile0[g] + tiles_for(p.numel, es, lead);
+            h.slices[g + 1] = h.slices[g] + slices_for(p.numel, es, h.tile0[g + 1] - h.tile0[g]);
             h.seg[g].numel = p.numel;
             h.seg[g].tile0 = h.tile0[g];
             h.seg[g].flat_byte = flat_byte;
