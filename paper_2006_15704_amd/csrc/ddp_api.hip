@@ -86,7 +86,7 @@ struct ddp_ctx {
     std::vector<int64_t> bucket_vecs;        // 16-byte vectors per bucket (padded)
     std::vector<int64_t> h_tile0, h_slices;  // [G+1], see HostTables
     void* d_tables = nullptr;                // one allocation holding all segment tables
-    int32_t* d_tile_seg = nullptr;           // [tiles] segment index of every tile
+    int32_t* d_tile_seg = nullptr;           // [tiles] segment index of every tile, and behind it the listed slices
     ddp::SegTables tables{};
     // participation: one mask per segment, bit r = replica r used the parameter
     int32_t find_unused = 0;                 // 1: parameters nobody used keep their gradients
@@ -297,7 +297,7 @@ int64_t launch_traffic(const ddp_ctx* c, int64_t launch_bytes) {
 // R = 32 53 / 49, R = 64 102 / 87, 512 R = 64 147 / 122; 16 bits, 384 R = 24 48 / 45, R = 64 118 / 97, 512 R = 24 56 / 52,
 // R = 32 74 / 64, R = 64 149 / 117, 1024 R = 32 143 / 144.  R = 16 in one pass is no slower.
 bool split_pass(const ddp_ctx* c, int32_t dtype, int64_t ntiles, int64_t nslices) {
-    if (c->nontemporal != 0 && ddp::takes_slices(c->R, ddp::elem_size(dtype), true, ntiles, nslices)) return false;
+    if (c->nontemporal != 0 && ddp::takes_slices(c->R, ddp::elem_size(dtype), true, ntiles, nslices, c->tables.slices != nullptr)) return false;
     return c->R > 16 && ntiles <= (dtype == DDP_FP32 ? 512 : 1024);
 }
 
@@ -827,7 +827,7 @@ int32_t launch_range(ddp_ctx* c, int32_t first, int32_t last, Target target) {
         const bool staged = c->pipeline == DDP_PIPELINE_STAGED;
         const ddp::FlatBuckets flat{staged ? c->slabs : nullptr, staged ? c->slab_stride : 0};
         if ((rc = timed_begin(c, DDP_K_REDUCE, id, st, &slot)) != DDP_OK) return rc;
-        HIPCHK(c, ddp::launch_fused_reduce(bf.dtype, c->tables, tile_base, ntiles, nslices, c->R,
+        HIPCHK(c, ddp::launch_fused_reduce(bf.dtype, c->tables, tile_base, ntiles, c->h_slices[seg_begin], nslices, c->R,
                                            c->write_all ? c->R : 1, masks, c->find_unused != 0, sc,
                                            c->nontemporal != 0, occupancy_lds(c, bytes, ddp::elem_size(bf.dtype), staged, need_flags),
                                            flat, gate, tag, sig, st));
@@ -1289,7 +1289,7 @@ static int32_t build_internal(ddp_ctx* c, uint64_t cap_bytes, const std::vector<
             if (c->write_all)
                 return fail(c, DDP_ERR_UNSUPPORTED, "binary32 outputs (ddp_set_outputs) cannot be combined with DDP_OPT_WRITE_ALL");
         }
-        ddp::build_host_tables(c->plan, c->grad_ptrs.data(), c->R, ht, c->out_ptrs.empty() ? nullptr : c->out_ptrs.data());
+        ddp::build_host_tables(c->plan, c->grad_ptrs.data(), c->R, ht, c->out_ptrs.empty() ? nullptr : c->out_ptrs.data(), true);
         c->bucket_slab_off = ht.bucket_slab_off;
         c->bucket_vecs = ht.bucket_vecs;
         c->slab_stride = ht.slab_stride;
@@ -1325,6 +1325,7 @@ static int32_t build_internal(ddp_ctx* c, uint64_t cap_bytes, const std::vector<
             if (!tile_seg.empty())
                 HIPCHK(c, hipMemcpy(c->d_tile_seg, tile_seg.data(), sizeof(int32_t) * tile_seg.size(), hipMemcpyHostToDevice));
             c->tables.tile_seg = c->d_tile_seg;
+            c->tables.slices = ht.listed ? c->d_tile_seg + c->h_tile0[n] : nullptr;
         }
 
         HIPCHK(c, hipMalloc(reinterpret_cast<void**>(&c->d_local), sizeof(uint64_t) * n));

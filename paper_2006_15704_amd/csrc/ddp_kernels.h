@@ -57,19 +57,29 @@ inline int64_t slices_for(int64_t numel, int es, int64_t ntiles) {
     return n < most ? n : most;
 }
 
-// Whether a launch takes slices.  The tiles of small tensors are mostly empty, and blocks of empty slices end at once, so for some numbers of
-// replicas the slices that hold something count, up to so many tiles.  (With many replicas an empty block's LDS holds the others
-// up.)  All marks in one call, 240 tensors of 1000 kB in all, us, by tiles -> by slices: staged, binary32 R = 5 10.5 -> 11.2, R = 8 12.6 -> 11.9, R = 12 16.7 ->
-// 14.0, R = 16 19.6 -> 16.0, R = 24 21.2 -> 20.5, bfloat16 R = 5 13.0 -> 12.1, R = 8 15.7 -> 12.8, R = 12 22.0 -> 15.0, R = 16 26.4 -> 17.0, R = 24 24.1 -> 23.3; of 600 kB,
-// R = 32 21.1 -> 21.3 and 24.0 -> 24.2, R = 64 33.6 -> 43.6 and 39.3 -> 51.1.  Fused, 140 of 300 kB / 200 of 300 / 240 of 1000: binary32 R = 12 5.7 -> 5.1 / - / -, R = 16 6.2 ->
-// 5.6 / - / (600 kB) 6.8 -> 7.4, R = 24 7.9 -> 5.8 / 7.9 -> 7.3 / -, bfloat16 R = 12 - / 7.1 -> 5.9 / 7.9 -> 8.5, R = 16 - / 7.5 -> 6.4 / 8.9 -> 9.3, R = 24 - / 9.6 -> 8.4 / 12.2 ->
-// 11.5, R = 8 (1200 kB) 6.9 -> 7.2, R = 32 (600 kB) 12.2 -> 12.7, R = 64 (600 kB) 21.7 -> 29.2.
-inline bool takes_slices(int R, int es, bool staged, int64_t ntiles, int64_t nslices) {
+// Whether a launch takes slices.  The tiles of small tensors are mostly empty.  Where the slices that hold something are listed
+// (SegTables::slices) they count, and the others have no block.  All marks in one call, 170 tensors of 200 kB in all / 240 of 600 / 240 of 1200, us, by tiles ->
+// by listed slices: fused, binary32 R = 16 6.3 -> 5.3 / 6.8 -> 5.8 / -, R = 24 8.1 -> 5.5 / 9.0 -> 6.0 / -, R = 32 9.5 -> 5.5 / 10.8 -> 6.6 / -, R = 64 16.2 -> 7.1 / 19.9 -> 12.3 / -;
+// bfloat16 R = 8 - / 6.1 -> 5.8 / 6.9 -> 5.8, R = 16 - / 8.1 -> 6.0 / 10.1 -> 7.4, R = 32 9.3 -> 5.6 / 12.2 -> 7.7 / 16.0 -> 11.2, R = 64 19.6 -> 7.9 / 21.7 -> 13.9 / -; staged,
+// binary32 R = 8 - / 10.6 -> 9.2 / 13.6 -> 10.6, R = 16 9.9 -> 8.8 / 15.1 -> 11.1 / 20.3 -> 14.8, R = 32 13.9 -> 10.2 / 21.1 -> 14.8 / 27.1 -> 24.7, R = 64 23.1 -> 15.0 / 33.6 -> 26.0 / -;
+// bfloat16 R = 8 - / 13.0 -> 9.5 / 15.9 -> 11.4, R = 16 10.7 -> 9.1 / 19.2 -> 11.8 / 24.8 -> 16.2, R = 64 27.3 -> 18.3 / 39.3 -> 30.3 / -.
+// Where they are not, blocks of empty slices end at once, but hold up others by the LDS they get, so that the slices that hold something
+// count for some numbers of replicas only, up to so many tiles: 240 tensors of 1000 kB, by tiles -> by slices: staged, binary32 R = 5 10.5 -> 11.2, R = 8 12.6 -> 11.9, R = 16
+// 19.6 -> 16.0, R = 24 21.2 -> 20.5, bfloat16 R = 5 13.0 -> 12.1, R = 16 26.4 -> 17.0, R = 24 24.1 -> 23.3; of 600 kB, R = 32 21.1 -> 21.3 and 24.0 -> 24.2, R = 64 33.6 -> 43.6 and
+// 39.3 -> 51.1.  Fused, 140 of 300 kB / 200 of 300 / 240 of 1000: binary32 R = 12 5.7 -> 5.1 / - / -, R = 16 6.2 -> 5.6 / - / (600 kB) 6.8 -> 7.4, R = 24 7.9 -> 5.8 / 7.9 -> 7.3 / -,
+// bfloat16 R = 12 - / 7.1 -> 5.9 / 7.9 -> 8.5, R = 16 - / 7.5 -> 6.4 / 8.9 -> 9.3, R = 24 - / 9.6 -> 8.4 / 12.2 -> 11.5, R = 8 (1200 kB) 6.9 -> 7.2, R = 64 (600 kB) 21.7 -> 29.2.
+inline bool takes_slices(int R, int es, bool staged, int64_t ntiles, int64_t nslices, bool listed) {
     const int64_t line = slice_tiles(R, es, staged);
     if (ntiles <= line) return true;
+    if (listed) return nslices <= line * SLICES;
     const int least = !staged ? 9 : es == 2 ? 5 : 8;
     if (R < least || R > 24 || nslices > line * SLICES) return false;
     return ntiles <= (!staged && R <= 16 ? line * 3 / 2 : line * 4);
+}
+// Whether a launch of slices goes by the list.  It is one more access in front of the others: 30 tensors of 300 kB, seven of ten slices of
+// their tiles, R = 64 7.3 us without and 7.75 with it, R = 32 5.2 / 5.4.
+inline bool takes_list(int R, int es, bool staged, int64_t ntiles, int64_t nslices) {
+    return ntiles > slice_tiles(R, es, staged) || 2 * nslices < ntiles * SLICES;
 }
 
 // Tiles of a segment.  Vectors are cut at 16-byte boundaries of the
@@ -108,6 +118,8 @@ struct SegTables {
                                // transport, Section 6.2.3), or null: averages go to the gradients
     int32_t G;
     int32_t R;
+    const int32_t* slices = nullptr;   // [slices that hold elements] tile * SLICES + slice within it, in ascending order; null: there are
+                                       // no such table, and slice launches have a block for every slice of their tiles
 };
 
 // The staged pipeline's flat buckets: replica r's slab at slab0 + r * stride (r < R), the averaged one
@@ -198,8 +210,8 @@ void pack_masks(const uint64_t* masks, int count, int R, uint64_t* words);
 // one pass instead: every replica's gradients are copied into its flat bucket
 // (zeros for a replica that did not use the parameter) and the average goes to
 // the averaged bucket; nwrite and keep_unused do not matter then.
-// nslices: slices of the range that hold elements, see slices_for.
-hipError_t launch_fused_reduce(int dtype, const SegTables& t, int64_t tile_base, int64_t ntiles, int64_t nslices,
+// slice_base, nslices: the slices of the range that hold elements (slices_for), numbered through all segments.
+hipError_t launch_fused_reduce(int dtype, const SegTables& t, int64_t tile_base, int64_t ntiles, int64_t slice_base, int64_t nslices,
                                int R, int nwrite, const Masks& masks, bool keep_unused, Scale sc,
                                bool nontemporal, unsigned lds, FlatBuckets flat,
                                const GateRecord* gate, uint32_t tag, DispatchSignal sig, hipStream_t s);

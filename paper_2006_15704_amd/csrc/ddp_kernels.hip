@@ -106,6 +106,11 @@ __device__ __forceinline__ PointerRow pointer_row(void* const* table, int g, int
 __device__ __forceinline__ int segment_of(const SegTables& t, int64_t tile) { return cload(t.tile_seg + tile); }
 __device__ __forceinline__ PointerRow gradients_of(const SegTables& t, int g) { return pointer_row(t.grad, g, t.R); }
 
+// Which slice a block of a slice launch takes, as tile * SLICES + slice (base: of the launch's tiles, or of its listed slices).
+__device__ __forceinline__ int64_t slice_of(const SegTables& t, int64_t base, int block) {
+    return t.slices != nullptr ? cload(t.slices + base + block) : base * SLICES + block;
+}
+
 // Tables that travel in the launch's arguments (WordTables has the layout).  There is no tile map: a wave compares the first
 // tiles of 64 segments with its own at a time.
 template <int N>
@@ -133,6 +138,8 @@ __device__ __forceinline__ int segment_of(const ArgTables<N>& t, int64_t tile) {
     }
     return __builtin_amdgcn_readfirstlane(before - 1);     // (segments without elements share the next one's first tile)
 }
+template <int N>
+__device__ __forceinline__ int64_t slice_of(const ArgTables<N>&, int64_t base, int block) { return base * SLICES + block; }
 template <int N>
 __device__ __forceinline__ ArgRow<N> gradients_of(const ArgTables<N>& t, int g) {
     return ArgRow<N>{t, t.at + g * t.step, t.dist != 0 ? t.w[t.dist + g] : 0};
@@ -936,7 +943,7 @@ __global__ __launch_bounds__(BLOCK) void fused_reduce_kernel(Tables t, int64_t t
 // Per byte a slice costs more than a tile (a whole wave per KiB of a replica, 4-byte stores): slice_tiles() has
 // the line.  Half as long slices, two replicas per load instruction, took three times as long.
 template <int DT, int C, int OUT, typename Masks, typename Tables = SegTables>
-__global__ __launch_bounds__(BLOCK) void slice_reduce_kernel(Tables t, int64_t tile_base, int R, int nwrite,
+__global__ __launch_bounds__(BLOCK) void slice_reduce_kernel(Tables t, int64_t base, int R, int nwrite,
                                                              Masks masks, int keep_unused, Scale sc, FlatBuckets flat,
                                                              const GateRecord* __restrict__ gate, uint32_t tag,
                                                              DispatchSignal sig) {
@@ -950,7 +957,7 @@ __global__ __launch_bounds__(BLOCK) void slice_reduce_kernel(Tables t, int64_t t
     uint32_t* const gathered = shared_words;       // [R][WORDS]
     signal_dispatch(sig);
     const uint32_t gate_word = gate != nullptr ? cload(&gate->failed_tag) : ~tag;
-    const int64_t tile = tile_base + blockIdx.x / SLICES;
+    const int64_t slice = slice_of(t, base, static_cast<int>(blockIdx.x)), tile = slice / SLICES;
     const int g = segment_of(t, tile);
     const auto row = gradients_of(t, g);
     const SegInfo si = segment(t, g);
@@ -960,7 +967,7 @@ __global__ __launch_bounds__(BLOCK) void slice_reduce_kernel(Tables t, int64_t t
     const int64_t numel = si.numel;
     const int sh = (OUT == OUT_FLAT ? static_cast<int>(si.flat_byte & 15) : si.lead_bytes()) / ES;
     // the slice holds the elements [e0, e0 + SLICE_BYTES / ES) as far as they exist
-    const int64_t e0 = (tile - si.tile0) * (TILE_BYTES / ES) + static_cast<int>(blockIdx.x % SLICES) * (SLICE_BYTES / ES) - sh;
+    const int64_t e0 = (tile - si.tile0) * (TILE_BYTES / ES) + static_cast<int>(slice % SLICES) * (SLICE_BYTES / ES) - sh;
     if (e0 >= numel) return;
     const uint64_t everyone = R >= 64 ? ~uint64_t(0) : ((uint64_t(1) << R) - 1);
     const uint64_t used = masked ? mask : everyone;
@@ -1572,25 +1579,28 @@ static hipError_t fused_launch(bool nt, int64_t ntiles, unsigned lds, hipStream_
 }
 
 template <int DT, int OUT, typename M>
-static hipError_t slice_launch(int64_t ntiles, hipStream_t s, const SegTables& t, int64_t tile_base, int R, int nwrite,
+static hipError_t slice_launch(int64_t blocks, hipStream_t s, const SegTables& t, int64_t base, int R, int nwrite,
                                const M& masks, int keep, Scale sc, FlatBuckets flat,
                                const GateRecord* gate, uint32_t tag, DispatchSignal sig) {
-    const dim3 grid(static_cast<unsigned>(ntiles * SLICES));
+    const dim3 grid(static_cast<unsigned>(blocks));
     const unsigned lds = static_cast<unsigned>(R * SLICE_BYTES);
     // (registers and code for sixteen replicas a wave cost 20 % where four will do)
-    if (R <= 16) return launch(slice_reduce_kernel<DT, 4, OUT, M>, grid, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
-    return launch(slice_reduce_kernel<DT, MAX_REPLICAS / 4, OUT, M>, grid, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
+    if (R <= 16) return launch(slice_reduce_kernel<DT, 4, OUT, M>, grid, lds, s, t, base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
+    return launch(slice_reduce_kernel<DT, MAX_REPLICAS / 4, OUT, M>, grid, lds, s, t, base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
 }
 
 template <int DT, int OUT>
-static hipError_t fused_dispatch(bool nt, int64_t ntiles, int64_t nslices, unsigned lds, hipStream_t s,
+static hipError_t fused_dispatch(bool nt, int64_t ntiles, int64_t slice_base, int64_t nslices, unsigned lds, hipStream_t s,
                                  const SegTables& t, int64_t tile_base, int R, int nwrite,
                                  const Masks& masks, int keep, Scale sc, FlatBuckets flat,
                                  const GateRecord* gate, uint32_t tag, DispatchSignal sig) {
     // (without the hint every launch takes tiles, so that both kernels can be had at any size)
-    const bool slices = nt && takes_slices(R, Fmt<DT>::ES, OUT == OUT_FLAT, ntiles, nslices);
+    const bool slices = nt && takes_slices(R, Fmt<DT>::ES, OUT == OUT_FLAT, ntiles, nslices, t.slices != nullptr);
+    SegTables ts = t;
+    if (!takes_list(R, Fmt<DT>::ES, OUT == OUT_FLAT, ntiles, nslices)) ts.slices = nullptr;
+    const int64_t blocks = ts.slices != nullptr ? nslices : ntiles * SLICES, base = ts.slices != nullptr ? slice_base : tile_base;
     auto with = [&](const auto& m) {
-        if (slices) return slice_launch<DT, OUT>(ntiles, s, t, tile_base, R, nwrite, m, keep, sc, flat, gate, tag, sig);
+        if (slices) return slice_launch<DT, OUT>(blocks, s, ts, base, R, nwrite, m, keep, sc, flat, gate, tag, sig);
         return fused_launch<DT, OUT>(nt, ntiles, lds, s, t, tile_base, R, nwrite, m, keep, sc, flat, gate, tag, sig);
     };
     if (masks.words != nullptr) {
@@ -1604,7 +1614,7 @@ static hipError_t fused_dispatch(bool nt, int64_t ntiles, int64_t nslices, unsig
     // instance, ResNet-50, R = 8, all marks in one call)
     if (masks.table == nullptr && (OUT != OUT_FLAT || slices)) {
         if constexpr (OUT != OUT_FLAT) return with(NoMasks{});
-        else return slice_launch<DT, OUT>(ntiles, s, t, tile_base, R, nwrite, NoMasks{}, keep, sc, flat, gate, tag, sig);
+        else return slice_launch<DT, OUT>(blocks, s, ts, base, R, nwrite, NoMasks{}, keep, sc, flat, gate, tag, sig);
     }
     return with(MaskTable{masks.table});
 }
@@ -1615,7 +1625,7 @@ void pack_masks(const uint64_t* masks, int count, int R, uint64_t* words) {
     for (int k = 0; k < count; ++k) words[(k << shift) >> 6] |= masks[k] << ((k << shift) & 63);
 }
 
-hipError_t launch_fused_reduce(int dtype, const SegTables& t, int64_t tile_base, int64_t ntiles, int64_t nslices,
+hipError_t launch_fused_reduce(int dtype, const SegTables& t, int64_t tile_base, int64_t ntiles, int64_t slice_base, int64_t nslices,
                                int R, int nwrite, const Masks& masks, bool keep_unused, Scale sc,
                                bool nontemporal, unsigned lds, FlatBuckets flat,
                                const GateRecord* gate, uint32_t tag, DispatchSignal sig, hipStream_t s) {
@@ -1625,23 +1635,23 @@ hipError_t launch_fused_reduce(int dtype, const SegTables& t, int64_t tile_base,
         // 16-bit gradients, binary32 averages to separate tensors
         if (nwrite != 1 || flat.slab0 != nullptr) return hipErrorInvalidValue;
         switch (dtype) {
-            case 1: return fused_dispatch<1, OUT_BINARY32>(nontemporal, ntiles, nslices, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
-            case 2: return fused_dispatch<2, OUT_BINARY32>(nontemporal, ntiles, nslices, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
+            case 1: return fused_dispatch<1, OUT_BINARY32>(nontemporal, ntiles, slice_base, nslices, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
+            case 2: return fused_dispatch<2, OUT_BINARY32>(nontemporal, ntiles, slice_base, nslices, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
             default: return hipErrorInvalidValue;
         }
     }
     if (flat.slab0 != nullptr) {
         switch (dtype) {
-            case 0: return fused_dispatch<0, OUT_FLAT>(nontemporal, ntiles, nslices, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
-            case 1: return fused_dispatch<1, OUT_FLAT>(nontemporal, ntiles, nslices, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
-            case 2: return fused_dispatch<2, OUT_FLAT>(nontemporal, ntiles, nslices, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
+            case 0: return fused_dispatch<0, OUT_FLAT>(nontemporal, ntiles, slice_base, nslices, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
+            case 1: return fused_dispatch<1, OUT_FLAT>(nontemporal, ntiles, slice_base, nslices, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
+            case 2: return fused_dispatch<2, OUT_FLAT>(nontemporal, ntiles, slice_base, nslices, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
             default: return hipErrorInvalidValue;
         }
     }
     switch (dtype) {
-        case 0: return fused_dispatch<0, OUT_GRAD>(nontemporal, ntiles, nslices, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
-        case 1: return fused_dispatch<1, OUT_GRAD>(nontemporal, ntiles, nslices, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
-        case 2: return fused_dispatch<2, OUT_GRAD>(nontemporal, ntiles, nslices, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
+        case 0: return fused_dispatch<0, OUT_GRAD>(nontemporal, ntiles, slice_base, nslices, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
+        case 1: return fused_dispatch<1, OUT_GRAD>(nontemporal, ntiles, slice_base, nslices, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
+        case 2: return fused_dispatch<2, OUT_GRAD>(nontemporal, ntiles, slice_base, nslices, lds, s, t, tile_base, R, nwrite, masks, keep, sc, flat, gate, tag, sig);
         default: return hipErrorInvalidValue;
     }
 }
@@ -1657,7 +1667,7 @@ static hipError_t value_launch(const WordTables& words, int64_t tile_base, int64
     t.dist = words.regular ? words.n + R : 0;
     const FlatBuckets flat{nullptr, 0};
     const DispatchSignal sig{nullptr, 0};
-    if (!takes_slices(R, Fmt<DT>::ES, false, ntiles, nslices))
+    if (!takes_slices(R, Fmt<DT>::ES, false, ntiles, nslices, false))
         return launch(fused_reduce_kernel<DT, true, RU, OUT_GRAD, NoMasks, 0, ArgTables<N>>, dim3(static_cast<unsigned>(ntiles)), edge_lds(R), s,
                       t, tile_base, R, 1, NoMasks{}, 0, sc, flat, nullptr, 0u, sig);
     const dim3 grid(static_cast<unsigned>(ntiles * SLICES));

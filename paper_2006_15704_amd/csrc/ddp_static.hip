@@ -293,7 +293,7 @@ extern "C" int32_t ddp_sync_static(int32_t R, int32_t device, void* stream, int3
 
     if (in_place) {
         HIPCHK0(for_each_run([&](int32_t dt, int64_t tile0, int64_t count, int64_t nslices) {
-            return ddp::launch_fused_reduce(dt, t, tile0, count, nslices, R, 1, ddp::Masks{}, false, sc, true, 0, ddp::FlatBuckets{nullptr, 0}, nullptr, 0,
+            return ddp::launch_fused_reduce(dt, t, tile0, count, 0, nslices, R, 1, ddp::Masks{}, false, sc, true, 0, ddp::FlatBuckets{nullptr, 0}, nullptr, 0,
                                             ddp::DispatchSignal{nullptr, 0}, s);
         }));
         return nb;

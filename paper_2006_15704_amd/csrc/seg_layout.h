@@ -19,7 +19,8 @@ struct HostTables {
     std::vector<int64_t> slices;            // [G + 1] slices with elements in front of every segment
     std::vector<SegInfo> seg;               // [G]
     std::vector<void*> grad;                // [G * R + 16], see SegTables::grad
-    std::vector<int32_t> tile_seg;          // [tile0[G]]
+    std::vector<int32_t> tile_seg;          // [tile0[G]], and behind it SegTables::slices, if listed
+    bool listed = false;
     std::vector<void*> out;                 // [G] binary32 output tensors (empty without outputs)
 };
 
@@ -85,9 +86,12 @@ inline void build_layout(const BucketPlan& plan, void* const* grad_ptrs, int R, 
     }
 }
 
-// ... and the two tables that grow with R n and with the bytes.
+// Models of up to so many slices (16 MiB a replica) list those that hold elements.
+constexpr int64_t kListedSlices = 16384;
+
+// ... and the tables that grow with R n and with the bytes.
 inline void build_host_tables(const BucketPlan& plan, void* const* grad_ptrs, int R, HostTables& h,
-                              void* const* out_ptrs = nullptr) {
+                              void* const* out_ptrs = nullptr, bool list_slices = false) {
     build_layout(plan, grad_ptrs, R, h, out_ptrs);
     const int32_t n = static_cast<int32_t>(plan.params.size());
     h.grad.assign(static_cast<size_t>(R) * n + 16, nullptr);
@@ -96,6 +100,11 @@ inline void build_host_tables(const BucketPlan& plan, void* const* grad_ptrs, in
     h.tile_seg.resize(static_cast<size_t>(h.tile0[n]));
     for (int32_t g = 0; g < n; ++g)
         for (int64_t tl = h.tile0[g]; tl < h.tile0[g + 1]; ++tl) h.tile_seg[tl] = g;
+    if (!list_slices || h.slices[n] > kListedSlices) return;
+    h.listed = true;
+    h.tile_seg.reserve(static_cast<size_t>(h.tile0[n] + h.slices[n]));
+    for (int32_t g = 0; g < n; ++g)
+        for (int64_t k = 0; k < h.slices[g + 1] - h.slices[g]; ++k) h.tile_seg.push_back(static_cast<int32_t>(h.tile0[g] * SLICES + k));
 }
 
 }  // namespace ddp
