@@ -153,7 +153,7 @@ struct ddp_ctx {
     int32_t flag_order = -1;                      // -1 = where the streams allow it, 0 = never (events)
     int64_t gate_wait_us = 100000;                // bound on one gate's wait
     int32_t num_cus = 256;                        // read from the device at creation
-    char* d_order_mem = nullptr;                  // OrderState followed by the two probe words
+    char* d_order_mem = nullptr;                  // OrderState followed by the three probe words
     ddp::OrderState* d_order = nullptr;
     unsigned long long* d_probe = nullptr;
     // Gate records: kGateRows rows of one record per bucket plus one that summarizes the row
@@ -408,7 +408,9 @@ void new_call(ddp_ctx* c) {
 
 // Whether stream `waiter` makes progress while stream `other` is busy and vice versa.  HIP
 // streams that share a hardware queue run one after the other.  The probe is a bounded wait on
-// `waiter` for a value written from `other`.
+// `waiter` for a value written from `other`, which waits for the waiter first: streams that passed it run at the same
+// time, as the gates need, and the value waits at the end of an iteration, which the runtime makes with a kernel that polls
+// as long as it takes: under a tool that lets one kernel run at a time both would be in each other's way, and events are used.
 int32_t probe_pair(ddp_ctx* c, hipStream_t waiter, hipStream_t other, bool* concurrent) {
     *concurrent = false;
     if (waiter == other) return DDP_OK;
@@ -1044,7 +1046,7 @@ int32_t ddp_create(ddp_ctx** out, int32_t R, int32_t device, void* reduce_stream
         int cus = 0;
         if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device);
         if (e == hipSuccess && cus > 0) c->num_cus = cus;
-        const size_t order_bytes = sizeof(ddp::OrderState) + 2 * sizeof(unsigned long long);
+        const size_t order_bytes = sizeof(ddp::OrderState) + 3 * sizeof(unsigned long long);
         if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&c->d_order_mem), order_bytes);
         if (e == hipSuccess) e = hipMemset(c->d_order_mem, 0, order_bytes);
         if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void**>(&c->h_progress), sizeof(unsigned long long), hipHostMallocDefault);

@@ -289,10 +289,11 @@ hipError_t launch_repair(int dtype, const SegTables& t, OrderState* st, const Ga
                          int R, int nwrite, const uint64_t* local, bool keep_unused, Scale sc,
                          int blocks, bool nontemporal, FlatBuckets flat, hipStream_t s);
 
-// Bounded probe: one wave on stream `waiter` polls word[0] for `value` (at most
-// wait_ticks), then a one-thread kernel on stream `writer` stores it.
-// word[1] = 1 if the waiter saw the value, i.e. if the two streams make progress
-// independently (streams that share a hardware queue run one after the other).
+// Bounded probe (each wait at most wait_ticks): one wave on stream `waiter` stores `value` to word[2] and polls word[0] for it; one on stream
+// `writer` waits for word[2] and then stores it to word[0].
+// word[1] = 1 if the waiter saw the value, i.e. if the two streams run at the same time.  Streams that share a hardware
+// queue run one after the other, and so does everything under tools that let one kernel run at a time: whichever of the
+// two is first then waits in vain.
 hipError_t launch_probe(unsigned long long* word, unsigned long long value, long long wait_ticks,
                         hipStream_t waiter, hipStream_t writer);
 

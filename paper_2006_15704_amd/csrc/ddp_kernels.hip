@@ -1175,24 +1175,25 @@ __global__ __launch_bounds__(BLOCK) void repair_kernel(SegTables t, OrderState* 
     }
 }
 
-__global__ __launch_bounds__(64) void probe_wait_kernel(unsigned long long* word, unsigned long long value,
-                                                        long long wait_ticks) {
-    if (threadIdx.x != 0) return;
+// Whether *word became `value` within `ticks`.
+__device__ __forceinline__ bool poll_for(unsigned long long* word, unsigned long long value, long long ticks) {
     const uint64_t t0 = wall_clock64();
-    unsigned long long seen = 0;
     for (uint32_t poll = 0; poll < MAX_GATE_POLLS; ++poll) {
-        if (__hip_atomic_load(&word[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == value) {
-            seen = 1;
-            break;
-        }
-        if (static_cast<long long>(wall_clock64() - t0) >= wait_ticks) break;
+        if (__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == value) return true;
+        if (static_cast<long long>(wall_clock64() - t0) >= ticks) break;
         __builtin_amdgcn_s_sleep(16);
     }
-    word[1] = seen;
+    return false;
 }
 
-__global__ __launch_bounds__(64) void probe_write_kernel(unsigned long long* word, unsigned long long value) {
-    if (threadIdx.x == 0)
+__global__ __launch_bounds__(64) void probe_wait_kernel(unsigned long long* word, unsigned long long value, long long wait_ticks) {
+    if (threadIdx.x != 0) return;
+    __hip_atomic_store(&word[2], value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    word[1] = poll_for(&word[0], value, wait_ticks) ? 1 : 0;
+}
+
+__global__ __launch_bounds__(64) void probe_write_kernel(unsigned long long* word, unsigned long long value, long long wait_ticks) {
+    if (threadIdx.x == 0 && poll_for(&word[2], value, wait_ticks))
         __hip_atomic_store(&word[0], value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
@@ -1762,7 +1763,7 @@ hipError_t launch_probe(unsigned long long* word, unsigned long long value, long
     hipLaunchKernelGGL(probe_wait_kernel, dim3(1), dim3(64), 0, waiter, word, value, wait_ticks);
     hipError_t e = after_launch();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(probe_write_kernel, dim3(1), dim3(64), 0, writer, word, value);
+    hipLaunchKernelGGL(probe_write_kernel, dim3(1), dim3(64), 0, writer, word, value, wait_ticks);
     return after_launch();
 }
 

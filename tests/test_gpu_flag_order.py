@@ -269,3 +269,41 @@ def test_launch_hold_under_a_running_backward_pass(hold, flag_order):
             for r in range(R):                 # back to NaN for the next iteration
                 grads.bufs[r].fill_(0xFF)
             torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("backward", ["null stream", "stream"])
+@pytest.mark.parametrize("reduction_streams", [-1, 1, 3])
+def test_gradients_produced_on_the_null_stream(backward, reduction_streams):
+    """A program that makes no stream for its backward pass: whatever order the library takes, work behind
+    ddp_finalize_backward on that stream sees the averages."""
+    import torch
+    d, harness = lib()
+    numel = [300000 + k for k in range(16)]
+    n, R = len(numel), 3
+    grads = harness.DeviceGrads(numel, [FP32] * n, R, fill=0)
+    produced = torch.cuda.Stream() if backward == "stream" else torch.cuda.default_stream()
+    reduce = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    ctx = d.ddp_create(R, 0, reduce.cuda_stream, produced.cuda_stream)
+    try:
+        d.ddp_set_option(ctx, d.DDP_OPT_PIPELINE, FUSED)
+        d.ddp_set_option(ctx, d.DDP_OPT_REDUCE_STREAMS, reduction_streams)
+        d.ddp_register_params(ctx, numel, [FP32] * n, grads.ptrs())
+        d.ddp_build_buckets(ctx, 1 << 20)
+        kept = []
+        for it in range(4):
+            with torch.cuda.stream(produced):
+                for r in range(R):
+                    grads.bufs[r][:grads.slab_bytes // 4 * 4].view(torch.float32).fill_(float(3 * r + it))
+            for p in range(n - 1, -1, -1):
+                d.ddp_mark_ready(ctx, p)
+            d.ddp_finalize_backward(ctx)
+            with torch.cuda.stream(produced):
+                kept.append([grads.view(0, i).view(torch.float32).clone() for i in range(n)])
+        d.ddp_synchronize(ctx)
+        torch.cuda.synchronize()
+        for it, tensors in enumerate(kept):
+            for i, t in enumerate(tensors):
+                assert bool((t == 3.0 + it).all()), f"iteration {it} parameter {i}"
+    finally:
+        d.ddp_destroy(ctx)
