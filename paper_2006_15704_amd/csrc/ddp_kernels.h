@@ -227,7 +227,7 @@ struct WordTables {
     const uint64_t* words;
     int32_t n;
     bool regular;
-    int count(int R) const { return regular ? 2 * n + R : n * (R + 1); }
+    int64_t count(int R) const { return regular ? 2 * int64_t(n) + R : int64_t(n) * (R + 1); }
 };
 hipError_t launch_fused_reduce_by_value(int dtype, const WordTables& t, int64_t tile_base, int64_t ntiles, int64_t nslices, int R, Scale sc,
                                         hipStream_t s);

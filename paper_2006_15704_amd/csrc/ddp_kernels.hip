@@ -1679,7 +1679,7 @@ static hipError_t value_launch(const WordTables& words, int64_t tile_base, int64
 
 template <int DT>
 static hipError_t value_dispatch(const WordTables& t, int64_t tile_base, int64_t ntiles, int64_t nslices, int R, Scale sc, hipStream_t s) {
-    const int count = t.count(R);
+    const int64_t count = t.count(R);
     if (count <= 128) return value_launch<DT, 128>(t, tile_base, ntiles, nslices, R, sc, s);
     if (count <= 256) return value_launch<DT, 256>(t, tile_base, ntiles, nslices, R, sc, s);
     return value_launch<DT, kTableWords>(t, tile_base, ntiles, nslices, R, sc, s);
