@@ -138,9 +138,12 @@ static PyObject* mark_ready_local(PyObject* self, PyObject* const* args, Py_ssiz
     return ok ? PyLong_FromLong((long)status) : NULL;
 }
 
-/* Bits per digit of an int's magnitude in this interpreter, 0 = not known here. */
-#if PY_VERSION_HEX < 0x030C0000
+/* Bits per digit of an int's magnitude in this interpreter, 0 = not known here.  (From 3.11 on the layout comes with Python.h, and
+ * there is no header of this name; 3.12 has another layout.) */
+#if PY_VERSION_HEX < 0x030B0000
 #include <longintrepr.h>
+#endif
+#if PY_VERSION_HEX < 0x030C0000
 #define DIGIT_BITS PyLong_SHIFT
 #else
 #define DIGIT_BITS 0

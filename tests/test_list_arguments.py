@@ -133,3 +133,27 @@ def test_values_arrive_as_they_are(form):
     assert got[0] == EDGES + [0]
     assert got[1] == ids
     assert got[2] == (sizes, [ids[0]] * len(sizes), (EDGES * 2)[:len(sizes)])
+
+
+@pytest.mark.parametrize("version", ["0x030A00F0", "0x030B00F0", "0x030C00F0"])
+def test_the_marshalling_module_compiles_for_newer_interpreters(version, tmp_path):
+    """As interpreters before 3.11, of 3.11 and from 3.12 on have the headers: 3.11 gives the layout of ints with Python.h and has no
+    longintrepr.h of its own, and from 3.12 on the layout is another one, which the module must not use."""
+    import os
+    import shutil
+    import subprocess
+    import sys
+    import sysconfig
+    cc = shutil.which("gcc") or shutil.which("cc")
+    if cc is None or sys.version_info >= (3, 11):
+        pytest.skip("needs a C compiler and an interpreter older than the ones it stands in for")
+    real = sysconfig.get_paths()["include"]
+    layout = '#include_next <longintrepr.h>\n' if version == "0x030B00F0" else ""
+    (tmp_path / "Python.h").write_text(f"#include_next <Python.h>\n#define TAKES_LAYOUT\n{layout}#undef TAKES_LAYOUT\n"
+                                       f"#undef PY_VERSION_HEX\n#define PY_VERSION_HEX {version}\n")
+    if version != "0x030A00F0":
+        (tmp_path / "longintrepr.h").write_text("#ifdef TAKES_LAYOUT\n#include_next <longintrepr.h>\n#else\n"
+                                                "#error longintrepr.h: No such file\n#endif\n")
+    csrc = os.path.join(os.path.dirname(os.path.abspath(d.__file__)), "csrc", "fastcall.c")
+    done = subprocess.run([cc, "-fsyntax-only", "-Wall", "-Wno-unused", f"-I{tmp_path}", f"-I{real}", csrc], capture_output=True, text=True)
+    assert done.returncode == 0, done.stderr
