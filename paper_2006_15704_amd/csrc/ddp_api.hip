@@ -10,6 +10,7 @@
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <thread>
 #include <utility>
 #include <vector>
 
@@ -622,17 +623,26 @@ int32_t order_call(ddp_ctx* c, int32_t first, bool look) {
 
 // Waits until the bitmap step of the iteration with this tag has run: every word it writes for the host carries the tag, so that
 // nothing else has to tell.  (An event behind it took the host 5 us, and the next kernel on the stream started 4 us later
-// for it.)  A bounded look, then the stream is waited for.
+// for it.)  What the caller has enqueued behind that step is not waited for: the words are looked at all the time for kLookUs, then
+// every kSleepUs with the core given up in between; a look at the stream, every kStreamUs, is for errors and for a stream
+// with nothing left to run.
 int32_t await_bitmap(ddp_ctx* c, uint64_t tag) {
+    constexpr int kLookUs = 1000, kSleepUs = 50, kStreamUs = 20000;
+    using clock = std::chrono::steady_clock;
     const int32_t n = static_cast<int32_t>(c->plan.params.size());
-    const auto until = std::chrono::steady_clock::now() + std::chrono::milliseconds(100);
-    bool waited = false;
+    const auto sleep_from = clock::now() + std::chrono::microseconds(kLookUs);
+    auto stream_from = clock::now() + std::chrono::microseconds(kStreamUs);
     for (int32_t g = 0; g < n; ++g)
-        while (__atomic_load_n(c->h_global + g, __ATOMIC_RELAXED) >> 1 < tag) {
-            if (waited) return fail(c, DDP_ERR_HIP, "the bitmap step of the closed iteration has not run");
-            if (std::chrono::steady_clock::now() < until) continue;
-            HIPCHK(c, hipStreamSynchronize(c->backward));
-            waited = true;
+        while (__atomic_load_n(c->h_global + g, __ATOMIC_ACQUIRE) >> 1 < tag) {
+            const auto now = clock::now();
+            if (now < sleep_from) continue;
+            if (now >= stream_from) {
+                const hipError_t q = hipStreamQuery(c->backward);
+                if (q == hipSuccess) return DDP_OK;
+                if (q != hipErrorNotReady) return fail(c, DDP_ERR_HIP, std::string("hipStreamQuery: ") + hipGetErrorString(q));
+                stream_from = now + std::chrono::microseconds(kStreamUs);
+            }
+            std::this_thread::sleep_for(std::chrono::microseconds(kSleepUs));
         }
     return DDP_OK;
 }

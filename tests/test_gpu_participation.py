@@ -449,3 +449,49 @@ def test_the_bitmap_read_back_is_that_of_the_closed_iteration(R, n):
                 mean[p] = np.float32(total / np.float32(R))
     for p in range(n):
         assert (grads.download(0, p) == mean[p]).all(), f"parameter {p}"
+
+
+@pytest.mark.parametrize("n", [5, 900])                # masks in arguments, and in pinned memory that is used again
+@pytest.mark.parametrize("call", ["bitmap", "marks"])
+def test_a_wait_for_the_bitmap_step_is_for_nothing_behind_it(n, call):
+    """The host is an iteration ahead of a slow GPU: what it waits for is 150 ms away, and 400 ms of backward work behind
+    that are enqueued already.  The call returns before they have run."""
+    import torch
+    d, harness = lib()
+    R = 2
+    numel = [1 + i % 7 for i in range(n)]
+    grads = harness.DeviceGrads(numel, [FP32] * n, R, fill=0)
+    values = [b[:b.numel() // 4 * 4].view(torch.float32) for b in grads.bufs]
+    rng = np.random.default_rng(n)
+    flags = [rng.random((n, R)) < 0.5 for _ in range(3)]
+    with harness.Session(grads, 1 << 20, FUSED) as s:
+        d.ddp_set_option(s.ctx, d.DDP_OPT_FIND_UNUSED, 1)
+
+        def iteration(flag):
+            with torch.cuda.stream(s.backward_stream):
+                for v in values:
+                    v.fill_(1.0)
+            for p in range(n - 1, -1, -1):
+                d.ddp_mark_ready_local(s.ctx, p, [int(u) for u in flag[p]])
+            d.ddp_finalize_backward(s.ctx)
+
+        iteration(flags[0])
+        assert d.ddp_get_global_used(s.ctx, n).tolist() == flags[0].any(axis=1).astype(int).tolist()
+        d.ddp_synchronize(s.ctx)
+        d.ddp_synth_backward(s.ctx, [0] * 3, [50_000_000] * 3, mark=False)
+        iteration(flags[1])
+        if call == "marks":
+            iteration(flags[0])                        # the pinned memory is used in turn
+        d.ddp_synth_backward(s.ctx, [0] * 4, [100_000_000] * 4, mark=False)
+        later = torch.cuda.Event()
+        later.record(s.backward_stream)
+        if call == "bitmap":
+            assert d.ddp_get_global_used(s.ctx, n).tolist() == flags[1].any(axis=1).astype(int).tolist()
+            assert not later.query()
+        iteration(flags[2])
+        assert not later.query()
+        assert d.ddp_get_global_used(s.ctx, n).tolist() == flags[2].any(axis=1).astype(int).tolist()
+        d.ddp_synchronize(s.ctx)
+    for p in range(n):
+        want = flags[2][p].sum() / R if flags[2][p].any() else 1.0
+        assert (grads.download(0, p) == np.float32(want)).all(), f"parameter {p}"
