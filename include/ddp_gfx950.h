@@ -103,7 +103,11 @@ typedef struct ddp_ctx ddp_ctx;
                                      buckets joins its last launch if it is at most a quarter of the
                                      limit; measured: short launches pay a fixed start-up and drain
                                      cost each, much longer ones lose throughput again).  A launch
-                                     hold (DDP_OPT_LAUNCH_HOLD) counts the limits before doubling */
+                                     hold (DDP_OPT_LAUNCH_HOLD) counts the limits before doubling.
+                                     Reads as the bytes that launches are filled up to, the doubling
+                                     included; writing those back makes them a limit of the caller's,
+                                     which a last launch does not exceed and a hold counts as they are:
+                                     -1 returns to the library's choice */
 #define DDP_OPT_FIND_UNUSED   11  /* any time between iterations: the paper's find_unused_parameters
                                      knob.  1 = gradients of parameters that no replica used in the
                                      iteration (the global bitmap of Section 4.2 says so) are left
@@ -160,9 +164,10 @@ typedef struct ddp_ctx ddp_ctx;
                                      launch and gains 2.5 points).  Default 360 MiB (40 MiB of bucket
                                      data at R = 8) */
 #define DDP_OPT_ACCUMULATE_BLOCKS_PER_CU 16 /* any time: likewise for the accumulate kernel (two loads
-                                     and a store per vector; registers allow 8 blocks).  Default 4; as long as it
-                                     has not been set, 3 where all gradients are 16-bit, and 6 (16-bit: 5) where
-                                     they are 368 MiB or less */
+                                     and a store per vector; registers allow 8 blocks).  Default -1 = chosen:
+                                     4 (3 where all gradients are 16-bit), or 6 (5) where the gradients of all
+                                     replicas are 368 MiB or less, counted in the 8 KiB tiles that each
+                                     tensor takes (a tensor of a few elements counts as 8 KiB) */
 #define DDP_OPT_TAIL_ON_BACKWARD 17 /* any time between iterations: 1 (default) = the buckets launched by
                                      the API call that completes an iteration (the call after which
                                      the last bucket is launchable: every gradient exists, nothing
@@ -262,7 +267,7 @@ int32_t ddp_set_option(ddp_ctx* ctx, int32_t option, int64_t value);
 
 /* Reads back what is in effect for every DDP_OPT_ option as it was set (-1
  * where that means "the library chooses"), except: DDP_OPT_COALESCE gives the
- * byte limit in effect (also when it was chosen from R) and DDP_OPT_FLAG_ORDER
+ * byte limit in effect (also when it was chosen from R; see there) and DDP_OPT_FLAG_ORDER
  * gives 1 if launches of the next iteration on a reduction stream would be
  * ordered through device flags (the option allows it, the buckets are built, every
  * reduction stream in use passed the concurrency probe, and not the staged

@@ -68,8 +68,7 @@ struct ddp_ctx {
                                                   // -1 = chosen from R, see auto_blocks_per_cu)
     int64_t cap_min_traffic = int64_t(360) << 20; // ... applied to launches that move at least this many bytes
     bool cap_min_set = false;                     // ... by the caller's choice: shorter launches have no cap then
-    int32_t acc_blocks_per_cu = 4;                // accumulate kernel: likewise
-    bool acc_blocks_set = false;                  // ... by the caller's choice, see auto_accumulate_blocks
+    int32_t acc_blocks_per_cu = -1;               // accumulate kernel: likewise, see auto_accumulate_blocks
     int64_t lds_per_cu = 160 * 1024;              // read from the device at creation
 
     bool registered = false, built = false;
@@ -1123,9 +1122,8 @@ int32_t ddp_set_option(ddp_ctx* c, int32_t option, int64_t value) {
             c->blocks_per_cu = static_cast<int32_t>(value);
             return DDP_OK;
         case DDP_OPT_ACCUMULATE_BLOCKS_PER_CU:
-            if (value < 0 || value > 16) return fail(c, DDP_ERR_ARG, "blocks per compute unit outside [0, 16]");
+            if (value < -1 || value > 16) return fail(c, DDP_ERR_ARG, "blocks per compute unit outside [-1, 16]");
             c->acc_blocks_per_cu = static_cast<int32_t>(value);
-            c->acc_blocks_set = true;
             return DDP_OK;
         case DDP_OPT_REDUCE_CAP_MIN_BYTES:
             if (value < 0) return fail(c, DDP_ERR_ARG, "bad size");
@@ -1835,8 +1833,8 @@ int32_t ddp_no_sync_accumulate(ddp_ctx* c, void* const* micro) {
     }
     size_t slot;
     int32_t rc;
-    const unsigned lds = lds_for_blocks(c, c->acc_blocks_set ? c->acc_blocks_per_cu
-                                                             : auto_accumulate_blocks(ddp::accumulate_streams(c->h_tile0[n], c->R), c->wide));
+    const unsigned lds = lds_for_blocks(c, c->acc_blocks_per_cu >= 0 ? c->acc_blocks_per_cu
+                                                                      : auto_accumulate_blocks(ddp::accumulate_streams(c->h_tile0[n], c->R), c->wide));
     if ((rc = timed_begin(c, DDP_K_ACCUMULATE, -1, c->backward, &slot)) != DDP_OK) return rc;
     if (form == MicroForm::kTable)
         HIPCHK(c, ddp::launch_accumulate(c->tables, c->h_tile0[n], c->R, c->d_micro, lds, c->backward));

@@ -511,3 +511,36 @@ def test_launch_hold_changes_neither_the_buckets_nor_the_launch_log(d, hold):
         assert e.value.code == d.DDP_ERR_ARG
     finally:
         d.ddp_destroy(ctx)
+
+
+def test_blocks_that_the_library_chooses_read_as_minus_one(d):
+    ctx, nb = plan(d, [100, 200, 300], [0, 0, 0], 1 << 20)
+    try:
+        for opt in (d.DDP_OPT_REDUCE_BLOCKS_PER_CU, d.DDP_OPT_ACCUMULATE_BLOCKS_PER_CU):
+            assert d.ddp_get_option(ctx, opt) == -1
+            for value in (4, 0, 16, -1):
+                d.ddp_set_option(ctx, opt, value)
+                assert d.ddp_get_option(ctx, opt) == value
+            for bad in (-2, 17):
+                with pytest.raises(d.DdpError) as e:
+                    d.ddp_set_option(ctx, opt, bad)
+                assert e.value.code == d.DDP_ERR_ARG
+            assert d.ddp_get_option(ctx, opt) == -1
+    finally:
+        d.ddp_destroy(ctx)
+
+
+def test_the_shared_launch_limit_can_be_given_back_to_the_library(d):
+    """The limit reads as the bytes in effect; those bytes written back are a limit of the caller's, -1 is the library's choice."""
+    ctx = d.ddp_create(8, d.DDP_DEVICE_NONE)
+    d.ddp_set_option(ctx, d.DDP_OPT_PIPELINE, d.DDP_PIPELINE_FUSED)
+    try:
+        chosen = d.ddp_get_option(ctx, d.DDP_OPT_COALESCE)
+        assert chosen == 200 << 20
+        for value in (chosen, 1, 0):
+            d.ddp_set_option(ctx, d.DDP_OPT_COALESCE, value)
+            assert d.ddp_get_option(ctx, d.DDP_OPT_COALESCE) == value
+        d.ddp_set_option(ctx, d.DDP_OPT_COALESCE, -1)
+        assert d.ddp_get_option(ctx, d.DDP_OPT_COALESCE) == chosen
+    finally:
+        d.ddp_destroy(ctx)
