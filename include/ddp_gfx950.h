@@ -149,7 +149,7 @@ typedef struct ddp_ctx ddp_ctx;
                                      gradients R = 4, too), 3 up to R = 6 (16-bit averages
                                      R = 7), else 2, and in launches below DDP_OPT_REDUCE_CAP_MIN_BYTES, unless
                                      that was set, 4 from R = 5 on (3 from R = 8 on where 200 MiB and more
-                                     of binary32 are moved) and 2 from R = 16 on; staged pipeline (its
+                                     of binary32 are moved and one replica is written) and 2 from R = 16 on; staged pipeline (its
                                      launches write as much as they read): 2 for R = 4, else none;
                                      DDP_OPT_WRITE_ALL: none in long launches for R <= 2 and
                                      R = 12 to 16, 3 for R = 3 in 16 bits, else 2 */

@@ -339,22 +339,23 @@ unsigned lds_for_blocks(const ddp_ctx* c, int32_t blocks) {
 // 2034 / 2025 / 2038, 240 MB in 8 MiB buckets, R = 12, 555 / 553 / 555, ResNet-50-sized, binary16, R = 16 369 /
 // 366 / 357; 120 MB, R = 4 230 / 230 / 249; all marks in one call, 16 MB, R = 8 25.1 / 25.0 / 25.5 (bfloat16 25.4 / 25.5 / 26.7), R = 16 46.5 / 46.5 /
 // 45.7.
-// Binary32 launches that move 200 MiB and more have three (one mark per call; two / three / four blocks): R = 8, BERT-large in 225 MiB
-// launches - / 1972 / 2006, a list in 252 MiB launches - / 202.5 / 201.9, in 72 MiB launches - / 242.7 / 239.7; R = 10, 252 MiB - / 203.7 / 204.2; R = 12, 217 MiB - / 207.5 /
-// 209.0.  Others do not: bfloat16, R = 10 - / 205.2 / 203.8; binary32 averages, R = 8 - / 404 / 402; with masks, ResNet-50, R = 8 - / 127.4 / 124.4; R = 5,
-// 240 MiB - / 204.4 / 202.1; R = 16, 212 MiB 205.0 / 207.9 / -, 108 MiB 219.8 / 223.3 / - (bfloat16 222.2 / 226.6), R = 32 219.2 / 226.7 / -; R = 4, 210 MiB 202.6 with three and 197.8 with
-// no cap.
+// Three for binary32 launches that move 200 MiB and more and write the averages once.  Ten buckets, % of the time with four, launches of 205 / 225 /
+// 250 / 300 / 350 MiB: R = 8 +0.5 / -0.4 / -1.4 / -2.2 / -1.4, R = 9 -1.2 / -1.1 / -0.5 / -1.5 / -2.1, R = 10 -0.3 / -1.6 / -3.1 / -3.5 / -2.0, R = 12 -2.2 / -1.5 / -2.4 /
+// -1.9 / -2.1, R = 15 -1.8 / -1.4 / -1.5 / -2.4 / -1.5; BERT-large in 25 MiB buckets R = 8 -2.3, R = 10 -1.9, R = 12 -0.3 (runs of one side differ by 0.5 to
+// 1.5).  Below, R = 8 in 72 MiB launches +1.3.  Every replica written it gains nothing: R = 8 -0.4 / -0.5 / -0.6 / +0.3 / -0.1 and BERT-large +1.2, R = 12 +0.7 / +0.3 /
+// +0.4 / +0.1 / -0.5, R = 14 +0.6 / +0.3 / +0.6 / 0 / +0.5.  Nor do (us, three / four blocks) bfloat16, R = 10 205.2 / 203.8, binary32 averages, R = 8 404 / 402, masks,
+// ResNet-50, R = 8 127.4 / 124.4, R = 5, 240 MiB 204.4 / 202.1; R = 16, 212 MiB 207.9 with three and 205.0 with two.
 constexpr int64_t kThreeBlocksFrom = int64_t(200) << 20;
-int32_t short_launch_blocks(int32_t R, int64_t moved, int es, bool masked) {
+int32_t short_launch_blocks(int32_t R, int64_t moved, int es, bool masked, bool write_all) {
     if (R <= 4) return 0;
     if (R >= 16) return 2;
-    return R >= 8 && es == 4 && moved >= kThreeBlocksFrom && !masked ? 3 : 4;
+    return R >= 8 && es == 4 && moved >= kThreeBlocksFrom && !masked && !write_all ? 3 : 4;
 }
 
 unsigned occupancy_lds(const ddp_ctx* c, int64_t launch_bytes, int es, bool copies, bool masked) {
     if (c->blocks_per_cu >= 0) return long_launch(c, launch_bytes) ? lds_for_blocks(c, c->blocks_per_cu) : 0;
     if (long_launch(c, launch_bytes)) return lds_for_blocks(c, auto_blocks_per_cu(c->R, es, copies, c->write_all, !c->out_ptrs.empty()));
-    return copies || c->cap_min_set ? 0 : lds_for_blocks(c, short_launch_blocks(c->R, launch_bytes * (c->R + 1), es, masked));
+    return copies || c->cap_min_set ? 0 : lds_for_blocks(c, short_launch_blocks(c->R, launch_bytes * (c->R + 1), es, masked, c->write_all));
 }
 
 using ddp::make_scale;
