@@ -57,24 +57,30 @@ inline int64_t slices_for(int64_t numel, int es, int64_t ntiles) {
     return n < most ? n : most;
 }
 
+// Tiles up to which a launch takes slices where those that hold something are not listed (SegTables::slices): models above
+// kListedSlices, and ddp_sync_static (a list is four bytes a slice; a context brings it to the device once, that call would on every
+// call, and its 4 KiB of arguments do not hold it).  Blocks of empty slices end at once, but hold up others by the LDS they
+// get.  GPU time of slices against tiles, %, by tiles of the launch; fused, binary32, 140 to 167 / 190 / 200 to 213 / 273:
+// R = 9 to 16 -5 to -20 / -4 to -13 / -8 to +10 / +7 to +15, R = 17 to 24 -1 to -24 / +2 to -14 / +23 to -1 / +11, R = 32 +2 to -12 / - / +13 to +18 / +22;
+// 16 bits, 200 to 234 / 250 to 262 / 320: R = 9 to 16 -5 to -22 / -3 to +10 / +13 to +18, R = 17 to 24 +11 to -7 / +1 to +4 / +8 to +11, R = 32 +7 to 0 / - / -.
+// Staged, binary32, 261 to 322 / 339 to 385 / 427 / 480 to 547: R = 8 to 16 -11 to -16 / -6 to -14 / -3 to -6 / +3 to +17, R = 17 to 24 +6 to -4 / +1 to +9 / +9 to +11 / +9 to
+// +16; bfloat16: R = 5 -2 to -12 / -8 to +8 / +14 / +24 to +34, R = 8 to 16 -12 to -21 / -4 to -18 / +2 to +6 / +9 to +26, R = 17 to 24 -2 to -8 / -6 to +2 / +2 to +3 / +2 to +6,
+// R = 32 +2 to -2 / +2 / - / +19.
+inline int64_t unlisted_tiles(int R, int es, bool staged) {
+    if (staged) return R >= 8 && R <= 16 ? 384 : es == 2 && R >= 5 && R <= 24 ? 340 : 0;
+    if (R < 9) return 0;
+    return es == 2 ? (R <= 16 ? 240 : 0) : (R <= 24 ? 192 : 0);
+}
+
 // Whether a launch takes slices.  The tiles of small tensors are mostly empty.  Where the slices that hold something are listed
-// (SegTables::slices) they count, and the others have no block.  All marks in one call, 170 tensors of 200 kB in all / 240 of 600 / 240 of 1200, us, by tiles ->
-// by listed slices: fused, binary32 R = 16 6.3 -> 5.3 / 6.8 -> 5.8 / -, R = 24 8.1 -> 5.5 / 9.0 -> 6.0 / -, R = 32 9.5 -> 5.5 / 10.8 -> 6.6 / -, R = 64 16.2 -> 7.1 / 19.9 -> 12.3 / -;
-// bfloat16 R = 8 - / 6.1 -> 5.8 / 6.9 -> 5.8, R = 16 - / 8.1 -> 6.0 / 10.1 -> 7.4, R = 32 9.3 -> 5.6 / 12.2 -> 7.7 / 16.0 -> 11.2, R = 64 19.6 -> 7.9 / 21.7 -> 13.9 / -; staged,
-// binary32 R = 8 - / 10.6 -> 9.2 / 13.6 -> 10.6, R = 16 9.9 -> 8.8 / 15.1 -> 11.1 / 20.3 -> 14.8, R = 32 13.9 -> 10.2 / 21.1 -> 14.8 / 27.1 -> 24.7, R = 64 23.1 -> 15.0 / 33.6 -> 26.0 / -;
-// bfloat16 R = 8 - / 13.0 -> 9.5 / 15.9 -> 11.4, R = 16 10.7 -> 9.1 / 19.2 -> 11.8 / 24.8 -> 16.2, R = 64 27.3 -> 18.3 / 39.3 -> 30.3 / -.
-// Where they are not, blocks of empty slices end at once, but hold up others by the LDS they get, so that the slices that hold something
-// count for some numbers of replicas only, up to so many tiles: 240 tensors of 1000 kB, by tiles -> by slices: staged, binary32 R = 5 10.5 -> 11.2, R = 8 12.6 -> 11.9, R = 16
-// 19.6 -> 16.0, R = 24 21.2 -> 20.5, bfloat16 R = 5 13.0 -> 12.1, R = 16 26.4 -> 17.0, R = 24 24.1 -> 23.3; of 600 kB, R = 32 21.1 -> 21.3 and 24.0 -> 24.2, R = 64 33.6 -> 43.6 and
-// 39.3 -> 51.1.  Fused, 140 of 300 kB / 200 of 300 / 240 of 1000: binary32 R = 12 5.7 -> 5.1 / - / -, R = 16 6.2 -> 5.6 / - / (600 kB) 6.8 -> 7.4, R = 24 7.9 -> 5.8 / 7.9 -> 7.3 / -,
-// bfloat16 R = 12 - / 7.1 -> 5.9 / 7.9 -> 8.5, R = 16 - / 7.5 -> 6.4 / 8.9 -> 9.3, R = 24 - / 9.6 -> 8.4 / 12.2 -> 11.5, R = 8 (1200 kB) 6.9 -> 7.2, R = 64 (600 kB) 21.7 -> 29.2.
+// they count, and the others have no block.  All marks in one call, 170 tensors of 200 kB in all / 240 of 600 / 240 of 1200, us, by tiles ->
+// by listed slices: fused, binary32 R = 16 6.3 -> 5.3 / 6.8 -> 5.8 / -, R = 64 16.2 -> 7.1 / 19.9 -> 12.3 / -; bfloat16 R = 8 - / 6.1 -> 5.8 / 6.9 -> 5.8,
+// R = 32 9.3 -> 5.6 / 12.2 -> 7.7 / 16.0 -> 11.2; staged, binary32 R = 8 - / 10.6 -> 9.2 / 13.6 -> 10.6, R = 32 13.9 -> 10.2 / 21.1 -> 14.8 / 27.1 -> 24.7;
+// bfloat16 R = 16 10.7 -> 9.1 / 19.2 -> 11.8 / 24.8 -> 16.2, R = 64 27.3 -> 18.3 / 39.3 -> 30.3 / -.
 inline bool takes_slices(int R, int es, bool staged, int64_t ntiles, int64_t nslices, bool listed) {
     const int64_t line = slice_tiles(R, es, staged);
     if (ntiles <= line) return true;
-    if (listed) return nslices <= line * SLICES;
-    const int least = !staged ? 9 : es == 2 ? 5 : 8;
-    if (R < least || R > 24 || nslices > line * SLICES) return false;
-    return ntiles <= (!staged && R <= 16 ? line * 3 / 2 : line * 4);
+    return nslices <= line * SLICES && (listed || ntiles <= unlisted_tiles(R, es, staged));
 }
 // Whether a launch of slices goes by the list.  It is one more access in front of the others: 30 tensors of 300 kB, seven of ten slices of
 // their tiles, R = 64 7.3 us without and 7.75 with it, R = 32 5.2 / 5.4.

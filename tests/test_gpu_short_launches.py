@@ -222,3 +222,59 @@ def test_lists_of_tensors_much_smaller_than_a_tile(dtype, R, pipeline, n):
 def torch_from(raw):
     import torch
     return torch.from_numpy(raw)
+
+
+@pytest.mark.parametrize("dtype,R,tiles", [(FP32, 8, 128), (FP32, 8, 129), (FP32, 9, 192), (FP32, 9, 193), (FP32, 24, 192), (FP32, 24, 193), (FP32, 25, 129),
+                                           (BF16, 9, 240), (BF16, 9, 241), (BF16, 16, 240), (BF16, 16, 241), (BF16, 17, 192), (BF16, 17, 193)])
+def test_context_free_lists_of_small_tensors(dtype, R, tiles):
+    """Slices without a list of them: on both sides of the numbers of tiles up to which they are taken, with tables in arguments
+    and in memory."""
+    d, harness = lib()
+    import torch
+    numel = [1 + (7 * i) % 23 for i in range(tiles)]
+    numel[tiles // 3] = 2 * SLICE // ES[dtype] + 3
+    reps = [workloads.gaussian_replica(980, r, 0, numel, 1e-2, dtype) for r in range(R)]
+    want, _, _ = oracle.synchronize(numel, [dtype] * tiles, 1 << 30, reps)
+    grads = harness.DeviceGrads(numel, [dtype] * tiles, R, align=ES[dtype], replica_skew=[ES[dtype] * (r % 3) for r in range(R)], fill=0x5A)
+    upload_packed(grads, reps)
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    assert d.ddp_sync_static(R, 0, stream.cuda_stream, numel, [dtype] * tiles, grads.ptrs(), 1 << 30) == 1
+    stream.synchronize()
+    check_packed(grads, want, reps)
+
+
+@pytest.mark.parametrize("dtype,R,tiles", [(FP32, 8, 384), (FP32, 8, 385), (BF16, 5, 340), (BF16, 5, 341), (BF16, 24, 340), (BF16, 24, 341)])
+def test_small_tensors_of_a_model_without_a_list_of_slices(dtype, R, tiles):
+    """More than 16 MiB a replica: the bucket of small tensors takes slices of its tiles, staged, up to so many of those."""
+    d, harness = lib()
+    numel = [(17 << 20) // ES[dtype]] + [1 + (7 * i) % 23 for i in range(tiles)]
+    n = tiles + 1
+    reps = [[np.full(numel[0], 0, dtype=harness.NP_STORAGE[dtype])] + workloads.gaussian_replica(990, r, 0, numel[1:], 1e-2, dtype) for r in range(R)]
+    cap = sum(numel[1:]) * ES[dtype]
+    want, _, _ = oracle.synchronize(numel, [dtype] * n, cap, reps)
+    grads = harness.DeviceGrads(numel, [dtype] * n, R, align=ES[dtype], replica_skew=[ES[dtype] * (r % 3) for r in range(R)], fill=0x5A)
+    upload_packed(grads, reps)
+    with harness.Session(grads, cap, STAGED) as s:
+        assert s.n_buckets == 2
+        d.ddp_set_option(s.ctx, d.DDP_OPT_COALESCE, 0)
+        s.sync()
+    check_packed(grads, want, reps)
+
+
+def upload_packed(grads, reps):
+    for r in range(grads.R):
+        raw = np.full(grads.bufs[r].numel(), 0x5A, dtype=np.uint8)
+        o = grads.offsets[0] + grads.replica_skew[r]
+        data = np.concatenate([x.view(np.uint8) for x in reps[r]])
+        raw[o:o + data.size] = data
+        grads.bufs[r].copy_(torch_from(raw))
+
+
+def check_packed(grads, want, reps):
+    for r in range(grads.R):
+        raw = grads.bufs[r].cpu().numpy()
+        o = grads.offsets[0] + grads.replica_skew[r]
+        data = np.concatenate([x.view(np.uint8) for x in (want if r == 0 else reps[r])])
+        assert raw[o:o + data.size].tobytes() == data.tobytes(), f"replica {r}"
+        assert outside_is_untouched(grads, r, 0x5A)
