@@ -190,33 +190,28 @@ def test_whole_tiles_with_tables_in_every_form(dtype, R, long_launch):
                 assert torch.equal(got, expect.view(torch.uint8)), f"replica {r} parameter {i} write_all {write_all}"
 
 
+def slice_line(R, es, staged):
+    """Tiles up to which every launch takes slices; eight slices a tile are what a list of slices may hold."""
+    return 128 if R <= 4 or R > 32 else 256 if staged else 192 if es == 2 else 128
+
+
 @pytest.mark.parametrize("dtype", [FP32, BF16])
-@pytest.mark.parametrize("R,pipeline", [(5, STAGED), (8, STAGED), (9, FUSED), (16, FUSED), (16, STAGED), (17, FUSED), (24, FUSED), (24, STAGED),
-                                        (25, FUSED), (25, STAGED)])
-@pytest.mark.parametrize("n", [129, 192, 193, 288, 289, 512, 513, 1024])
-def test_lists_of_tensors_much_smaller_than_a_tile(dtype, R, pipeline, n):
-    """A tile for each tensor, most of it empty: on both sides of the numbers of tiles up to which the slices that hold
-    something decide."""
+@pytest.mark.parametrize("R,pipeline", [(5, STAGED), (16, FUSED), (16, STAGED), (24, FUSED), (25, STAGED)])
+@pytest.mark.parametrize("slices", ["of one tile more than the line", "as many as may be listed", "one more"])
+def test_lists_of_tensors_much_smaller_than_a_tile(dtype, R, pipeline, slices):
+    """A tile for each tensor, most of it empty: up to so many slices that hold something, and one more, which takes tiles."""
     d, harness = lib()
-    numel = [1 + (7 * i) % 23 for i in range(n)]
+    line = slice_line(R, ES[dtype], pipeline == STAGED)
+    n = line + 1 if slices == "of one tile more than the line" else 8 * line - 2 + (slices == "one more")
+    numel = [1 + (7 * i) % 23 for i in range(n)]             # a slice each, but for one that holds three
     numel[n // 3] = 2 * SLICE // ES[dtype] + 3
     reps = [workloads.gaussian_replica(960, r, 0, numel, 1e-2, dtype) for r in range(R)]
     want, _, _ = oracle.synchronize(numel, [dtype] * n, 1 << 30, reps)
     grads = harness.DeviceGrads(numel, [dtype] * n, R, align=ES[dtype], replica_skew=[ES[dtype] * (r % 3) for r in range(R)], fill=0x5A)
-    for r in range(R):
-        raw = np.full(grads.bufs[r].numel(), 0x5A, dtype=np.uint8)
-        o = grads.offsets[0] + grads.replica_skew[r]
-        data = np.concatenate([x.view(np.uint8) for x in reps[r]])
-        raw[o:o + data.size] = data
-        grads.bufs[r].copy_(torch_from(raw))
+    upload_packed(grads, reps)
     with harness.Session(grads, 1 << 30, pipeline) as s:
         s.sync()
-    for r in range(R):
-        raw = grads.bufs[r].cpu().numpy()
-        o = grads.offsets[0] + grads.replica_skew[r]
-        data = np.concatenate([x.view(np.uint8) for x in (want if r == 0 else reps[r])])
-        assert raw[o:o + data.size].tobytes() == data.tobytes(), f"replica {r}"
-        assert outside_is_untouched(grads, r, 0x5A)
+    check_packed(grads, want, reps)
 
 
 def torch_from(raw):
