@@ -307,3 +307,39 @@ def test_gradients_produced_on_the_null_stream(backward, reduction_streams):
                 assert bool((t == 3.0 + it).all()), f"iteration {it} parameter {i}"
     finally:
         d.ddp_destroy(ctx)
+
+
+@pytest.mark.parametrize("streams,n", [(-1, 3), (-1, 4), (3, 4), (3, 5), (3, 6), (8, 9)])
+def test_work_behind_finalize_sees_a_held_up_stream_where_the_last_launch_is_chained(streams, n):
+    """Launches of more than 160 MiB, the last of them on the backward stream and chained to the one in front of it: the
+    other streams' numbers are then waited for on the stream that got the latest launch.  The first reduction stream is held up for
+    80 ms, and the launches chained to its own give up waiting after 10 ms, so that everything else, the last launch included, is over long
+    before its launch has begun; the results are read, and the gradients overwritten, on the backward stream at once."""
+    d, harness = lib()
+    import torch
+    R, elems = 3, 13 << 20                               # (R + 1) x 52 MiB
+    grads = harness.DeviceGrads([elems] * n, [FP32] * n, R, fill=0)
+    keep = harness.DeviceGrads([elems] * n, [FP32] * n, 1, fill=0)
+    marker = harness.DeviceGrads([16], [FP32], 1, fill=0)
+    with session_with_flags(d, harness, grads, 4 * elems, streams) as s, \
+            harness.Session(marker, 1 << 20, FUSED, streams=(s.backward_stream, s.reduce_stream)) as delay:
+        assert s.n_buckets == n
+        d.ddp_set_option(s.ctx, d.DDP_OPT_GATE_WAIT_US, 10_000)
+        for it in range(2):
+            for r in range(R):
+                for p in range(n):
+                    grads.view(r, p).view(torch.float32).fill_(float(3 * r * (it + 1) + p))
+            keep.bufs[0].fill_(0)
+            torch.cuda.synchronize()
+            d.ddp_synth_backward(delay.ctx, [0], [80_000_000], mark=False)
+            for p in range(n - 1, -1, -1):
+                d.ddp_mark_ready(s.ctx, p)
+            d.ddp_finalize_backward(s.ctx)
+            with torch.cuda.stream(s.backward_stream):
+                keep.bufs[0].copy_(grads.bufs[0], non_blocking=True)
+                grads.bufs[0].fill_(0xFF)
+            d.ddp_synchronize(s.ctx)
+            torch.cuda.synchronize()
+            for p in range(n):
+                assert bool((keep.view(0, p).view(torch.float32) == float(3 * (it + 1) + p)).all()), f"iteration {it} parameter {p}"
+        assert d.ddp_get_option(s.ctx, d.DDP_STAT_REPAIRED_LAUNCHES) == 0
