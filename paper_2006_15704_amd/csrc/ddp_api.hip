@@ -896,12 +896,14 @@ int32_t flush_deferred(ddp_ctx* c) {
         size_t j = i;
         const int64_t limit = launch_limit(c);
         if (limit > 0) {
-            // the run of consecutive buckets of one type that starts here
+            // the run of consecutive buckets of one type that starts here, as far as a last launch reaches
+            const uint64_t most = static_cast<uint64_t>(last_launch_limit(c));
             size_t end = i + 1;
             uint64_t bytes = c->plan.buckets[todo[i]].bytes(), run = bytes;
-            while (end < todo.size() && todo[end] == todo[end - 1] + 1 && c->plan.buckets[todo[end]].dtype == c->plan.buckets[todo[i]].dtype)
+            while (end < todo.size() && run <= most && todo[end] == todo[end - 1] + 1 &&
+                   c->plan.buckets[todo[end]].dtype == c->plan.buckets[todo[i]].dtype)
                 run += c->plan.buckets[todo[end++]].bytes();
-            if (run <= static_cast<uint64_t>(last_launch_limit(c))) j = end - 1;
+            if (run <= most) j = end - 1;
             else
                 while (j + 1 < end && bytes + c->plan.buckets[todo[j + 1]].bytes() <= static_cast<uint64_t>(limit))
                     bytes += c->plan.buckets[todo[++j]].bytes();

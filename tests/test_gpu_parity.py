@@ -433,6 +433,34 @@ def test_buckets_share_launches_up_to_the_limit_chosen_for_them(R, pipeline, wri
         assert bool((grads.bufs[r][:n << 20].view(torch.float32) == float(want)).all()), f"replica {r}"
 
 
+@pytest.mark.gpu
+def test_a_small_launch_limit_costs_the_host_nothing_for_each_further_bucket():
+    """Twenty thousand buckets, each with a launch of its own because nothing more fits the limit: the host takes no longer over a
+    launch than without a limit."""
+    import time
+    import torch
+    d, harness = lib()
+    n = 20000
+    grads = harness.DeviceGrads([4] * n, [FP32] * n, 2, align=16, fill=0)
+    values = [b[:16 * n].view(torch.float32) for b in grads.bufs]
+    took = {}
+    with harness.Session(grads, 16, FUSED) as s:
+        assert s.n_buckets == n
+        order = list(range(n - 1, -1, -1))
+        for limit in (0, 16) * 3:
+            for r in range(2):
+                values[r].fill_(float(2 * r + 1))
+            torch.cuda.synchronize()
+            d.ddp_set_option(s.ctx, d.DDP_OPT_COALESCE, limit)
+            t = time.perf_counter()
+            d.ddp_mark_ready_many(s.ctx, order)
+            took.setdefault(limit, []).append(time.perf_counter() - t)
+            d.ddp_finalize_backward(s.ctx)
+            d.ddp_synchronize(s.ctx)
+            assert bool((values[0] == 2.0).all())
+    assert min(took[16]) < 1.25 * min(took[0]), took
+
+
 # ---- kernel time stamps ------------------------------------------------------------------------
 @pytest.mark.gpu
 @pytest.mark.parametrize("pipeline", [STAGED, FUSED])
